@@ -1,6 +1,6 @@
 """The work that users of this library have it do, as timed cases.
 
-Seven kinds of work, each through the public entry points of ``paper_2104_05343_amd``:
+Six kinds of work, each through the public entry points of ``paper_2104_05343_amd``:
 
 ``layer``   one training step (forward and backward) of a transformer layer for ONE device of the q x q grid, the other
             devices' blocks resident: what each rank of the 2D scheme does per layer.  bf16, both attention forms.
@@ -395,3 +395,192 @@ def run(st):
     """One pass through the public entry points; the outputs are the state's own buffers."""
     case = st["case"]
     return _KINDS[case["kind"]][1](case, st["state"])
+
+
+# ------------------------------------------------------------------------------------------------ the same in 64 bits
+def _logical(t, rows, cols, q):
+    """Block-major [q][q][rows/q][cols/q] -> [rows, cols] in 64 bits."""
+    return t.view(q, q, rows // q, cols // q).permute(0, 2, 1, 3).reshape(rows, cols).double()
+
+
+def _part(T, q, i, j):
+    """What device (i, j) holds of a matrix, or the whole of it block-major (i < 0), flat."""
+    r, c = T.shape[0] // q, T.shape[1] // q
+    blocks = T.view(q, r, q, c).permute(0, 2, 1, 3)
+    return (blocks if i < 0 else blocks[i, j]).reshape(-1)
+
+
+def _column_sums(T, q, i, j):
+    """Sums over each device's own rows: the partial vector gradients, [q][q][cols/q] flat or device (i, j)'s."""
+    sums = T.view(q, T.shape[0] // q, q, T.shape[1] // q).sum(dim=1)
+    return (sums if i < 0 else sums[i, j]).reshape(-1)
+
+
+def _norm64(x, gamma, beta, eps=1e-5):
+    rstd = torch.rsqrt(x.var(dim=1, unbiased=False, keepdim=True) + eps)
+    xhat = (x - x.mean(dim=1, keepdim=True)) * rstd
+    return xhat * gamma + beta, xhat, rstd
+
+
+def _norm_bwd64(dy, xhat, rstd, gamma):
+    g = dy * gamma
+    return rstd * (g - xhat * (xhat * g).mean(dim=1, keepdim=True) - g.mean(dim=1, keepdim=True))
+
+
+def _gelu64(z):
+    return 0.5 * z * (1.0 + torch.erf(z / math.sqrt(2.0)))
+
+
+def _gelu_grad64(z):
+    return 0.5 * (1.0 + torch.erf(z / math.sqrt(2.0))) + z * torch.exp(-0.5 * z * z) / math.sqrt(2.0 * math.pi)
+
+
+def _attention64(qkv, b, s, heads, causal, d_attn=None):
+    """[b*s, 3*heads*d] with columns (head, {Q, K, V}, d): attention output and log-sum-exp, or the gradient for qkv."""
+    d = qkv.shape[1] // (3 * heads)
+    mask = torch.ones(s, s, dtype=torch.bool, device=DEV).triu(1) if causal else None
+    outs, lses = [], []
+    for seq in range(b):
+        Q, K, V = qkv[seq * s:(seq + 1) * s].view(s, heads, 3, d).permute(2, 1, 0, 3)
+        S = torch.matmul(Q, K.transpose(1, 2)) / math.sqrt(d)
+        if causal:
+            S.masked_fill_(mask, -math.inf)
+        lse = torch.logsumexp(S, dim=2)
+        P = S.sub_(lse[:, :, None]).exp_()
+        if d_attn is None:
+            outs.append(torch.matmul(P, V).permute(1, 0, 2).reshape(s, heads * d))
+            lses.append(lse)
+            continue
+        dO = d_attn[seq * s:(seq + 1) * s].view(s, heads, d).permute(1, 0, 2)
+        dV = torch.matmul(P.transpose(1, 2), dO)
+        dP = torch.matmul(dO, V.transpose(1, 2))
+        dS = P * (dP - (dP * P).sum(dim=2, keepdim=True))
+        dQ, dK = torch.matmul(dS, K) / math.sqrt(d), torch.matmul(dS.transpose(1, 2), Q) / math.sqrt(d)
+        outs.append(torch.stack((dQ, dK, dV)).permute(2, 1, 0, 3).reshape(s, 3 * heads * d))
+    return (torch.cat(outs), torch.stack(lses)) if d_attn is None else torch.cat(outs)
+
+
+def _params64(p, h, q):
+    out = {name: p[name].double() for name in _VECTORS}
+    for name, (rows, cols) in {"w_qkv": (h, 3 * h), "w_o": (h, h), "w1": (h, 4 * h), "w2": (4 * h, h)}.items():
+        out[name] = _logical(p[name], rows, cols, q)
+    return out
+
+
+def _layer_fwd64(x, p, b, s, n, causal):
+    t = {}
+    t["ln1_out"], t["xhat1"], rstd1 = _norm64(x, p["ln1_g"], p["ln1_b"])
+    t["qkv"] = t["ln1_out"] @ p["w_qkv"] + p["b_qkv"]
+    t["attn"] = _attention64(t["qkv"], b, s, n, causal)[0]
+    t["h_mid"] = x + t["attn"] @ p["w_o"] + p["b_o"]
+    t["ln2_out"], t["xhat2"], rstd2 = _norm64(t["h_mid"], p["ln2_g"], p["ln2_b"])
+    t["pre_gelu"] = t["ln2_out"] @ p["w1"] + p["b1"]
+    t["gelu"] = _gelu64(t["pre_gelu"])
+    t["out"] = t["h_mid"] + t["gelu"] @ p["w2"] + p["b2"]
+    return t, rstd1, rstd2
+
+
+def _layer_bwd64(d_out, f, rstd1, rstd2, p, b, s, n, causal):
+    """Activation gradients, weight gradients, and the matrices whose column sums are the vector gradients."""
+    t, w, v = {}, {}, {}
+    w["d_w2"], v["d_b2"] = f["gelu"].T @ d_out, d_out
+    t["d_pre_gelu"] = (d_out @ p["w2"].T) * _gelu_grad64(f["pre_gelu"])
+    t["d_ln2_out"] = t["d_pre_gelu"] @ p["w1"].T
+    w["d_w1"], v["d_b1"] = f["ln2_out"].T @ t["d_pre_gelu"], t["d_pre_gelu"]
+    v["d_ln2_g"], v["d_ln2_b"] = t["d_ln2_out"] * f["xhat2"], t["d_ln2_out"]
+    t["d_h_mid"] = d_out + _norm_bwd64(t["d_ln2_out"], f["xhat2"], rstd2, p["ln2_g"])
+    t["d_attn"] = t["d_h_mid"] @ p["w_o"].T
+    w["d_w_o"], v["d_b_o"] = f["attn"].T @ t["d_h_mid"], t["d_h_mid"]
+    t["d_qkv"] = _attention64(f["qkv"], b, s, n, causal, t["d_attn"])
+    t["d_ln1_out"] = t["d_qkv"] @ p["w_qkv"].T
+    w["d_w_qkv"], v["d_b_qkv"] = f["ln1_out"].T @ t["d_qkv"], t["d_qkv"]
+    v["d_ln1_g"], v["d_ln1_b"] = t["d_ln1_out"] * f["xhat1"], t["d_ln1_out"]
+    t["d_x"] = t["d_h_mid"] + _norm_bwd64(t["d_ln1_out"], f["xhat1"], rstd1, p["ln1_g"])
+    return t, w, v
+
+
+def _exact_layer(case, r):
+    b, s, h, n, q, i, j = (case[k] for k in "bshnqij")
+    p = _params64(_layer_params(r, h), h, q)
+    x, d_out = _logical(r.normal(b * s * h), b * s, h, q), _logical(r.normal(b * s * h), b * s, h, q)
+    f, rstd1, rstd2 = _layer_fwd64(x, p, b, s, n, case["causal"])
+    t, w, v = _layer_bwd64(d_out, f, rstd1, rstd2, p, b, s, n, case["causal"])
+    return {**{k: _part(T, q, i, j) for k, T in {**f, **t, **w}.items()}, **{k: _column_sums(T, q, i, j) for k, T in v.items()}}
+
+
+def _exact_stack(case, r):
+    b, s, h, n, q, causal = (case[k] for k in ("b", "s", "h", "n", "q", "causal"))
+    params = [_params64(_layer_params(r, h), h, q) for _ in range(case["layers"])]
+    x, d = _logical(r.normal(b * s * h), b * s, h, q), _logical(r.normal(b * s * h), b * s, h, q)
+    kept, out = [], {}
+    for p in params:
+        kept.append(_layer_fwd64(x, p, b, s, n, causal))
+        x = kept[-1][0]["out"]
+    out["out"] = _part(x, q, -1, -1)
+    for layer in reversed(range(len(params))):
+        t, w, v = _layer_bwd64(d, *kept.pop(), params[layer], b, s, n, causal)
+        d = t["d_x"]
+        out.update({f"{k}.{layer}": _part(T, q, -1, -1) for k, T in w.items()})
+        out.update({f"{k}.{layer}": _column_sums(T, q, -1, -1) for k, T in v.items()})
+    out["d_x"] = _part(d, q, -1, -1)
+    return out
+
+
+def _exact_ends(case, r):
+    b, s, h, v, q, i, j = (case[k] for k in "bshvqij")
+    M, dt = b * s, torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    tokens, labels = r.zipf(M, v).long(), r.zipf(M, v).long()
+    table, hidden = _logical(r.normal(v * h, 0.02, dt), v, h, q), _logical(r.normal(M * h, 1.0, dt), M, h, q)
+    d_x = _logical(r.normal(M * h, 1e-3, dt), M, h, q)
+    logits = hidden @ table.T
+    lse = torch.logsumexp(logits, dim=1)
+    at = torch.arange(M, device=DEV)
+    loss = lse - logits[at, labels]
+    d_logits = torch.exp(logits - lse[:, None])
+    d_logits[at, labels] -= 1.0
+    d_logits /= M
+    rows = slice(i * (M // q), (i + 1) * (M // q))   # every device of a grid row holds its rows' losses
+    mats = {"x": table[tokens], "logits": logits, "d_logits": d_logits, "d_hidden": d_logits @ table, "d_table_head": d_logits.T @ hidden,
+            "d_table": torch.zeros(v, h, dtype=torch.float64, device=DEV).index_add_(0, tokens, d_x)}
+    return {**{k: _part(T, q, i, j) for k, T in mats.items()}, "loss": loss[rows], "lse": lse[rows]}
+
+
+def _exact_mlp(case, r):
+    b, s, h, q, i, j = (case[k] for k in "bshqij")
+    M, f32 = b * s, torch.float32
+    x, d_out = _logical(r.normal(M * h, 1.0, f32), M, h, q), _logical(r.normal(M * h, 1.0, f32), M, h, q)
+    w1, w2 = _logical(r.normal(4 * h * h, 0.02, f32), h, 4 * h, q), _logical(r.normal(4 * h * h, 0.02, f32), 4 * h, h, q)
+    b1, b2 = r.normal(4 * h, 0.1, f32).double(), r.normal(h, 0.1, f32).double()
+    g, be = r.normal(h, 0.1, f32, 1.0).double(), r.normal(h, 0.1, f32).double()
+    y, xhat, rstd = _norm64(x, g, be)
+    pre = y @ w1 + b1
+    gelu = _gelu64(pre)
+    d_pre = (d_out @ w2.T) * _gelu_grad64(pre)
+    d_y = d_pre @ w1.T
+    mats = {"y": y, "pre": pre, "gelu": gelu, "out": x + gelu @ w2 + b2, "d_pre": d_pre, "d_y": d_y,
+            "d_x": d_out + _norm_bwd64(d_y, xhat, rstd, g), "d_w1": y.T @ d_pre, "d_w2": gelu.T @ d_out}
+    sums = {"d_b1": d_pre, "d_b2": d_out, "d_g": d_y * xhat, "d_be": d_y}
+    return {**{k: _part(T, q, i, j) for k, T in mats.items()}, **{k: _column_sums(T, q, i, j) for k, T in sums.items()}}
+
+
+def _exact_linear(case, r):
+    M, K, N, q, i, j = case["b"] * case["s"], case["k"], case["n"], case["q"], case["i"], case["j"]
+    x, w, d_y = _logical(r.normal(M * K), M, K, q), _logical(r.normal(K * N, 0.02), K, N, q), _logical(r.normal(M * N), M, N, q)
+    bias = r.normal(N, 0.1, torch.float32).double()
+    return {"y": _part(x @ w + bias, q, i, j), "d_x": _part(d_y @ w.T, q, i, j), "d_w": _part(x.T @ d_y, q, i, j)}
+
+
+def _exact_attention(case, r):
+    b, s, h, n, q, i, j = (case[k] for k in "bshnqij")
+    M = b * s
+    qkv, d_attn = _block(r.normal(3 * M * h), q, i, j), _block(r.normal(M * h), q, i, j)   # attention is local to the device
+    qkv, d_attn = qkv.view(M // q, 3 * h // q).double(), d_attn.view(M // q, h // q).double()
+    attn, lse = _attention64(qkv, b // q, s, n // q, case["causal"])
+    return {"attn": attn.reshape(-1), "lse": lse.reshape(-1), "d_qkv": _attention64(qkv, b // q, s, n // q, case["causal"], d_attn).reshape(-1)}
+
+
+def exact(case, seed):
+    """What ``run`` returns for these inputs, from the definitions in 64 bits."""
+    one = {"layer": _exact_layer, "stack": _exact_stack, "ends": _exact_ends, "mlp": _exact_mlp, "linear": _exact_linear,
+           "attention": _exact_attention}[case["kind"]]
+    return one(case, _Rand(seed))
