@@ -247,37 +247,68 @@ int launch_ln_bwd_apply(const void* dY, const void* xhat, const float* rstd, con
 }
 
 // ---- column sums over the rows of a block: dgamma/dbeta partials, bias gradients ----
-// Workgroup = 1024 threads = (1024 / CL) row lanes x CL column lanes covering CS_COLS = 8 * CL columns; each thread
-// accumulates 8 adjacent columns (one 16-byte load per row for bf16) over rows ty, ty + 1024 / CL, ...  The row lanes
-// inside a wavefront are added by butterfly exchanges, the 16 wavefronts through LDS, both in a fixed order (the
-// result does not depend on the launch).  Narrow column strips and many row lanes keep the chain of dependent
-// loads short: the matrices here have thousands of rows and only a few hundred columns per block.
-constexpr int CS_THREADS = 1024;
-// CS_COLS = 64: whole 128-byte lines per row (large blocks, bandwidth matters).  CS_COLS = 32: twice the workgroups
-// and half the rows per lane (small blocks, where the kernel is two dependent memory round trips long).
-template <typename T, bool PROD, int CS_COLS>
-__global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out,
-                                                            float* __restrict__ out2, int rows, int cols, int ld, long long sX,
-                                                            long long sOut) {
-  constexpr int CS_CL = CS_COLS / 8;  // column lanes
-  __shared__ float red[16][CS_COLS];
-  __shared__ float red2[16][CS_COLS];
-  const int tx = threadIdx.x & (CS_CL - 1), ty = threadIdx.x / CS_CL;
-  const int wave = threadIdx.x >> 6;
-  const int c0 = blockIdx.x * CS_COLS + tx * 8;
+// 128 row lanes; a thread accumulates 8 adjacent columns (16-byte loads) over rows ty, ty + 128, ...  Groups of eight row
+// lanes are added by butterfly exchanges, the 16 groups through LDS in order.  A workgroup covers CL column lanes.
+// Bound: memory round trips and CUs in use, not bytes.  The blocks have thousands of rows and a few hundred to a few
+// thousand columns, so strips of whole 128-byte lines give 4 to 64 workgroups, each with a long chain of loads.  Strips
+// of 8 columns (CL = 1) give up whole lines per wavefront for workgroups; the strips that share a line run on the same
+// XCD, one after the other in its range, and find the line in its L2.  The order of the additions does not depend on CL,
+// so a launch over many blocks may take wider strips than a launch over one and get the same bits.
+// Measured (one launch alone, strips of 64 or 32 columns, fp32 element by element / now): fp32 [1024 x 256] 16.5 / 5.1 us,
+// with products 31 / 7.2 us; bf16 [64 x 128] and the like 3.5 us, a launch's length.  Strips of 8 columns for whole-grid
+// launches too (16 blocks of [1024 x 256]) made the four-layer stack 5 % longer: 128-byte lines in eight pieces.
+constexpr int CS_ROWS = 128;
+template <typename T>
+__device__ __forceinline__ void cs_load(const T* p, float (&f)[8]) {
+  Vec<T>::load(p, f);
+  if constexpr (sizeof(T) == 4) Vec<T>::load(p + 4, f + 4);
+}
+// v: eight columns summed over this lane's rows.  Returns column k = cs_column(lane) summed over the eight row lanes of the
+// group: three exchanges that halve the columns a lane is in charge of.
+template <int CL>
+__device__ __forceinline__ float cs_group(float (&v)[8], int lane) {
+#pragma unroll
+  for (int half = 4, d = CL; half > 0; half >>= 1, d <<= 1) {
+    const bool up = lane & d;
+#pragma unroll
+    for (int k = 0; k < half; ++k) {
+      const float give = up ? v[k] : v[k + half], keep = up ? v[k + half] : v[k];
+      v[k] = keep + __shfl_xor(give, d, 64);
+    }
+  }
+  return v[0];
+}
+template <int CL>
+__device__ __forceinline__ int cs_column(int lane) {   // the group's row-lane bits, lowest first, are the column's, highest first
+  const int g = lane / CL;
+  return ((g & 1) << 2) | (g & 2) | ((g >> 2) & 1);
+}
+template <typename T, bool PROD, int CL>
+__global__ __launch_bounds__(CS_ROWS * CL) void colsum_kernel(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out,
+                                                              float* __restrict__ out2, int rows, int cols, int ld, long long sX,
+                                                              long long sOut) {
+  constexpr int CS_COLS = 8 * CL, GROUPS = CS_ROWS / 8;
+  __shared__ float red[GROUPS][CS_COLS];
+  __shared__ float red2[GROUPS][CS_COLS];
+  const int tx = threadIdx.x & (CL - 1), ty = threadIdx.x / CL;
+  const int lane = threadIdx.x & 63;
+  // workgroups are dealt round-robin to the 8 XCDs: a contiguous range of strips each (whatever XCD the entry starts on)
+  const int nwg = gridDim.x, slot = blockIdx.x >> 3, xcd = blockIdx.x & 7, rem = nwg & 7;
+  const int strip = xcd * (nwg >> 3) + (xcd < rem ? xcd : rem) + slot;
+  const int c0 = strip * CS_COLS + tx * 8;
   const long long zoff = (long long)blockIdx.y * sX;
   float acc[8], acc2[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) { acc[k] = 0.f; acc2[k] = 0.f; }
-  const bool vec = (ld % 8 == 0) && (sX % 8 == 0) && (c0 + 8 <= cols) && sizeof(T) == 2 && (((uintptr_t)X & 15) == 0) &&
-                   (!PROD || ((uintptr_t)W & 15) == 0);
-#pragma unroll 4
-  for (int r = ty; r < rows; r += CS_THREADS / CS_CL) {
+  const bool vec = (ld % 8 == 0) && (sX % 8 == 0) && (c0 + 8 <= cols) && (((uintptr_t)X & 15) == 0) && (!PROD || ((uintptr_t)W & 15) == 0);
+  constexpr int IN_FLIGHT = PROD ? 4 : 8;
+#pragma unroll IN_FLIGHT
+  for (int r = ty; r < rows; r += CS_ROWS) {
     const long long off = zoff + (long long)r * ld + c0;
     float x[8], w[8];
     if (vec) {
-      Vec<bf16_t>::load((const bf16_t*)X + off, x);
-      if (PROD) Vec<bf16_t>::load((const bf16_t*)W + off, w);
+      cs_load(X + off, x);
+      if (PROD) cs_load(W + off, w);
     } else {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -292,44 +323,37 @@ __global__ __launch_bounds__(CS_THREADS) void colsum_kernel(const T* __restrict_
       if (PROD) acc2[k] += x[k] * w[k];    // sum x*w         (dgamma)
     }
   }
-  // the row lanes of a wavefront: lanes that differ in the bits above the column-lane bits
-#pragma unroll
-  for (int d = CS_CL; d < 64; d <<= 1) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      acc[k] += __shfl_xor(acc[k], d, 64);
-      if (PROD) acc2[k] += __shfl_xor(acc2[k], d, 64);
-    }
-  }
-  if ((threadIdx.x & 63) < CS_CL) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) { red[wave][tx * 8 + k] = acc[k]; if (PROD) red2[wave][tx * 8 + k] = acc2[k]; }
-  }
+  const int k = cs_column<CL>(lane);
+  red[ty >> 3][tx * 8 + k] = cs_group<CL>(acc, lane);
+  if (PROD) red2[ty >> 3][tx * 8 + k] = cs_group<CL>(acc2, lane);
   __syncthreads();
   if (threadIdx.x < CS_COLS) {
-    int c = blockIdx.x * CS_COLS + threadIdx.x;
+    int c = strip * CS_COLS + threadIdx.x;
     if (c < cols) {
       float s = 0.f, s2 = 0.f;
-      for (int r = 0; r < 16; ++r) { s += red[r][threadIdx.x]; if (PROD) s2 += red2[r][threadIdx.x]; }
+#pragma unroll
+      for (int r = 0; r < GROUPS; ++r) { s += red[r][threadIdx.x]; if (PROD) s2 += red2[r][threadIdx.x]; }
       out[(long long)blockIdx.y * sOut + c] = s;
       if (PROD) out2[(long long)blockIdx.y * sOut + c] = s2;
     }
   }
 }
 
-// strip width from the block shape only (never from the batch): grid mode and device mode then add in the same order
 bool colsum_narrow(int rows, int cols) { return (long long)rows * cols <= (1LL << 20); }
 
+// The widest strips (64, 32, 16 or 8 columns) that still make a workgroup for every CU.
 template <typename T, bool PROD>
 static void colsum_launch(dim3 batch, const T* X, const T* W, float* out, float* out2, int rows, int cols, int ld, long long sX,
                           long long sOut, hipStream_t stream) {
-  if (colsum_narrow(rows, cols)) {
-    dim3 grid((unsigned)((cols + 31) / 32), batch.y);
-    hipLaunchKernelGGL((colsum_kernel<T, PROD, 32>), grid, dim3(CS_THREADS), 0, stream, X, W, out, out2, rows, cols, ld, sX, sOut);
-  } else {
-    dim3 grid((unsigned)((cols + 63) / 64), batch.y);
-    hipLaunchKernelGGL((colsum_kernel<T, PROD, 64>), grid, dim3(CS_THREADS), 0, stream, X, W, out, out2, rows, cols, ld, sX, sOut);
-  }
+#define OPTIMUS_COLSUM(CL)                                                                                                        \
+  hipLaunchKernelGGL((colsum_kernel<T, PROD, CL>), dim3((unsigned)((cols + 8 * CL - 1) / (8 * CL)), batch.y), dim3(CS_ROWS * CL), 0, \
+                     stream, X, W, out, out2, rows, cols, ld, sX, sOut)
+  const long long width = (long long)cols * batch.y;
+  if (width >= 64 * 256) OPTIMUS_COLSUM(8);
+  else if (width >= 32 * 256) OPTIMUS_COLSUM(4);
+  else if (width >= 16 * 256) OPTIMUS_COLSUM(2);
+  else OPTIMUS_COLSUM(1);
+#undef OPTIMUS_COLSUM
 }
 
 int launch_colsum(const void* X, float* out, int rows, int cols, int ld, int nz, long long sX, long long sOut, int dtype,
