@@ -1,0 +1,46 @@
+"""GPU: the embedding gradient where its sort and its runs are cut: one row for all tokens, runs that end and begin at the
+wavefronts' parts, more than one chunk of tokens, widths that are no multiple of four, against sums in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2104_05343_amd as opt
+from workloads import round_to_bf16
+from gpu_util import mat_to_dev, empty, dt, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _tokens(kind, M, v, rng):
+    if kind == "one":
+        return np.full(M, v // 2, dtype=np.int32)
+    if kind == "two":                       # neighbours in the same workgroup's rows, alternating
+        return (v // 2 + (np.arange(M) & 1)).astype(np.int32)
+    if kind == "outside":                   # clamped to the table
+        return rng.integers(-3, v + 3, M).astype(np.int32)
+    return np.minimum(rng.zipf(1.2, M) - 1, v - 1).astype(np.int32)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("kind", ["one", "two", "zipf", "outside"])
+@pytest.mark.parametrize("q,rows,vb,hb", [(1, 1, 1, 1), (2, 33, 31, 6), (2, 2100, 70, 260), (1, 4097, 33, 5)])
+def test_against_64_bit_sums(q, rows, vb, hb, kind, dtype):
+    rng = np.random.default_rng(rows + hb)
+    M, v, h = q * rows, q * vb, q * hb
+    tok = _tokens(kind, M, v, rng)
+    dX = rng.standard_normal((M, h)).astype(np.float32)
+    dX = round_to_bf16(dX) if dtype == "bf16" else dX
+    d, t = mat_to_dev(dX, q, dtype), torch.from_numpy(tok).to("cuda:0")
+    grid, dev = empty(v * h, "fp32"), empty(v * h, "fp32")
+    opt.embedding_bwd(t, d, grid, M, v, h, q, -1, -1, dt(dtype))
+    for l in range(q):
+        for j in range(q):
+            opt.embedding_bwd(t, d, dev, M, v, h, q, l, j, dt(dtype))
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(grid), to_host(dev))
+    want, mag = np.zeros((v, h)), np.zeros((v, h))
+    np.add.at(want, np.clip(tok, 0, v - 1), dX.astype(np.float64))
+    np.add.at(mag, np.clip(tok, 0, v - 1), np.abs(dX).astype(np.float64))
+    got = to_host(grid).reshape(q, q, vb, hb).transpose(0, 2, 1, 3).reshape(v, h)
+    # at most one fp32 addition per token and three per wavefront and chunk that meet in a row
+    assert np.all(np.abs(got - want) <= (M + 96) * 2.0 ** -24 * mag)
