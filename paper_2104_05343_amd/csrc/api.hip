@@ -395,6 +395,21 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
   return OPTIMUS_OK;
 }
 
+// Whether the second stream pays.  A fork or the join costs the host 25 us (the wait on another stream's event, for the
+// most part), and there are five of them in a backward pass: where its kernels take no longer than that, the host is what
+// the pass waits for.  The line is drawn by the flops of the pass's products.  Measured, step of one layer, two streams /
+// one (us): 1.6 GF 250 / 150, 13 GF 307 / 240 and 315 / 247, 39 GF 308 / 368, 51 GF 303 / 347, 103 GF 440 / 522,
+// 412 GF 893 / 999; checkpointed stack of two small layers (0.8 GF each) 584 / 355.  A captured pass pays the host once
+// and keeps both streams.
+bool branch_pays(const optimus_layer_cfg* c, bool grid, hipStream_t caller) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(caller, &cs) != hipSuccess) (void)hipGetLastError();
+  if (cs != hipStreamCaptureStatusNone) return true;
+  const double devices = grid ? (double)c->q * c->q : 1.0;
+  const double flops = 48.0 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
+  return flops >= 24e9;
+}
+
 // Device address of `scratch` on the current device (each GPU holds its own copy at its own address): looked up on
 // the first call made with that device current, kept afterwards.
 std::mutex g_scratch_mutex;
@@ -807,7 +822,8 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   LnDesc ln;
   if ((rc = ln_desc(M, h, q, i, j, dt, c->eps, &ln))) return rc;
   // gradient branch: its own stream and its own split workspace (see SideStream)
-  SideStream* ss = side_stream(st);
+  SideStream* ss = branch_pays(c, grid, st) ? side_stream(st) : nullptr;
+  const int co_chain = ss ? 1 : 0, co_branch = ss ? 2 : 0;   // products planned for company only where they have it
   hipStream_t gst = ss ? ss->s : st;
   void* gstream = (void*)gst;
   void* grad_ws = ss ? (char*)gemm_ws + gemm_bytes : gemm_ws;
@@ -828,29 +844,29 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   BRANCH_AFTER_MAIN(ss->fork);
   // ---- out = h_mid + gelu W2 + b2 ----
   e = {}; e.gelu_grad_of = t->pre_gelu;  // d_pre = (d_out W2^T) * GeLU'(pre)
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_out, t->w2, t->d_pre_gelu, M, h, 4 * h, q, i, j, dt, &e, gemm_ws, gemm_bytes, stream, 1));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->gelu, t->d_out, t->d_w2, 4 * h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, 2));
+  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_out, t->w2, t->d_pre_gelu, M, h, 4 * h, q, i, j, dt, &e, gemm_ws, gemm_bytes, stream, co_chain));
+  RUN(run_summa(OPTIMUS_FORM_ATB, t->gelu, t->d_out, t->d_w2, 4 * h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
   RUN(optimus_bias_grad(t->d_out, t->d_b2, M, h, q, i, j, dt, gstream));
   // ---- pre = ln2_out W1 + b1 ----
   BRANCH_AFTER_MAIN(ss->ready[0]);  // d_pre_gelu is complete
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_pre_gelu, t->w1, t->d_ln2_out, M, 4 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, 1));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->ln2_out, t->d_pre_gelu, t->d_w1, h, M, 4 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, 2));
+  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_pre_gelu, t->w1, t->d_ln2_out, M, 4 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
+  RUN(run_summa(OPTIMUS_FORM_ATB, t->ln2_out, t->d_pre_gelu, t->d_w1, h, M, 4 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
   RUN(optimus_bias_grad(t->d_pre_gelu, t->d_b1, M, 4 * h, q, i, j, dt, gstream));
   // ---- LN2 backward, plus the residual branch: d_h_mid = d_out + LN2'(d_ln2_out) ----
   RUN(ln_backward(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, ln2_grads_on_branch ? nullptr : t->d_ln2_g,
                   ln2_grads_on_branch ? nullptr : t->d_ln2_b, t->bstats2, ln, grid, st));
   // ---- h_mid = x + attn Wo + bo ----
   BRANCH_AFTER_MAIN(ss->ready[1]);  // d_h_mid is complete
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_h_mid, t->w_o, t->d_attn, M, h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, 1));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->attn, t->d_h_mid, t->d_w_o, h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, 2));
+  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_h_mid, t->w_o, t->d_attn, M, h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
+  RUN(run_summa(OPTIMUS_FORM_ATB, t->attn, t->d_h_mid, t->d_w_o, h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
   RUN(optimus_bias_grad(t->d_h_mid, t->d_b_o, M, h, q, i, j, dt, gstream));
   if (ln2_grads_on_branch) RUN(launch_ln_param_grads(t->d_ln2_out, t->xhat2, t->d_ln2_g, t->d_ln2_b, ln, gst));
   // ---- local attention backward ----
   RUN(layer_attention(true, c, t, i, j, attn_ws, attn_bytes, stream));
   // ---- qkv = ln1_out Wqkv + b ----
   BRANCH_AFTER_MAIN(ss->ready[2]);  // d_qkv is complete
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_qkv, t->w_qkv, t->d_ln1_out, M, 3 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, 1));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->ln1_out, t->d_qkv, t->d_w_qkv, h, M, 3 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, 2));
+  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_qkv, t->w_qkv, t->d_ln1_out, M, 3 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
+  RUN(run_summa(OPTIMUS_FORM_ATB, t->ln1_out, t->d_qkv, t->d_w_qkv, h, M, 3 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
   RUN(optimus_bias_grad(t->d_qkv, t->d_b_qkv, M, 3 * h, q, i, j, dt, gstream));
   // ---- LN1 backward, plus the residual branch: d_x = d_h_mid + LN1'(d_ln1_out) ----
   RUN(ln_backward(t->d_ln1_out, t->xhat1, t->rstd1, t->ln1_g, t->d_h_mid, t->d_x, t->d_ln1_g, t->d_ln1_b, t->bstats1, ln, grid, st));
