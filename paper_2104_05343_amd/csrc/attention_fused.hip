@@ -5,8 +5,8 @@
 //
 // Forward keeps one fp32 number per query row, L = log sum_u exp(S_tu); backward rebuilds P = exp(S - L) tile by tile
 // and uses rowsum(dO * O) in place of rowsum(dP * P).
-// Backward is two bodies (dQ; dK and dV), each recomputing S; small launches run them as one grid ordered by loop
-// length (attn_fused_bwd_kernel), large ones as two kernels.
+// Backward is two bodies (dQ; dK and dV), each recomputing S; most launches run them as one grid ordered by loop length
+// (attn_fused_bwd_kernel, attn_fused_bwd_wide_kernel), large ones without a mask as two kernels.
 //
 // Work layout (forward and both backward bodies).  A workgroup of four wavefronts owns 64 rows (queries in the forward and dQ
 // kernels, keys in the dK/dV kernel).  Wavefront w works on rows 32*(w & 1).. and on every second 64-wide block of the
@@ -66,6 +66,11 @@ struct FusedArgs {
   float scale, scale_log2;               // 1/sqrt(d), log2(e)/sqrt(d)
 };
 
+// Grids are ordered by loop length: x = matrix (times kind), y = rank of the tile, z = device.  Workgroups start with x
+// fastest, and a causal tile's loop is as long as its rank says: all matrices' longest tiles first keeps the compute units
+// busy to the end, where one matrix after the other lets the last one's longest tiles start last (16 matrices, s = 4096,
+// width 128: forward 130 us that way, 81 this way).
+
 // ---- LDS tile [rows][D] bf16, chunk position = chunk ^ g(row) ----
 template <int D>
 __device__ __forceinline__ int swz(int row) {
@@ -121,16 +126,16 @@ __device__ __forceinline__ float halfwave_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// ---- direct global -> LDS copy of a PAIR x D tile (rows row0 .. row0 + 127 of a [s][ld] matrix) by NW wavefronts ----
+// ---- direct global -> LDS copy of a ROWS x D tile (rows row0 .. row0 + ROWS - 1 of a [s][ld] matrix) by NW wavefronts ----
 __device__ __forceinline__ i32x4 make_rsrc(const bf16_t* base) {  // raw buffer, 2 GiB window (offsets used are far below)
   const unsigned long long p = (unsigned long long)base;  // wave-uniform by construction; say so to the compiler
   const int lo = __builtin_amdgcn_readfirstlane((int)(unsigned)p);
   const int hi = __builtin_amdgcn_readfirstlane((int)(unsigned)((p >> 32) & 0xffffu));
   return i32x4{lo, hi, (int)0x80000000u, 0x00020000};
 }
-template <int D, int NW = NWAVES>
-struct PairLoader {
-  static constexpr int CH = D / 8, ROWS_PER_KIB = 64 / CH, PIECES = PAIR * D * 2 / 1024, PER = PIECES / NW;
+template <int D, int NW = NWAVES, int ROWS = PAIR>
+struct TileLoader {
+  static constexpr int CH = D / 8, ROWS_PER_KIB = 64 / CH, PIECES = ROWS * D * 2 / 1024, PER = PIECES / NW;
   static_assert(PIECES % NW == 0, "tile must divide over the wavefronts");
   unsigned off[PER];  // byte offsets of this lane's chunks for a tile that lies entirely inside the matrix
   int ld, wave, lane;
@@ -147,10 +152,10 @@ struct PairLoader {
     const int src = min(row0 + row, last_row) - base_row;
     return (unsigned)(src * ld + chunk * 8) * 2u;
   }
-  // mat: row 0 of the [s][ld] matrix (already offset to the head's columns); tile: LDS destination, PAIR * D elements
+  // mat: row 0 of the [s][ld] matrix (already offset to the head's columns); tile: LDS destination, ROWS * D elements
   __device__ __forceinline__ void issue(const bf16_t* mat, int row0, int s, bf16_t* tile) const {
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) bf16_t*)tile;
-    if (row0 + PAIR <= s) {
+    if (row0 + ROWS <= s) {
       const i32x4 rsrc = make_rsrc(mat + (long long)row0 * ld);
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
@@ -158,7 +163,7 @@ struct PairLoader {
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off[it]), "s"(rsrc), "s"(m0v) : "memory", "m0");
       }
     } else {  // the tile reaches past the last row: clamp (wave-uniform branch, taken for the last pair only)
-      const int base_row = max(0, s - PAIR);
+      const int base_row = max(0, s - ROWS);
       const i32x4 rsrc = make_rsrc(mat + (long long)base_row * ld);
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
@@ -186,8 +191,8 @@ __global__ __launch_bounds__(NRG * 128) void attn_fused_fwd_kernel(FusedArgs a) 
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rg = wave % NRG, par = wave / NRG;
-  const int tile = gridDim.x - 1 - blockIdx.x;  // the tiles with the longest causal loops start first
-  const int mat = blockIdx.y, dev = blockIdx.z, s = a.s;
+  const int tile = gridDim.y - 1 - blockIdx.y;  // the tiles with the longest causal loops start first
+  const int mat = blockIdx.x, dev = blockIdx.z, s = a.s;
   const int seq = mat / a.nh, head = mat % a.nh;
   const bf16_t* Qp = a.qkv + dev * a.dev_qkv + (long long)seq * s * a.ld + head * 3 * D;
   const bf16_t* Kp = Qp + D;
@@ -209,7 +214,7 @@ __global__ __launch_bounds__(NRG * 128) void attn_fused_fwd_kernel(FusedArgs a) 
   for (int dt = 0; dt < DT; ++dt) oacc[dt] = zero16();
   float m_run = -INFINITY, l_run = 0.f;
 
-  PairLoader<D, 2 * NRG> ldr;
+  TileLoader<D, 2 * NRG> ldr;
   ldr.init(a.ld, wave, lane);
   ldr.issue(Kp, 0, s, lds[0][0]);
   ldr.issue(Vp, 0, s, lds[0][1]);
@@ -384,7 +389,7 @@ __device__ __forceinline__ void bwd_dq_body(const FusedArgs& a, bf16_t (*lds)[2]
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dqacc[dt] = zero16();
 
-  PairLoader<D, 2 * NRG> ldr;
+  TileLoader<D, 2 * NRG> ldr;
   ldr.init(a.ld, wave, lane);
   ldr.issue(Kp, 0, s, lds[0][0]);
   ldr.issue(Vp, 0, s, lds[0][1]);
@@ -522,7 +527,7 @@ __device__ __forceinline__ void bwd_dkv_body(const FusedArgs& a, bf16_t (*lds)[2
     dkacc[dt] = zero16();
     dvacc[dt] = zero16();
   }
-  PairLoader<D, 2 * NRG> ldq, ldg;
+  TileLoader<D, 2 * NRG> ldq, ldg;
   ldq.init(a.ld, wave, lane);
   ldg.init(a.ldo, wave, lane);
   auto load_pair = [&](int it, int st) {
@@ -638,6 +643,159 @@ __global__ __launch_bounds__(NRG * 128) void attn_fused_bwd_dkv_kernel(FusedArgs
   bwd_dkv_body<D, CAUSAL, NRG>(a, lds, ldsL, ldsD, blockIdx.x, blockIdx.y, blockIdx.z);  // early key tiles: longest causal loops
 }
 
+// Head width 128: 128 keys per workgroup, eight wavefronts, two per SIMD, so that one's matrix instructions run beside the
+// other's soft-max arithmetic and LDS reads.  A lane has 256 registers then, and 128 of them are the dK and dV
+// accumulators: the wavefront's own V fragments and half of its K fragments stay in LDS (with all of K in registers a
+// dozen were spilled, and with the mask in a branch of its own), the blocks come one at a time, and a wavefront takes one
+// 32-query half (par) of every 64-query block instead of every second block.
+// The queries' lse and rowsum(dO * O) go through a register and reach LDS at the end of an iteration: stored at its top,
+// the store would wait for its load and for all the tile loads issued before it.
+// Bound: LDS reads (44 KiB per wavefront and 32 x 32 scores, beside 1024 clk of matrix instructions).  Measured, 16
+// matrices, s = 4096, causal: four wavefronts with every fragment in registers, 64 keys per workgroup, 456 us; now 313 us.
+template <int D>
+struct WideLds {
+  bf16_t block[2][2][BLK * D];   // [stage][Q, dO]
+  bf16_t v[128 * D], k[128 * D]; // the workgroup's own rows
+  float l[2][BLK], d[2][BLK];
+};
+// 32 x 32 scores S (rows: queries q0 .., columns: keys) and dP = dO V^T in accumulators -> P and dS in their place.
+// l, d: lse * log2(e) and rowsum(dO * O) of the 32 queries.
+template <bool CAUSAL>
+__device__ __forceinline__ void dkv_scores(f32x16& sacc, f32x16& pacc, const float* l, const float* d, int q0, int key, int s, bool need_mask,
+                                           float scale_log2, int g) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int qi = 8 * c + 4 * g;
+    const float4 l4 = *(const float4*)(l + qi);
+    const float4 d4 = *(const float4*)(d + qi);
+    const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 4 * c + e, qy = q0 + qi + e;
+      float p = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale_log2, -lv[e]));
+      float ds = p * (pacc[r] - dv[e]);
+      if (need_mask && (qy >= s || (CAUSAL && qy < key))) { p = 0.f; ds = 0.f; }
+      sacc[r] = p;
+      pacc[r] = ds;
+    }
+  }
+}
+template <int D, bool CAUSAL>
+__device__ __forceinline__ void bwd_dkv_wide_body(const FusedArgs& a, WideLds<D>& lds, int tile, int mat, int dev) {
+  constexpr int KS = D / 16, DT = D / 32, BKW = 128, KREG = KS / 2;   // KREG: K fragments kept in registers
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = wave & 3, par = wave >> 2;
+  const int s = a.s;
+  const int seq = mat / a.nh, head = mat % a.nh;
+  const bf16_t* Qp = a.qkv + dev * a.dev_qkv + (long long)seq * s * a.ld + head * 3 * D;
+  const bf16_t* Kp = Qp + D;
+  const bf16_t* Gp = a.d_attn + dev * a.dev_attn + (long long)seq * s * a.ldo + head * D;
+  const float* Lp = a.lse + dev * a.dev_vec + (long long)mat * s;
+  const float* Dp = a.delta + dev * a.dev_vec + (long long)mat * s;
+  const int k0 = tile * BKW + rg * 32;
+  const int key = k0 + (lane & 31);
+  const int krow = min(key, s - 1);
+  bf16x8 kf[KREG];
+#pragma unroll
+  for (int ks = 0; ks < KREG; ++ks) kf[ks] = *(const bf16x8*)(Kp + (long long)krow * a.ld + ks * 16 + g * 8);
+  const int nqb = (s + BLK - 1) / BLK;
+  const int qb_lo = CAUSAL ? (tile * BKW) / BLK : 0;
+  const int n_it = nqb - qb_lo;
+
+  f32x16 dkacc[DT], dvacc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) {
+    dkacc[dt] = zero16();
+    dvacc[dt] = zero16();
+  }
+  {
+    TileLoader<D, 8, BKW> ldv;
+    ldv.init(a.ld, wave, lane);
+    ldv.issue(Qp + 2 * D, tile * BKW, s, lds.v);
+    ldv.issue(Kp, tile * BKW, s, lds.k);
+  }
+  TileLoader<D, 8, BLK> ldq, ldg;
+  ldq.init(a.ld, wave, lane);
+  ldg.init(a.ldo, wave, lane);
+  float next_l = 0.f, next_d = 0.f;
+  auto load_block = [&](int it, int st) {
+    const int row0 = (qb_lo + it) * BLK;
+    if (tid < BLK) {
+      const int row = min(row0 + tid, s - 1);
+      next_l = Lp[row];
+      next_d = Dp[row];
+    }
+    ldq.issue(Qp, row0, s, lds.block[st][0]);
+    ldg.issue(Gp, row0, s, lds.block[st][1]);
+  };
+  auto store_rows = [&](int st) {
+    if (tid < BLK) {
+      lds.l[st][tid] = next_l * LOG2E;
+      lds.d[st][tid] = next_d;
+    }
+  };
+  load_block(0, 0);
+  store_rows(0);
+  wait_loads_and_barrier();
+  for (int it = 0; it < n_it; ++it) {
+    const int st = it & 1;
+    if (it + 1 < n_it) load_block(it + 1, st ^ 1);
+    const int q0 = (qb_lo + it) * BLK + par * 32;   // this wavefront's queries
+    if (k0 < s && q0 < s && (!CAUSAL || q0 + 31 >= k0)) {
+      const bf16_t* tQ = lds.block[st][0];
+      const bf16_t* tG = lds.block[st][1];
+      f32x16 sacc = zero16(), pacc = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tQ, par * 32, ks, lane),
+                                                       ks < KREG ? kf[ks < KREG ? ks : 0] : frag_rows<D>(lds.k, rg * 32, ks, lane), sacc, 0, 0, 0);
+        pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tG, par * 32, ks, lane), frag_rows<D>(lds.v, rg * 32, ks, lane), pacc, 0, 0, 0);
+      }
+      const bool need_mask = (CAUSAL && q0 < k0 + 31) || (q0 + 32 > s);
+      dkv_scores<CAUSAL>(sacc, pacc, lds.l[st] + par * 32, lds.d[st] + par * 32, q0, key, s, need_mask, a.scale_log2, g);
+      const bf16x8 pf[2] = {pack_acc<0>(sacc), pack_acc<1>(sacc)}, dsf[2] = {pack_acc<0>(pacc), pack_acc<1>(pacc)};
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          dvacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tG, par * 32 + u * 16, dt * 32, lane), pf[u], dvacc[dt], 0, 0, 0);
+          dkacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tQ, par * 32 + u * 16, dt * 32, lane), dsf[u], dkacc[dt], 0, 0, 0);
+        }
+    }
+    if (it + 1 < n_it) store_rows(st ^ 1);
+    wait_loads_and_barrier();
+  }
+  // merge the two halves' sums, dV first: the odd one hands over through LDS (64 KiB, all block tiles are free)
+  float* xch = (float*)&lds.block[0][0][0] + rg * (DT * 16) * 64;
+  bf16_t* dKp = a.d_qkv + dev * a.dev_qkv + ((long long)seq * s + key) * a.ld + head * 3 * D + D;
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    f32x16 (&acc)[DT] = which == 0 ? dvacc : dkacc;
+    if (which == 1) __syncthreads();
+    if (par == 1) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xch[(dt * 16 + r) * 64 + lane] = acc[dt][r];
+    }
+    __syncthreads();
+    if (par == 0 && key < s) {
+      const float w = which == 0 ? 1.0f : a.scale;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float o[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = (acc[dt][4 * c + e] + xch[(dt * 16 + 4 * c + e) * 64 + lane]) * w;
+          u32x2 x = {pack2_bf16(o[0], o[1]), pack2_bf16(o[2], o[3])};
+          *(u32x2*)(dKp + (which == 0 ? D : 0) + dt * 32 + 8 * c + 4 * g) = x;
+        }
+    }
+  }
+}
+
 // dQ and dK/dV of one launch side by side.  A causal launch of either kernel alone is as long as its longest row or
 // column tile while the average tile is half as long, and one workgroup fills a compute unit (registers), so with
 // about one workgroup per compute unit half the chip idles.  Here the workgroups of both are one grid, ordered by loop
@@ -654,6 +812,29 @@ __global__ __launch_bounds__(256) void attn_fused_bwd_kernel(FusedArgs a, int nt
   const int mat = (int)(rem >> 1), dev = (int)blockIdx.y;
   if (rem & 1) bwd_dq_body<D, CAUSAL, 2, false>(a, lds, ntiles - 1 - (int)rank, mat, dev);
   else bwd_dkv_body<D, CAUSAL, 2>(a, lds, ldsL, ldsD, (int)rank, mat, dev);
+}
+// The same for launches with a 128-row workgroup for every compute unit: eight wavefronts share the tiles of K/V or Q/dO.
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(512) void attn_fused_bwd_wide_kernel(FusedArgs a) {
+  const int rank = blockIdx.y, mat = blockIdx.x >> 1, kind = blockIdx.x & 1, ntiles = gridDim.y, dev = blockIdx.z;
+  if constexpr (D == 128) {
+    __shared__ __attribute__((aligned(1024))) char lds[sizeof(WideLds<D>)];
+    static_assert(sizeof(WideLds<D>) >= 2 * 2 * PAIR * D * sizeof(bf16_t), "room for the dQ body's tiles");
+    if (kind) bwd_dq_body<D, CAUSAL, 4, false>(a, (bf16_t (*)[2][PAIR * D])lds, ntiles - 1 - rank, mat, dev);
+    else bwd_dkv_wide_body<D, CAUSAL>(a, *(WideLds<D>*)lds, rank, mat, dev);
+  } else {
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][PAIR * D];
+    __shared__ __attribute__((aligned(16))) float ldsL[2][PAIR];
+    __shared__ __attribute__((aligned(16))) float ldsD[2][PAIR];
+    if (kind) bwd_dq_body<D, CAUSAL, 4, false>(a, lds, ntiles - 1 - rank, mat, dev);
+    else bwd_dkv_body<D, CAUSAL, 4>(a, lds, ldsL, ldsD, rank, mat, dev);
+  }
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(512) void attn_fused_bwd_dkv_wide_kernel(FusedArgs a) {
+  __shared__ __attribute__((aligned(1024))) WideLds<D> lds;
+  bwd_dkv_wide_body<D, CAUSAL>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 FusedArgs make_args(const AttnFusedDesc& d) {
@@ -680,39 +861,46 @@ template <int D>
 void fwd_launch(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
   // 128-row workgroups from one per two compute units on (measured: equal or faster than 64-row ones from there)
   const bool big = (long long)((d.s + 127) / 128) * d.nb * d.nh * d.ndev >= 128;
+  const int rows = big ? 128 : BLK;
+  const dim3 grid(d.nb * d.nh, (d.s + rows - 1) / rows, d.ndev);
   if (big) {
-    const dim3 grid((d.s + 127) / 128, d.nb * d.nh, d.ndev), block(512);
-    if (d.causal) attn_fused_fwd_kernel<D, true, 4><<<grid, block, 0, st>>>(a);
-    else attn_fused_fwd_kernel<D, false, 4><<<grid, block, 0, st>>>(a);
+    if (d.causal) attn_fused_fwd_kernel<D, true, 4><<<grid, 512, 0, st>>>(a);
+    else attn_fused_fwd_kernel<D, false, 4><<<grid, 512, 0, st>>>(a);
   } else {
-    const dim3 grid((d.s + BLK - 1) / BLK, d.nb * d.nh, d.ndev), block(256);
-    if (d.causal) attn_fused_fwd_kernel<D, true, 2><<<grid, block, 0, st>>>(a);
-    else attn_fused_fwd_kernel<D, false, 2><<<grid, block, 0, st>>>(a);
+    if (d.causal) attn_fused_fwd_kernel<D, true, 2><<<grid, 256, 0, st>>>(a);
+    else attn_fused_fwd_kernel<D, false, 2><<<grid, 256, 0, st>>>(a);
   }
 }
+// Which form of the backward.  The forms of head width 128 add up dK and dV in different orders, so there the choice follows
+// one device's matrices, whatever the launch covers; at 64 they do not, and it follows the launch.
+// Measured, us, 128-row form against the others, head width 128.  Not causal: 512 workgroups (8 matrices, s = 4096) 298
+// against 510, 256 (8, 2048) 87 against 138, 128 (4, 2048) 81 against 75: below a workgroup per compute unit the longest
+// tile's loop is what counts, and two blocks per iteration walk it faster.  Causal: 512 157 against 267, 256 (16, 1024) 48
+// against 54 alone, but beside the products of the layer's gradient branch, which take compute units away, the longest
+// tiles then start second: the 4096-wide layer step 874 against 850.  Both kinds in one grid against one after the other, 16
+// matrices, s = 4096: causal 308 against 477 (width 64: 189 against 279), not causal 596 against 507 (327 against 295).
 template <int D, bool CAUSAL>
 void bwd_launch_c(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
-  const dim3 grid((d.s + BLK - 1) / BLK, d.nb * d.nh, d.ndev), block(NWAVES * 64);
-  // 128-row workgroups of eight wavefronts for big launches, where the kernel fits 256 registers per lane (the dK/dV
-  // kernel at head width 128 does not: it would spill a hundred registers)
-  const bool big = (long long)((d.s + 127) / 128) * d.nb * d.nh * d.ndev >= 512;
-  const dim3 grid_big((d.s + 127) / 128, d.nb * d.nh, d.ndev), block_big(512);
-  const long long ntiles = (d.s + BLK - 1) / BLK, nmat = (long long)d.nb * d.nh;
-  if (!big && 2 * ntiles * nmat < (1ll << 30)) {
-    // small launches (about a workgroup per compute unit or less): both kinds of workgroup in one grid
-    attn_fused_delta_kernel<D><<<dim3((d.s + 127) / 128, d.nb * d.nh, d.ndev), 256, 0, st>>>(a);
-    attn_fused_bwd_kernel<D, CAUSAL><<<dim3((unsigned)(2 * ntiles * nmat), d.ndev), 256, 0, st>>>(a, (int)ntiles, (int)nmat);
+  const long long tiles64 = (d.s + BLK - 1) / BLK, tiles128 = (d.s + 127) / 128, nmat = (long long)d.nb * d.nh;
+  const bool big = tiles128 * nmat * d.ndev >= 512;
+  const dim3 grid128((unsigned)tiles128, (unsigned)nmat, d.ndev);
+  const bool wide = D == 128 ? 2 * tiles128 * nmat >= (CAUSAL ? 512 : 256) : big;
+  if (wide && (CAUSAL || !big)) {
+    attn_fused_delta_kernel<D><<<grid128, 256, 0, st>>>(a);
+    attn_fused_bwd_wide_kernel<D, CAUSAL><<<dim3((unsigned)(2 * nmat), (unsigned)tiles128, d.ndev), 512, 0, st>>>(a);
     return;
   }
-  if (big) attn_fused_bwd_dq_kernel<D, CAUSAL, 4><<<grid_big, block_big, 0, st>>>(a);
-  else attn_fused_bwd_dq_kernel<D, CAUSAL, 2><<<grid, block, 0, st>>>(a);
-  if constexpr (D == 64) {
-    if (big) {
-      attn_fused_bwd_dkv_kernel<D, CAUSAL, 4><<<grid_big, block_big, 0, st>>>(a);
-      return;
-    }
+  if (!big) {
+    // small launches (about a workgroup per compute unit or less): both kinds of workgroup in one grid
+    attn_fused_delta_kernel<D><<<grid128, 256, 0, st>>>(a);
+    attn_fused_bwd_kernel<D, CAUSAL><<<dim3((unsigned)(2 * tiles64 * nmat), d.ndev), 256, 0, st>>>(a, (int)tiles64, (int)nmat);
+    return;
   }
-  attn_fused_bwd_dkv_kernel<D, CAUSAL, 2><<<grid, block, 0, st>>>(a);
+  // without a mask all loops are alike: one kind after the other, which saves the delta kernel and mixes no tile sizes
+  attn_fused_bwd_dq_kernel<D, CAUSAL, 4><<<grid128, 512, 0, st>>>(a);
+  if constexpr (D == 64) attn_fused_bwd_dkv_kernel<D, CAUSAL, 4><<<grid128, 512, 0, st>>>(a);   // (not causal: else wide, above)
+  else if (wide) attn_fused_bwd_dkv_wide_kernel<D, CAUSAL><<<grid128, 512, 0, st>>>(a);
+  else attn_fused_bwd_dkv_kernel<D, CAUSAL, 2><<<dim3((unsigned)tiles64, (unsigned)nmat, d.ndev), 256, 0, st>>>(a);   // many devices' blocks of few matrices
 }
 template <int D>
 void bwd_launch(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
