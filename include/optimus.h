@@ -403,7 +403,7 @@ int optimus_debug_mfma_rate(float* out, int workgroups, int iters, int random_da
 
 /* ---- tuning hooks for benchmark sweeps (no effect on results beyond summation order) ----
  * Force the matrix-core tile variant used by bf16 products: 0 = 256x256, 1 = 256x128, 2 = 128x256,
- * 3 = 128x128, 4 = alias of 0, 5 = bounds-checked 128x128, 6 = 128x64, 7 = 64x64, 8 = 256x128 and 9 = 128x256 with
+ * 3 = 128x128, 4 = alias of 0, 5 = the any-shape kernel, 6 = 128x64, 7 = 64x64, 8 = 256x128 and 9 = 128x256 with
  * four wavefronts; -1 = automatic.  1000 + v selects, for the tiles compiled with two k-loops (0, 1, 2, 8, 9), the
  * four-slab ring instead of the 64-wide stages (identical bits); 1255 = automatic tile with that loop.
  * A variant whose tile does not divide the block falls back to the bounds-checked kernel. */

@@ -113,6 +113,21 @@ int launch_reduce_partials(const float* parts, void* dst, long long n, int count
 int launch_colsum(const void* X, float* out, int rows, int cols, int ld, int nz, long long sX, long long sOut,
                   int dtype, hipStream_t stream);
 
+// column sums of bf16 blocks [rows x cols], stored one after the other per source, nz of each: sum of X, and with W also of
+// X * W (element by element)
+struct ColsumJob {
+  const void* X;
+  const void* W;   // or nullptr
+  float* sum;      // [nz][cols]
+  float* sum_w;    // [nz][cols], with W
+  int cols;
+};
+struct ColsumJobs {
+  ColsumJob j[6];
+  int n;
+};
+int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, hipStream_t stream);
+
 struct LnDesc {
   int rows, cols;  // block dims M/q, H/q
   int H;           // full hidden size

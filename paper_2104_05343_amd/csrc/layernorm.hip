@@ -283,28 +283,23 @@ __device__ __forceinline__ int cs_column(int lane) {   // the group's row-lane b
   const int g = lane / CL;
   return ((g & 1) << 2) | (g & 2) | ((g >> 2) & 1);
 }
+// one strip of one block
 template <typename T, bool PROD, int CL>
-__global__ __launch_bounds__(CS_ROWS * CL) void colsum_kernel(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out,
-                                                              float* __restrict__ out2, int rows, int cols, int ld, long long sX,
-                                                              long long sOut) {
+__device__ __forceinline__ void colsum_strip(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out, float* __restrict__ out2,
+                                             int rows, int cols, int ld, int strip, bool vec_rows, float (&red)[CS_ROWS / 8][8 * CL],
+                                             float (&red2)[CS_ROWS / 8][8 * CL]) {
   constexpr int CS_COLS = 8 * CL, GROUPS = CS_ROWS / 8;
-  __shared__ float red[GROUPS][CS_COLS];
-  __shared__ float red2[GROUPS][CS_COLS];
   const int tx = threadIdx.x & (CL - 1), ty = threadIdx.x / CL;
   const int lane = threadIdx.x & 63;
-  // workgroups are dealt round-robin to the 8 XCDs: a contiguous range of strips each (whatever XCD the entry starts on)
-  const int nwg = gridDim.x, slot = blockIdx.x >> 3, xcd = blockIdx.x & 7, rem = nwg & 7;
-  const int strip = xcd * (nwg >> 3) + (xcd < rem ? xcd : rem) + slot;
   const int c0 = strip * CS_COLS + tx * 8;
-  const long long zoff = (long long)blockIdx.y * sX;
   float acc[8], acc2[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) { acc[k] = 0.f; acc2[k] = 0.f; }
-  const bool vec = (ld % 8 == 0) && (sX % 8 == 0) && (c0 + 8 <= cols) && (((uintptr_t)X & 15) == 0) && (!PROD || ((uintptr_t)W & 15) == 0);
+  const bool vec = vec_rows && c0 + 8 <= cols;
   constexpr int IN_FLIGHT = PROD ? 4 : 8;
 #pragma unroll IN_FLIGHT
   for (int r = ty; r < rows; r += CS_ROWS) {
-    const long long off = zoff + (long long)r * ld + c0;
+    const long long off = (long long)r * ld + c0;
     float x[8], w[8];
     if (vec) {
       cs_load(X + off, x);
@@ -333,10 +328,41 @@ __global__ __launch_bounds__(CS_ROWS * CL) void colsum_kernel(const T* __restric
       float s = 0.f, s2 = 0.f;
 #pragma unroll
       for (int r = 0; r < GROUPS; ++r) { s += red[r][threadIdx.x]; if (PROD) s2 += red2[r][threadIdx.x]; }
-      out[(long long)blockIdx.y * sOut + c] = s;
-      if (PROD) out2[(long long)blockIdx.y * sOut + c] = s2;
+      out[c] = s;
+      if (PROD) out2[c] = s2;
     }
   }
+}
+// workgroups are dealt round-robin to the 8 XCDs: a contiguous range of strips each (whatever XCD the entry starts on)
+__device__ __forceinline__ int cs_place() {
+  const int nwg = gridDim.x, slot = blockIdx.x >> 3, xcd = blockIdx.x & 7, rem = nwg & 7;
+  return xcd * (nwg >> 3) + (xcd < rem ? xcd : rem) + slot;
+}
+template <typename T, bool PROD, int CL>
+__global__ __launch_bounds__(CS_ROWS * CL) void colsum_kernel(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out,
+                                                              float* __restrict__ out2, int rows, int cols, int ld, long long sX,
+                                                              long long sOut) {
+  __shared__ float red[CS_ROWS / 8][8 * CL];
+  __shared__ float red2[CS_ROWS / 8][8 * CL];
+  const bool vec_rows = (ld % 8 == 0) && (sX % 8 == 0) && (((uintptr_t)X & 15) == 0) && (!PROD || ((uintptr_t)W & 15) == 0);
+  const long long zx = (long long)blockIdx.y * sX, zo = (long long)blockIdx.y * sOut;
+  colsum_strip<T, PROD, CL>(X + zx, PROD ? W + zx : nullptr, out + zo, PROD ? out2 + zo : nullptr, rows, cols, ld, cs_place(), vec_rows, red, red2);
+}
+// Several sums in one launch: a layer's vector gradients, whose sources all live until the end of the backward pass.  As six
+// launches of 4 to 7 us each, the step of a 1024-wide layer (one device of 4 x 4) takes 268 us, as one 244.
+template <int CL>
+__global__ __launch_bounds__(CS_ROWS * CL) void colsum_jobs_kernel(const ColsumJobs jobs, int rows) {
+  __shared__ float red[CS_ROWS / 8][8 * CL];
+  __shared__ float red2[CS_ROWS / 8][8 * CL];
+  int strip = cs_place(), k = 0;
+  while (k + 1 < jobs.n && strip >= (jobs.j[k].cols + 8 * CL - 1) / (8 * CL)) strip -= (jobs.j[k++].cols + 8 * CL - 1) / (8 * CL);
+  const ColsumJob& j = jobs.j[k];
+  const long long zx = (long long)blockIdx.y * rows * j.cols, zo = (long long)blockIdx.y * j.cols;
+  const bf16_t* X = (const bf16_t*)j.X + zx;
+  const bf16_t* W = j.W ? (const bf16_t*)j.W + zx : nullptr;
+  const bool vec_rows = j.cols % 8 == 0 && (((uintptr_t)j.X | (uintptr_t)j.W) & 15) == 0;
+  if (W) colsum_strip<bf16_t, true, CL>(X, W, j.sum + zo, j.sum_w + zo, rows, j.cols, j.cols, strip, vec_rows, red, red2);
+  else colsum_strip<bf16_t, false, CL>(X, nullptr, j.sum + zo, nullptr, rows, j.cols, j.cols, strip, vec_rows, red, red2);
 }
 
 bool colsum_narrow(int rows, int cols) { return (long long)rows * cols <= (1LL << 20); }
@@ -354,6 +380,22 @@ static void colsum_launch(dim3 batch, const T* X, const T* W, float* out, float*
   else if (width >= 16 * 256) OPTIMUS_COLSUM(2);
   else OPTIMUS_COLSUM(1);
 #undef OPTIMUS_COLSUM
+}
+
+int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, hipStream_t stream) {
+  long long width = 0;
+  for (int k = 0; k < jobs.n; ++k) width += jobs.j[k].cols;
+  const int cl = width * nz >= 64 * 256 ? 8 : width * nz >= 32 * 256 ? 4 : width * nz >= 16 * 256 ? 2 : 1;   // as colsum_launch
+  unsigned strips = 0;
+  for (int k = 0; k < jobs.n; ++k) strips += (unsigned)((jobs.j[k].cols + 8 * cl - 1) / (8 * cl));
+  const dim3 grid(strips, (unsigned)nz);
+  switch (cl) {
+    case 8: hipLaunchKernelGGL(colsum_jobs_kernel<8>, grid, dim3(CS_ROWS * 8), 0, stream, jobs, rows); break;
+    case 4: hipLaunchKernelGGL(colsum_jobs_kernel<4>, grid, dim3(CS_ROWS * 4), 0, stream, jobs, rows); break;
+    case 2: hipLaunchKernelGGL(colsum_jobs_kernel<2>, grid, dim3(CS_ROWS * 2), 0, stream, jobs, rows); break;
+    default: hipLaunchKernelGGL(colsum_jobs_kernel<1>, grid, dim3(CS_ROWS), 0, stream, jobs, rows); break;
+  }
+  return hip_launch_status();
 }
 
 int launch_colsum(const void* X, float* out, int rows, int cols, int ld, int nz, long long sX, long long sOut, int dtype,
