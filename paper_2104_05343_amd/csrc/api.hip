@@ -831,6 +831,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   // the column sums are one more serial step of it, so they go to the branch (measured: the step 5 % shorter at
   // [1024 x 256] blocks).  Large blocks: the branch, with its transposing products, is the longer stream already.
   const bool ln2_grads_on_branch = ss && colsum_narrow((int)(M / q), (int)(h / q));
+  const bool sums_at_end = !ss || ln2_grads_on_branch;   // small blocks: the column sums are launches, not bytes
   optimus_epilogue e = {};
   optimus_epilogue e32 = {};
   e32.out_fp32 = 1;
@@ -851,7 +852,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   BRANCH_AFTER_MAIN(ss->ready[0]);  // d_pre_gelu is complete
   RUN(run_summa(OPTIMUS_FORM_ABT, t->d_pre_gelu, t->w1, t->d_ln2_out, M, 4 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
   RUN(run_summa(OPTIMUS_FORM_ATB, t->ln2_out, t->d_pre_gelu, t->d_w1, h, M, 4 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
-  if (ss) RUN(optimus_bias_grad(t->d_pre_gelu, t->d_b1, M, 4 * h, q, i, j, dt, gstream));
+  if (!sums_at_end) RUN(optimus_bias_grad(t->d_pre_gelu, t->d_b1, M, 4 * h, q, i, j, dt, gstream));
   // ---- LN2 backward, plus the residual branch: d_h_mid = d_out + LN2'(d_ln2_out) ----
   RUN(ln_backward(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_g,
                   ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_b, t->bstats2, ln, grid, st));
@@ -859,16 +860,15 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   BRANCH_AFTER_MAIN(ss->ready[1]);  // d_h_mid is complete
   RUN(run_summa(OPTIMUS_FORM_ABT, t->d_h_mid, t->w_o, t->d_attn, M, h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
   RUN(run_summa(OPTIMUS_FORM_ATB, t->attn, t->d_h_mid, t->d_w_o, h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
-  if (ss) RUN(optimus_bias_grad(t->d_h_mid, t->d_b_o, M, h, q, i, j, dt, gstream));
-  if (ln2_grads_on_branch) RUN(launch_ln_param_grads(t->d_ln2_out, t->xhat2, t->d_ln2_g, t->d_ln2_b, ln, gst));
+  if (!sums_at_end) RUN(optimus_bias_grad(t->d_h_mid, t->d_b_o, M, h, q, i, j, dt, gstream));
   // ---- local attention backward ----
   RUN(layer_attention(true, c, t, i, j, attn_ws, attn_bytes, stream));
   // ---- qkv = ln1_out Wqkv + b ----
   BRANCH_AFTER_MAIN(ss->ready[2]);  // d_qkv is complete
   RUN(run_summa(OPTIMUS_FORM_ABT, t->d_qkv, t->w_qkv, t->d_ln1_out, M, 3 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
   RUN(run_summa(OPTIMUS_FORM_ATB, t->ln1_out, t->d_qkv, t->d_w_qkv, h, M, 3 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
-  if (ss) RUN(optimus_bias_grad(t->d_qkv, t->d_b_qkv, M, 3 * h, q, i, j, dt, gstream));
-  if (!ss) {   // one stream: all column sums of the pass in one launch, their sources are still there
+  if (!sums_at_end) RUN(optimus_bias_grad(t->d_qkv, t->d_b_qkv, M, 3 * h, q, i, j, dt, gstream));
+  if (sums_at_end) {   // column sums in one launch, their sources are still there; on a branch without the two that would wait
     const int rows = (int)(M / q), hb = (int)(h / q);
     const long long dev = grid ? 0 : (long long)i * q + j;
     const auto job = [&](const void* X, const void* W, float* sum, float* sum_w, int k) {
@@ -876,9 +876,9 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
       return ColsumJob{off(X, at, 2), off(W, at, 2), sum + to, W ? sum_w + to : nullptr, k * hb};
     };
     const ColsumJobs jobs = {{job(t->d_pre_gelu, nullptr, t->d_b1, nullptr, 4), job(t->d_qkv, nullptr, t->d_b_qkv, nullptr, 3),
-                              job(t->d_ln2_out, t->xhat2, t->d_ln2_b, t->d_ln2_g, 1), job(t->d_ln1_out, t->xhat1, t->d_ln1_b, t->d_ln1_g, 1),
-                              job(t->d_out, nullptr, t->d_b2, nullptr, 1), job(t->d_h_mid, nullptr, t->d_b_o, nullptr, 1)}, 6};
-    RUN(launch_colsum_jobs(jobs, rows, grid ? q * q : 1, st));
+                              job(t->d_ln2_out, t->xhat2, t->d_ln2_b, t->d_ln2_g, 1), job(t->d_h_mid, nullptr, t->d_b_o, nullptr, 1),
+                              job(t->d_ln1_out, t->xhat1, t->d_ln1_b, t->d_ln1_g, 1), job(t->d_out, nullptr, t->d_b2, nullptr, 1)}, ss ? 4 : 6};
+    RUN(launch_colsum_jobs(jobs, rows, grid ? q * q : 1, gst));
   }
   // ---- LN1 backward, plus the residual branch: d_x = d_h_mid + LN1'(d_ln1_out) ----
   RUN(ln_backward(t->d_ln1_out, t->xhat1, t->rstd1, t->ln1_g, t->d_h_mid, t->d_x, ss ? t->d_ln1_g : nullptr, ss ? t->d_ln1_b : nullptr,
