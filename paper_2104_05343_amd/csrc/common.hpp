@@ -92,9 +92,9 @@ struct GemmDesc {
   int plan_for_batch;
 };
 
-int launch_gemm(const GemmDesc& d, hipStream_t stream);           // picks MFMA or generic kernel
-int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);    // scalar FMA kernel, any shape
-int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);       // bf16 matrix-core kernel
+int launch_gemm(const GemmDesc& d, hipStream_t stream);           // picks one of the two below
+int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);    // fp32, or any bf16 shape, stride and alignment
+int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);       // bf16 rows on the 16-byte grid: direct-to-LDS tiles
 bool gemm_mfma_supported(const GemmDesc& d);
 int launch_mfma_rate(float* out, int workgroups, int iters, int random_data, hipStream_t stream);   // probe.hip
 size_t gemm_plan_bytes(const GemmDesc& d);                         // workspace the planned launch wants (0: none)

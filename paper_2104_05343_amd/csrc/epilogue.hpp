@@ -1,4 +1,4 @@
-// Accumulator -> C epilogue shared by the matrix-core and the scalar product kernels
+// Accumulator -> C epilogue shared by the product kernels
 // (bias slice, GeLU, GeLU' scaling, residual; Sections 3.2.1-3.2.2 of the paper: applied locally per block).
 #pragma once
 #include "common.hpp"
