@@ -308,7 +308,9 @@ typedef struct {
  * returns, every kernel of both is ordered before later work on `stream`.
  * The library creates that stream (default priority) and its events on the
  * first call per device that is not made under stream capture; until then the
- * branch runs on `stream` itself.  They are shared by all calls on a device:
+ * branch runs on `stream` itself, as it does in every call too short for a
+ * second stream to pay unless that call is captured.  They are shared by all
+ * calls on a device:
  * optimus_layer_bwd must not be called from several host threads at once
  * for the same device.) */
 size_t optimus_layer_workspace_bytes(const optimus_layer_cfg* cfg);

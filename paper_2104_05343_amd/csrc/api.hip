@@ -400,10 +400,10 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
 // the pass waits for.  The line is drawn by the flops of the pass's products.  Measured, step of one layer, two streams /
 // one (us): 1.6 GF 250 / 150, 13 GF 307 / 240 and 315 / 247, 39 GF 308 / 368, 51 GF 303 / 347, 103 GF 440 / 522,
 // 412 GF 893 / 999; checkpointed stack of two small layers (0.8 GF each) 584 / 355.  A captured pass pays the host once
-// and keeps both streams.
+// and keeps both streams (which an earlier pass, short or not, has created).
 bool branch_pays(const optimus_layer_cfg* c, bool grid, hipStream_t caller) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(caller, &cs) != hipSuccess) (void)hipGetLastError();
+  if (hipStreamIsCapturing(caller, &cs) != hipSuccess) { (void)hipGetLastError(); cs = hipStreamCaptureStatusNone; }
   if (cs != hipStreamCaptureStatusNone) return true;
   const double devices = grid ? (double)c->q * c->q : 1.0;
   const double flops = 48.0 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
@@ -822,7 +822,8 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   LnDesc ln;
   if ((rc = ln_desc(M, h, q, i, j, dt, c->eps, &ln))) return rc;
   // gradient branch: its own stream and its own split workspace (see SideStream)
-  SideStream* ss = branch_pays(c, grid, st) ? side_stream(st) : nullptr;
+  SideStream* ss = side_stream(st);   // asked for in any case: a later call may be captured, and then it has to be there
+  if (!branch_pays(c, grid, st)) ss = nullptr;
   const int co_chain = ss ? 1 : 0, co_branch = ss ? 2 : 0;   // products planned for company only where they have it
   hipStream_t gst = ss ? ss->s : st;
   void* gstream = (void*)gst;

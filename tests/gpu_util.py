@@ -3,9 +3,12 @@
 Packing to block-major is done on the host with the oracle's block partition, so the GPU path's own
 block addressing is checked against an independent implementation.
 """
+import ctypes
+
 import numpy as np
 import torch
 
+import paper_2104_05343_amd as opt
 from oracle import blocks
 from workloads import bf16_bits, bits_to_f32
 
@@ -49,3 +52,15 @@ def empty(n, dtype):
 
 def dt(dtype):
     return {"fp32": 0, "bf16": 1}[dtype]
+
+
+def graph_forks(graph):
+    """Whether a captured graph has parallel arms: a node that more than one node waits for.  Needs keep_graph=True.  (The
+    runtime is asked through the library's own handle: the one its kernels are launched with.)"""
+    edges_of = opt.binding.lib().hipGraphGetEdges
+    edges_of.argtypes = [ctypes.c_void_p] * 4
+    n = ctypes.c_size_t()
+    assert edges_of(graph.raw_cuda_graph(), None, None, ctypes.byref(n)) == 0
+    src, dst = (ctypes.c_void_p * n.value)(), (ctypes.c_void_p * n.value)()
+    assert edges_of(graph.raw_cuda_graph(), src, dst, ctypes.byref(n)) == 0
+    return len(set(src)) < n.value

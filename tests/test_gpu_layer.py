@@ -258,8 +258,9 @@ def test_layer_errors():
 
 def test_first_call_under_graph_capture_then_eager():
     """In a fresh process the very first layer_fwd/layer_bwd calls are made while a HIP graph is being captured
-    (the library must not create its gradient-branch stream there); replays, then eager calls (which do create it),
-    then a second captured graph with the forked branch: all give the same bits."""
+    (the library must not create its gradient-branch stream there); replays, then eager calls (which do create it, although
+    a layer of this size runs on one stream when called eagerly), then a second captured graph, which has the forked
+    branch: all give the same bits."""
     import os
     import subprocess
     import sys
@@ -271,6 +272,7 @@ import torch
 import paper_2104_05343_amd as opt
 from workloads import LayerShape, layer_inputs
 from layer_util import alloc_layer
+from gpu_util import graph_forks
 shp = LayerShape(b=4, s=64, h=128, n=4, q=2)
 inp = layer_inputs(3, shp, "bf16", perturb_affine=True)
 cfg, T, lt, ws = alloc_layer(inp, shp, True)
@@ -284,15 +286,19 @@ def same(a, b):
     return all(torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)) for k in a)
 side = torch.cuda.Stream()
 with torch.cuda.stream(side):
-    g1 = torch.cuda.CUDAGraph()
+    g1 = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(g1):
         step()
+assert not graph_forks(g1)
+g1.instantiate()
 g1.replay(); r1 = snap()
 g1.replay(); r2 = snap()
 step(); e1 = snap()
-g2 = torch.cuda.CUDAGraph()
+g2 = torch.cuda.CUDAGraph(keep_graph=True)
 with torch.cuda.graph(g2):
     step()
+assert graph_forks(g2), "captured on one stream"
+g2.instantiate()
 g2.replay(); r3 = snap()
 step(); e2 = snap()
 g2.replay(); r4 = snap()

@@ -8,7 +8,7 @@ import paper_2104_05343_amd as opt
 from oracle import stack as ostack
 from oracle.metrics import rel_frobenius
 from workloads import LayerShape, layer_inputs, round_to_bf16
-from gpu_util import mat_to_dev, mat_to_host, to_host, vec_to_dev, empty
+from gpu_util import mat_to_dev, mat_to_host, to_host, vec_to_dev, empty, graph_forks
 from layer_util import alloc_layer, MAT_SHAPES, TOL_BEHIND_LOGITS
 
 pytestmark = pytest.mark.gpu
@@ -161,9 +161,11 @@ def test_stack_graph_replays_equal_eager():
         step()
     torch.cuda.current_stream().wait_stream(side)
     torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         step()
+    assert graph_forks(graph)
+    graph.instantiate()
     for replay in range(3):
         poison()
         graph.replay()
