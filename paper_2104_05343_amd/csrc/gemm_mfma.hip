@@ -137,14 +137,37 @@ bool gemm_mfma_supported(const GemmDesc& d) {
   return true;
 }
 
-// buffer addressing: per-lane byte offset (< 256 * ld * 2) plus slab byte offset (< (Kp + 64) * ld * 2) inside a 2 GiB window
-static bool window_ok(const GemmDesc& d) {
+// Buffer addressing: a lane's byte offset plus the slab's inside the resource's 2 GiB window, which starts at the tile's
+// corner of a panel.  k-contiguous operand: rows of the tile, ld apart, times the panel's length; k-strided: the panel's k
+// rows, ld apart.
+constexpr long long kWindow = 1LL << 31;
+static bool panel_in_window(bool kcontig, int ld, long long k, int rows) {
+  return 2 * (kcontig ? (long long)(rows - 1) * ld + k : (k - 1) * (long long)ld + rows) <= kWindow;
+}
+static bool panels_in_window(const GemmDesc& d) {   // as every form but the long one needs them; ragged blocks walk slabs in pairs
+  const long long k = ((long long)d.Kp + 2 * BK - 1) / (2 * BK) * (2 * BK);
+  return panel_in_window(d.a_kcontig, d.lda, k, 256) && panel_in_window(d.b_kcontig, d.ldb, k, 256);
+}
+// The long form starts a new window inside a panel of a k-strided operand: a slab of 32 k rows has to fit.  128x128 tiles.
+static bool long_panels_ok(const GemmDesc& d) {
+  const long long k = ((long long)d.Kp + 2 * BK - 1) / (2 * BK) * (2 * BK);
+  return !d.b_kcontig && panel_in_window(d.a_kcontig, d.lda, d.a_kcontig ? k : BK, 128) && panel_in_window(false, d.ldb, BK, 128);
+}
+// Panels of over 1 GiB: the any-shape kernel, whose eight wavefronts share a 64x64 tile's k, or the tiles of this file.
+// Measured, us, any-shape kernel / these.  A B, K = 32768: [512 x 1024] outputs 139 / 189, [1024 x 1024] 121 / 191,
+// [1024 x 2048] 240 / 223, [2048 x 2048] 482 / 315, [2048 x 4096] 1085 / 445; K = 131072: [2048 x 1024] 1205 / 1405,
+// [2048 x 2048] 2320 / 1433.  A^T B, second operand 2 GiB: 64 rows of output (256 tiles of 64x64) 428 / 571, 256 rows 2502 /
+// 1350.  A k-contiguous operand whose rows are 2 MiB apart (A B^T, K = 1048576): [1024 x 1024] 5642 / 14585, [2048 x 2048]
+// 23314 / 31273.
+static bool any_shape_pays(const GemmDesc& d) {
   const long long ld = d.lda > d.ldb ? d.lda : d.ldb;
-  return 512 * ld < (1LL << 30) && 2 * ((long long)d.Kp + 2 * BK) * ld < (1LL << 30);
+  if (512 * ld < (1LL << 30) && 2 * (long long)d.Kp * ld < (1LL << 30)) return false;
+  const bool rows_far = (d.a_kcontig && d.lda > (1 << 18)) || (d.b_kcontig && d.ldb > (1 << 18));
+  return rows_far || (long long)((d.Mb + 63) / 64) * ((d.Nb + 63) / 64) <= 512;
 }
 static bool variant_fits(const Variant& v, const GemmDesc& d) {
   if (d.Mb % v.BM || d.Nb % v.BN || d.Kp % (2 * BK)) return false;  // slabs are walked in pairs
-  return window_ok(d);
+  return panels_in_window(d);
 }
 // Blocks that no tile divides (64x64 is the smallest), or whose C allows no vector epilogue, take the ragged form of the
 // tiles that share a CU: edges are cut at any size there, and a cut tile of 256 rows would be mostly edge.
@@ -159,7 +182,7 @@ static bool ragged_tile(int v) { return v == 3 || v == 6 || v == 7; }
 struct Plan {
   int variant;
   int splits;
-  int ragged;  // 1: the tile's ragged form
+  int ragged;  // 1: the tile's ragged form; 2: the same for long panels
   int seq;  // 1: the split is emulated inside each workgroup (KArgs::seq_splits): same bits, no partial tiles, no combine
 };
 
@@ -182,14 +205,17 @@ static Plan make_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
   Plan best = {kAnyVariant, 1, 0, 0};
   int forced = g_variant.load();                       // one consistent view of the hooks per plan
   int forced_corun = d.corun > 0 ? g_corun_variant[d.corun - 1].load() : -1;
-  if (!window_ok(d) || forced == kAnyVariant) return best;
+  if (forced == kAnyVariant) return best;
+  const bool long_panels = !panels_in_window(d);
+  if (long_panels && !long_panels_ok(d)) return best;
+  if (forced < 0 && any_shape_pays(d)) return best;
   const bool ragged = !vec_ok || !variant_fits(kVariants[7], d);
-  if (ragged) {   // a forced tile that has no ragged form is ignored
-    best.ragged = 1;
-    if (!ragged_tile(forced)) forced = -1;
-    if (!ragged_tile(forced_corun)) forced_corun = -1;
+  const auto fits = [&](int v) { return long_panels ? v == 3 : ragged ? ragged_tile(v) : variant_fits(kVariants[v], d); };
+  if (ragged) {   // a forced tile that has no such form is ignored
+    best.ragged = long_panels ? 2 : 1;
+    if (!fits(forced)) forced = -1;
+    if (!fits(forced_corun)) forced_corun = -1;
   }
-  const auto fits = [&](int v) { return ragged ? ragged_tile(v) : variant_fits(kVariants[v], d); };
   const auto tiles_of = [&](int v) {
     return (long long)((d.Mb + kVariants[v].BM - 1) / kVariants[v].BM) * ((d.Nb + kVariants[v].BN - 1) / kVariants[v].BN);
   };
@@ -260,7 +286,7 @@ static Plan make_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
       if (!found || cost < best_cost) {
         found = true;
         best_cost = cost;
-        best = {v, sp, ragged ? 1 : 0, 0};
+        best = {v, sp, best.ragged, 0};
       }
       // A launch with many blocks has workgroups enough without the split: one workgroup then walks all the slabs of
       // its tile and adds them up range by range as the split workgroups and their combine would (identical bits).
@@ -273,7 +299,7 @@ static Plan make_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
         const float cost1 = c.fixed_us + c.out_us_per_mib * out_mib * (float)batch + (float)rounds1 * (float)slabs * t1;
         if (cost1 < best_cost) {
           best_cost = cost1;
-          best = {v, sp, ragged ? 1 : 0, 1};
+          best = {v, sp, best.ragged, 1};
         }
       }
     }
@@ -380,7 +406,7 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   long long nwg = (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits;
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
   int rc;
-  if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
+  if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, plan.ragged == 2, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   else switch (vi) {
     case 0: rc = launch_layout<256, 256, 2, 4>(d, ka, nwg, stream); break;
     case 1: rc = launch_layout<256, 128, 4, 2>(d, ka, nwg, stream); break;

@@ -97,8 +97,8 @@ struct KArgs {
   EpiArgs epi;
 };
 
-// tile variants 3, 6, 7 in their ragged form (gemm_mfma_ragged.hip)
-int launch_gemm_mfma_ragged(int variant, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
+// tile variants 3, 6, 7 in their ragged form, 3 also for long panels (gemm_mfma_ragged.hip)
+int launch_gemm_mfma_ragged(int variant, bool long_panels, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
 
 // element offset inside an LDS tile
 // The LDS of this part serves 256 bytes per clock (64 four-byte banks).  A ds_read_b128 is served 16 lanes at a
@@ -154,6 +154,9 @@ __device__ __forceinline__ i32x4 make_rsrc(const bf16_t* base) {
   const unsigned long long p = (unsigned long long)base;
   return i32x4{(int)(unsigned)p, (int)(unsigned)((p >> 32) & 0xffffu), (int)0x80000000u, 0x00020000};
 }
+
+// The most k rows of a k-strided operand, in whole slabs, that one resource reaches: (rows - 1) * ld + 128 columns of a tile.
+__device__ __forceinline__ int segment_rows(int ld) { return (int)(((1u << 30) - 128u) / (unsigned)ld + 1u) / BK * BK; }
 
 // Ragged blocks.  A lane offset of 2 GiB fails the range check of the resource whatever the slab offset: the load writes
 // zeros to LDS.  direct_cut gives it to the chunks of rows (columns) that do not exist, `left` of which do, and notes every
@@ -377,6 +380,7 @@ struct Occ {
 
 // RAG = the block is cut by the tiles, or its rows do not allow the vector epilogue everywhere: masked loads, and a
 // bounds-checked epilogue for the wavefronts on the edge.
+// LONG (with RAG) = a panel of a k-strided operand does not fit one buffer resource's window: see the load cursors.
 // PLAIN (not with RAG) = the epilogue is a bare store of the accumulator (alpha 1, no bias / activation / residual):
 // a short, fully unrolled store sequence instead of the general epilogue, whose straight-line code costs
 // microseconds per tile.
@@ -391,11 +395,12 @@ struct Loop2 {
   static constexpr int RING32 = 2 * NST;                                        // the same space in 32-wide slabs
 };
 
-template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool PLAIN, bool SEQ = false, int LOOP = 1, bool RAG = false>
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool PLAIN, bool SEQ = false, int LOOP = 1, bool RAG = false, bool LONG = false>
 __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gemm_mfma_kernel(const KArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   static_assert(!SEQ || !PLAIN, "the range-wise accumulation exists with the full epilogue");
   static_assert(!RAG || (LOOP == 1 && !PLAIN), "ragged blocks: the four-slab ring, the full epilogue");
+  static_assert(!LONG || RAG, "long panels: the ragged form");
   using T = Tile<BM, BN, WM, WN>;
   constexpr int THREADS = T::THREADS, NW = T::NW;
   constexpr int TM = T::TM, TN = T::TN, MI = T::MI, NI = T::NI;
@@ -711,27 +716,60 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
         direct_cut<BM, AKC, NW, PA>(offA, kinA, a.Mb - m0, wave, lane);
         direct_cut<BN, BKC, NW, PB>(offB, kinB, a.Nb - n0, wave, lane);
       }
-      // one load cursor per operand: panel, k offset, buffer resource of the panel, byte offset inside the panel
+      // one load cursor per operand: panel, k offset, buffer resource of the panel, byte offset inside the panel.  LONG: the
+      // panels of a k-strided operand are walked in segments of k rows, each with a resource of its own.
       constexpr int KA = AKC ? 2 * BK : BK, KB = BKC ? 2 * BK : BK;  // k advance per issue
       const unsigned stepA = (unsigned)(AKC ? KA : KA * a.lda) * 2u;
       const unsigned stepB = (unsigned)(BKC ? KB : KB * a.ldb) * 2u;
       int lqa = l, kqa = k0, lqb = l, kqb = k0;
       i32x4 ra = make_rsrc(Atile + lqa * a.sAl), rb = make_rsrc(Btile + lqb * a.sBl);
       unsigned sa = (unsigned)(AKC ? kqa : kqa * a.lda) * 2u, sb = (unsigned)(BKC ? kqb : kqb * a.ldb) * 2u;
+      constexpr bool SEGA = LONG && !AKC, SEGB = LONG && !BKC;
+      [[maybe_unused]] int endA = Kw, endB = Kw;
+      [[maybe_unused]] auto segment = [&](i32x4& r, unsigned& off, int& end, const bf16_t* panel, int k, int ld, int seg) {
+        r = make_rsrc(panel + (long long)k * ld);
+        off = 0;
+        end = Kw - k > seg ? k + seg : Kw;
+      };
+      int segA = 0, segB = 0;
+      if constexpr (SEGA) { segA = segment_rows(a.lda); segment(ra, sa, endA, Atile + lqa * a.sAl, kqa, a.lda, segA); }
+      if constexpr (SEGB) { segB = segment_rows(a.ldb); segment(rb, sb, endB, Btile + lqb * a.sBl, kqb, a.ldb, segB); }
       const int nslab = t_hi - t_lo;
+#define OPTIMUS_NEXT_A()                                                               \
+  do {                                                                                 \
+    kqa += KA;                                                                         \
+    if constexpr (SEGA) {                                                              \
+      if (kqa >= endA) {                                                               \
+        if (kqa >= Kw) { kqa = 0; ++lqa; }                                             \
+        segment(ra, sa, endA, Atile + lqa * a.sAl, kqa, a.lda, segA);                  \
+      } else sa += stepA;                                                              \
+    } else {                                                                           \
+      if (kqa >= Kw) { kqa = 0; ++lqa; sa = 0; ra = make_rsrc(Atile + lqa * a.sAl); }  \
+      else sa += stepA;                                                                \
+    }                                                                                  \
+  } while (0)
+#define OPTIMUS_NEXT_B()                                                               \
+  do {                                                                                 \
+    kqb += KB;                                                                         \
+    if constexpr (SEGB) {                                                              \
+      if (kqb >= endB) {                                                               \
+        if (kqb >= Kw) { kqb = 0; ++lqb; }                                             \
+        segment(rb, sb, endB, Btile + lqb * a.sBl, kqb, a.ldb, segB);                  \
+      } else sb += stepB;                                                              \
+    } else {                                                                           \
+      if (kqb >= Kw) { kqb = 0; ++lqb; sb = 0; rb = make_rsrc(Btile + lqb * a.sBl); }  \
+      else sb += stepB;                                                                \
+    }                                                                                  \
+  } while (0)
 #define OPTIMUS_ISSUE_A(DST)                                                         \
   do {                                                                               \
     direct_issue<RAG, PA>(ra, sa, offA, kinA, a.Kp - kqa, DST, wave);                \
-    kqa += KA;                                                                       \
-    if (kqa >= Kw) { kqa = 0; ++lqa; sa = 0; ra = make_rsrc(Atile + lqa * a.sAl); } \
-    else sa += stepA;                                                                \
+    OPTIMUS_NEXT_A();                                                                \
   } while (0)
 #define OPTIMUS_ISSUE_B(DST)                                                         \
   do {                                                                               \
     direct_issue<RAG, PB>(rb, sb, offB, kinB, a.Kp - kqb, DST, wave);                \
-    kqb += KB;                                                                       \
-    if (kqb >= Kw) { kqb = 0; ++lqb; sb = 0; rb = make_rsrc(Btile + lqb * a.sBl); } \
-    else sb += stepB;                                                                \
+    OPTIMUS_NEXT_B();                                                                \
   } while (0)
       // pair P (0/1) of the k-contiguous operands; slab S (0..3) of the k-strided ones
 #define OPTIMUS_ISSUE_KC(P)                                                          \
@@ -828,16 +866,8 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
       // cursor advance once a group is out: every operand that had loads in it
 #define OPTIMUS_ADVANCE(ODD)                                                                  \
   do {                                                                                        \
-    if constexpr ((ODD) || !AKC) {                                                            \
-      kqa += KA;                                                                              \
-      if (kqa >= Kw) { kqa = 0; ++lqa; sa = 0; ra = make_rsrc(Atile + lqa * a.sAl); }         \
-      else sa += stepA;                                                                       \
-    }                                                                                         \
-    if constexpr ((ODD) || !BKC) {                                                            \
-      kqb += KB;                                                                              \
-      if (kqb >= Kw) { kqb = 0; ++lqb; sb = 0; rb = make_rsrc(Btile + lqb * a.sBl); }         \
-      else sb += stepB;                                                                       \
-    }                                                                                         \
+    if constexpr ((ODD) || !AKC) OPTIMUS_NEXT_A();                                            \
+    if constexpr ((ODD) || !BKC) OPTIMUS_NEXT_B();                                            \
   } while (0)
       // S = slab position (0..3) of slab i; the previous step's group refills position (S + 3) & 3.
       // ST = 1: steady state, i >= 4 and i + 8 <= nslab at the top of the four steps: every group exists, so every
@@ -930,6 +960,8 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
 #undef OPTIMUS_DMA_SLOT
 #undef OPTIMUS_DMA_N
 #undef OPTIMUS_ADVANCE
+#undef OPTIMUS_NEXT_A
+#undef OPTIMUS_NEXT_B
 #undef OPTIMUS_ISSUE_KS
 #undef OPTIMUS_ISSUE_KC
 #undef OPTIMUS_ISSUE_A

@@ -40,6 +40,28 @@ def test_panel_split_depends_on_the_block_shape_only(case):
                     assert p[0] not in (0, 4)  # the 256x256 tile has no registers for a second accumulator set
 
 
+# panels up to the 2 GiB that the loads of a full tile reach from its corner (k-strided operand: panel length times row
+# length; k-contiguous: rows of the tile times row length): the same plan as a little shorter
+@pytest.mark.parametrize("form,M,K,N,shorter", [("atb", 4096, 23168, 23168, 23104), ("ab", 4096, 23168, 2048, 23104),
+                                                ("atb", 1024, 65536, 16384, 65472), ("ab", 4096, 131072, 4096, 131008)])
+def test_panels_inside_the_load_window_take_a_full_tile(form, M, K, N, shorter):
+    p = plan(form, M, K, N, 1, 0, 0)
+    assert p[0] != 5 and p == plan(form, M, shorter, N, 1, 0, 0)
+
+
+# longer panels: the tiles that walk a panel in several windows, not the any-shape kernel
+@pytest.mark.parametrize("form,M,K,N,q", [("atb", 1024, 65600, 16384, 1), ("ab", 2048, 65536, 32768, 1), ("atb", 128, 80000, 66048, 2),
+                                          ("atb", 8192, 8192, 151936, 1), ("atb", 4194368, 128, 256, 1), ("ab", 512, 1024, 4194368, 1)])
+def test_panels_beyond_the_load_window(form, M, K, N, q):
+    assert plan(form, M, K, N, q, 0, 0)[0] in (3, 6, 7)
+
+
+# few tiles and long panels, or rows far apart: the any-shape kernel
+@pytest.mark.parametrize("form,M,K,N", [("ab", 512, 32768, 1024), ("abt", 1024, 1 << 20, 1024), ("atb", 64, 65600, 16384), ("abt", 1024, 4194368, 1024)])
+def test_few_tiles_of_panels_over_a_gib(form, M, K, N):
+    assert plan(form, M, K, N, 1, 0, 0)[0] == 5
+
+
 def test_no_split_without_panels_and_errors():
     # q = 1: one panel, nothing to split
     assert plan("ab", 2048, 4096, 1024, 1, 0, 0)[1] == 1
