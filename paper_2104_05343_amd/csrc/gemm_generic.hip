@@ -12,191 +12,16 @@
 //   64x64 tile: eight wavefronts, 32x32 outputs each, wavefronts 0-3 on the first half of every slab, 4-7 on the second.
 //   32x32 tile: the eight wavefronts share the output and take one eighth of every slab each; outputs too small to give
 //   every CU a 64x64 tile then still use all CUs.
-// Both tiles keep the sums of the eight parts of the slabs apart and add them in the same order at the end, so the tile
+// All tiles keep the sums of the eight parts of the slabs apart and add them in the same order at the end, so the tile
 // choice, and with it whole-grid against one-device launches, changes no bit.
+// Short panels in launches that fill the chip: gemm_short.hip.
 //
 // Measured (fp32, 1024-wide layer on a 4 x 4 grid, one device): [1024 x 1024 x 1024] blocks 29 us (64x64 tiles, 74 TFLOP/s),
 // [1024 x 4096 x 256] blocks 32 us (32x32 tiles, 67 TFLOP/s); scalar fused multiply-adds on 64x64 tiles took 180 and 733 us.
 // With one wavefront per SIMD and slabs of 128 bytes 39 and 57 us; with bounds arithmetic in every slab 36 and 45 us.
-#include <type_traits>
-
-#include "common.hpp"
-#include "epilogue.hpp"
+#include "gemm_any.hpp"
 
 namespace optimus {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 gbf16x8;
-typedef __attribute__((ext_vector_type(16))) float gf32x16;
-typedef __attribute__((ext_vector_type(4))) short gs16x4;
-typedef __attribute__((ext_vector_type(8))) short gs16x8;
-
-struct GArgs {
-  const void* A;
-  const void* B;
-  int Mb, Nb, Kp, nl;
-  int lda, ldb;
-  long long sAl, sBl;
-  int nz0;
-  long long sA0, sA1, sB0, sB1, sC0, sC1, sBias0;
-  int tiles_m, tiles_n;
-  int skip_upper, k_hi_diag, k_lo_diag;
-  EpiArgs epi;
-};
-
-__device__ const uint4 g_zero_chunk[1] = {};
-typedef unsigned gu32x4 __attribute__((ext_vector_type(4), aligned(2)));        // a chunk at any alignment of the element type
-typedef __attribute__((address_space(1))) gu32x4 gchunk;
-
-constexpr int GT_THREADS = 512;
-
-// One operand's slab of ROWS rows (or columns) by 256 bytes of k, in LDS:
-//   KC (k contiguous in memory): [ROWS][256 bytes + 16]; a fragment read is 16 bytes of one row, and 16 rows at a pitch of
-//     68 banks cover the 64 banks once.
-//   !KC, fp32: [64 k][ROWS + 8 floats]; a fragment read is one float per lane, the two half-waves four k-rows apart.
-//   !KC, bf16: [128 k][ROWS], 16-column granules XOR 2 * (k & 3), read with the transposing ds_read_b64_tr_b16.
-template <typename T, int ROWS, bool KC, bool TINY>
-struct Slab {
-  static constexpr int E = 16 / (int)sizeof(T);       // elements per 16-byte chunk
-  static constexpr int KS = 256 / (int)sizeof(T);     // k per slab
-  static constexpr int CHUNKS = ROWS * 16 / GT_THREADS;  // chunks per thread
-  static constexpr int BYTES = KC ? ROWS * 272 : (sizeof(T) == 4 ? KS * (ROWS + 8) * 4 : KS * ROWS * 2);
-
-  // element offset of the chunk from the slab's origin, and its place in the tile
-  static __device__ __forceinline__ void place(int tid, int it, int& row, int& k) {
-    const int c = tid + it * GT_THREADS;
-    if (KC) { row = c >> 4; k = (c & 15) * E; }
-    else { k = c / (ROWS / E); row = (c % (ROWS / E)) * E; }
-  }
-  static __device__ __forceinline__ int lds_off(int row, int k) {   // bytes
-    if (KC) return row * 272 + k * (int)sizeof(T);
-    if (sizeof(T) == 4) return (k * (ROWS + 8) + row) * 4;
-    return (k * ROWS + ((((row >> 4) ^ (((k & 3) << 1) & (ROWS / 16 - 1)))) << 4) + (row & 15)) * 2;
-  }
-  static_assert(CHUNKS * GT_THREADS * E == ROWS * KS && KS * (int)sizeof(T) == 256, "the threads' chunks cover the slab once");
-
-  // The chunks of a slab that exists in full: one per-lane offset (bytes) per chunk, computed once, behind a uniform base.
-  static __device__ __forceinline__ void offsets(unsigned (&off)[CHUNKS], int ld, int tid) {
-#pragma unroll
-    for (int it = 0; it < CHUNKS; ++it) {
-      int row, k;
-      place(tid, it, row, k);
-      off[it] = (unsigned)((KC ? row * ld + k : k * ld + row) * (int)sizeof(T));
-    }
-  }
-  static __device__ __forceinline__ void load_full(uint4 (&r)[CHUNKS], const T* origin, const unsigned (&off)[CHUNKS]) {
-    const __attribute__((address_space(1))) char* base = (const __attribute__((address_space(1))) char*)origin;
-#pragma unroll
-    for (int it = 0; it < CHUNKS; ++it) {
-      const gu32x4 v = *(const gchunk*)(base + off[it]);
-      r[it] = make_uint4(v[0], v[1], v[2], v[3]);
-    }
-  }
-  static __device__ __forceinline__ void store_full(const uint4 (&r)[CHUNKS], char* lds, int tid) {
-#pragma unroll
-    for (int it = 0; it < CHUNKS; ++it) {
-      int row, k;
-      place(tid, it, row, k);
-      *(uint4*)(lds + lds_off(row, k)) = r[it];
-    }
-  }
-  // Requests the chunks of a slab of which rows_left rows and k_left k exist.  Every lane issues every load, so that the
-  // compiler can count the loads in flight: chunks that do not exist come from a block of zeros, and a chunk that the end
-  // of a row cuts is fetched so that it ends there (store() shifts it into place).  Where a row may be shorter than a chunk
-  // (TINY) cut chunks are left to store() altogether.
-  static __device__ __forceinline__ void load(uint4 (&r)[CHUNKS], const T* origin, int ld, int rows_left, int k_left, int tid) {
-#pragma unroll
-    for (int it = 0; it < CHUNKS; ++it) {
-      int row, k;
-      place(tid, it, row, k);
-      const int run = KC ? k_left - k : rows_left - row;             // elements that exist along the chunk
-      const bool across = KC ? row < rows_left : k < k_left;
-      const int back = run < E ? E - run : 0;
-      const T* p = origin + (KC ? (long long)row * ld + k : (long long)k * ld + row) - back;
-      const bool there = across && run > 0 && !(TINY && back);
-      const gchunk* src = there ? (const gchunk*)p : (const gchunk*)g_zero_chunk;
-      const gu32x4 v = *src;
-      r[it] = make_uint4(v[0], v[1], v[2], v[3]);
-    }
-  }
-  static __device__ __forceinline__ void store(uint4 (&r)[CHUNKS], char* lds, const T* origin, int ld, int rows_left, int k_left, int tid) {
-    const int len = KC ? k_left : rows_left;                         // uniform: does the end of the rows cut a chunk here?
-    const bool cut = len < (KC ? KS : ROWS) && len % E != 0;
-#pragma unroll
-    for (int it = 0; it < CHUNKS; ++it) {
-      int row, k;
-      place(tid, it, row, k);
-      if (cut) {
-        const int run = KC ? k_left - k : rows_left - row;
-        const bool across = KC ? row < rows_left : k < k_left;
-        if (across && run > 0 && run < E) {
-          if constexpr (TINY) {
-            const T* p = origin + (KC ? (long long)row * ld + k : (long long)k * ld + row);
-            T e[E];
-#pragma unroll
-            for (int c = 0; c < E; ++c) e[c] = c < run ? p[c] : (T)0;
-            __builtin_memcpy(&r[it], e, 16);
-          } else {
-            const int bits = (E - run) * (int)sizeof(T) * 8;         // 16 .. 112
-            const unsigned long long lo = r[it].x | ((unsigned long long)r[it].y << 32), hi = r[it].z | ((unsigned long long)r[it].w << 32);
-            const unsigned long long nlo = bits >= 64 ? hi >> (bits - 64) : (lo >> bits) | (hi << (64 - bits)), nhi = bits >= 64 ? 0ull : hi >> bits;
-            r[it] = make_uint4((unsigned)nlo, (unsigned)(nlo >> 32), (unsigned)nhi, (unsigned)(nhi >> 32));
-          }
-        }
-      }
-      *(uint4*)(lds + lds_off(row, k)) = r[it];
-    }
-  }
-  // this lane's share of part s (0 .. 7) of the slab for the 32 rows from r0: eight k of an fp32 operand (lanes 0-31 take the
-  // first four of them, lanes 32-63 the last four), or sixteen k of a bf16 operand (eight each)
-  static __device__ __forceinline__ void frag(float (&f)[4], const char* lds, int r0, int s, int lane) {
-    if (KC) {
-      const float4 v = *(const float4*)(lds + lds_off(r0 + (lane & 31), s * 8 + (lane >> 5) * 4));
-      f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) f[t] = *(const float*)(lds + lds_off(r0 + (lane & 31), s * 8 + (lane >> 5) * 4 + t));
-    }
-  }
-  static __device__ __forceinline__ void frag(gbf16x8& f, const char* lds, int r0, int s, int lane) {
-    if (KC) {
-      f = *(const gbf16x8*)(lds + lds_off(r0 + (lane & 31), s * 16 + (lane >> 5) * 8));
-    } else {
-#if defined(__HIP_DEVICE_COMPILE__)
-      const int lg = lane & 15;
-      const char* p0 = lds + lds_off(r0 + (((lane >> 4) & 1) << 4) + ((lg & 3) << 2), s * 16 + ((lane >> 5) << 3) + (lg >> 2));
-      const char* p1 = p0 + 4 * ROWS * 2;   // four k further: same swizzle term
-      gs16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) gs16x4*)p0);
-      gs16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) gs16x4*)p1);
-      f = __builtin_bit_cast(gbf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-#endif
-    }
-  }
-};
-
-// one eighth of a slab for a 32x32 output: operands swapped, so that a lane ends up with four consecutive columns of one row
-template <typename SA, typename SB>
-__device__ __forceinline__ void eighth(gf32x16& acc, const char* la, const char* lb, int rm, int rn, int s, int lane) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  if constexpr (SA::E == 4) {
-    float fa[4], fb[4];
-    SA::frag(fa, la, rm, s, lane);
-    SB::frag(fb, lb, rn, s, lane);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[t], fa[t], acc, 0, 0, 0);
-  } else {
-    gbf16x8 fa, fb;
-    SA::frag(fa, la, rm, s, lane);
-    SB::frag(fb, lb, rn, s, lane);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb, fa, acc, 0, 0, 0);
-  }
-#endif
-}
-
-// LDS traffic of this wavefront done, then the barrier: unlike __syncthreads() it leaves the slab loads in flight
-#define OPTIMUS_LDS_BARRIER()                                        \
-  do {                                                               \
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  \
-  } while (0)
 
 template <typename T, int BT, bool AKC, bool BKC, bool TINY>
 __global__ __launch_bounds__(GT_THREADS, 2) void gemm_any_kernel(const GArgs a) {
@@ -385,11 +210,23 @@ int launch_gemm_generic(const GemmDesc& d, hipStream_t stream) {
   const int chunk = d.dtype == OPTIMUS_BF16 ? 8 : 4;
   const bool tiny = (d.a_kcontig ? d.Kp : d.Mb) < chunk || (d.b_kcontig ? d.Kp : d.Nb) < chunk;   // rows shorter than a 16-byte load
   const bool wide = !tiny && (long long)((d.Mb + 63) / 64) * ((d.Nb + 63) / 64) * nz >= 192;
-  const int bt = wide ? 64 : 32;
+  // The short kernel where two of its slabs hold a panel and the launch has a tile for every CU, and, up to half of the other
+  // kernel's slabs, where at most three of its slabs stand for one of those and CUs get several tiles.  Measured, us, fp32,
+  // gemm_any_kernel / short.  [2046 x 2046] outputs, one panel: Kp = 16 27.4 / 13.0, 32 27.3 / 16.0, 48 27.2 / 19.0, 64 26.2 /
+  // 21.1; 16 blocks of four panels each: 16 594 / 159, 32 595 / 286, 48 594 / 504, 64 540 / 647, 96 934 / 875.  16 blocks of
+  // [256 x 256], four panels: 16 11.1 / 6.7, 32 11.2 / 9.8, 48 11.3 / 13.7.  (Scalar fused multiply-adds on 64x64 tiles, slabs
+  // of 16: [2046 x 2046], one panel, 16 13.8; 16 blocks 16 230, 48 502.)
+  const int ks = d.dtype == OPTIMUS_BF16 ? 32 : 16, slabs = (d.Kp + ks - 1) / ks;
+  const long long tiles64 = (long long)((d.Mb + 63) / 64) * ((d.Nb + 63) / 64) * nz;
+  const bool brief = (d.a_kcontig || !d.b_kcontig) &&
+                     ((slabs <= (tiny ? 1 : 2) && tiles64 >= 256) ||
+                      (!tiny && slabs <= 8 && slabs <= 3 * ((slabs + 3) / 4) && tiles64 >= 1024 && d.Mb >= 64 && d.Nb >= 64));
+  const int bt = wide || brief ? 64 : 32;
   a.tiles_m = (d.Mb + bt - 1) / bt;
   a.tiles_n = (d.Nb + bt - 1) / bt;
   const long long nwg = (long long)a.tiles_m * a.tiles_n * nz;
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
+  if (brief) return launch_gemm_short(a, d, tiny, (unsigned)nwg, stream);
   if (d.dtype == OPTIMUS_BF16) launch_type<bf16_t>(a, d, wide, tiny, (unsigned)nwg, stream);
   else launch_type<float>(a, d, wide, tiny, (unsigned)nwg, stream);
   return hip_launch_status();
