@@ -247,17 +247,18 @@ int launch_ln_bwd_apply(const void* dY, const void* xhat, const float* rstd, con
 }
 
 // ---- column sums over the rows of a block: dgamma/dbeta partials, bias gradients ----
-// 128 row lanes; a thread accumulates 8 adjacent columns (16-byte loads) over rows ty, ty + 128, ...  Groups of eight row
-// lanes are added by butterfly exchanges, the 16 groups through LDS in order.  A workgroup covers CL column lanes.
-// Bound: memory round trips and CUs in use, not bytes.  The blocks have thousands of rows and a few hundred to a few
-// thousand columns, so strips of whole 128-byte lines give 4 to 64 workgroups, each with a long chain of loads.  Strips
-// of 8 columns (CL = 1) give up whole lines per wavefront for workgroups; the strips that share a line run on the same
-// XCD, one after the other in its range, and find the line in its L2.  The order of the additions does not depend on CL,
-// so a launch over many blocks may take wider strips than a launch over one and get the same bits.
-// Measured (one launch alone, strips of 64 or 32 columns, fp32 element by element / now): fp32 [1024 x 256] 16.5 / 5.1 us,
-// with products 31 / 7.2 us; bf16 [64 x 128] and the like 3.5 us, a launch's length.  Strips of 8 columns for whole-grid
-// launches too (16 blocks of [1024 x 256]) made the four-layer stack 5 % longer: 128-byte lines in eight pieces.
-constexpr int CS_ROWS = 128;
+// ROWS = 128 or 256 row lanes; a row lane accumulates 8 adjacent columns (16-byte loads) over rows y, y + ROWS, ...  Groups of
+// eight row lanes are added by butterfly exchanges, the groups through LDS in order (256 row lanes: group r and group r + 16
+// first).  A workgroup covers CL column lanes; a thread is PER row lanes: one, or y and y + ROWS / 2.
+// Bound: memory round trips, CUs and loads in flight, not bytes.  The blocks have thousands of rows and a few hundred to a few
+// thousand columns, so strips of whole 128-byte lines (CL = 8) give 4 to 64 workgroups, each with a long chain of loads, and
+// strips of 8 columns (CL = 1) fetch every line eight times (the strips that share a line run on the same XCD, one after the
+// other in its range, and find it in its L2).  The order of the additions depends on ROWS but not on CL: ROWS follows the
+// block's shape and CL the launch, and a launch over many blocks gets the same bits as one over a single block.
+// Measured, us, bf16, ROWS and CL of 128 and 8, 128 and 1 / as chosen below: [1024 x 256] 4.7, 4.2 / 4.1, 16 blocks of it 4.9,
+// 5.2 / 4.4, 16 of [1024 x 1024] 5.6, 11.5 / 5.6, [4096 x 512] 8.7, 8.5 / 5.8, [4096 x 2048] 8.7, 10.8 / 6.6, 16 of [8192 x 64]
+// 14.2, 30.0 / 10.8, [32768 x 4096] 101, 109 / 69, [1000 x 250] 12.7, 13.6 / 6.7.  fp32 [1024 x 256] 4.5, 3.7 / 3.7, with products
+// 5.1, 3.3 / 3.3.
 template <typename T>
 __device__ __forceinline__ void cs_load(const T* p, float (&f)[8]) {
   Vec<T>::load(p, f);
@@ -283,118 +284,176 @@ __device__ __forceinline__ int cs_column(int lane) {   // the group's row-lane b
   const int g = lane / CL;
   return ((g & 1) << 2) | (g & 2) | ((g >> 2) & 1);
 }
+// one row's 8 columns from c0 on
+template <typename T, bool PROD>
+__device__ __forceinline__ void cs_add(float (&acc)[8], float (&acc2)[8], const T* __restrict__ X, const T* __restrict__ W, long long off,
+                                       bool vec, int c0, int cols) {
+  float x[8], w[8];
+  if (vec) {
+    cs_load(X + off, x);
+    if (PROD) cs_load(W + off, w);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      bool in = c0 + k < cols;
+      x[k] = in ? Vec<T>::ld1(X + off + k) : 0.f;
+      if (PROD) w[k] = in ? Vec<T>::ld1(W + off + k) : 0.f;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    acc[k] += x[k];                      // sum x           (dbeta / bias gradient)
+    if (PROD) acc2[k] += x[k] * w[k];    // sum x*w         (dgamma)
+  }
+}
 // one strip of one block
-template <typename T, bool PROD, int CL>
+template <typename T, bool PROD, int ROWS, int CL, int PER>
 __device__ __forceinline__ void colsum_strip(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out, float* __restrict__ out2,
-                                             int rows, int cols, int ld, int strip, bool vec_rows, float (&red)[CS_ROWS / 8][8 * CL],
-                                             float (&red2)[CS_ROWS / 8][8 * CL]) {
-  constexpr int CS_COLS = 8 * CL, GROUPS = CS_ROWS / 8;
+                                             int rows, int cols, int ld, int strip, bool vec_rows, float (&red)[ROWS / 8][8 * CL],
+                                             float (&red2)[ROWS / 8][8 * CL]) {
+  constexpr int CS_COLS = 8 * CL, GROUPS = ROWS / 8;
   const int tx = threadIdx.x & (CL - 1), ty = threadIdx.x / CL;
   const int lane = threadIdx.x & 63;
   const int c0 = strip * CS_COLS + tx * 8;
-  float acc[8], acc2[8];
+  float acc[8], acc2[8], bcc[8], bcc2[8];   // bcc: the thread's second row lane
 #pragma unroll
-  for (int k = 0; k < 8; ++k) { acc[k] = 0.f; acc2[k] = 0.f; }
+  for (int k = 0; k < 8; ++k) { acc[k] = 0.f; acc2[k] = 0.f; bcc[k] = 0.f; bcc2[k] = 0.f; }
   const bool vec = vec_rows && c0 + 8 <= cols;
-  constexpr int IN_FLIGHT = PROD ? 4 : 8;
+  constexpr int LANES = ROWS / PER;
+  constexpr int IN_FLIGHT = (PROD || (ROWS == 256 && CL == 4) ? 4 : 8) / PER;   // (256 x 4 with eight: 22 us instead of 14)
+  int r = ty;
 #pragma unroll IN_FLIGHT
-  for (int r = ty; r < rows; r += CS_ROWS) {
+  for (; r + (PER - 1) * LANES < rows; r += ROWS) {
     const long long off = (long long)r * ld + c0;
-    float x[8], w[8];
-    if (vec) {
-      cs_load(X + off, x);
-      if (PROD) cs_load(W + off, w);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        bool in = c0 + k < cols;
-        x[k] = in ? Vec<T>::ld1(X + off + k) : 0.f;
-        if (PROD) w[k] = in ? Vec<T>::ld1(W + off + k) : 0.f;
-      }
+    cs_add<T, PROD>(acc, acc2, X, W, off, vec, c0, cols);
+    if constexpr (PER == 2) {
+      cs_add<T, PROD>(bcc, bcc2, X, W, off + (long long)LANES * ld, vec, c0, cols);
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      acc[k] += x[k];                      // sum x           (dbeta / bias gradient)
-      if (PROD) acc2[k] += x[k] * w[k];    // sum x*w         (dgamma)
-    }
+  }
+  if (PER == 2 && r < rows) {
+    const long long off = (long long)r * ld + c0;
+    cs_add<T, PROD>(acc, acc2, X, W, off, vec, c0, cols);
   }
   const int k = cs_column<CL>(lane);
   red[ty >> 3][tx * 8 + k] = cs_group<CL>(acc, lane);
   if (PROD) red2[ty >> 3][tx * 8 + k] = cs_group<CL>(acc2, lane);
+  if constexpr (PER == 2) {
+    red[(ty + LANES) >> 3][tx * 8 + k] = cs_group<CL>(bcc, lane);
+    if (PROD) red2[(ty + LANES) >> 3][tx * 8 + k] = cs_group<CL>(bcc2, lane);
+  }
   __syncthreads();
   if (threadIdx.x < CS_COLS) {
     int c = strip * CS_COLS + threadIdx.x;
     if (c < cols) {
       float s = 0.f, s2 = 0.f;
 #pragma unroll
-      for (int r = 0; r < GROUPS; ++r) { s += red[r][threadIdx.x]; if (PROD) s2 += red2[r][threadIdx.x]; }
+      for (int r = 0; r < 16; ++r) {
+        s += GROUPS == 16 ? red[r][threadIdx.x] : red[r][threadIdx.x] + red[r + GROUPS - 16][threadIdx.x];
+        if (PROD) s2 += GROUPS == 16 ? red2[r][threadIdx.x] : red2[r][threadIdx.x] + red2[r + GROUPS - 16][threadIdx.x];
+      }
       out[c] = s;
       if (PROD) out2[c] = s2;
     }
   }
 }
-// workgroups are dealt round-robin to the 8 XCDs: a contiguous range of strips each (whatever XCD the entry starts on)
+// workgroups are dealt round-robin to the 8 XCDs: a contiguous range of strips each (whatever XCD the entry starts on), unless
+// a strip is whole lines, which no other shares
+template <int CL>
 __device__ __forceinline__ int cs_place() {
+  if (CL == 8) return blockIdx.x;
   const int nwg = gridDim.x, slot = blockIdx.x >> 3, xcd = blockIdx.x & 7, rem = nwg & 7;
   return xcd * (nwg >> 3) + (xcd < rem ? xcd : rem) + slot;
 }
-template <typename T, bool PROD, int CL>
-__global__ __launch_bounds__(CS_ROWS * CL) void colsum_kernel(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out,
+template <typename T, bool PROD, int ROWS, int CL, int PER>
+__global__ __launch_bounds__(ROWS / PER * CL) void colsum_kernel(const T* __restrict__ X, const T* __restrict__ W, float* __restrict__ out,
                                                               float* __restrict__ out2, int rows, int cols, int ld, long long sX,
                                                               long long sOut) {
-  __shared__ float red[CS_ROWS / 8][8 * CL];
-  __shared__ float red2[CS_ROWS / 8][8 * CL];
+  __shared__ float red[ROWS / 8][8 * CL];
+  __shared__ float red2[ROWS / 8][8 * CL];
   const bool vec_rows = (ld % 8 == 0) && (sX % 8 == 0) && (((uintptr_t)X & 15) == 0) && (!PROD || ((uintptr_t)W & 15) == 0);
   const long long zx = (long long)blockIdx.y * sX, zo = (long long)blockIdx.y * sOut;
-  colsum_strip<T, PROD, CL>(X + zx, PROD ? W + zx : nullptr, out + zo, PROD ? out2 + zo : nullptr, rows, cols, ld, cs_place(), vec_rows, red, red2);
+  colsum_strip<T, PROD, ROWS, CL, PER>(X + zx, PROD ? W + zx : nullptr, out + zo, PROD ? out2 + zo : nullptr, rows, cols, ld, cs_place<CL>(), vec_rows, red, red2);
 }
 // Several sums in one launch: a layer's vector gradients, whose sources all live until the end of the backward pass.  As six
 // launches of 4 to 7 us each, the step of a 1024-wide layer (one device of 4 x 4) takes 268 us, as one 244.
-template <int CL>
-__global__ __launch_bounds__(CS_ROWS * CL) void colsum_jobs_kernel(const ColsumJobs jobs, int rows) {
-  __shared__ float red[CS_ROWS / 8][8 * CL];
-  __shared__ float red2[CS_ROWS / 8][8 * CL];
-  int strip = cs_place(), k = 0;
+template <int ROWS, int CL, int PER>
+__global__ __launch_bounds__(ROWS / PER * CL) void colsum_jobs_kernel(const ColsumJobs jobs, int rows) {
+  __shared__ float red[ROWS / 8][8 * CL];
+  __shared__ float red2[ROWS / 8][8 * CL];
+  int strip = cs_place<CL>(), k = 0;
   while (k + 1 < jobs.n && strip >= (jobs.j[k].cols + 8 * CL - 1) / (8 * CL)) strip -= (jobs.j[k++].cols + 8 * CL - 1) / (8 * CL);
   const ColsumJob& j = jobs.j[k];
   const long long zx = (long long)blockIdx.y * rows * j.cols, zo = (long long)blockIdx.y * j.cols;
   const bf16_t* X = (const bf16_t*)j.X + zx;
   const bf16_t* W = j.W ? (const bf16_t*)j.W + zx : nullptr;
   const bool vec_rows = j.cols % 8 == 0 && (((uintptr_t)j.X | (uintptr_t)j.W) & 15) == 0;
-  if (W) colsum_strip<bf16_t, true, CL>(X, W, j.sum + zo, j.sum_w + zo, rows, j.cols, j.cols, strip, vec_rows, red, red2);
-  else colsum_strip<bf16_t, false, CL>(X, nullptr, j.sum + zo, nullptr, rows, j.cols, j.cols, strip, vec_rows, red, red2);
+  if (W) colsum_strip<bf16_t, true, ROWS, CL, PER>(X, W, j.sum + zo, j.sum_w + zo, rows, j.cols, j.cols, strip, vec_rows, red, red2);
+  else colsum_strip<bf16_t, false, ROWS, CL, PER>(X, nullptr, j.sum + zo, nullptr, rows, j.cols, j.cols, strip, vec_rows, red, red2);
 }
 
 bool colsum_narrow(int rows, int cols) { return (long long)rows * cols <= (1LL << 20); }
 
-// The widest strips (64, 32, 16 or 8 columns) that still make a workgroup for every CU.
+// 256 row lanes for tall bf16 blocks, where the chain of loads is what a launch waits for, and for bf16 rows without 16-byte
+// alignment (eight loads a row).  fp32 rows keep twice the loads in flight, and gain nothing.
+template <typename T>
+static bool cs_tall(int rows, int cols) { return sizeof(T) == 2 && (rows > 2048 || cols % 8 != 0); }
+// Column lanes.  Narrow strips where one block is all there is, wider ones as the launch fills the chip.  bf16: 16 columns
+// are as fast as 8 there and less to fetch twice; blocks of one 128-byte line or less want half a line as soon as there are
+// several (16 blocks of [8192 x 64]: strips of 32, 16, 8 columns 10.8, 16.7, 20.7 us).
+template <typename T>
+static int cs_lanes(long long width, int cols, unsigned blocks) {
+  if (sizeof(T) == 4) return width >= 64 * 256 ? 8 : width >= 32 * 256 ? 4 : width >= 12 * 256 ? 2 : 1;
+  if (cols <= 8) return 1;
+  if (width >= 64 * 256) return 8;
+  return width >= 32 * 256 || (cols <= 64 && blocks > 1) ? 4 : 2;
+}
 template <typename T, bool PROD>
 static void colsum_launch(dim3 batch, const T* X, const T* W, float* out, float* out2, int rows, int cols, int ld, long long sX,
                           long long sOut, hipStream_t stream) {
-#define OPTIMUS_COLSUM(CL)                                                                                                        \
-  hipLaunchKernelGGL((colsum_kernel<T, PROD, CL>), dim3((unsigned)((cols + 8 * CL - 1) / (8 * CL)), batch.y), dim3(CS_ROWS * CL), 0, \
-                     stream, X, W, out, out2, rows, cols, ld, sX, sOut)
+#define OPTIMUS_COLSUM(ROWS, CL, PER)                                                                                                    \
+  hipLaunchKernelGGL((colsum_kernel<T, PROD, ROWS, CL, PER>), dim3((unsigned)((cols + 8 * CL - 1) / (8 * CL)), batch.y),                 \
+                     dim3(ROWS / PER * CL), 0, stream, X, W, out, out2, rows, cols, ld, sX, sOut)
+  const bool tall = cs_tall<T>(rows, cols);
   const long long width = (long long)cols * batch.y;
-  if (width >= 64 * 256) OPTIMUS_COLSUM(8);
-  else if (width >= 32 * 256) OPTIMUS_COLSUM(4);
-  else if (width >= 16 * 256) OPTIMUS_COLSUM(2);
-  else OPTIMUS_COLSUM(1);
+  const int cl = cs_lanes<T>(width, cols, batch.y);
+  if constexpr (sizeof(T) == 2) {
+    if (tall) {
+      // two row lanes a thread also where the launch has loads enough without: with products, 4 of [4096 x 2048] 26.0 and 23.3 us
+      if (cl == 8) OPTIMUS_COLSUM(256, 8, 2);
+      else if (PROD && width >= 32 * 256) OPTIMUS_COLSUM(256, 4, 2);
+      else if (cl == 4) OPTIMUS_COLSUM(256, 4, 1);
+      else if (cl == 2) OPTIMUS_COLSUM(256, 2, 1);
+      else OPTIMUS_COLSUM(256, 1, 1);
+      return;
+    }
+  }
+  if (cl == 8) OPTIMUS_COLSUM(128, 8, 1);
+  else if (cl == 4) OPTIMUS_COLSUM(128, 4, 1);
+  else if (cl == 2) OPTIMUS_COLSUM(128, 2, 1);
+  else OPTIMUS_COLSUM(128, 1, 1);
 #undef OPTIMUS_COLSUM
 }
 
 int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, hipStream_t stream) {
   long long width = 0;
-  for (int k = 0; k < jobs.n; ++k) width += jobs.j[k].cols;
-  const int cl = width * nz >= 64 * 256 ? 8 : width * nz >= 32 * 256 ? 4 : width * nz >= 16 * 256 ? 2 : 1;   // as colsum_launch
+  int least = jobs.j[0].cols;
+  for (int k = 0; k < jobs.n; ++k) { width += jobs.j[k].cols; least = jobs.j[k].cols < least ? jobs.j[k].cols : least; }
+  const bool tall = cs_tall<bf16_t>(rows, least);   // one block's width is a multiple of 8 with all of them (the caller's heads are)
+  const int cl = cs_lanes<bf16_t>(width * nz, least, (unsigned)nz);
   unsigned strips = 0;
   for (int k = 0; k < jobs.n; ++k) strips += (unsigned)((jobs.j[k].cols + 8 * cl - 1) / (8 * cl));
   const dim3 grid(strips, (unsigned)nz);
-  switch (cl) {
-    case 8: hipLaunchKernelGGL(colsum_jobs_kernel<8>, grid, dim3(CS_ROWS * 8), 0, stream, jobs, rows); break;
-    case 4: hipLaunchKernelGGL(colsum_jobs_kernel<4>, grid, dim3(CS_ROWS * 4), 0, stream, jobs, rows); break;
-    case 2: hipLaunchKernelGGL(colsum_jobs_kernel<2>, grid, dim3(CS_ROWS * 2), 0, stream, jobs, rows); break;
-    default: hipLaunchKernelGGL(colsum_jobs_kernel<1>, grid, dim3(CS_ROWS), 0, stream, jobs, rows); break;
-  }
+#define OPTIMUS_COLSUM_JOBS(ROWS, CL, PER) \
+  hipLaunchKernelGGL((colsum_jobs_kernel<ROWS, CL, PER>), grid, dim3(ROWS / PER * CL), 0, stream, jobs, rows)
+  if (tall && cl == 8) OPTIMUS_COLSUM_JOBS(256, 8, 2);
+  else if (tall && cl == 4) OPTIMUS_COLSUM_JOBS(256, 4, 1);
+  else if (tall && cl == 2) OPTIMUS_COLSUM_JOBS(256, 2, 1);
+  else if (tall) OPTIMUS_COLSUM_JOBS(256, 1, 1);
+  else if (cl == 8) OPTIMUS_COLSUM_JOBS(128, 8, 1);
+  else if (cl == 4) OPTIMUS_COLSUM_JOBS(128, 4, 1);
+  else if (cl == 2) OPTIMUS_COLSUM_JOBS(128, 2, 1);
+  else OPTIMUS_COLSUM_JOBS(128, 1, 1);
+#undef OPTIMUS_COLSUM_JOBS
   return hip_launch_status();
 }
 
