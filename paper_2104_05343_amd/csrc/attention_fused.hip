@@ -7,15 +7,17 @@ namespace {
 // ---------------------------------------------------------------- forward
 // NRG: row groups of 32 queries per workgroup (2: 64 rows, four wavefronts; 4: 128 rows, eight wavefronts -- half the
 // K/V bytes per flop and two wavefronts per SIMD, for launches with more workgroups than compute units).
-template <int D, bool CAUSAL, int NRG>
+// TILES_FIRST: a matrix's tiles first instead of all matrices' tiles of a rank first (see fwd_launch).
+template <int D, bool CAUSAL, int NRG, bool TILES_FIRST = false>
 __global__ __launch_bounds__(NRG * 128) void attn_fused_fwd_kernel(FusedArgs a) {
   constexpr int KS = D / 16, DT = D / 32, BQ = NRG * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][PAIR * D];  // [stage][K, V][pair tile]
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rg = wave % NRG, par = wave / NRG;
-  const int tile = gridDim.y - 1 - blockIdx.y;  // the tiles with the longest causal loops start first
-  const int mat = blockIdx.x, dev = blockIdx.z, s = a.s;
+  // the tiles with the longest causal loops start first
+  const int tile = TILES_FIRST ? gridDim.x - 1 - blockIdx.x : gridDim.y - 1 - blockIdx.y;
+  const int mat = TILES_FIRST ? blockIdx.y : blockIdx.x, dev = blockIdx.z, s = a.s;
   const int seq = mat / a.nh, head = mat % a.nh;
   const bf16_t* Qp = a.qkv + dev * a.dev_qkv + (long long)seq * s * a.ld + head * 3 * D;
   const bf16_t* Kp = Qp + D;
@@ -228,10 +230,14 @@ template <int D>
 void fwd_launch(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
   // 128-row workgroups from one per two compute units on (measured: equal or faster than 64-row ones from there)
   const bool big = (long long)((d.s + 127) / 128) * d.nb * d.nh * d.ndev >= 128;
+  // Without a mask all loops are alike and the order is a matter of caches: once a matrix's K and V fill an XCD's L2 (4 MiB)
+  // its tiles run together (8 matrices, s = 8192, width 128: 275 us, by rank 286; 2 matrices, 16384: 265, 277), below that
+  // the matrices side by side (16, 4096: 149, 149; 64, 1024: 58, 49).
   const int rows = big ? 128 : BLK;
   const dim3 grid(d.nb * d.nh, (d.s + rows - 1) / rows, d.ndev);
   if (big) {
     if (d.causal) attn_fused_fwd_kernel<D, true, 4><<<grid, 512, 0, st>>>(a);
+    else if (4ll * D * d.s >= 4ll << 20) attn_fused_fwd_kernel<D, false, 4, true><<<dim3(grid.y, grid.x, grid.z), 512, 0, st>>>(a);
     else attn_fused_fwd_kernel<D, false, 4><<<grid, 512, 0, st>>>(a);
   } else {
     if (d.causal) attn_fused_fwd_kernel<D, true, 2><<<grid, 256, 0, st>>>(a);

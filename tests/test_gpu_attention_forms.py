@@ -1,5 +1,6 @@
 """GPU: the forms of the fused attention's kernels (64- and 128-row workgroups, both gradients in one grid or one after the
-other) on both sides of the lines between them, sequence lengths that cut their tiles, against fp64 on the GPU."""
+other) on both sides of the lines between them, sequence lengths that cut their tiles, against fp64 on the GPU; whole grid
+against one device bit for bit."""
 import math
 
 import pytest
@@ -48,3 +49,47 @@ def test_forms_against_fp64(b, n, s, d, causal):
         assert (dv - dO.double().view(b, n, d)).abs().max().item() == 0.0
     else:
         assert ((dQKV.double() - g64).norm() / g64.norm()).item() <= TOL
+
+
+# b, n of the whole q = 2 grid.  Head width 128: one device on the wide side of the causal line, and without a mask in one
+# grid where the whole grid runs one kind after the other; 64: either side of the launch's line
+@pytest.mark.parametrize("b,n,s,d,causal", [(32, 16, 130, 128, True), (8, 8, 1025, 128, False), (16, 8, 300, 128, True), (16, 16, 250, 64, True),
+                                            (32, 16, 100, 64, True), (8, 16, 520, 64, False)])
+def test_whole_grid_equals_one_device(b, n, s, d, causal):
+    q, h = 2, n * d
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(s)
+    qkv = torch.randn(b * s * 3 * h, generator=g, device="cuda:0").to(torch.bfloat16)
+    dO = torch.randn(b * s * h, generator=g, device="cuda:0").to(torch.bfloat16)
+    ws = torch.empty(opt.attention_fused_workspace_bytes(b, s, h, n, q), dtype=torch.uint8, device="cuda:0")
+    out = []
+    for where in ([(-1, -1)], [(i, j) for i in range(q) for j in range(q)]):
+        O, dQKV = torch.full_like(dO, float("nan")), torch.full_like(qkv, float("nan"))
+        lse = torch.full((b * n * s,), float("nan"), device="cuda:0")
+        for i, j in where:
+            opt.attention_fused_fwd(qkv, O, lse, b, s, h, n, q, i, j, causal, opt.BF16)
+            opt.attention_fused_bwd(qkv, O, lse, dO, dQKV, b, s, h, n, q, i, j, causal, opt.BF16, ws)
+        torch.cuda.synchronize()
+        out.append((O, lse, dQKV))
+    assert not any(torch.isnan(t).any() for t in out[0])
+    assert all(torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("d,s", [(64, 16390), (128, 8200)])
+def test_long_sequences_without_a_mask(d, s):
+    """K and V of a matrix beyond an XCD's L2: its tiles run together.  Sampled rows of two heads against fp64."""
+    n, h = 2, 2 * d
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    qkv = torch.randn(s, 3 * h, generator=g, device="cuda:0").to(torch.bfloat16)
+    O, lse = torch.full((s, h), float("nan"), dtype=torch.bfloat16, device="cuda:0"), torch.full((n, s), float("nan"), device="cuda:0")
+    opt.attention_fused_fwd(qkv, O, lse, 1, s, h, n, 1, 0, 0, 0, opt.BF16)
+    torch.cuda.synchronize()
+    assert not torch.isnan(O).any() and not torch.isnan(lse).any()
+    rows = torch.cat([torch.arange(0, 4), torch.randint(0, s, (120,)), torch.arange(s - 4, s)]).to("cuda:0")
+    for head in range(n):
+        Q, K, V = (qkv[:, head * 3 * d + k * d:head * 3 * d + (k + 1) * d].double() for k in range(3))
+        S = Q[rows] @ K.T.contiguous() / math.sqrt(d)
+        want = torch.softmax(S, dim=1) @ V
+        assert ((O[rows, head * d:(head + 1) * d].double() - want).norm() / want.norm()).item() <= TOL
+        assert (lse[head, rows].double() - torch.logsumexp(S, dim=1)).abs().max().item() <= 1e-2
