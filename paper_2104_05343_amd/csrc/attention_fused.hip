@@ -252,13 +252,15 @@ void fwd_launch(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
 // against 54 alone, but beside the products of the layer's gradient branch, which take compute units away, the longest
 // tiles then start second: the 4096-wide layer step 874 against 850.  Both kinds in one grid against one after the other, 16
 // matrices, s = 4096: causal 308 against 477 (width 64: 189 against 279), not causal 596 against 507 (327 against 295).
+// Width 64, causal, one tile per matrix: 512 matrices of s = 128 43 against 38, 1024 of 64 53 against 48; two or three tiles
+// between 0.87 and 1.07 of one after the other, from 512 on 0.92 and less.
 template <int D, bool CAUSAL>
 void bwd_launch_c(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
   const long long tiles64 = (d.s + BLK - 1) / BLK, tiles128 = (d.s + 127) / 128, nmat = (long long)d.nb * d.nh;
   const bool big = tiles128 * nmat * d.ndev >= 512;
   const dim3 grid128((unsigned)tiles128, (unsigned)nmat, d.ndev);
   const bool wide = D == 128 ? 2 * tiles128 * nmat >= (CAUSAL ? 512 : 256) : big;
-  if (wide && (CAUSAL || !big)) {
+  if (wide && (CAUSAL || !big) && !(D == 64 && tiles128 == 1)) {
     attn_fused_delta_kernel<D><<<grid128, 256, 0, st>>>(a);
     launch_attn_fused_bwd_wide(a, D, CAUSAL, grid128, st);
     return;
@@ -269,9 +271,10 @@ void bwd_launch_c(const FusedArgs& a, const AttnFusedDesc& d, hipStream_t st) {
     attn_fused_bwd_kernel<D, CAUSAL><<<dim3((unsigned)(2 * tiles64 * nmat), d.ndev), 256, 0, st>>>(a, (int)tiles64, (int)nmat);
     return;
   }
-  // without a mask all loops are alike: one kind after the other, which saves the delta kernel and mixes no tile sizes
+  // Without a mask, or with one tile per matrix, all loops are alike: one kind after the other, which saves the delta kernel and
+  // mixes no tile sizes.
   attn_fused_bwd_dq_kernel<D, CAUSAL, 4><<<grid128, 512, 0, st>>>(a);
-  if constexpr (D == 64) attn_fused_bwd_dkv_kernel<D, CAUSAL, 4><<<grid128, 512, 0, st>>>(a);   // (not causal: else wide, above)
+  if constexpr (D == 64) attn_fused_bwd_dkv_kernel<D, CAUSAL, 4><<<grid128, 512, 0, st>>>(a);
   else if (wide) launch_attn_fused_bwd_dkv_wide(a, grid128, st);
   else attn_fused_bwd_dkv_kernel<D, CAUSAL, 2><<<dim3((unsigned)tiles64, (unsigned)nmat, d.ndev), 256, 0, st>>>(a);   // many devices' blocks of few matrices
 }

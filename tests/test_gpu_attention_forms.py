@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_2104_05343_amd as opt
+from bench import event_time_ms
 
 pytestmark = pytest.mark.gpu
 TOL = 5e-3   # bf16 operands and results, fp32 sums: the bound the other attention tests use
@@ -29,7 +30,7 @@ def _reference(qkv, dO, b, s, n, d, causal):
 
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("b,n,s,d", [(1, 2, 1, 128), (2, 3, 65, 128), (16, 4, 129, 128), (32, 8, 130, 128), (64, 8, 63, 128),
-                                     (32, 8, 193, 128), (33, 8, 250, 64), (8, 8, 1025, 64)])
+                                     (32, 8, 193, 128), (33, 8, 250, 64), (8, 8, 1025, 64), (64, 8, 127, 64)])
 def test_forms_against_fp64(b, n, s, d, causal):
     g = torch.Generator(device="cuda:0")
     g.manual_seed(s + n)
@@ -93,3 +94,18 @@ def test_long_sequences_without_a_mask(d, s):
         want = torch.softmax(S, dim=1) @ V
         assert ((O[rows, head * d:(head + 1) * d].double() - want).norm() / want.norm()).item() <= TOL
         assert (lse[head, rows].double() - torch.logsumexp(S, dim=1)).abs().max().item() <= 1e-2
+
+
+def test_one_tile_per_matrix_costs_no_more_with_a_mask():
+    """512 matrices of s = 128, width 64: 38.4 us causal, 37.6 without a mask; both kinds in one grid 42.7."""
+    b, n, s, d = 64, 8, 128, 64
+    h = n * d
+    qkv, dO = torch.randn(b * s, 3 * h, device="cuda:0").to(torch.bfloat16), torch.randn(b * s, h, device="cuda:0").to(torch.bfloat16)
+    O, dQKV, lse = torch.empty_like(dO), torch.empty_like(qkv), torch.empty(b * n * s, device="cuda:0")
+    ws = torch.empty(opt.attention_fused_workspace_bytes(b, s, h, n, 1), dtype=torch.uint8, device="cuda:0")
+    ms = []
+    for causal in (1, 0):
+        opt.attention_fused_fwd(qkv, O, lse, b, s, h, n, 1, 0, 0, causal, opt.BF16)
+        ms.append(min(event_time_ms(lambda: opt.attention_fused_bwd(qkv, O, lse, dO, dQKV, b, s, h, n, 1, 0, 0, causal, opt.BF16, ws), 20, warm=2)
+                      for _ in range(3)))
+    assert ms[0] <= 1.08 * ms[1], ms
