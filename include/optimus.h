@@ -425,6 +425,9 @@ int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, i
  * (1 << 16 if the split is emulated inside each workgroup);
  * -1 before the first one.  Host state only, not synchronised between threads. */
 int optimus_debug_last_gemm_plan(void);
+/* The streams an optimus_layer_bwd of this size runs on when it is not captured (a captured one: two, once the library
+ * has its stream): 1 or 2, or -1 for arguments that optimus_layer_bwd refuses.  Host arithmetic only. */
+int optimus_debug_layer_bwd_streams(const optimus_layer_cfg* cfg, int i, int j);
 
 #ifdef __cplusplus
 }

@@ -125,6 +125,7 @@ SIGNATURES = {
     "optimus_debug_set_gemm_variant": (None, [_INT]),
     "optimus_debug_set_corun_variants": (None, [_INT, _INT]),
     "optimus_debug_last_gemm_plan": (_INT, []),
+    "optimus_debug_layer_bwd_streams": (_INT, [C.POINTER(LayerCfg), _INT, _INT]),
     "optimus_debug_plan_summa": (_INT, [_INT, _I64, _I64, _I64, _INT, _INT, _INT, _INT, _INT, C.POINTER(C.c_int)]),
     "optimus_debug_mfma_rate": (_INT, [_P, _INT, _INT, _INT, _P]),
 }
@@ -434,3 +435,7 @@ def debug_last_gemm_plan():
     """(variant, panel splits, 1 if the split is emulated inside each workgroup) of the most recent matrix-core product."""
     p = lib().optimus_debug_last_gemm_plan()
     return (p & 0xFF, (p >> 8) & 0xFF, p >> 16) if p >= 0 else None
+
+
+def debug_layer_bwd_streams(cfg: LayerCfg, i, j) -> int:
+    return lib().optimus_debug_layer_bwd_streams(C.byref(cfg), i, j)

@@ -395,19 +395,26 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
   return OPTIMUS_OK;
 }
 
-// Whether the second stream pays.  A fork or the join costs the host 25 us (the wait on another stream's event, for the
-// most part), and there are five of them in a backward pass: where its kernels take no longer than that, the host is what
-// the pass waits for.  The line is drawn by the flops of the pass's products.  Measured, step of one layer, two streams /
-// one (us): 1.6 GF 250 / 150, 13 GF 307 / 240 and 315 / 247, 39 GF 308 / 368, 51 GF 303 / 347, 103 GF 440 / 522,
-// 412 GF 893 / 999; checkpointed stack of two small layers (0.8 GF each) 584 / 355.  A captured pass pays the host once
-// and keeps both streams (which an earlier pass, short or not, has created).
-bool branch_pays(const optimus_layer_cfg* c, bool grid, hipStream_t caller) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(caller, &cs) != hipSuccess) { (void)hipGetLastError(); cs = hipStreamCaptureStatusNone; }
-  if (cs != hipStreamCaptureStatusNone) return true;
+// Whether the second stream pays in a pass that is not captured.  A fork or the join costs the host 25 us (the wait on another
+// stream's event, for the most part), and there are five of them in a backward pass: the host needs about 200 us for a pass on
+// two streams (165 with q = 1, where no product is split), and where the kernels on one stream take no longer than that it is
+// what the pass waits for.  Their time: the products, and the attention, which on a device with few matrices is a chain along
+// the sequence (30 us per 1024 rows fused, 36 with the scores in memory).  From 24 GF of products on two streams always.
+// Measured, step of one layer, two streams / one (us): 0.8 GF 338 / 225, 13 GF, s = 512 270 / 203 and 296 / 223, 13 GF, s = 1024
+// 259 / 219, 13 GF, s = 2048 266 / 248 fused, 309 / 348 in memory, 13 GF, s = 4096 308 / 338 and 430 / 481, 3 GF, s = 4096 278 /
+// 305, 6 GF, s = 8192 437 / 497, 13 GF, s = 16384 817 / 974, q = 1, 6 GF, s = 2048 212 / 228, q = 1, 13 GF, s = 1024 214 / 199,
+// 20 GF, s = 512 248 / 225, 39 GF 289 / 299, 51 GF 343 / 377; checkpointed stack of two small layers (0.8 GF each) 584 / 355.
+bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
   const double devices = grid ? (double)c->q * c->q : 1.0;
-  const double flops = 48.0 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
-  return flops >= 24e9;
+  const double gf = 48e-9 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
+  const double one_us = 100.0 + 2.5 * gf + (c->fused_attention ? 0.030 : 0.036) * c->s;
+  return gf >= 24.0 || one_us >= (c->q == 1 ? 165.0 : 200.0);
+}
+// A captured pass pays the host once and keeps both streams (which an earlier pass, short or not, has created).
+bool captured(hipStream_t caller) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(caller, &cs) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cs != hipStreamCaptureStatusNone;
 }
 
 // Device address of `scratch` on the current device (each GPU holds its own copy at its own address): looked up on
@@ -823,7 +830,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   if ((rc = ln_desc(M, h, q, i, j, dt, c->eps, &ln))) return rc;
   // gradient branch: its own stream and its own split workspace (see SideStream)
   SideStream* ss = side_stream(st);   // asked for in any case: a later call may be captured, and then it has to be there
-  if (!branch_pays(c, grid, st)) ss = nullptr;
+  if (ss && !two_streams_pay(c, grid) && !captured(st)) ss = nullptr;
   const int co_chain = ss ? 1 : 0, co_branch = ss ? 2 : 0;   // products planned for company only where they have it
   hipStream_t gst = ss ? ss->s : st;
   void* gstream = (void*)gst;
@@ -929,5 +936,10 @@ int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, i
   return gemm_plan_of(d, have_ws != 0, out3) ? OPTIMUS_OK : OPTIMUS_EDTYPE;
 }
 int optimus_debug_last_gemm_plan(void) { return gemm_last_plan(); }
+int optimus_debug_layer_bwd_streams(const optimus_layer_cfg* c, int i, int j) {
+  AttnDims a;
+  if (layer_check(c, i, j, &a)) return -1;
+  return two_streams_pay(c, is_grid(i, j)) ? 2 : 1;
+}
 
 }  // extern "C"

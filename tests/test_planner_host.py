@@ -76,3 +76,22 @@ def test_no_split_without_panels_and_errors():
         plan("ab", 2048, 4096, 1024, 4, 4, 0)            # coordinate outside the grid
     with pytest.raises(opt.OptimusError):
         plan("ab", 36, 36, 36, 4, 0, 0)                  # blocks of 9: not a matrix-core shape
+
+
+# q, b, s, h, n, fused: short passes, then passes whose products are small and whose attention is long, or both are large
+@pytest.mark.parametrize("streams,shape", [(1, (4, 8, 512, 1024, 16, 0)), (1, (4, 8, 512, 1024, 16, 1)), (1, (2, 4, 64, 128, 4, 0)),
+                                           (1, (2, 2, 2048, 512, 8, 1)), (1, (1, 1, 1024, 512, 8, 1)),
+                                           (2, (4, 4, 4096, 256, 4, 1)), (2, (4, 4, 4096, 512, 8, 0)), (2, (4, 4, 16384, 256, 4, 1)),
+                                           (2, (2, 2, 4096, 256, 4, 0)), (2, (4, 8, 2048, 512, 8, 0)), (2, (1, 1, 2048, 256, 4, 1)),
+                                           (2, (4, 8, 1024, 4096, 32, 1))])
+def test_streams_of_an_eager_backward_pass(streams, shape):
+    q, b, s, h, n, fused = shape
+    cfg = opt.LayerCfg(b, s, h, n, q, 1e-5, 1, opt.BF16, fused)
+    assert opt.binding.debug_layer_bwd_streams(cfg, 0, 0) == streams
+
+
+def test_streams_of_the_whole_grid_and_refused_arguments():
+    cfg = opt.LayerCfg(8, 512, 1024, 16, 4, 1e-5, 1, opt.BF16, 0)
+    assert opt.binding.debug_layer_bwd_streams(cfg, -1, -1) == 2      # 16 devices' products
+    assert opt.binding.debug_layer_bwd_streams(cfg, 4, 0) == -1
+    assert opt.binding.debug_layer_bwd_streams(opt.LayerCfg(8, 512, 1024, 15, 4, 1e-5, 1, opt.BF16, 0), 0, 0) == -1
