@@ -77,8 +77,8 @@ def test_exact_integer_pattern(form, q, dtype):
         assert np.array_equal(g1, blocks.block(want, q, i, j).astype(np.float32))
 
 
-# per-block shapes: matrix-core fast path (multiples of the tile), bounds-checked matrix-core path
-# (multiples of 8, ragged against the 128-tile), scalar path (odd sizes)
+# per-block shapes: full tiles (multiples of 64), ragged tiles (rows of multiples of 8, blocks that no tile divides), the
+# any-shape kernel (odd sizes)
 SHAPES = [(384, 192, 256), (200, 72, 136), (37, 19, 50), (512, 64, 128), (264, 520, 1032)]
 
 
@@ -103,8 +103,8 @@ def test_bf16_random_blocks(form, q):
 @pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("kp", [32, 96, 64, 192, 320])
 def test_bf16_short_and_odd_panel_lengths(form, kp):
-    """Tile-multiple blocks whose panel length is an odd or even number of 32-slabs: odd counts cannot use the
-    pair-wise k-loop and take the bounds-checked kernel; 64 is the shortest fast case (one pair per panel)."""
+    """Tile-multiple blocks whose panel length is an odd or even number of 32-slabs: odd counts leave half of the k-loop's
+    last pair empty and take the ragged tiles; 64 is the shortest full case (one pair per panel)."""
     q, mb, nb = 2, 256, 256
     M, K, N = mb * q, kp * q, nb * q
     A, B = gemm_inputs(300 + kp, form, M, K, N, "bf16", "n1", "n1")
@@ -212,6 +212,72 @@ def test_tile_variants_give_identical_bits_and_grid_equals_device(form, q, mb, k
                 print("forced", variant, "grid plan", gp)
         finally:
             opt.debug_set_gemm_variant(-1)
+
+
+# blocks that no tile divides, skinny enough for a panel split; A B^T also with rows of C that allow no vector access
+RAGGED = [("ab", 4, 264, 520, 1032), ("abt", 4, 264, 520, 1032), ("atb", 4, 264, 520, 1032), ("abt", 4, 200, 520, 301),
+          ("abt", 4, 130, 1000, 67), ("ab", 8, 136, 264, 72)]
+
+
+@pytest.mark.parametrize("form,q,mb,kp,nb", RAGGED)
+def test_ragged_panel_split(form, q, mb, kp, nb):
+    """Cut blocks: the split with its partial tiles in memory, the same walked inside the workgroups (no workspace), whole
+    grid against one device, and the three ragged tiles, all bit for bit; against the oracle."""
+    M, K, N = mb * q, kp * q, nb * q
+    i, j = q - 1, 1
+    A, B = gemm_inputs(58, form, M, K, N, "bf16", "n1", "n1")
+    want = summa.product(form, A, B)
+    ws = torch.empty(opt.summa_workspace_bytes(form, M, K, N, q, i, j, opt.BF16), dtype=torch.uint8, device="cuda:0")
+    split = _run(form, A, B, M, K, N, q, "bf16", i, j, ws=ws)
+    plan = opt.binding.debug_last_gemm_plan()
+    assert plan[1] > 1 and plan[2] == 0 and plan[0] in (3, 6, 7), plan
+    _check_blocks(split, want, M, N, q, TOL["bf16"], coords={(i, j)})
+    inside = _run(form, A, B, M, K, N, q, "bf16", i, j)
+    assert opt.binding.debug_last_gemm_plan()[1:] == (plan[1], 1)
+    assert torch.equal(inside.view(torch.int16), split.view(torch.int16))
+    big = torch.empty(max(256, opt.summa_workspace_bytes(form, M, K, N, q, -1, -1, opt.BF16)), dtype=torch.uint8, device="cuda:0")
+    blk = slice((i * q + j) * mb * nb, (i * q + j + 1) * mb * nb)
+    for w in (big, None):
+        grid = _run(form, A, B, M, K, N, q, "bf16", ws=w)
+        assert opt.binding.debug_last_gemm_plan()[1] == plan[1]
+        assert torch.equal(grid.view(torch.int16)[blk], split.view(torch.int16)[blk])
+        _check_blocks(grid, want, M, N, q, TOL["bf16"])
+    room = torch.empty(64 << 20, dtype=torch.uint8, device="cuda:0")
+    by_split = {plan[1]: split}
+    try:
+        for variant in (3, 6, 7):
+            opt.debug_set_gemm_variant(variant)
+            for w in (room, None):
+                c = _run(form, A, B, M, K, N, q, "bf16", i, j, ws=w)
+                p = opt.binding.debug_last_gemm_plan()
+                assert p[0] == variant
+                same = by_split.setdefault(p[1], c)
+                assert torch.equal(c.view(torch.int16), same.view(torch.int16)), (variant, p)
+    finally:
+        opt.debug_set_gemm_variant(-1)
+
+
+def test_ragged_panel_split_with_epilogue():
+    """bias, saved pre-activation, GeLU and residual through the combine of cut partial tiles, C's rows not a multiple of four."""
+    form, q, mb, kp, nb = "abt", 4, 200, 520, 301
+    M, K, N = mb * q, kp * q, nb * q
+    i, j = 2, 3
+    rng = np.random.default_rng(59)
+    A, B = gemm_inputs(60, form, M, K, N, "bf16", "n1", "n1")
+    A = round_to_bf16(A * 0.05)
+    bias, res = (round_to_bf16(rng.standard_normal(n).astype(np.float32)) for n in (N, (M, N)))
+    dA, dB, dRes, dBias = mat_to_dev(A, q, "bf16"), mat_to_dev(B, q, "bf16"), mat_to_dev(res, q, "bf16"), vec_to_dev(bias)
+    out = []
+    for ws in (torch.empty(opt.summa_workspace_bytes(form, M, K, N, q, i, j, opt.BF16), dtype=torch.uint8, device="cuda:0"), None):
+        dC, dPre = empty(M * N, "bf16"), empty(M * N, "bf16")
+        opt.summa_ex(form, dA, dB, dC, M, K, N, q, i, j, opt.BF16, bias=dBias, pre_act=dPre, act=1, residual=dRes, ws=ws)
+        torch.cuda.synchronize()
+        assert opt.binding.debug_last_gemm_plan()[1] > 1
+        out.append((dC, dPre))
+    assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(*out))
+    pre = summa.product(form, A, B) + bias[None, :]
+    _check_blocks(out[0][1], pre, M, N, q, TOL["bf16"], coords={(i, j)})
+    _check_blocks(out[0][0], olayer.gelu(pre) + res, M, N, q, TOL["bf16"], coords={(i, j)})
 
 
 def test_closed_forms_and_identities():
