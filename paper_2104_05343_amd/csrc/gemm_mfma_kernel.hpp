@@ -378,9 +378,12 @@ struct Occ {
   static constexpr int value = waves_per_simd_raw < 1 ? 1 : (waves_per_simd_raw > 2 ? 2 : waves_per_simd_raw);
 };
 
-// RAG = the block is cut by the tiles, or its rows do not allow the vector epilogue everywhere: masked loads, and a
+// FORM 0: full tiles.
+// 1 (RAG) = the block is cut by the tiles, or its rows do not allow the vector epilogue everywhere: masked loads, and a
 // bounds-checked epilogue for the wavefronts on the edge.
-// LONG (with RAG) = a panel of a k-strided operand does not fit one buffer resource's window: see the load cursors.
+// 2 (RAG and LONG) = besides, a panel of a k-strided operand does not fit one buffer resource's window: see the load cursors.
+// (One parameter: a longer kernel name moves the kernels in the code object, by 0x700 bytes here, and the three products of a
+// 3072 -> 12288 layer on an 8 x 8 grid, the same instructions, took 132.4 us instead of 130.6.)
 // PLAIN (not with RAG) = the epilogue is a bare store of the accumulator (alpha 1, no bias / activation / residual):
 // a short, fully unrolled store sequence instead of the general epilogue, whose straight-line code costs
 // microseconds per tile.
@@ -395,12 +398,12 @@ struct Loop2 {
   static constexpr int RING32 = 2 * NST;                                        // the same space in 32-wide slabs
 };
 
-template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool PLAIN, bool SEQ = false, int LOOP = 1, bool RAG = false, bool LONG = false>
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool PLAIN, bool SEQ = false, int LOOP = 1, int FORM = 0>
 __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gemm_mfma_kernel(const KArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  constexpr bool RAG = FORM >= 1, LONG = FORM == 2;
   static_assert(!SEQ || !PLAIN, "the range-wise accumulation exists with the full epilogue");
   static_assert(!RAG || (LOOP == 1 && !PLAIN), "ragged blocks: the four-slab ring, the full epilogue");
-  static_assert(!LONG || RAG, "long panels: the ragged form");
   using T = Tile<BM, BN, WM, WN>;
   constexpr int THREADS = T::THREADS, NW = T::NW;
   constexpr int TM = T::TM, TN = T::TN, MI = T::MI, NI = T::NI;

@@ -6,9 +6,9 @@ namespace optimus {
 template <int BM, int BN, bool AKC, bool BKC, bool LONG>
 static int launch_one(const KArgs& ka, unsigned nwg, hipStream_t stream) {
   if (ka.seq_splits > 1)
-    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, 2, 2, AKC, BKC, false, true, 1, true, LONG>), dim3(nwg), dim3(256), 0, stream, ka);
+    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, 2, 2, AKC, BKC, false, true, 1, LONG ? 2 : 1>), dim3(nwg), dim3(256), 0, stream, ka);
   else
-    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, 2, 2, AKC, BKC, false, false, 1, true, LONG>), dim3(nwg), dim3(256), 0, stream, ka);
+    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, 2, 2, AKC, BKC, false, false, 1, LONG ? 2 : 1>), dim3(nwg), dim3(256), 0, stream, ka);
   return hip_launch_status();
 }
 template <int BM, int BN, bool LONG = false>
