@@ -104,7 +104,8 @@ int optimus_summa_reduce(const float* c_temps, int count, void* C, int64_t M, in
  * ws / ws_bytes: optional device scratch (may be NULL / 0).  When it is at
  * least optimus_summa_workspace_bytes(...) the library may split the panel
  * loop of skinny outputs over several workgroups and combine the fp32 partial
- * tiles in a fixed order (still deterministic); without it no split is used. */
+ * tiles in a fixed order (still deterministic); without it the same split is
+ * walked inside the workgroups, with the same bits. */
 int optimus_summa_ab(const void* A, const void* B, void* C, int64_t M, int64_t K, int64_t N,
                      int q, int i, int j, int dtype, void* ws, size_t ws_bytes, void* stream);
 int optimus_summa_abt(const void* A, const void* B, void* C, int64_t M, int64_t K, int64_t N,
@@ -408,7 +409,9 @@ int optimus_debug_mfma_rate(float* out, int workgroups, int iters, int random_da
  * 3 = 128x128, 4 = alias of 0, 5 = the any-shape kernel, 6 = 128x64, 7 = 64x64, 8 = 256x128 and 9 = 128x256 with
  * four wavefronts; -1 = automatic.  1000 + v selects, for the tiles compiled with two k-loops (0, 1, 2, 8, 9), the
  * four-slab ring instead of the 64-wide stages (identical bits); 1255 = automatic tile with that loop.
- * A variant whose tile does not divide the block falls back to the bounds-checked kernel. */
+ * A tile with a ragged form (3, 6, 7) runs it where it does not divide the block.  Another tile that does not divide the block
+ * gives way: to the any-shape kernel if 64x64 tiles divide the block, else to the automatic choice.  Same bits where the panel
+ * split is the same; optimus_debug_last_gemm_plan tells what ran. */
 void optimus_debug_set_gemm_variant(int v);
 /* The same for the products optimus_layer_bwd runs side by side on two streams only: chain_v for the
  * activation-gradient chain (the four A B^T products), branch_v for the parameter-gradient branch (the four A^T B
@@ -419,7 +422,8 @@ void optimus_debug_set_corun_variants(int chain_v, int branch_v);
  * no GPU is needed.  corun: 0 = the product runs alone, 1 / 2 = it is the chain / branch product of a pair that
  * optimus_layer_bwd runs side by side; have_ws: whether the caller would pass the workspace the plan asks for.
  * The panel split (the only part of a plan that changes bits) depends on the block shape alone: not on (i, j) versus
- * grid mode, not on corun.  OPTIMUS_EDTYPE when the matrix-core kernels do not take the shape (ragged sizes). */
+ * grid mode, not on corun.  OPTIMUS_EDTYPE when the matrix-core tiles do not take the shape (rows of A or B not
+ * multiples of 8 elements, panels beyond the 2 GiB a buffer load reaches, shapes the any-shape kernel runs faster). */
 int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, int i, int j, int corun, int have_ws, int* out3);
 /* The plan of the most recent matrix-core product launched by this process: variant | (panel splits << 8) |
  * (1 << 16 if the split is emulated inside each workgroup);

@@ -6,7 +6,9 @@
 // Forward keeps one fp32 number per query row, L = log sum_u exp(S_tu); backward rebuilds P = exp(S - L) tile by tile
 // and uses rowsum(dO * O) in place of rowsum(dP * P).
 // Backward is two bodies (dQ; dK and dV), each recomputing S; most launches run them as one grid ordered by loop length
-// (attn_fused_bwd_kernel, attn_fused_bwd_wide_kernel), large ones without a mask as two kernels.
+// (attn_fused_bwd_kernel, attn_fused_bwd_wide_kernel), large ones without a mask and those of width 64 with one tile per
+// matrix as two kernels.  The choice and the kernels of four wavefronts are in attention_fused.hip, the wide backward in
+// attention_fused_wide.hip: beside it in one translation unit the forward came out slower.
 //
 // Work layout (forward and both backward bodies).  A workgroup of four wavefronts owns 64 rows (queries in the forward and dQ
 // kernels, keys in the dK/dV kernel).  Wavefront w works on rows 32*(w & 1).. and on every second 64-wide block of the

@@ -1,6 +1,7 @@
-// Products with short panels in launches that fill the chip: the 64x64 tiles of gemm_generic.hip, but slabs of 64 bytes of k (16 of fp32, 32 of bf16; two of
-// the eight parts), four wavefronts with the accumulators of all NACC parts of a 32x32 output each.  The bits of
-// gemm_any_kernel: a k goes to the same part, the parts are added up the same way, and those past a panel's end are zeros there.
+// Products with short panels in launches that fill the chip: the 64x64 tiles of gemm_generic.hip, but slabs of 64 bytes of k
+// (16 of fp32, 32 of bf16; two of the eight parts), four wavefronts with the accumulators of all NACC parts of a 32x32 output
+// each.  The bits of gemm_any_kernel: a k goes to the same part, the parts are added up the same way, and those past a panel's
+// end are zeros there.
 // What bounds gemm_any_kernel at such panels is work for the missing part of its slabs of 256 bytes; here it is the stores,
 // which leave through LDS as whole rows (straight from the accumulators 17.8 us for a [2046 x 2046] output, this way 13.0).
 #include "gemm_any.hpp"
