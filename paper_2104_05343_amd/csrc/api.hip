@@ -761,14 +761,14 @@ int optimus::layer_forward(const optimus_layer_cfg* c, const optimus_layer_tenso
       !(c->fused_attention ? (const void*)t->lse : (const void*)t->probs) || !t->attn ||
       !t->h_mid || !t->ln2_out || !t->xhat2 || !t->rstd2 || !t->stats2 || !t->pre_gelu || !t->gelu || (!skip_out && !t->out))
     return OPTIMUS_EINVAL;
-  if (!ws || ws_bytes < optimus_layer_workspace_bytes(c)) return OPTIMUS_EWORKSPACE;
+  const size_t gemm_bytes = layer_gemm_ws(c);
+  if (!ws || ws_bytes < layer_attn_ws(c, a) + 2 * gemm_bytes) return OPTIMUS_EWORKSPACE;
   const int q = c->q, dt = c->dtype;
   const int64_t M = (int64_t)c->b * c->s, h = c->h;
   const bool grid = is_grid(i, j);
   hipStream_t st = as_stream(stream);
   // workspace: [products, chain][products, branch][attention: everything that is left]
   void* gemm_ws = ws;
-  const size_t gemm_bytes = layer_gemm_ws(c);
   void* attn_ws = (char*)ws + 2 * gemm_bytes;
   const size_t attn_bytes = ws_bytes - 2 * gemm_bytes;
   LnDesc ln;
@@ -818,14 +818,14 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
       !t->bstats2 || !t->d_w_qkv || !t->d_w_o || !t->d_w1 || !t->d_w2 || !t->d_b_qkv || !t->d_b_o || !t->d_b1 || !t->d_b2 ||
       !t->d_ln1_g || !t->d_ln1_b || !t->d_ln2_g || !t->d_ln2_b)
     return OPTIMUS_EINVAL;
-  if (!ws || ws_bytes < optimus_layer_workspace_bytes(c)) return OPTIMUS_EWORKSPACE;
+  const size_t gemm_bytes = layer_gemm_ws(c);
+  if (!ws || ws_bytes < layer_attn_ws(c, a) + 2 * gemm_bytes) return OPTIMUS_EWORKSPACE;
   const int q = c->q, dt = c->dtype;
   const int64_t M = (int64_t)c->b * c->s, h = c->h;
   const bool grid = is_grid(i, j);
   hipStream_t st = as_stream(stream);
   // workspace: [products, chain][products, branch][attention: everything that is left]
   void* gemm_ws = ws;
-  const size_t gemm_bytes = layer_gemm_ws(c);
   void* attn_ws = (char*)ws + 2 * gemm_bytes;
   const size_t attn_bytes = ws_bytes - 2 * gemm_bytes;
   LnDesc ln;
