@@ -418,7 +418,8 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   ka.tiles_m = (d.Mb + v.BM - 1) / v.BM;
   ka.tiles_n = (d.Nb + v.BN - 1) / v.BN;
   {
-    const long long per_xcd = ((long long)ka.tiles_m * ka.tiles_n + 7) / 8;
+    const long long all = (long long)ka.tiles_m * ka.tiles_n, mine = (all * (plan.seq ? 1 : plan.splits) + 7) / 8;
+    const long long per_xcd = mine < all ? mine : all;
     int g = 1;
     while ((long long)(2 * g) * (2 * g) * v.BM <= per_xcd * v.BN * 2 && 2 * g <= 16) g *= 2;  // g ~ sqrt(per_xcd * BN / BM)
     ka.group = g;
