@@ -128,8 +128,19 @@ GemmDesc attn_base_desc(const AttnDims& a) {
   return d;
 }
 
+AttnProbsDesc probs_desc(const bf16_t* qkv_blk, const bf16_t* probs_blk, const AttnDims& a, int causal) {
+  AttnProbsDesc p = {};
+  p.qkv = qkv_blk; p.probs = const_cast<bf16_t*>(probs_blk);
+  p.s = a.s; p.d = a.d; p.nh = a.nh; p.ld = a.ld; p.ldo = a.ldo; p.causal = causal;
+  p.nmat = a.nmat;
+  return p;
+}
+
 int attention_fwd_device(const bf16_t* qkv_blk, bf16_t* probs_blk, bf16_t* attn_blk, const AttnDims& a, int causal, void* ws,
                          hipStream_t st) {
+  AttnProbsDesc p = probs_desc(qkv_blk, probs_blk, a, causal);
+  p.attn = attn_blk;
+  if (attn_probs_supported(p)) return launch_attn_probs_fwd(p, st);
   float* scores = (float*)ws;
   const long long ss = (long long)a.s * a.s;
   const float scale = 1.0f / sqrtf((float)a.d);
@@ -175,7 +186,11 @@ int attention_bwd_device(const bf16_t* qkv_blk, const bf16_t* probs_blk, const b
     g.k_lo_diag = causal;
     if ((rc = launch_gemm(g, st))) return rc;
   }
-  {  // dP = dO V^T
+  AttnProbsDesc p = probs_desc(qkv_blk, probs_blk, a, causal);
+  p.d_attn = dattn_blk; p.d_scores = dS; p.d_qkv = dqkv_blk;
+  const bool joined = attn_probs_supported(p);   // dS and dQ in one launch, dP never in memory
+  if (joined && (rc = launch_attn_probs_bwd(p, st))) return rc;
+  if (!joined) {  // dP = dO V^T
     GemmDesc g = attn_base_desc(a);
     g.A = dattn_blk; g.B = qkv_blk + 2 * a.d; g.C = dP;
     g.Mb = a.s; g.Nb = a.s; g.Kp = a.d;
@@ -184,8 +199,8 @@ int attention_bwd_device(const bf16_t* qkv_blk, const bf16_t* probs_blk, const b
     g.out_fp32 = 1; g.skip_upper = causal;
     if ((rc = launch_gemm(g, st))) return rc;
   }
-  if ((rc = launch_softmax_bwd(dP, probs_blk, dS, (int)a.nmat, a.s, causal, st))) return rc;
-  {  // dQ = dS K / sqrt(d)
+  if (!joined && (rc = launch_softmax_bwd(dP, probs_blk, dS, (int)a.nmat, a.s, causal, st))) return rc;
+  if (!joined) {  // dQ = dS K / sqrt(d)
     GemmDesc g = attn_base_desc(a);
     g.A = dS; g.B = qkv_blk + a.d; g.C = dqkv_blk;
     g.Mb = a.s; g.Nb = a.d; g.Kp = a.s;

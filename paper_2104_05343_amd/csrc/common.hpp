@@ -173,6 +173,22 @@ bool attn_fused_supported(int d);
 int launch_attn_fused_fwd(const AttnFusedDesc& d, hipStream_t stream);
 int launch_attn_fused_bwd(const AttnFusedDesc& d, hipStream_t stream);
 
+// Attention that keeps the probabilities, head widths 64 and 128 (attention_probs.hip): nmat matrices of consecutive sequences,
+// nh heads each.
+struct AttnProbsDesc {
+  const void* qkv;      // rows of ld
+  void* probs;          // [nmat][s][s]: written by the forward, read by the backward
+  void* attn;           // forward: rows of ldo
+  const void* d_attn;   // backward: rows of ldo
+  void* d_scores;       // backward, written: [nmat][s][s]; with the mask zeros are written up to 256 columns past the diagonal
+  void* d_qkv;          // backward: the Q part is written
+  int s, d, nh, ld, ldo, causal;
+  long long nmat;
+};
+bool attn_probs_supported(const AttnProbsDesc& d);
+int launch_attn_probs_fwd(const AttnProbsDesc& d, hipStream_t stream);   // P and O
+int launch_attn_probs_bwd(const AttnProbsDesc& d, hipStream_t stream);   // dS and dQ
+
 // model ends (embedding, cross entropy) on the devices i0..i0+ni-1 x j0..j0+nj-1 of the grid
 struct EndDesc {
   int rows, vb, hb, q, v;   // M/q, v/q, h/q, grid size, vocabulary size

@@ -1,0 +1,65 @@
+"""GPU parity of the attention that keeps the probabilities at the edges of its row and column tiles: head widths 64 and 128,
+sequences of one 8-row piece up to several 128-row tiles, launches of few matrices (64-row workgroups) and of many (128-row)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2104_05343_amd as opt
+from oracle import attention as oatt
+from oracle.metrics import rel_frobenius
+from workloads import round_to_bf16
+from gpu_util import mat_to_dev, mat_to_host, empty, to_host
+
+pytestmark = pytest.mark.gpu
+TOL = 5e-3   # two bf16 roundings (P or dS, then the result), 2^-9 each
+
+# (sequences, s, heads, head width): 64 * 2 tiles of 128 rows and more make the 128-row workgroups
+SHAPES = [(2, 8, 2, 64), (1, 64, 1, 128), (1, 72, 2, 128), (2, 200, 1, 64), (16, 136, 4, 128), (8, 200, 8, 64), (16, 264, 4, 64)]
+
+
+def _attention(qkv, d_attn, b, s, n, d, causal):
+    h, M = n * d, b * s
+    ws = torch.empty(opt.attention_workspace_bytes(b, s, h, n, 1), dtype=torch.uint8, device="cuda:0")
+    P, O, G = empty(b * n * s * s, "bf16"), empty(M * h, "bf16"), empty(M * 3 * h, "bf16")
+    x, dO = mat_to_dev(qkv, 1, "bf16"), mat_to_dev(d_attn, 1, "bf16")
+    opt.attention_fwd(x, P, O, b, s, h, n, 1, 0, 0, causal, opt.BF16, ws)
+    opt.attention_bwd(x, P, dO, G, b, s, h, n, 1, 0, 0, causal, opt.BF16, ws)
+    torch.cuda.synchronize()
+    return P, O, G
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("b,s,n,d", SHAPES)
+def test_edges(b, s, n, d, causal):
+    h, M = n * d, b * s
+    rng = np.random.default_rng(s + d)
+    qkv = round_to_bf16((rng.standard_normal((M, 3 * h)) * 2).astype(np.float32))
+    d_attn = round_to_bf16(rng.standard_normal((M, h)).astype(np.float32))
+    P, O, G = _attention(qkv, d_attn, b, s, n, d, causal)
+    attn_o, probs_o = oatt.forward(qkv, b, s, n, causal)
+    p = to_host(P).reshape(b, n, s, s)
+    assert rel_frobenius(p, probs_o) <= TOL
+    if causal:
+        iu = np.triu_indices(s, 1)
+        assert np.all(p[..., iu[0], iu[1]] == 0.0) and np.all(p[..., 0, 0] == 1.0)
+    assert rel_frobenius(mat_to_host(O, M, h, 1), attn_o) <= TOL
+    got, want = mat_to_host(G, M, 3 * h, 1), oatt.backward(qkv, d_attn, b, s, n, causal)
+    part = (np.arange(3 * h) // d) % 3
+    for k in range(3):   # P rounded to bf16 before the backward: a third rounding
+        assert rel_frobenius(got[:, part == k], want[:, part == k]) <= 1.5 * TOL, k
+
+
+@pytest.mark.parametrize("s,d", [(136, 128), (200, 64)])
+def test_workgroups_of_64_and_128_rows_same_bits(s, d):
+    b, n = 16, 8
+    h = n * d
+    rng = np.random.default_rng(d)
+    qkv = round_to_bf16(rng.standard_normal((b * s, 3 * h)).astype(np.float32))
+    d_attn = round_to_bf16(rng.standard_normal((b * s, h)).astype(np.float32))
+    P, O, G = _attention(qkv, d_attn, b, s, n, d, True)
+    rows = slice(3 * s, 4 * s)
+    P1, O1, G1 = _attention(qkv[rows], d_attn[rows], 1, s, n, d, True)
+    assert torch.equal(P.view(torch.int16).view(b, -1)[3], P1.view(torch.int16))
+    assert torch.equal(O.view(torch.int16).view(b, -1)[3], O1.view(torch.int16))
+    cols = torch.from_numpy(np.flatnonzero((np.arange(3 * h) // d) % 3 == 0)).to("cuda:0")
+    assert torch.equal(G.view(torch.int16).view(b * s, -1)[rows][:, cols], G1.view(torch.int16).view(s, -1)[:, cols])
