@@ -105,6 +105,7 @@ int run_summa(int form, const void* A, const void* B, void* C, int64_t M, int64_
 struct AttnDims {
   int nb, nh, d, s, ld, ldo;
   long long blk_qkv, blk_attn, blk_probs, nmat;
+  long long nmat_dev;   // of one device, whatever a launch covers
 };
 int attn_dims(int b, int s, int h, int n, int q, AttnDims* a) {
   if (q <= 0 || b <= 0 || s <= 0 || h <= 0 || n <= 0) return OPTIMUS_ESHAPE;
@@ -114,7 +115,7 @@ int attn_dims(int b, int s, int h, int n, int q, AttnDims* a) {
   a->ld = 3 * h / q; a->ldo = h / q;
   a->blk_qkv = (long long)a->nb * s * a->ld;
   a->blk_attn = (long long)a->nb * s * a->ldo;
-  a->nmat = (long long)a->nb * a->nh;
+  a->nmat = a->nmat_dev = (long long)a->nb * a->nh;
   a->blk_probs = a->nmat * s * s;
   return OPTIMUS_OK;
 }
@@ -126,6 +127,20 @@ GemmDesc attn_base_desc(const AttnDims& a) {
   GemmDesc d = {};
   d.dtype = OPTIMUS_BF16; d.nl = 1; d.nz1 = a.nb; d.nz0 = a.nh; d.alpha = 1.0f; d.splits = 1;
   return d;
+}
+
+// One launch for scores, soft-max and their product, or one each.  The joint kernels walk a row's columns twice in one workgroup,
+// so a few long matrices take as long as the separate launches and more; by one device's matrices, as the sums are added in
+// another order.  Measured, us, separate / joint, causal: forward, width 64: one matrix of s = 512 13 / 12, 1024 18 / 19, 4096 55 /
+// 66, two 20 / 20, 76 / 67; width 128: 256 14 / 11, four of 1024 25 / 28, six 30 / 28, two of 4096 79 / 94, four 144 / 95.
+// Backward (dV and dK included), width 64: one of 256 21 / 19, of 512 25 / 26, four of 1024 41 / 43, eight 46 / 43, two of 4096 127 / 139, four
+// 216 / 142; width 128: one of 256 22 / 22, eight of 512 30 / 32, 16 36 / 34, eight of 1024 47 / 52, 16 61 / 58, four of 2048 75
+// / 94, eight 100 / 94.
+bool attn_joint(const AttnDims& a, bool bwd) {
+  const long long n = a.nmat_dev;
+  const bool many = n * a.s >= 16384;
+  if (!bwd) return a.d == 64 ? a.s <= 768 || n >= 2 : a.s <= 256 || n >= 6 || many;
+  return a.d == 64 ? a.s <= 512 || n >= 6 || many : a.s <= 256 || n >= 16 || many;
 }
 
 AttnProbsDesc probs_desc(const bf16_t* qkv_blk, const bf16_t* probs_blk, const AttnDims& a, int causal) {
@@ -140,7 +155,7 @@ int attention_fwd_device(const bf16_t* qkv_blk, bf16_t* probs_blk, bf16_t* attn_
                          hipStream_t st) {
   AttnProbsDesc p = probs_desc(qkv_blk, probs_blk, a, causal);
   p.attn = attn_blk;
-  if (attn_probs_supported(p)) return launch_attn_probs_fwd(p, st);
+  if (attn_joint(a, false) && attn_probs_supported(p)) return launch_attn_probs_fwd(p, st);
   float* scores = (float*)ws;
   const long long ss = (long long)a.s * a.s;
   const float scale = 1.0f / sqrtf((float)a.d);
@@ -188,7 +203,7 @@ int attention_bwd_device(const bf16_t* qkv_blk, const bf16_t* probs_blk, const b
   }
   AttnProbsDesc p = probs_desc(qkv_blk, probs_blk, a, causal);
   p.d_attn = dattn_blk; p.d_scores = dS; p.d_qkv = dqkv_blk;
-  const bool joined = attn_probs_supported(p);   // dS and dQ in one launch, dP never in memory
+  const bool joined = attn_joint(a, true) && attn_probs_supported(p);   // dS and dQ in one launch, dP never in memory
   if (joined && (rc = launch_attn_probs_bwd(p, st))) return rc;
   if (!joined) {  // dP = dO V^T
     GemmDesc g = attn_base_desc(a);
@@ -262,7 +277,7 @@ int attn_fused_dims(int b, int s, int h, int n, int q, AttnDims* a) {
   a->ld = 3 * h / q; a->ldo = h / q;
   a->blk_qkv = (long long)a->nb * s * a->ld;
   a->blk_attn = (long long)a->nb * s * a->ldo;
-  a->nmat = (long long)a->nb * a->nh;
+  a->nmat = a->nmat_dev = (long long)a->nb * a->nh;
   a->blk_probs = 0;
   if (a->nmat > 65535) return OPTIMUS_ESHAPE;
   return OPTIMUS_OK;

@@ -19,8 +19,8 @@
 //
 // Measured, us, causal, separate launches (products of 64x64 tiles, soft-max over rows) against these.  128 matrices, s = 512,
 // d = 64 (all devices of a 1024-wide layer on a 4 x 4 grid): forward 32 + 25 + 19 against 28 (67 MiB of P: 2.4 TB/s), backward
-// beside the weight gradients 42 + 37 + 20 against 49.  16 matrices, s = 1024, d = 128 (one device of a 4096-wide layer):
-// forward 20 + 14 + 13 against 38.  Passes: checkpointed stack of four such 1024-wide layers 3721 / 3112, 4096-wide layer
+// beside the weight gradients 42 + 37 + 20 against 49.  16 matrices, s = 1024, d = 128 (one device of a 4096-wide layer), the
+// whole call: forward 40 / 29, backward 61 / 58.  Passes: checkpointed stack of four such 1024-wide layers 3721 / 3112, 4096-wide layer
 // 871 / 857, two 256-wide layers 321 / 301.
 #include "attention_fused_kernel.hpp"
 
@@ -311,8 +311,10 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
 
 template <int D, bool CAUSAL, bool BWD>
 void launch_rows(const ProbArgs& a, long long nmat, hipStream_t st) {
-  // 128-row workgroups (half the tiles' bytes per row) where there is one for every second compute unit; the sums are the same
-  const bool big = (long long)((a.s + 127) / 128) * nmat >= 128;
+  // 128-row workgroups (half the tiles' bytes per row) where every compute unit gets one; the sums are the same.  64 against 128
+  // rows, us, forward / backward, causal: 128 workgroups of 128 rows (16 matrices, s = 1024, d = 128) 29 / 58 against 34 / 69, (32,
+  // 512, 64) 14 / 30 against 16 / 34; 256 (128, 256, 128) 22 / 43 against 16 / 39, (16, 2048, 128) 66 / 125 against 62 / 133.
+  const bool big = (long long)((a.s + 127) / 128) * nmat >= 256;
   const int rows = big ? 128 : BLK;
   const dim3 grid((unsigned)nmat, (a.s + rows - 1) / rows);
   if (big) attn_probs_kernel<D, CAUSAL, 4, BWD><<<grid, 512, 0, st>>>(a);

@@ -13,8 +13,9 @@ from gpu_util import mat_to_dev, mat_to_host, empty, to_host
 pytestmark = pytest.mark.gpu
 TOL = 5e-3   # two bf16 roundings (P or dS, then the result), 2^-9 each
 
-# (sequences, s, heads, head width): 64 * 2 tiles of 128 rows and more make the 128-row workgroups
-SHAPES = [(2, 8, 2, 64), (1, 64, 1, 128), (1, 72, 2, 128), (2, 200, 1, 64), (16, 136, 4, 128), (8, 200, 8, 64), (16, 264, 4, 64)]
+# (sequences, s, heads, head width): 256 tiles of 128 rows and more make the 128-row workgroups
+SHAPES = [(2, 8, 2, 64), (1, 64, 1, 128), (1, 72, 2, 128), (2, 200, 1, 64), (32, 136, 4, 128), (16, 200, 8, 64), (22, 264, 4, 64), (2, 520, 3, 128),
+          (2, 520, 8, 128)]
 
 
 def _attention(qkv, d_attn, b, s, n, d, causal):
@@ -51,7 +52,7 @@ def test_edges(b, s, n, d, causal):
 
 @pytest.mark.parametrize("s,d", [(136, 128), (200, 64)])
 def test_workgroups_of_64_and_128_rows_same_bits(s, d):
-    b, n = 16, 8
+    b, n = 16, 8   # 256 tiles of 128 rows; one sequence: 16
     h = n * d
     rng = np.random.default_rng(d)
     qkv = round_to_bf16(rng.standard_normal((b * s, 3 * h)).astype(np.float32))
