@@ -437,7 +437,12 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   long long nwg = (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits;
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
   int rc;
-  if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, plan.ragged == 2, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
+  // 64x64 tiles, at most two workgroups per CU: twice the loads in flight (figures: gemm_mfma_deep.hip).  From the third on they
+  // fill each other's gaps and need the LDS: [2048 x 2048 x 1024] of A B (512) 17.2 / 17.0 us.
+  if (vi == 7 && !plan.ragged && !plan.seq && g_loop == 2 && nwg <= 2LL * num_cus()) {
+    const bool plain = ka.splits == 1 && e.alpha == 1.0f && !e.bias && !e.pre_act && !e.act && !e.gelu_grad_of && !e.residual;
+    rc = launch_gemm_mfma_deep(plain, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
+  } else if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, plan.ragged == 2, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   else switch (vi) {
     case 0: rc = launch_layout<256, 256, 2, 4>(d, ka, nwg, stream); break;
     case 1: rc = launch_layout<256, 128, 4, 2>(d, ka, nwg, stream); break;

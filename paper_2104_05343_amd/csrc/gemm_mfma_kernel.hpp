@@ -97,6 +97,8 @@ struct KArgs {
   EpiArgs epi;
 };
 
+// tile variant 7 with four stages of 64 k in LDS (gemm_mfma_deep.hip)
+int launch_gemm_mfma_deep(bool plain, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
 // tile variants 3, 6, 7 in their ragged form, 3 also for long panels (gemm_mfma_ragged.hip)
 int launch_gemm_mfma_ragged(int variant, bool long_panels, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
 
@@ -390,11 +392,12 @@ struct Occ {
 // LOOP selects the k-loop: 1 = ring of four 32-wide slabs, fragments read one sub-step ahead
 // (the loop described above); 2 = stages of 64 k, the fragments of a whole stage read into registers while the
 // matrix cores work on the registers of the stage before it (see the loop).
-template <int BM, int BN>
+// 3 = the loop of 2 with four stages, for 64x64 tiles in launches of few workgroups (gemm_mfma_deep.hip).
+template <int BM, int BN, int LOOP = 2>
 struct Loop2 {
   // three stages where one workgroup owns the CU anyway (the 384-row tiles: 144 KiB); two stages otherwise, which is the
   // LDS footprint of the four-slab ring, so that as many workgroups share a CU as with it
-  static constexpr int NST = (BM + BN == 384) ? 3 : 2;
+  static constexpr int NST = LOOP == 3 ? 4 : (BM + BN == 384) ? 3 : 2;
   static constexpr int RING32 = 2 * NST;                                        // the same space in 32-wide slabs
 };
 
@@ -407,7 +410,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
   using T = Tile<BM, BN, WM, WN>;
   constexpr int THREADS = T::THREADS, NW = T::NW;
   constexpr int TM = T::TM, TN = T::TN, MI = T::MI, NI = T::NI;
-  constexpr int RING = LOOP == 2 ? Loop2<BM, BN>::RING32 : NSTAGE;   // slabs per operand (see read_frag_ring)
+  constexpr int RING = LOOP >= 2 ? Loop2<BM, BN, LOOP>::RING32 : NSTAGE;   // slabs per operand (see read_frag_ring)
   constexpr int LDS_BYTES = RING * (T::A_ELEMS + T::B_ELEMS) * 2;
   __shared__ __attribute__((aligned(1024))) bf16_t lds_all[RING * (T::A_ELEMS + T::B_ELEMS)];
   bf16_t* const ldsA = lds_all;
@@ -505,7 +508,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
   if (t_lo < t_hi) {
     // slab index -> (panel l, offset k0 inside the panel); advanced incrementally
     int l = t_lo / tpp, k0 = (t_lo - l * tpp) * BK;
-    if constexpr (LOOP == 2) {
+    if constexpr (LOOP >= 2) {
       // ---- stages of 64 k ----
       // LDS holds NST stages of [BM x 64] + [64 x BN].  An iteration (one stage, four 16-wide sub-steps) has two halves:
       //   first half:  matrix-core instructions of sub-steps 0, 1 (registers h0) | LDS reads of sub-steps 2, 3 (-> h1)
@@ -516,7 +519,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
       // iterations, so neither wait is normally exposed.  The memory instructions of a half are spread between its
       // matrix-core instructions: issued in one burst they fill the CU's LDS and memory-instruction queues, and a
       // wavefront that waits for queue space issues no matrix-core instruction either.
-      constexpr int NST = Loop2<BM, BN>::NST;
+      constexpr int NST = Loop2<BM, BN, LOOP>::NST;
       constexpr int PA1 = DirectPlan<BM, NW>::PER, PB1 = DirectPlan<BN, NW>::PER;   // KiB chunks per wavefront per 32 k
       constexpr int NOA = AKC ? 2 * PA1 : PA1, NOB = BKC ? 2 * PB1 : PB1;             // distinct lane offsets
       constexpr int LP = 2 * PA1 + 2 * PB1;                                          // loads per wavefront per stage
@@ -628,9 +631,23 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
       issue_stage(0);
       if (n64 > 1) issue_stage(1);
       if (NST > 2 && n64 > 2) issue_stage(2);
+      if constexpr (NST > 3) {
+        if (n64 > 3) issue_stage(3);
+      }
+      // all but the n youngest stages have landed, and this wavefront's reads are done
+      [[maybe_unused]] auto wait_younger = [&](int n) {
+        static_assert(NST <= 4 && (NST - 1) * LP <= 63, "the cases below; vmcnt has six bits");
+        switch (n) {
+          case 1: OPTIMUS_WAIT_VMCNT_LGKM0(LP); break;
+          case 2: OPTIMUS_WAIT_VMCNT_LGKM0(NST > 2 ? 2 * LP : 0); break;
+          case 3: OPTIMUS_WAIT_VMCNT_LGKM0(NST > 3 ? 3 * LP : 0); break;
+          default: OPTIMUS_WAIT_VMCNT_LGKM0(0); break;
+        }
+      };
       {
         const int younger = (n64 > NST ? NST : n64) - 1;
-        if (younger >= 2) OPTIMUS_WAIT_VMCNT(2 * LP);
+        if constexpr (NST > 3) wait_younger(younger);
+        else if (younger >= 2) OPTIMUS_WAIT_VMCNT(2 * LP);
         else if (younger == 1) OPTIMUS_WAIT_VMCNT(LP);
         else OPTIMUS_WAIT_VMCNT(0);
       }
@@ -677,8 +694,8 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
 #if OPTIMUS_LAB_DBG & 64
         const unsigned long long lab_ta = clock64();
 #endif
-        // stage i+1 has landed (stage i+2's loads stay in flight); my reads of stage i are done
-        if constexpr (!(OPTIMUS_LAB_DBG & 16)) OPTIMUS_WAIT_VMCNT_LGKM0(NST > 2 ? LP : 0);
+        // stage i+1 has landed (the NST-2 younger ones stay in flight); my reads of stage i are done
+        if constexpr (!(OPTIMUS_LAB_DBG & 16)) OPTIMUS_WAIT_VMCNT_LGKM0((NST - 2) * LP);
         if constexpr (!(OPTIMUS_LAB_DBG & 2)) OPTIMUS_BARRIER();
 #if OPTIMUS_LAB_DBG & 64
         lab_sum_a += lab_ta;
@@ -696,7 +713,8 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
       for (; i + 1 < n64; ++i) {
         range_end(i);
         half(first, yes, no, st_cur, 0);
-        if (NST > 2 && i + 2 < n64) OPTIMUS_WAIT_VMCNT_LGKM0(LP);
+        if constexpr (NST > 3) wait_younger(n64 - 2 - i);
+        else if (NST > 2 && i + 2 < n64) OPTIMUS_WAIT_VMCNT_LGKM0(LP);
         else OPTIMUS_WAIT_VMCNT_LGKM0(0);
         OPTIMUS_BARRIER();
         half(second, yes, no, st_nxt, st_cur);
