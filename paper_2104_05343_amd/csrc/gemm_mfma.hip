@@ -273,6 +273,9 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
       if (v == 3) t_slab *= d.a_kcontig && d.b_kcontig ? 1.14f : (d.a_kcontig ? 0.92f : 1.04f);
       if (v == 6 && d.a_kcontig && d.b_kcontig) t_slab *= 1.18f;
       if (v == 7 && !d.a_kcontig) t_slab *= 1.25f;   // both operands through the transposing LDS reads
+      // the form with four stages (at most two workgroups per CU).  [1024 x 4096 x 256] in four ranges instead of eight: A B 14.8 us to
+      // 12.8, A^T B 15.3 to 12.8
+      if (v == 7 && !ragged && wgs <= 2 * ncu) t_slab *= resident == 1 ? 0.7f : 0.9f;
       const float per_wg = (float)((((slabs + sp - 1) / sp) + 1) & ~1LL) * t_slab;
       // split: the combine launch, and the fp32 partial tiles read back by it (their writes overlap the products)
       const float traffic_us =
