@@ -203,10 +203,9 @@ static int num_cus() {
   return cached[dev];
 }
 
-static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
+// forced, forced_corun: the hooks as make_plan read them
+static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int forced, int forced_corun) {
   Plan best = {kAnyVariant, 1, 0, 0};
-  int forced = g_variant.load();                       // one consistent view of the hooks per plan
-  int forced_corun = d.corun > 0 ? g_corun_variant[d.corun - 1].load() : -1;
   if (forced == kAnyVariant) return best;
   const bool long_panels = !panels_in_window(d);
   if (long_panels && !long_panels_ok(d)) return best;
@@ -343,6 +342,7 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
 
 // The plan is arithmetic on shapes, 1 us of host time for its sixty combinations of tile and split, and a layer's pass asked for it a
 // hundred times (workspace sizes, every product): a thread keeps the last plans it computed, by everything a plan depends on.
+// The hooks are read once, for the key and the plan: another thread may set them at any time.
 // Host time of a pass before and now: two checkpointed layers of [128 x 128] blocks 266 / 232 us, one device of a 1024-wide
 // layer 144 / 113.
 struct PlanKey {
@@ -363,7 +363,7 @@ static Plan make_plan(const GemmDesc& d, bool vec_ok, bool have_ws) {
   for (unsigned i = 0; i < sizeof(k) / sizeof(int); ++i) h = (h ^ (unsigned)w[i]) * 2654435761u;
   Entry& e = table[(h >> 16) % kEntries];
   if (memcmp(&e.key, &k, sizeof(k)) != 0) {
-    e.plan = compute_plan(d, vec_ok, have_ws);
+    e.plan = compute_plan(d, vec_ok, have_ws, k.forced, k.forced_corun);
     e.key = k;
   }
   return e.plan;

@@ -2,6 +2,11 @@
 256 compute units).  The panel split is the only part of a plan that changes the bits of a result (it fixes the order
 in which the panels' contributions are added), so it must be a function of ONE device's block shape alone: the same
 for device mode and grid mode, with and without a co-running product, with and without workspace.  The tile may differ."""
+import ctypes
+import shutil
+import subprocess
+import threading
+
 import pytest
 
 import paper_2104_05343_amd as opt
@@ -95,3 +100,43 @@ def test_streams_of_the_whole_grid_and_refused_arguments():
     assert opt.binding.debug_layer_bwd_streams(cfg, -1, -1) == 2      # 16 devices' products
     assert opt.binding.debug_layer_bwd_streams(cfg, 4, 0) == -1
     assert opt.binding.debug_layer_bwd_streams(opt.LayerCfg(8, 512, 1024, 15, 4, 1e-5, 1, opt.BF16, 0), 0, 0) == -1
+
+
+SWITCH_HOOK = """
+extern void optimus_debug_set_gemm_variant(int);
+void switch_hook(volatile int* stop) { while (!*stop) { optimus_debug_set_gemm_variant(3); optimus_debug_set_gemm_variant(-1); } }
+"""
+
+
+# The plans a thread keeps are those of the hooks they are filed under, also where another thread changes a hook meanwhile.
+@pytest.mark.skipif(not shutil.which("gcc"), reason="needs a C compiler")
+def test_kept_plans_belong_to_their_hooks(tmp_path):
+    src, so = tmp_path / "switch_hook.c", tmp_path / "switch_hook.so"
+    src.write_text(SWITCH_HOOK)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so), str(src), opt.binding.LIB_PATH], check=True)
+    opt.lib()
+    helper, stop = ctypes.CDLL(str(so)), ctypes.c_int(0)
+    shapes = [("ab", 4 * 64 * m, 4 * 512, 4 * 64 * n, 4, 0, 0) for m in range(3, 13) for n in range(3, 13)]
+    plans = {}
+
+    def ask(key):
+        plans[key] = [plan(*s) for s in shapes]
+
+    def ask_while_and_after():
+        try:
+            ask("while")
+        finally:
+            stop.value = 1
+            switching.join()
+            opt.debug_set_gemm_variant(-1)
+        ask("after")
+
+    fresh = threading.Thread(target=ask, args=("alone",))
+    fresh.start()
+    fresh.join()
+    switching = threading.Thread(target=helper.switch_hook, args=(ctypes.byref(stop),))
+    worker = threading.Thread(target=ask_while_and_after)
+    switching.start()
+    worker.start()
+    worker.join()
+    assert plans["after"] == plans["alone"]
