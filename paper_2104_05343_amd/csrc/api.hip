@@ -97,7 +97,7 @@ int run_summa(int form, const void* A, const void* B, void* C, int64_t M, int64_
     // a planned panel split writes its partial tiles to the workspace if it is there and large enough; otherwise the
     // same split is emulated inside the workgroups: the bits of a result do not depend on the workspace
     const size_t need = gemm_plan_bytes(d);
-    if (need > 0 && ws && ws_bytes >= need) d.partials = (float*)ws;
+    if (need > 0 && ws && ws_bytes >= need) { d.partials = (float*)ws; d.partials_bytes = ws_bytes; }
   }
   return launch_gemm(d, as_stream(stream));
 }

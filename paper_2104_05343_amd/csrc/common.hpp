@@ -83,6 +83,7 @@ struct GemmDesc {
   // split of the panel loop over several workgroups (fixed-order combine)
   int splits;          // 1 = none
   float* partials;     // workspace [splits][nz][Mb][Nb] fp32 when splits > 1
+  size_t partials_bytes;   // of that workspace
   // 0: the product has the chip to itself; 1 / 2: it is one of two products that the layer's backward pass runs
   // side by side on two streams (1: activation-gradient chain, 2: parameter-gradient branch)
   int corun;

@@ -400,8 +400,10 @@ bool gemm_plan_of(const GemmDesc& d, bool have_ws, int out[3]) {
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   if (!gemm_mfma_supported(d)) return OPTIMUS_EINVAL;
   const bool vec_ok = epilogue_vec_ok(d);
-  // d.partials != nullptr means the caller provided the workspace that the planned split asked for
-  const Plan plan = make_plan(d, vec_ok, d.partials != nullptr);
+  // d.partials: the workspace that the planned split asked for.  A hook that another thread has set since may ask for more: then
+  // as without a workspace.
+  Plan plan = make_plan(d, vec_ok, d.partials != nullptr);
+  if (!plan.seq && gemm_partials_bytes(d, plan.splits) > d.partials_bytes) plan = make_plan(d, vec_ok, false);
   const int vi = plan.variant;
   if (vi == kAnyVariant) {
     g_last_plan = kAnyVariant | (1 << 8);
@@ -436,7 +438,7 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   e.alpha = d.alpha; e.bias = d.bias; e.C = d.C; e.pre_act = d.pre_act; e.gelu_grad_of = d.gelu_grad_of;
   e.residual = d.residual; e.ldc = d.ldc; e.act = d.act; e.out_fp32 = d.out_fp32; e.in_bf16 = 1;
   e.vec_ok = vec_ok ? 1 : 0;
-  if (ka.splits > 1 && !d.partials) return OPTIMUS_EWORKSPACE;
+  if (ka.splits > 1 && gemm_partials_bytes(d, ka.splits) > d.partials_bytes) return OPTIMUS_EWORKSPACE;
   long long nwg = (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits;
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
   int rc;

@@ -8,6 +8,7 @@ import subprocess
 import threading
 
 import pytest
+import torch
 
 import paper_2104_05343_amd as opt
 from bench import layer_gemm_list
@@ -108,14 +109,32 @@ void switch_hook(volatile int* stop) { while (!*stop) { optimus_debug_set_gemm_v
 """
 
 
-# The plans a thread keeps are those of the hooks they are filed under, also where another thread changes a hook meanwhile.
-@pytest.mark.skipif(not shutil.which("gcc"), reason="needs a C compiler")
-def test_kept_plans_belong_to_their_hooks(tmp_path):
+@pytest.fixture
+def switched_hook(tmp_path):
+    """A callable that runs another one while a second thread forces the 128x128 tile and lets it go, over and over."""
+    if not shutil.which("gcc"):
+        pytest.skip("needs a C compiler")
     src, so = tmp_path / "switch_hook.c", tmp_path / "switch_hook.so"
     src.write_text(SWITCH_HOOK)
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so), str(src), opt.binding.LIB_PATH], check=True)
     opt.lib()
-    helper, stop = ctypes.CDLL(str(so)), ctypes.c_int(0)
+    helper = ctypes.CDLL(str(so))
+
+    def run(f):
+        stop = ctypes.c_int(0)
+        switching = threading.Thread(target=helper.switch_hook, args=(ctypes.byref(stop),))
+        switching.start()
+        try:
+            return f()
+        finally:
+            stop.value = 1
+            switching.join()
+            opt.debug_set_gemm_variant(-1)
+    return run
+
+
+# The plans a thread keeps are those of the hooks they are filed under, also where another thread changes a hook meanwhile.
+def test_kept_plans_belong_to_their_hooks(switched_hook):
     shapes = [("ab", 4 * 64 * m, 4 * 512, 4 * 64 * n, 4, 0, 0) for m in range(3, 13) for n in range(3, 13)]
     plans = {}
 
@@ -123,20 +142,35 @@ def test_kept_plans_belong_to_their_hooks(tmp_path):
         plans[key] = [plan(*s) for s in shapes]
 
     def ask_while_and_after():
-        try:
-            ask("while")
-        finally:
-            stop.value = 1
-            switching.join()
-            opt.debug_set_gemm_variant(-1)
+        switched_hook(lambda: ask("while"))
         ask("after")
 
-    fresh = threading.Thread(target=ask, args=("alone",))
-    fresh.start()
-    fresh.join()
-    switching = threading.Thread(target=helper.switch_hook, args=(ctypes.byref(stop),))
-    worker = threading.Thread(target=ask_while_and_after)
-    switching.start()
-    worker.start()
-    worker.join()
+    for target, args in ((ask, ("alone",)), (ask_while_and_after, ())):   # a thread each: plans are kept per thread
+        t = threading.Thread(target=target, args=args)
+        t.start()
+        t.join()
     assert plans["after"] == plans["alone"]
+
+
+# A launch never writes partial tiles beyond the workspace it was given, whatever the hooks say by then.  (Without a device the
+# launch itself is refused; the plan it was refused with stays readable.)
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the operands are no memory")
+def test_partial_tiles_fit_the_workspace_under_changing_hooks(switched_hook):
+    M, K, N, q = 4 * 512, 4 * 1024, 4 * 512, 4
+    need = {}
+    for variant in (-1, 3):
+        opt.debug_set_gemm_variant(variant)
+        need[variant] = opt.summa_workspace_bytes("ab", M, K, N, q, 0, 0, opt.BF16)
+    opt.debug_set_gemm_variant(-1)
+    small = min(need.values())
+    assert 0 < small < max(need.values())
+    one, seen = ctypes.c_void_p(256), set()
+
+    def launches():
+        for _ in range(20000):
+            opt.lib().optimus_summa_ab(one, one, one, M, K, N, q, 0, 0, opt.BF16, one, small, None)
+            seen.add(opt.binding.debug_last_gemm_plan())
+    switched_hook(launches)
+    assert len(seen) >= 2
+    for _, splits, walked in seen:
+        assert walked or splits == 1 or 4 * splits * (M // q) * (N // q) <= small, seen
