@@ -123,7 +123,8 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
   auto masked = [&](int kbase) { return CAUSAL ? kbase + BLK - 1 > q0 : kbase + BLK > s; };   // uniform
 
   // ---- first walk: maximum and sum of a row (forward), or its rowsum (backward)
-  float m_run = -INFINITY, l_run = 0.f;               // backward: l_run only
+  // The maximum starts at a finite number: blocks whose scores are all -inf add exp(-inf) = 0.  A row of nothing else is 0 / 0.
+  float m_run = -__FLT_MAX__, l_run = 0.f;            // backward: l_run only
   ldr.issue(Xp, 0, s, lds[0][0]);
   if constexpr (BWD) load_p(par);
   wait_and_barrier<0>();
@@ -169,7 +170,6 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[t2][r]);
         }
-        // finite unless the scores are not: a block's first column is never past the wavefront's first row
         const float m_new = fmaxf(m_run, halfwave_max(mx) * a.scale_log2);
         float sum = 0.f;
 #pragma unroll
@@ -194,8 +194,8 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
       stat_l = l0 + l1;
     } else {
       const float m0 = lds_stat[rg][1][lane], m1 = lds_stat[rg + NRG][1][lane];
-      stat_m = fmaxf(m0, m1);                         // m0 belongs to column 0; m1 is -inf where the odd parity had no block
-      stat_l = 1.0f / (l0 * __builtin_amdgcn_exp2f(m0 - stat_m) + (m1 == -INFINITY ? 0.f : l1 * __builtin_amdgcn_exp2f(m1 - stat_m)));
+      stat_m = fmaxf(m0, m1);                         // where the odd parity had no block l1 is 0
+      stat_l = 1.0f / (l0 * __builtin_amdgcn_exp2f(m0 - stat_m) + l1 * __builtin_amdgcn_exp2f(m1 - stat_m));
     }
   }
 

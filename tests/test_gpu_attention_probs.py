@@ -64,3 +64,31 @@ def test_workgroups_of_64_and_128_rows_same_bits(s, d):
     assert torch.equal(O.view(torch.int16).view(b, -1)[3], O1.view(torch.int16))
     cols = torch.from_numpy(np.flatnonzero((np.arange(3 * h) // d) % 3 == 0)).to("cuda:0")
     assert torch.equal(G.view(torch.int16).view(b * s, -1)[rows][:, cols], G1.view(torch.int16).view(s, -1)[:, cols])
+
+
+def _peaked(b, s, n, d, rng):
+    """qkv whose scores are the product of the first component of Q and of K, the rest small."""
+    qkv = round_to_bf16((rng.standard_normal((b * s, 3 * n * d)) * 0.5).astype(np.float32))
+    first = lambda part: (np.arange(n) * 3 + part) * d
+    return qkv, first(0), first(1)
+
+
+# Head width 64 and 128; 64-row and 128-row workgroups.
+NONFINITE = [(1, 328, 2, 64), (32, 328, 4, 64), (1, 328, 8, 128), (32, 328, 4, 128)]
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("b,s,n,d", NONFINITE)
+def test_blocks_of_minus_infinity(b, s, n, d, causal):
+    """Scores that overflow to -inf weigh nothing, also where they are the first that a wavefront meets in a row."""
+    rng = np.random.default_rng(5)
+    qkv, q0, k0 = _peaked(b, s, n, d, rng)
+    qkv[:, q0], qkv[:, k0] = 2.0 ** 66, 0.0
+    rows = np.arange(b * s) % s
+    qkv[np.ix_(rows < 128, k0)] = -2.0 ** 66   # the first block of either parity
+    P, O, _ = _attention(qkv, np.ones((b * s, n * d), np.float32), b, s, n, d, causal)
+    p = to_host(P).reshape(b, n, s, s)[:, :, 128:]
+    assert np.all(p[..., :128] == 0.0)
+    want = oatt.forward(qkv, b, s, n, causal)
+    assert rel_frobenius(p, want[1][:, :, 128:]) <= TOL
+    assert rel_frobenius(mat_to_host(O, b * s, n * d, 1)[rows >= 128], want[0][rows >= 128]) <= TOL
