@@ -120,6 +120,10 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
         if (column(kbase, t2, r) > limit) p[r] = 0.f;
     }
   };
+  // exp of a score against the row's largest.  The difference first: it is 0 for the largest itself, where one fused multiply-add
+  // keeps the rounding error of the largest's product, which is beyond any exponent for scores of 1e9.  The second operation is 2 to
+  // 5 % of the forward: 16 matrices, s = 2048, d = 64, causal 44.6 -> 46.7 us, 20 without a mask 84 -> 89.
+  auto weight = [&](float score, float largest) { return __builtin_amdgcn_exp2f((score - largest) * a.scale_log2); };
   auto masked = [&](int kbase) { return CAUSAL ? kbase + BLK - 1 > q0 : kbase + BLK > s; };   // uniform
 
   // ---- first walk: maximum and sum of a row (forward), or its rowsum (backward)
@@ -170,13 +174,13 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[t2][r]);
         }
-        const float m_new = fmaxf(m_run, halfwave_max(mx) * a.scale_log2);
+        const float m_new = fmaxf(m_run, halfwave_max(mx));
         float sum = 0.f;
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(acc[t2][r], a.scale_log2, -m_new));
-        l_run = fmaf(l_run, __builtin_amdgcn_exp2f(m_run - m_new), sum);
+          for (int r = 0; r < 16; ++r) sum += weight(acc[t2][r], m_new);
+        l_run = fmaf(l_run, weight(m_run, m_new), sum);
         m_run = m_new;
       }
     }
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
     } else {
       const float m0 = lds_stat[rg][1][lane], m1 = lds_stat[rg + NRG][1][lane];
       stat_m = fmaxf(m0, m1);                         // where the odd parity had no block l1 is 0
-      stat_l = 1.0f / (l0 * __builtin_amdgcn_exp2f(m0 - stat_m) + l1 * __builtin_amdgcn_exp2f(m1 - stat_m));
+      stat_l = 1.0f / (l0 * weight(m0, stat_m) + l1 * weight(m1, stat_m));
     }
   }
 
@@ -233,7 +237,7 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
           for (int r = 0; r < 16; ++r) acc[t2][r] = p[r] * (acc[t2][r] - stat_l);
         } else {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[t2][r] = __builtin_amdgcn_exp2f(fmaf(acc[t2][r], a.scale_log2, -stat_m)) * stat_l;
+          for (int r = 0; r < 16; ++r) acc[t2][r] = weight(acc[t2][r], stat_m) * stat_l;
         }
         if (need_mask) {
 #pragma unroll

@@ -92,3 +92,20 @@ def test_blocks_of_minus_infinity(b, s, n, d, causal):
     want = oatt.forward(qkv, b, s, n, causal)
     assert rel_frobenius(p, want[1][:, :, 128:]) <= TOL
     assert rel_frobenius(mat_to_host(O, b * s, n * d, 1)[rows >= 128], want[0][rows >= 128]) <= TOL
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("b,s,n,d", NONFINITE)
+def test_scores_far_beyond_the_exponent(b, s, n, d, causal):
+    """Finite scores of any size: a row's largest score weighs exp(0) however coarse the scores' last bit is."""
+    rng = np.random.default_rng(6)
+    qkv, q0, k0 = _peaked(b, s, n, d, rng)
+    rows = np.arange(b * s) % s
+    qkv[:, q0] = round_to_bf16((1e9 * (1 + rng.random((b * s, n)))).astype(np.float32))
+    qkv[:, k0] = (rng.permutation(s)[rows] - s // 2)[:, None]   # distinct, exact in bf16: one key per row has all the weight
+    P, O, G = _attention(qkv, np.ones((b * s, n * d), np.float32), b, s, n, d, causal)
+    attn_o, probs_o = oatt.forward(qkv, b, s, n, causal)
+    assert np.all((probs_o == 0.0) | (probs_o == 1.0))
+    assert np.array_equal(to_host(P).reshape(b, n, s, s), probs_o)
+    assert rel_frobenius(mat_to_host(O, b * s, n * d, 1), attn_o) <= TOL
+    assert np.all(np.isfinite(mat_to_host(G, b * s, 3 * n * d, 1)))
