@@ -135,13 +135,13 @@ __device__ __forceinline__ float halfwave_sum(float v) {
 }
 
 // ---- direct global -> LDS copy of a ROWS x D tile (rows row0 .. row0 + ROWS - 1 of a [s][ld] matrix) by NW wavefronts ----
-__device__ __forceinline__ i32x4 make_rsrc(const bf16_t* base) {  // raw buffer, 2 GiB window (offsets used are far below)
+__device__ __forceinline__ i32x4 make_rsrc(const bf16_t* base, unsigned bytes = 0x80000000u) {  // raw buffer, 2 GiB window (offsets used are far below)
   const unsigned long long p = (unsigned long long)base;  // wave-uniform by construction; say so to the compiler
   const int lo = __builtin_amdgcn_readfirstlane((int)(unsigned)p);
   const int hi = __builtin_amdgcn_readfirstlane((int)(unsigned)((p >> 32) & 0xffffu));
-  return i32x4{lo, hi, (int)0x80000000u, 0x00020000};
+  return i32x4{lo, hi, (int)bytes, 0x00020000};
 }
-template <int D, int NW = NWAVES, int ROWS = PAIR>
+template <int D, int NW = NWAVES, int ROWS = PAIR, bool ZEROS = false>
 struct TileLoader {
   static constexpr int CH = D / 8, ROWS_PER_KIB = 64 / CH, PIECES = ROWS * D * 2 / 1024, PER = PIECES / NW;
   static_assert(PIECES % NW == 0, "tile must divide over the wavefronts");
@@ -153,7 +153,8 @@ struct TileLoader {
     for (int it = 0; it < PER; ++it) off[it] = offset_of(it, 0, 0x7fffffff, 0);
   }
   // LDS position p = lane of KiB piece (wave*PER + it) is (row, chunk position lane % CH): fetch chunk pos ^ g(row).
-  // The source row is clamped to the last row of the matrix (rows past the end are only ever multiplied by zeros).
+  // The source row is clamped to the last row of the matrix (rows past the end are only ever multiplied by zeros), or, with
+  // ZEROS, lies beyond the resource, whose loads write zeros to LDS: zero times the last row's infinity would be NaN.
   __device__ __forceinline__ unsigned offset_of(int it, int row0, int last_row, int base_row) const {
     const int row = (wave * PER + it) * ROWS_PER_KIB + lane / CH;
     const int chunk = (lane % CH) ^ swz<D>(row);
@@ -172,10 +173,10 @@ struct TileLoader {
       }
     } else {  // the tile reaches past the last row: clamp (wave-uniform branch, taken for the last pair only)
       const int base_row = max(0, s - ROWS);
-      const i32x4 rsrc = make_rsrc(mat + (long long)base_row * ld);
+      const i32x4 rsrc = make_rsrc(mat + (long long)base_row * ld, ZEROS ? (unsigned)((s - 1 - base_row) * ld + D) * 2u : 0x80000000u);
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
-        const unsigned o = offset_of(it, row0, s - 1, base_row);
+        const unsigned o = offset_of(it, row0, ZEROS ? 0x7fffffff : s - 1, base_row);
         const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base + (unsigned)(wave * PER + it) * 1024u);
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(o), "s"(rsrc), "s"(m0v) : "memory", "m0");
       }

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
   const int limit = CAUSAL ? rowc : s - 1;            // last column this lane's row has
   bf16_t* const Tp = a.tile_out + (long long)mat * s * s;
 
-  TileLoader<D, NW> ldr;
+  TileLoader<D, NW, PAIR, true> ldr;
   ldr.init(a.ld, wave, lane);
   u32x4 p_next[4];   // backward: P of the next block, 16 bytes a lane: columns 16 * n + 8 * g + 0..7 of the lane's row
   auto load_p = [&](int kb) {

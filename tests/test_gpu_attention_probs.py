@@ -109,3 +109,17 @@ def test_scores_far_beyond_the_exponent(b, s, n, d, causal):
     assert np.array_equal(to_host(P).reshape(b, n, s, s), probs_o)
     assert rel_frobenius(mat_to_host(O, b * s, n * d, 1), attn_o) <= TOL
     assert np.all(np.isfinite(mat_to_host(G, b * s, 3 * n * d, 1)))
+
+
+@pytest.mark.parametrize("b,s,n,d", NONFINITE)
+def test_infinite_last_value(b, s, n, d):
+    """The rows past the end of V weigh nothing: an infinity in its last row comes through, and nothing else does."""
+    rng = np.random.default_rng(7)
+    qkv = round_to_bf16(rng.standard_normal((b * s, 3 * n * d)).astype(np.float32))
+    clean = _attention(qkv, np.ones((b * s, n * d), np.float32), b, s, n, d, False)[1]
+    last, col = np.arange(b * s) % s == s - 1, 2 * d + 5
+    qkv[last, col] = np.inf
+    got = mat_to_host(_attention(qkv, np.ones((b * s, n * d), np.float32), b, s, n, d, False)[1], b * s, n * d, 1)
+    want = mat_to_host(clean, b * s, n * d, 1)
+    want[:, 5] = np.inf
+    assert np.array_equal(got, want)
