@@ -315,10 +315,15 @@ __global__ __launch_bounds__(NRG * 128) void attn_probs_kernel(ProbArgs a) {
 
 template <int D, bool CAUSAL, bool BWD>
 void launch_rows(const ProbArgs& a, long long nmat, hipStream_t st) {
-  // 128-row workgroups (half the tiles' bytes per row) where every compute unit gets one; the sums are the same.  64 against 128
-  // rows, us, forward / backward, causal: 128 workgroups of 128 rows (16 matrices, s = 1024, d = 128) 29 / 58 against 34 / 69, (32,
-  // 512, 64) 14 / 30 against 16 / 34; 256 (128, 256, 128) 22 / 43 against 16 / 39, (16, 2048, 128) 66 / 125 against 62 / 133.
-  const bool big = (long long)((a.s + 127) / 128) * nmat >= 256;
+  // Workgroups of 64 or of 128 rows (half the tiles' bytes per row); the sums are the same, and either kind has a compute unit to
+  // itself (LDS).  A workgroup of 64 is 0.85 of the time, so without a mask 64 rows where those workgroups are one round, 128 from
+  // the first that would be the second on.  With the mask the second round is short tiles behind long ones: 128 rows from one
+  // workgroup of theirs per compute unit on.  64 / 128 rows, us, forward: 256 of 64 rows, mask 22 / 25 (16 matrices, s = 1024, d = 64),
+  // none 22 / 26; 288 (12, 1536, 64) 30 / 34 and 55 / 35; 384 (24, 1024, 64) 25 / 26 and 40 / 27; 512 (32, 1024, 64) 30 / 26 and 41 / 28;
+  // the backward the same way, 0.86 of the time to 1.02 with the mask, 0.86 to 1.2 without.  Short rows have little to
+  // fill in behind: 384 of (96, 256, 64) with the mask 15 / 11.
+  const long long cus = num_cus();
+  const bool big = CAUSAL ? (a.s + 127) / 128 * nmat >= cus : (a.s + BLK - 1) / BLK * nmat > cus;
   const int rows = big ? 128 : BLK;
   const dim3 grid((unsigned)nmat, (a.s + rows - 1) / rows);
   if (big) attn_probs_kernel<D, CAUSAL, 4, BWD><<<grid, 512, 0, st>>>(a);

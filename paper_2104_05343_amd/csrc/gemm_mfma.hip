@@ -191,7 +191,7 @@ struct Plan {
 // have_ws: the caller's workspace holds the partial tiles of the planned split.  Without it the same split is
 // emulated inside each workgroup (identical bits, see KArgs::seq_splits), so a result never depends on the workspace.
 // compute units of the current device (the planner's unit of parallelism); 256 when there is no device to ask
-static int num_cus() {
+int num_cus() {
   static int cached[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { (void)hipGetLastError(); return 256; }

@@ -13,9 +13,9 @@ from gpu_util import mat_to_dev, mat_to_host, empty, to_host
 pytestmark = pytest.mark.gpu
 TOL = 5e-3   # two bf16 roundings (P or dS, then the result), 2^-9 each
 
-# (sequences, s, heads, head width): 256 tiles of 128 rows and more make the 128-row workgroups
+# (sequences, s, heads, head width): 256 tiles of 128 rows and more make the 128-row workgroups, without a mask more than 256 of 64
 SHAPES = [(2, 8, 2, 64), (1, 64, 1, 128), (1, 72, 2, 128), (2, 200, 1, 64), (32, 136, 4, 128), (16, 200, 8, 64), (22, 264, 4, 64), (2, 520, 3, 128),
-          (2, 520, 8, 128)]
+          (2, 520, 8, 128), (6, 200, 12, 128), (6, 264, 8, 64), (4, 264, 8, 64)]
 
 
 def _attention(qkv, d_attn, b, s, n, d, causal):
