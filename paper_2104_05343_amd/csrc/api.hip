@@ -131,16 +131,20 @@ GemmDesc attn_base_desc(const AttnDims& a) {
 
 // One launch for scores, soft-max and their product, or one each.  The joint kernels walk a row's columns twice in one workgroup,
 // so a few long matrices take as long as the separate launches and more; by one device's matrices, as the sums are added in
-// another order.  Measured, us, separate / joint, causal: forward, width 64: one matrix of s = 512 13 / 12, 1024 18 / 19, 4096 55 /
-// 66, two 20 / 20, 76 / 67; width 128: 256 14 / 11, four of 1024 25 / 28, six 30 / 28, two of 4096 79 / 94, four 144 / 95.
-// Backward (dV and dK included), width 64: one of 256 21 / 19, of 512 25 / 26, four of 1024 41 / 43, eight 46 / 43, two of 4096 127 / 139, four
-// 216 / 142; width 128: one of 256 22 / 22, eight of 512 30 / 32, 16 36 / 34, eight of 1024 47 / 52, 16 61 / 58, four of 2048 75
-// / 94, eight 100 / 94.
-bool attn_joint(const AttnDims& a, bool bwd) {
+// another order.  Measured, us, separate / joint.  Forward, causal, width 64: two of s = 512 13 / 12, of 768 15 / 17, of 1024 18 / 21, of
+// 4096 68 / 71, three of 1024 20 / 21, of 3072 60 / 54, four of 1024 22 / 22; width 128: six of 384 13 / 15, of 1024 27 / 30, eight of
+// 512 16 / 18, of 1024 31 / 30, twelve of 512 19 / 18, four of 4096 138 / 100.  Forward, no mask, width 64: one of 768 14 / 16, two 17 / 16,
+// of 2048 34 / 37; width 128: four of 384 13 / 13, six 14 / 14.  Backward (dV and dK included), causal and without a mask, width 64:
+// one of 256 19 / 18 and 19 / 17, of 512 22 / 24 and 23 / 24, six of 1024 38 / 40 and 41 / 41, of 1536 53 / 58 and 63 / 59, two of 4096 110 / 131
+// and 144 / 132, four 192 / 133 and 269 / 161; width 128: one of 256 19 / 21 and 20 / 21, 16 22 / 23 and 23 / 22, 16 of 512 32 / 32 and 33 / 33,
+// eight of 1024 42 / 49 and 47 / 50, 16 60 / 57 and 75 / 62, four of 2048 67 / 90 and 77 / 93, eight 94 / 92 and 169 / 108: one line for
+// both, which costs the joint short ones up to a tenth and the separate long ones without a mask up to a third.
+bool attn_joint(const AttnDims& a, int causal, bool bwd) {
   const long long n = a.nmat_dev;
   const bool many = n * a.s >= 16384;
-  if (!bwd) return a.d == 64 ? a.s <= 768 || n >= 2 : a.s <= 256 || n >= 6 || many;
-  return a.d == 64 ? a.s <= 512 || n >= 6 || many : a.s <= 256 || n >= 16 || many;
+  if (bwd) return a.d == 64 ? a.s <= 512 || n >= 6 || many : a.s <= 256 || n >= 16 || many;
+  if (!causal) return a.d == 64 ? a.s <= 768 || n >= 2 : a.s <= 256 || n >= 6 || many;
+  return a.d == 64 ? a.s <= 512 || n >= 4 || n * a.s > 8192 : a.s <= 256 || n >= 12 || (n >= 8 && a.s > 768) || many;
 }
 
 AttnProbsDesc probs_desc(const bf16_t* qkv_blk, const bf16_t* probs_blk, const AttnDims& a, int causal) {
@@ -155,7 +159,7 @@ int attention_fwd_device(const bf16_t* qkv_blk, bf16_t* probs_blk, bf16_t* attn_
                          hipStream_t st) {
   AttnProbsDesc p = probs_desc(qkv_blk, probs_blk, a, causal);
   p.attn = attn_blk;
-  if (attn_joint(a, false) && attn_probs_supported(p)) return launch_attn_probs_fwd(p, st);
+  if (attn_joint(a, causal, false) && attn_probs_supported(p)) return launch_attn_probs_fwd(p, st);
   float* scores = (float*)ws;
   const long long ss = (long long)a.s * a.s;
   const float scale = 1.0f / sqrtf((float)a.d);
@@ -203,7 +207,7 @@ int attention_bwd_device(const bf16_t* qkv_blk, const bf16_t* probs_blk, const b
   }
   AttnProbsDesc p = probs_desc(qkv_blk, probs_blk, a, causal);
   p.d_attn = dattn_blk; p.d_scores = dS; p.d_qkv = dqkv_blk;
-  const bool joined = attn_joint(a, true) && attn_probs_supported(p);   // dS and dQ in one launch, dP never in memory
+  const bool joined = attn_joint(a, causal, true) && attn_probs_supported(p);   // dS and dQ in one launch, dP never in memory
   if (joined && (rc = launch_attn_probs_bwd(p, st))) return rc;
   if (!joined) {  // dP = dO V^T
     GemmDesc g = attn_base_desc(a);
