@@ -422,8 +422,15 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   ka.sBias0 = d.sBias0;
   ka.tiles_m = (d.Mb + v.BM - 1) / v.BM;
   ka.tiles_n = (d.Nb + v.BN - 1) / v.BN;
+  // Order of a split product's workgroups by the bytes of one block's panels.  Operands outside the L2s, us, tile after tile / range after
+  // range: A B [2048 x 16384 x 1024] (96 MiB) 82 / 80, A^T B [512 x 32768 x 1536] 78 / 72, [384 x 16384 x 384] (24 MiB) of A B 19.5 / 17.2,
+  // of A^T B 20.0 / 18.1, [256 x 16384 x 512] 16.6 / 16.9, A B^T [320 x 12288 x 384] (16.5 MiB) 15.3 / 14.4; below, A^T B [1216 x 5632 x
+  // 192] (15 MiB) 13.8 / 14.5, [512 x 8192 x 256] (12 MiB) 11.9 / 12.7, [1024 x 4096 x 256] (10 MiB) 12.3 / 13.1, A B [512 x 4096 x 512]
+  // 11.8 / 12.7, [256 x 4096 x 256] 9.1 / 9.5: there an XCD's L2 (4 MiB) holds most of what its tiles need.
+  ka.ranges_first = 2LL * d.nl * d.Kp * (d.Mb + d.Nb) > (16LL << 20);
   {
-    const long long all = (long long)ka.tiles_m * ka.tiles_n, mine = (all * (plan.seq ? 1 : plan.splits) + 7) / 8;
+    const long long all = (long long)ka.tiles_m * ka.tiles_n;
+    const long long mine = (all * (plan.seq || !ka.ranges_first ? 1 : plan.splits) + 7) / 8;
     const long long per_xcd = mine < all ? mine : all;
     int g = 1;
     while ((long long)(2 * g) * (2 * g) * v.BM <= per_xcd * v.BN * 2 && 2 * g <= 16) g *= 2;  // g ~ sqrt(per_xcd * BN / BM)

@@ -89,6 +89,7 @@ struct KArgs {
   int group;  // tile rows walked together (see the tile walk in the kernel)
   int skip_upper, k_hi_diag, k_lo_diag;
   int splits;
+  int ranges_first;  // order of a split product's workgroups: range after range, or tile after tile
   float* partials;
   // > 1 (with splits == 1): one workgroup walks all slabs but adds them up as `seq_splits` panel-split workgroups and
   // their fixed-order combine would -- a fresh accumulator per range, the ranges' sums added in range order
@@ -433,15 +434,22 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
     long long start = xcd * per + (xcd < rem ? xcd : rem);  // XCDs 0..rem-1 own per+1 workgroups
     wg = start + slot;
   }
-  // Panel split: range after range, not tile after tile.  An XCD then works on one range of k (or two) and many tiles, so the panels
+  // Panel split: range after range where the panels are too much for the L2s (a.ranges_first; the line and both sides' times:
+  // launch_gemm_mfma), otherwise tile after tile.  Range after range an XCD works on one range of k (or two) and many tiles, so the panels
   // it fetches are a part of k long: half the lines across the fabric that a few tiles with all of k need ([2048 x 16384 x 1024],
-  // four ranges: 134 MiB instead of 268).  Operands outside the L2s, us: that product 81.5 -> 79.5, [512 x 32768 x 1536] of A^T B
-  // 77.8 -> 71.6, [384 x 16384 x 1536] of A^T B 37.3 -> 33.9; small blocks in eight ranges lose, [1024 x 4096 x 256] of A^T B
-  // 13.8 -> 15.8.
+  // four ranges: 134 MiB instead of 268).
   const int tiles = a.tiles_m * a.tiles_n;
-  long long z = wg / tiles;
-  const int split = (int)(z / a.nz);
-  z -= split * a.nz;
+  int split;
+  long long z;
+  if (a.ranges_first) {
+    z = wg / tiles;
+    split = (int)(z / a.nz);
+    z -= split * a.nz;
+  } else {
+    split = (int)(wg % a.splits);
+    wg /= a.splits;
+    z = wg / tiles;
+  }
   int t = (int)(wg % tiles);
   int tm, tn;
   {  // column-major walk within groups of a.group tile rows: the contiguous tile range of an XCD is then a
