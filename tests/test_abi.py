@@ -100,3 +100,13 @@ def test_flop_accounting_matches_table1():
     assert opt.layer_workspace_bytes(cfg) >= 16 * 1024 * 1024 * 6
     bad = opt.LayerCfg(8, 1024, 4096, 30, 4, 1e-5, 1, opt.BF16)   # n not divisible by q
     assert opt.layer_flops(bad, 0) == -1 and opt.layer_workspace_bytes(bad) == 0
+
+
+def test_current_stream_without_torchs_private_name(monkeypatch):
+    """The current stream's handle comes from torch's public call where the cheaper private one does not exist."""
+    import torch
+    monkeypatch.setattr(binding, "_raw_stream", None, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 1234}))
+    assert binding._stream(None) == 1234
+    assert binding._stream(77) == 77
