@@ -426,27 +426,26 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
   // ---- which tile: XCD-aware remap of the linear workgroup id ----
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous range of tiles so that
   // neighbours sharing A rows / B columns also share an L2.
-  long long nwg = (long long)gridDim.x;
-  long long wg = blockIdx.x;
+  // 32 bits: a launch has fewer than 2^31 workgroups, and short ones feel 64-bit divisions (the products of an attention backward, 16
+  // matrices, s = 1000, d = 80: 70.2 us with them, 66.0 without).
+  unsigned wg = blockIdx.x;
   {
-    long long per = nwg >> 3, rem = nwg & 7;
-    long long xcd = wg & 7, slot = wg >> 3;
-    long long start = xcd * per + (xcd < rem ? xcd : rem);  // XCDs 0..rem-1 own per+1 workgroups
+    const unsigned nwg = gridDim.x, per = nwg >> 3, rem = nwg & 7, xcd = wg & 7, slot = wg >> 3;
+    const unsigned start = xcd * per + (xcd < rem ? xcd : rem);  // XCDs 0..rem-1 own per+1 workgroups
     wg = start + slot;
   }
   // Panel split: range after range where the panels are too much for the L2s (a.ranges_first; the line and both sides' times:
   // launch_gemm_mfma), otherwise tile after tile.  Range after range an XCD works on one range of k (or two) and many tiles, so the panels
   // it fetches are a part of k long: half the lines across the fabric that a few tiles with all of k need ([2048 x 16384 x 1024],
   // four ranges: 134 MiB instead of 268).
-  const int tiles = a.tiles_m * a.tiles_n;
-  int split;
-  long long z;
+  const unsigned tiles = a.tiles_m * a.tiles_n;
+  unsigned split, z;
   if (a.ranges_first) {
     z = wg / tiles;
-    split = (int)(z / a.nz);
-    z -= split * a.nz;
+    split = z / (unsigned)a.nz;
+    z -= split * (unsigned)a.nz;
   } else {
-    split = (int)(wg % a.splits);
+    split = wg % a.splits;
     wg /= a.splits;
     z = wg / tiles;
   }
@@ -482,7 +481,7 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
     int total = t_hi - t_lo;
     int per = (total + a.splits - 1) / a.splits;
     per = (per + 1) & ~1;  // slabs are walked in pairs
-    int lo = t_lo + split * per;
+    int lo = t_lo + (int)split * per;
     t_hi = min(t_hi, lo + per);
     t_lo = lo;
   }
