@@ -438,7 +438,13 @@ def debug_plan_summa(form, M, K, N, q, i, j, corun=0, have_ws=True):
 def debug_last_gemm_plan():
     """(variant, panel splits, 1 if the split is emulated inside each workgroup) of the most recent matrix-core product."""
     p = lib().optimus_debug_last_gemm_plan()
-    return (p & 0xFF, (p >> 8) & 0xFF, p >> 16) if p >= 0 else None
+    return (p & 0xFF, (p >> 8) & 0xFF, (p >> 16) & 1) if p >= 0 else None
+
+
+def debug_last_gemm_deep() -> bool:
+    """Whether that product ran 64x64 tiles with four stages in LDS."""
+    p = lib().optimus_debug_last_gemm_plan()
+    return p >= 0 and bool(p >> 17 & 1)
 
 
 def debug_layer_bwd_streams(cfg: LayerCfg, i, j) -> int:

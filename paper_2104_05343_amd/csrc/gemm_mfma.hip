@@ -409,7 +409,6 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     g_last_plan = kAnyVariant | (1 << 8);
     return launch_gemm_generic(d, stream);
   }
-  g_last_plan = plan.variant | (plan.splits << 8) | (plan.seq << 16);
   const Variant& v = kVariants[vi];
   KArgs ka;
   ka.A = (const bf16_t*)d.A;
@@ -449,9 +448,11 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   long long nwg = (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits;
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
   int rc;
-  // 64x64 tiles, at most two workgroups per CU: twice the loads in flight (figures: gemm_mfma_deep.hip).  From the third on they
-  // fill each other's gaps and need the LDS: [2048 x 2048 x 1024] of A B (512) 17.2 / 17.0 us.
-  if (vi == 7 && !plan.ragged && !plan.seq && g_loop == 2 && nwg <= 2LL * num_cus()) {
+  // 64x64 tiles, at most two workgroups per CU (all that the LDS of the four stages admits): twice the loads in flight (figures:
+  // gemm_mfma_deep.hip).
+  const bool deep = vi == 7 && !plan.ragged && !plan.seq && g_loop == 2 && nwg <= 2LL * num_cus();
+  g_last_plan = plan.variant | (plan.splits << 8) | (plan.seq << 16) | (deep ? 1 << 17 : 0);
+  if (deep) {
     const bool plain = ka.splits == 1 && e.alpha == 1.0f && !e.bias && !e.pre_act && !e.act && !e.gelu_grad_of && !e.residual;
     rc = launch_gemm_mfma_deep(plain, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   } else if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, plan.ragged == 2, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);

@@ -1,5 +1,6 @@
 """The 64x64 tile with four stages of 64 k in LDS (launches of at most two workgroups per CU): contractions that fill the stages
-partly, exactly and several times over, against the oracle and, bit for bit, against the same tile's four-slab ring."""
+partly, exactly and several times over, against the oracle and, bit for bit, against the same tile's four-slab ring; the last
+launch that takes it and the first that does not; partial tiles of a panel split, in either order of the workgroups."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +12,12 @@ from workloads import gemm_inputs
 from gpu_util import mat_to_dev, mat_to_host, empty
 
 pytestmark = pytest.mark.gpu
+TOL = 5e-3   # one rounding to bf16: 2^-9
+RING = 1000  # + variant: the older k-loop
+
+
+def _same_bits(x, y):
+    return torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
 @pytest.mark.parametrize("form", ["ab", "abt", "atb"])
@@ -22,16 +29,79 @@ def test_stages(form, q, K):
     bias = torch.randn(N, device="cuda:0")
     out = []
     try:
-        for variant in (7, 1007):
+        for variant in (7, RING + 7):
             opt.binding.debug_set_gemm_variant(variant)
             plain, act = empty(M * N, "bf16"), empty(M * N, "bf16")
-            opt.summa(form, dA, dB, plain, M, K, N, q, -1, -1, opt.BF16)
-            opt.summa_ex(form, dA, dB, act, M, K, N, q, -1, -1, opt.BF16, bias=bias, act=1)
+            for run in (lambda: opt.summa(form, dA, dB, plain, M, K, N, q, -1, -1, opt.BF16),
+                        lambda: opt.summa_ex(form, dA, dB, act, M, K, N, q, -1, -1, opt.BF16, bias=bias, act=1)):
+                run()
+                tile, splits, walked = opt.binding.debug_last_gemm_plan()
+                assert tile == 7
+                assert opt.binding.debug_last_gemm_deep() == (variant == 7 and not walked), (splits, walked)
             torch.cuda.synchronize()
-            assert tuple(opt.binding.debug_last_gemm_plan())[0] == 7
             out.append((plain, act))
     finally:
         opt.binding.debug_set_gemm_variant(-1)
-    assert rel_frobenius(mat_to_host(out[0][0], M, N, q), summa.product(form, A, B)) <= 5e-3   # one rounding to bf16: 2^-9
+    assert rel_frobenius(mat_to_host(out[0][0], M, N, q), summa.product(form, A, B)) <= TOL
     for x, y in zip(*out):
-        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+        assert _same_bits(x, y)
+
+
+@pytest.mark.parametrize("form", ["ab", "abt", "atb"])
+def test_two_workgroups_per_compute_unit_and_one_more(form):
+    tiles = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    M, K = 64, 320
+    for n, deep in ((tiles, True), (tiles + 1, False)):
+        N = 64 * n
+        A, B = gemm_inputs(n, form, M, K, N, "bf16", "n1", "n1")
+        dA, dB = mat_to_dev(A, 1, "bf16"), mat_to_dev(B, 1, "bf16")
+        out = []
+        try:
+            for variant in (7, RING + 7):
+                opt.binding.debug_set_gemm_variant(variant)
+                C = empty(M * N, "bf16")
+                opt.summa(form, dA, dB, C, M, K, N, 1, -1, -1, opt.BF16)
+                torch.cuda.synchronize()
+                assert opt.binding.debug_last_gemm_plan() == (7, 1, 0)
+                assert opt.binding.debug_last_gemm_deep() == (deep and variant == 7)
+                out.append(C)
+        finally:
+            opt.binding.debug_set_gemm_variant(-1)
+        assert _same_bits(*out)
+        assert rel_frobenius(mat_to_host(out[0], M, N, 1), summa.product(form, A, B)) <= TOL
+
+
+# one device's block [Mb x q*Kp x Nb]: panels of up to 16 MiB (tile after tile) and of more (range after range), four stages and the
+# ring, 128x128 tiles, blocks that no tile divides
+@pytest.mark.parametrize("form", ["ab", "abt", "atb"])
+@pytest.mark.parametrize("variant,Mb,Kp,Nb,q,deep", [(7, 128, 512, 192, 4, True), (7, 512, 1024, 512, 4, True), (7, 384, 3072, 384, 4, True),
+                                                     (3, 256, 1024, 256, 4, False), (3, 512, 2048, 768, 4, False),
+                                                     (7, 200, 328, 136, 4, False), (7, 392, 2808, 392, 4, False)])
+def test_partial_tiles_of_a_split(form, variant, Mb, Kp, Nb, q, deep):
+    M, K, N, i, j = q * Mb, q * Kp, q * Nb, 1, 2
+    gen = torch.Generator(device="cuda:0").manual_seed(Mb + Kp)
+    dA = torch.randn(M * K, device="cuda:0", generator=gen).to(torch.bfloat16)
+    dB = torch.randn(K * N, device="cuda:0", generator=gen).to(torch.bfloat16)
+    out = {}
+    try:
+        for loop in (0, RING):
+            opt.binding.debug_set_gemm_variant(loop + variant)
+            ws = torch.full((opt.summa_workspace_bytes(form, M, K, N, q, i, j, opt.BF16),), 0xFF, dtype=torch.uint8, device="cuda:0")
+            for w in (ws, None):
+                C = empty(M * N, "bf16")
+                opt.summa(form, dA, dB, C, M, K, N, q, i, j, opt.BF16, ws=w)
+                torch.cuda.synchronize()
+                plan = opt.binding.debug_last_gemm_plan()
+                assert plan[0] == variant and plan[1] > 1 and plan[2] == (w is None)
+                assert opt.binding.debug_last_gemm_deep() == (deep and not loop and w is not None)
+                out[loop, w is None] = C
+    finally:
+        opt.binding.debug_set_gemm_variant(-1)
+    got = out[0, False].view(q, q, Mb, Nb)
+    for C in out.values():
+        assert torch.equal(C.view(q, q, Mb, Nb)[i, j].view(torch.int16), got[i, j].view(torch.int16))
+    assert torch.isnan(got[i, j]).sum() == 0 and torch.isnan(got).sum() == (q * q - 1) * Mb * Nb
+    a = dA.view(q, q, Kp, Mb)[:, i].reshape(K, Mb).t() if form == "atb" else dA.view(q, q, Mb, Kp)[i].permute(1, 0, 2).reshape(Mb, K)
+    b = dB.view(q, q, Nb, Kp)[j].permute(1, 0, 2).reshape(Nb, K).t() if form == "abt" else dB.view(q, q, Kp, Nb)[:, j].reshape(K, Nb)
+    want = a.float().cpu().double() @ b.float().cpu().double()
+    assert rel_frobenius(got[i, j].float().cpu().numpy(), want.numpy()) <= TOL
