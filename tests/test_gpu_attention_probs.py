@@ -16,14 +16,22 @@ TOL = 5e-3   # two bf16 roundings (P or dS, then the result), 2^-9 each
 # (sequences, s, heads, head width): 256 tiles of 128 rows and more make the 128-row workgroups, without a mask more than 256 of 64
 SHAPES = [(2, 8, 2, 64), (1, 64, 1, 128), (1, 72, 2, 128), (2, 200, 1, 64), (32, 136, 4, 128), (16, 200, 8, 64), (22, 264, 4, 64), (2, 520, 3, 128),
           (2, 520, 8, 128), (6, 200, 12, 128), (6, 264, 8, 64), (4, 264, 8, 64)]
+# long walks: 64-row and 128-row workgroups of either width
+SHAPES += [(1, 2048, 6, 64), (1, 1032, 32, 64), (2, 1024, 8, 128), (1, 1024, 32, 128)]
+
+
+def _workspace(b, s, n, d):
+    # all bits set: a NaN in bf16 and in fp32
+    return torch.full((opt.attention_workspace_bytes(b, s, n * d, n, 1),), 0xFF, dtype=torch.uint8, device="cuda:0")
 
 
 def _attention(qkv, d_attn, b, s, n, d, causal):
     h, M = n * d, b * s
-    ws = torch.empty(opt.attention_workspace_bytes(b, s, h, n, 1), dtype=torch.uint8, device="cuda:0")
+    ws = _workspace(b, s, n, d)
     P, O, G = empty(b * n * s * s, "bf16"), empty(M * h, "bf16"), empty(M * 3 * h, "bf16")
     x, dO = mat_to_dev(qkv, 1, "bf16"), mat_to_dev(d_attn, 1, "bf16")
     opt.attention_fwd(x, P, O, b, s, h, n, 1, 0, 0, causal, opt.BF16, ws)
+    ws.fill_(0xFF)
     opt.attention_bwd(x, P, dO, G, b, s, h, n, 1, 0, 0, causal, opt.BF16, ws)
     torch.cuda.synchronize()
     return P, O, G
@@ -48,6 +56,44 @@ def test_edges(b, s, n, d, causal):
     part = (np.arange(3 * h) // d) % 3
     for k in range(3):   # P rounded to bf16 before the backward: a third rounding
         assert rel_frobenius(got[:, part == k], want[:, part == k]) <= 1.5 * TOL, k
+
+
+@pytest.mark.parametrize("variant", [6, 3, 1])   # 128x64, 128x128, 256x128
+@pytest.mark.parametrize("b,s,n,d", [(1, 512, 16, 128), (3, 768, 16, 128)])
+def test_zeros_past_the_diagonal_for_every_tile_of_dk(variant, b, s, n, d):
+    """dS is read past the diagonal by the product that makes dK, up to the end of its tile's rows: 64 to 256."""
+    h, M = n * d, b * s
+    rng = np.random.default_rng(variant)
+    qkv = round_to_bf16(rng.standard_normal((M, 3 * h)).astype(np.float32))
+    d_attn = round_to_bf16(rng.standard_normal((M, h)).astype(np.float32))
+    P, _, want = _attention(qkv, d_attn, b, s, n, d, True)
+    assert torch.isnan(want).sum() == 0
+    x, dO, got = mat_to_dev(qkv, 1, "bf16"), mat_to_dev(d_attn, 1, "bf16"), empty(M * 3 * h, "bf16")
+    opt.debug_set_gemm_variant(variant)
+    try:
+        opt.attention_bwd(x, P, dO, got, b, s, h, n, 1, 0, 0, True, opt.BF16, _workspace(b, s, n, d))
+        torch.cuda.synchronize()
+        assert opt.debug_last_gemm_plan()[0] == variant
+    finally:
+        opt.debug_set_gemm_variant(-1)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("b,s,n,d", [(2, 200, 4, 64), (32, 136, 4, 128)])
+def test_probabilities_above_the_diagonal_are_not_read(b, s, n, d):
+    """Gradients of Q and K do not depend on what P holds above the diagonal (that of V does: its product reads whole tiles)."""
+    h, M = n * d, b * s
+    rng = np.random.default_rng(s)
+    qkv = round_to_bf16(rng.standard_normal((M, 3 * h)).astype(np.float32))
+    d_attn = round_to_bf16(rng.standard_normal((M, h)).astype(np.float32))
+    P, _, want = _attention(qkv, d_attn, b, s, n, d, True)
+    upper = torch.triu(torch.ones(s, s, dtype=torch.bool, device="cuda:0"), 1)
+    P.view(b * n, s, s).masked_fill_(upper, float("nan"))
+    x, dO, got = mat_to_dev(qkv, 1, "bf16"), mat_to_dev(d_attn, 1, "bf16"), empty(M * 3 * h, "bf16")
+    opt.attention_bwd(x, P, dO, got, b, s, h, n, 1, 0, 0, True, opt.BF16, _workspace(b, s, n, d))
+    torch.cuda.synchronize()
+    qk = torch.from_numpy(np.flatnonzero((np.arange(3 * h) // d) % 3 < 2)).to("cuda:0")
+    assert torch.equal(got.view(torch.int16).view(M, -1)[:, qk], want.view(torch.int16).view(M, -1)[:, qk])
 
 
 @pytest.mark.parametrize("s,d", [(136, 128), (200, 64)])
