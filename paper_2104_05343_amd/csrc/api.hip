@@ -434,10 +434,10 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
 // two streams (165 with q = 1, where no product is split), and where the kernels on one stream take no longer than that it is
 // what the pass waits for.  Their time: the products, and the attention, which on a device with few matrices is a chain along
 // the sequence (30 us per 1024 rows fused, 36 with the scores in memory).  From 24 GF of products on two streams always.
-// Measured, step of one layer, two streams / one (us): 0.8 GF 338 / 225, 13 GF, s = 512 270 / 203 and 296 / 223, 13 GF, s = 1024
-// 259 / 219, 13 GF, s = 2048 266 / 248 fused, 309 / 348 in memory, 13 GF, s = 4096 308 / 338 and 430 / 481, 3 GF, s = 4096 278 /
-// 305, 6 GF, s = 8192 437 / 497, 13 GF, s = 16384 817 / 974, q = 1, 6 GF, s = 2048 212 / 228, q = 1, 13 GF, s = 1024 214 / 199,
-// 20 GF, s = 512 248 / 225, 39 GF 289 / 299, 51 GF 343 / 377; checkpointed stack of two small layers (0.8 GF each) 584 / 355.
+// Measured, step of one layer, two streams / one (us), fused and with P in memory: 0.2 GF, P 175 / 104; 13 GF, s = 512 212 / 174 and
+// 205 / 191, s = 1024 209 / 190 and 211 / 204, s = 2048 223 / 238 and 265 / 282, s = 4096 284 / 300 and 369 / 390; 3 GF, s = 4096 262 / 278 and
+// 266 / 279; 6 GF, s = 4096, P 325 / 331; 13 GF, s = 16384, fused 769 / 876; q = 1, 26 GF, s = 2048 236 / 239 and 269 / 273, 52 GF, s = 1024
+// 265 / 257 and 280 / 276; P, s = 512, 19 GF 207 / 211, 39 GF 256 / 272, 52 GF 298 / 315: within 7 % of the better one.
 bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
   const double devices = grid ? (double)c->q * c->q : 1.0;
   const double gf = 48e-9 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;

@@ -17,11 +17,11 @@
 // sixteen writes.  A wavefront's 32 rows pass through LDS of its own and leave as 64 or 128 bytes a row, and a wait for the
 // next tiles leaves those stores in flight.
 //
-// Measured, us, causal, separate launches (products of 64x64 tiles, soft-max over rows) against these.  128 matrices, s = 512,
-// d = 64 (all devices of a 1024-wide layer on a 4 x 4 grid): forward 32 + 25 + 19 against 28 (67 MiB of P: 2.4 TB/s), backward
-// beside the weight gradients 42 + 37 + 20 against 49.  16 matrices, s = 1024, d = 128 (one device of a 4096-wide layer), the
-// whole call: forward 40 / 29, backward 61 / 58.  Passes: checkpointed stack of four such 1024-wide layers 3721 / 3112, 4096-wide layer
-// 871 / 857, two 256-wide layers 321 / 301.
+// Measured, us, whole calls (the backward with dV and dK), separate launches / these, causal and without a mask.  128 matrices, s = 512,
+// d = 64 (all devices of a 1024-wide layer on a 4 x 4 grid): forward 61 / 27 (64 MiB of P: 2.5 TB/s) and 78 / 32, backward 94 / 58 and
+// 134 / 78.  16 matrices, s = 1024, d = 128 (one device of a 4096-wide layer): forward 39 / 31 and 51 / 31, backward 60 / 57 and 75 / 61.
+// Passes with the separate launches and with these: checkpointed stack of four such 1024-wide layers 3721 / 3112, 4096-wide layer
+// 871 / 846, two 256-wide layers 321 / 301.
 #include "attention_fused_kernel.hpp"
 
 namespace optimus {

@@ -97,8 +97,9 @@ static int launch_one(const KArgs& ka, long long nwg, hipStream_t stream) {
   if (ka.seq_splits > 1) return OPTIMUS_EINVAL;
   const bool plain = ka.splits == 1 && e.alpha == 1.0f && !e.bias && !e.pre_act && !e.act && !e.gelu_grad_of && !e.residual;
   // The 64-wide stages are measured 2-6 % faster than the four-slab ring on the tiles that own a CU (256x256, 256x128,
-  // 128x256, 8 or 4 wavefronts) and slower or equal on the tiles that share one (128x128, 128x64, 64x64: several
-  // workgroups per CU fill each other's gaps, and the finer ring refills sooner), so each keeps its own loop.
+  // 128x256, 8 or 4 wavefronts) and, with two stages, slower or equal on the tiles that share one (128x128, 128x64, 64x64: several
+  // workgroups per CU fill each other's gaps, and the finer ring refills sooner), so each keeps its own loop.  64x64 tiles in
+  // launches of at most two workgroups per CU: launch_gemm_mfma.
   constexpr bool HAS_LOOP2 = BM + BN >= 384;
   if constexpr (HAS_LOOP2) {
     if (g_loop == 2) {
@@ -272,8 +273,9 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
       if (v == 3) t_slab *= d.a_kcontig && d.b_kcontig ? 1.14f : (d.a_kcontig ? 0.92f : 1.04f);
       if (v == 6 && d.a_kcontig && d.b_kcontig) t_slab *= 1.18f;
       if (v == 7 && !d.a_kcontig) t_slab *= 1.25f;   // both operands through the transposing LDS reads
-      // the form with four stages (at most two workgroups per CU).  [1024 x 4096 x 256] in four ranges instead of eight: A B 14.8 us to
-      // 12.8, A^T B 15.3 to 12.8
+      // The form with four stages (at most two workgroups per CU), for long contractions and all layouts alike (by itself, one workgroup
+      // per CU: A B 0.74 of the ring's time, A B^T 0.66, A^T B 0.86, nothing at 256 k).  [1024 x 4096 x 256] in four ranges of it against
+      // the ring's eight: A B 14.8 us to 12.3, A B^T 15.4 to 12.2, A^T B 13.5 to 12.0.
       if (v == 7 && !ragged && wgs <= 2 * ncu) t_slab *= resident == 1 ? 0.7f : 0.9f;
       const float per_wg = (float)((((slabs + sp - 1) / sp) + 1) & ~1LL) * t_slab;
       // split: the combine launch, and the fp32 partial tiles read back by it (their writes overlap the products)
@@ -285,7 +287,8 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
       // half the CUs idle when the product runs by itself (the other product's workgroups take those).  Measured on
       // the backward pass of the 4096-wide layers (one device of the q = 4 / q = 8 grids): 256x128 tiles for both
       // products 0.55 / 0.61 ms, 128x128 tiles for both 0.64 / 0.72 ms, 256x128 for the chain and 128x128 for the
-      // branch 0.65 / 0.69 ms, the reverse 0.58 / 0.63 ms.
+      // branch 0.65 / 0.69 ms, the reverse 0.58 / 0.63 ms.  The factor, whole steps of one layer, 1 / 1.25 / 1.5: 4096-wide, q = 4, 897 /
+      // 846 / 840 us, fused 877 / 842 / 836, q = 8 872 / 863 / 874; 1024-wide, q = 2, s = 1792, 705 / 680 / 676; q = 4 191 / 193 / 193.
       if (d.corun > 0 && c.per_cu >= 2 && pass == 1 && batch == 1) cost *= 1.25f;
       if (!found || cost < best_cost) {
         found = true;
