@@ -447,5 +447,11 @@ def debug_last_gemm_deep() -> bool:
     return p >= 0 and bool(p >> 17 & 1)
 
 
+def debug_last_gemm_pair() -> bool:
+    """Whether that product shared its launch with another one."""
+    p = lib().optimus_debug_last_gemm_plan()
+    return p >= 0 and bool(p >> 18 & 1)
+
+
 def debug_layer_bwd_streams(cfg: LayerCfg, i, j) -> int:
     return lib().optimus_debug_layer_bwd_streams(C.byref(cfg), i, j)

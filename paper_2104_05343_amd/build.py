@@ -10,7 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liboptimus.so")
-SOURCES = ["api.hip", "gemm_mfma.hip", "gemm_mfma_ragged.hip", "gemm_mfma_deep.hip", "gemm_generic.hip", "gemm_short.hip", "layernorm.hip", "softmax.hip", "attention_fused.hip", "attention_fused_wide.hip", "attention_probs.hip", "blocks.hip", "stack.hip", "model_ends.hip", "probe.hip"]
+SOURCES = ["api.hip", "gemm_mfma.hip", "gemm_mfma_ragged.hip", "gemm_mfma_deep.hip", "gemm_mfma_pair64.hip", "gemm_mfma_pair128.hip", "gemm_generic.hip", "gemm_short.hip", "layernorm.hip", "softmax.hip", "attention_fused.hip", "attention_fused_wide.hip", "attention_probs.hip", "blocks.hip", "stack.hip", "model_ends.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

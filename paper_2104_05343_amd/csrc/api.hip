@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "common.hpp"
+#include "epilogue.hpp"
 
 using namespace optimus;
 
@@ -100,6 +101,30 @@ int run_summa(int form, const void* A, const void* B, void* C, int64_t M, int64_
     if (need > 0 && ws && ws_bytes >= need) { d.partials = (float*)ws; d.partials_bytes = ws_bytes; }
   }
   return launch_gemm(d, as_stream(stream));
+}
+
+// The two products of a linear layer's backward pass, d_in = d_out W^T (with its epilogue) and d_W = in^T d_out in fp32, in one
+// launch where they go together; otherwise one after the other.
+struct LinearGrads {
+  const void *d_out, *w, *in;
+  void *d_in, *d_w;
+  int64_t M, K, N;              // d_in is [M x K], d_out [M x N], W [K x N]
+  const void* gelu_grad_of;     // or nullptr
+};
+int run_linear_grads(const LinearGrads& g, int q, int i, int j, void* ws_x, void* ws_y, size_t ws_bytes, hipStream_t st) {
+  optimus_epilogue ex = {}, ey = {};
+  ex.gelu_grad_of = g.gelu_grad_of;
+  ey.out_fp32 = 1;
+  GemmDesc x = summa_desc(OPTIMUS_FORM_ABT, g.d_out, g.w, g.d_in, g.M, g.N, g.K, q, i, j, OPTIMUS_BF16, &ex);
+  GemmDesc y = summa_desc(OPTIMUS_FORM_ATB, g.in, g.d_out, g.d_w, g.K, g.M, g.N, q, i, j, OPTIMUS_BF16, &ey);
+  const size_t nx = gemm_plan_bytes(x), ny = gemm_plan_bytes(y);
+  if (nx > 0 && nx <= ws_bytes) { x.partials = (float*)ws_x; x.partials_bytes = ws_bytes; }
+  if (ny > 0 && ny <= ws_bytes) { y.partials = (float*)ws_y; y.partials_bytes = ws_bytes; }
+  CombineJobs combines = {};
+  int rc;
+  if (launch_gemm_pair(x, y, &combines, st, &rc)) return rc ? rc : launch_gemm_combines(combines, st);
+  if ((rc = launch_gemm(x, st))) return rc;
+  return launch_gemm(y, st);
 }
 
 struct AttnDims {
@@ -429,20 +454,24 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
   return OPTIMUS_OK;
 }
 
-// Whether the second stream pays in a pass that is not captured.  A fork or the join costs the host 25 us (the wait on another
-// stream's event, for the most part), and there are five of them in a backward pass: the host needs about 200 us for a pass on
-// two streams (165 with q = 1, where no product is split), and where the kernels on one stream take no longer than that it is
-// what the pass waits for.  Their time: the products, and the attention, which on a device with few matrices is a chain along
-// the sequence (30 us per 1024 rows fused, 36 with the scores in memory).  From 24 GF of products on two streams always.
-// Measured, step of one layer, two streams / one (us), fused and with P in memory: 0.2 GF, P 175 / 104; 13 GF, s = 512 212 / 174 and
-// 205 / 191, s = 1024 209 / 190 and 211 / 204, s = 2048 223 / 238 and 265 / 282, s = 4096 284 / 300 and 369 / 390; 3 GF, s = 4096 262 / 278 and
-// 266 / 279; 6 GF, s = 4096, P 325 / 331; 13 GF, s = 16384, fused 769 / 876; q = 1, 26 GF, s = 2048 236 / 239 and 269 / 273, 52 GF, s = 1024
-// 265 / 257 and 280 / 276; P, s = 512, 19 GF 207 / 211, 39 GF 256 / 272, 52 GF 298 / 315: within 7 % of the better one.
+// Whether the second stream pays in a pass that is not captured.  On one stream both products of a linear layer go in one launch
+// (launch_gemm_pair); on two, a fork or the join costs the host 25 us (the wait on another stream's event, for the most part), five of
+// them in a backward pass: the host needs about 200 us for such a pass (165 with q = 1, where no product is split).  Two streams win
+// where the kernels on one take longer than that and the products run beside a long chain: the attention of a device with few
+// matrices is one along the sequence (30 us per 1024 rows fused, 36 with the scores in memory); and from 35 GF of products, where
+// tiles of 256x128 on both are the better use of the chip.  With q = 1 the weight gradients are few long workgroups that the pair's other
+// product fills up: from 200 GF there, below 24 as the kernels' time has it.
+// Measured, step of one layer, two streams / one (us): 3 GF, s = 4096 262 / 278; 13 GF, s = 4096 284 / 300, s = 16384 769 / 876; 26 GF, s = 1024
+// 216 / 209, s = 1856 301 / 276, P 237 / 229; 29 GF, s = 512 229 / 216, P 235 / 220; 39 GF, s = 1000 267 / 276; 50 GF, s = 777 284 / 289; 52 GF,
+// s = 512 256 / 250, s = 2048 323 / 352; 75 GF, s = 333 369 / 356, P, s = 1504 439 / 450; 90 GF 406 / 427; 103 GF, s = 512 389 / 461, s = 4096
+// 764 / 781; 226 GF, s = 1000 782 / 728; 412 GF 952 / 973; 824 GF 862 / 902; q = 1, 52 GF, s = 1024 273 / 258, s = 4096 435 / 414, 79 GF 471 / 447,
+// 103 GF 377 / 343, 170 GF 730 / 692, 232 GF 604 / 632.
 bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
   const double devices = grid ? (double)c->q * c->q : 1.0;
   const double gf = 48e-9 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
-  const double one_us = 100.0 + 2.5 * gf + (c->fused_attention ? 0.030 : 0.036) * c->s;
-  return gf >= 24.0 || one_us >= (c->q == 1 ? 165.0 : 200.0);
+  const double one_us = 120.0 + 0.6 * gf + (c->fused_attention ? 0.030 : 0.036) * c->s;
+  if (c->q == 1) return gf >= 200.0 || c->s > 8192 || (gf < 24.0 && one_us >= 165.0);
+  return gf >= 35.0 || one_us >= 200.0;
 }
 // A captured pass pays the host once and keeps both streams (which an earlier pass, short or not, has created).  Replayed,
 // one stream / two: 1024-wide layer, one device of 4 x 4, step 219 / 196 us, fused 200 / 173, 3 GF 155 / 138, 4096-wide
@@ -888,29 +917,33 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
 #define BRANCH_AFTER_MAIN(EV) do { if (ss && rc == OPTIMUS_OK) { rc = stream_after(gst, st, EV); forked = forked || rc == OPTIMUS_OK; } } while (0)
   BRANCH_AFTER_MAIN(ss->fork);
   // ---- out = h_mid + gelu W2 + b2 ----
-  e = {}; e.gelu_grad_of = t->pre_gelu;  // d_pre = (d_out W2^T) * GeLU'(pre)
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_out, t->w2, t->d_pre_gelu, M, h, 4 * h, q, i, j, dt, &e, gemm_ws, gemm_bytes, stream, co_chain));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->gelu, t->d_out, t->d_w2, 4 * h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
+  // One stream: both products of a linear layer in one launch.  Two: the gradient of the weight on the branch.
+  const auto linear = [&](const void* d_y, const void* w, const void* in, void* d_in, float* d_w, int64_t k, int64_t n, const void* gelu_grad_of) {
+    const LinearGrads g = {d_y, w, in, d_in, d_w, M, k * h, n * h, gelu_grad_of};
+    if (!ss) return run_linear_grads(g, q, i, j, gemm_ws, (char*)gemm_ws + gemm_bytes, gemm_bytes, st);
+    e = {}; e.gelu_grad_of = gelu_grad_of;
+    const int r = run_summa(OPTIMUS_FORM_ABT, d_y, w, d_in, M, n * h, k * h, q, i, j, dt, &e, gemm_ws, gemm_bytes, stream, co_chain);
+    if (r) return r;
+    return run_summa(OPTIMUS_FORM_ATB, in, d_y, d_w, k * h, M, n * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch);
+  };
+  RUN(linear(t->d_out, t->w2, t->gelu, t->d_pre_gelu, t->d_w2, 4, 1, t->pre_gelu));   // d_pre = (d_out W2^T) * GeLU'(pre)
   if (ss) RUN(optimus_bias_grad(t->d_out, t->d_b2, M, h, q, i, j, dt, gstream));
   // ---- pre = ln2_out W1 + b1 ----
   BRANCH_AFTER_MAIN(ss->ready[0]);  // d_pre_gelu is complete
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_pre_gelu, t->w1, t->d_ln2_out, M, 4 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->ln2_out, t->d_pre_gelu, t->d_w1, h, M, 4 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
+  RUN(linear(t->d_pre_gelu, t->w1, t->ln2_out, t->d_ln2_out, t->d_w1, 1, 4, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_pre_gelu, t->d_b1, M, 4 * h, q, i, j, dt, gstream));
   // ---- LN2 backward, plus the residual branch: d_h_mid = d_out + LN2'(d_ln2_out) ----
   RUN(ln_backward(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_g,
                   ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_b, t->bstats2, ln, grid, st));
   // ---- h_mid = x + attn Wo + bo ----
   BRANCH_AFTER_MAIN(ss->ready[1]);  // d_h_mid is complete
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_h_mid, t->w_o, t->d_attn, M, h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->attn, t->d_h_mid, t->d_w_o, h, M, h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
+  RUN(linear(t->d_h_mid, t->w_o, t->attn, t->d_attn, t->d_w_o, 1, 1, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_h_mid, t->d_b_o, M, h, q, i, j, dt, gstream));
   // ---- local attention backward ----
   RUN(layer_attention(true, c, t, i, j, attn_ws, attn_bytes, stream));
   // ---- qkv = ln1_out Wqkv + b ----
   BRANCH_AFTER_MAIN(ss->ready[2]);  // d_qkv is complete
-  RUN(run_summa(OPTIMUS_FORM_ABT, t->d_qkv, t->w_qkv, t->d_ln1_out, M, 3 * h, h, q, i, j, dt, nullptr, gemm_ws, gemm_bytes, stream, co_chain));
-  RUN(run_summa(OPTIMUS_FORM_ATB, t->ln1_out, t->d_qkv, t->d_w_qkv, h, M, 3 * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch));
+  RUN(linear(t->d_qkv, t->w_qkv, t->ln1_out, t->d_ln1_out, t->d_w_qkv, 1, 3, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_qkv, t->d_b_qkv, M, 3 * h, q, i, j, dt, gstream));
   if (sums_at_end) {   // column sums in one launch, their sources are still there; on a branch without the two that would wait
     const int rows = (int)(M / q), hb = (int)(h / q);

@@ -96,6 +96,11 @@ struct GemmDesc {
 int launch_gemm(const GemmDesc& d, hipStream_t stream);           // picks one of the two below
 int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);    // fp32, or any bf16 shape, stride and alignment
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);       // bf16 rows on the 16-byte grid: direct-to-LDS tiles
+// A B^T (x) and A^T B (y) in one launch, y not reading what x writes; the combines that their panel splits want are added to
+// *combines.  False if the two do not go together: nothing is launched then.  *rc: status of the launch.
+struct CombineJobs;
+bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combines, hipStream_t stream, int* rc);
+int launch_gemm_combines(const CombineJobs& jobs, hipStream_t stream);
 bool gemm_mfma_supported(const GemmDesc& d);
 int launch_mfma_rate(float* out, int workgroups, int iters, int random_data, hipStream_t stream);   // probe.hip
 size_t gemm_plan_bytes(const GemmDesc& d);                         // workspace the planned launch wants (0: none)

@@ -19,6 +19,22 @@ struct EpiArgs {
   int vec_ok;  // all bases/strides allow 4-element vector accesses
 };
 
+// The partial tiles of a panel split, to be added in order: partials [splits][nz][Mb][Nb]
+struct CombineJob {
+  const float* partials;
+  int splits;
+  long long nz;
+  int Mb, Nb, nz0;
+  long long sC0, sC1, sBias0;
+  EpiArgs epi;
+};
+constexpr int kCombineJobs = 5;
+struct CombineJobs {
+  CombineJob j[kCombineJobs];
+  unsigned blocks[kCombineJobs];   // workgroups of each job, set at the launch
+  int n;
+};
+
 __device__ __forceinline__ float load_elem(const void* p, long long idx, int bf16) {
   return bf16 ? bf16_to_f32(((const bf16_t*)p)[idx]) : ((const float*)p)[idx];
 }

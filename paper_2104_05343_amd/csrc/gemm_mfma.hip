@@ -4,7 +4,7 @@
 
 #include <atomic>
 
-#include "gemm_mfma_kernel.hpp"
+#include "gemm_mfma_pair.hpp"
 
 namespace optimus {
 
@@ -25,12 +25,13 @@ static std::atomic<int> g_last_plan{-1};
 int gemm_last_plan() { return g_last_plan; }
 
 // ---- fixed-order combine of panel-split partials + epilogue ----
-__global__ __launch_bounds__(256) void gemm_combine_kernel(const float* partials, int splits, long long nz, int Mb, int Nb,
-                                                           int nz0, long long sC0, long long sC1, long long sBias0,
-                                                           EpiArgs e) {
+// The partial tiles of one product; a launch combines those of up to kCombineJobs products.
+__device__ __forceinline__ void combine_quad(const CombineJob& j, long long idx) {
+  const float* const partials = j.partials;
+  const int splits = j.splits, Mb = j.Mb, Nb = j.Nb;
+  EpiArgs e = j.epi;
   long long quads_per_row = (Nb + 3) / 4;
-  long long total = nz * Mb * quads_per_row;
-  long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  long long total = j.nz * Mb * quads_per_row;
   if (idx >= total) return;
   int nq = (int)(idx % quads_per_row);
   long long r = idx / quads_per_row;
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(256) void gemm_combine_kernel(const float* partials
   float v[4] = {0.f, 0.f, 0.f, 0.f};
   if ((Nb & 3) == 0 && ((size_t)partials & 15) == 0) {  // rows of the partial tiles are 16-byte aligned: one load per split, all in flight together
     const float* p = partials + z * (long long)Mb * Nb + (long long)m * Nb + n;
-    const long long sstride = nz * (long long)Mb * Nb;
+    const long long sstride = j.nz * (long long)Mb * Nb;
 #pragma unroll 8
     for (int s = 0; s < splits; ++s) {
       const float4 w = *(const float4*)(p + s * sstride);
@@ -49,13 +50,35 @@ __global__ __launch_bounds__(256) void gemm_combine_kernel(const float* partials
     }
   } else {
     for (int s = 0; s < splits; ++s) {
-      const float* p = partials + ((long long)s * nz + z) * (long long)Mb * Nb + (long long)m * Nb + n;
+      const float* p = partials + ((long long)s * j.nz + z) * (long long)Mb * Nb + (long long)m * Nb + n;
       for (int c = 0; c < nvalid; ++c) v[c] += p[c];
     }
   }
-  int z1 = (int)(z / nz0), z0 = (int)(z % nz0);
-  if (e.bias) e.bias += z0 * sBias0;
-  epilogue_store4<false>(e, z1 * sC1 + z0 * sC0, m, n, v, nvalid);
+  int z1 = (int)(z / j.nz0), z0 = (int)(z % j.nz0);
+  if (e.bias) e.bias += z0 * j.sBias0;
+  epilogue_store4<false>(e, z1 * j.sC1 + z0 * j.sC0, m, n, v, nvalid);
+}
+__global__ __launch_bounds__(256) void gemm_combine_kernel(const CombineJob j) {
+  combine_quad(j, (long long)blockIdx.x * blockDim.x + threadIdx.x);
+}
+__global__ __launch_bounds__(256) void gemm_combine_jobs_kernel(const CombineJobs jobs) {
+  unsigned wg = blockIdx.x;
+  int k = 0;
+  while (k + 1 < jobs.n && wg >= jobs.blocks[k]) wg -= jobs.blocks[k++];
+  combine_quad(jobs.j[k], (long long)wg * blockDim.x + threadIdx.x);
+}
+static long long combine_blocks(const CombineJob& j) { return (j.nz * j.Mb * ((j.Nb + 3) / 4) + 255) / 256; }
+int launch_gemm_combines(const CombineJobs& in, hipStream_t stream) {
+  if (in.n == 0) return OPTIMUS_OK;
+  if (in.n == 1) {
+    hipLaunchKernelGGL(gemm_combine_kernel, dim3((unsigned)combine_blocks(in.j[0])), dim3(256), 0, stream, in.j[0]);
+    return hip_launch_status();
+  }
+  CombineJobs jobs = in;
+  long long blocks = 0;
+  for (int k = 0; k < jobs.n; ++k) blocks += jobs.blocks[k] = (unsigned)combine_blocks(jobs.j[k]);
+  hipLaunchKernelGGL(gemm_combine_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jobs);
+  return hip_launch_status();
 }
 
 // ---- host side ----
@@ -400,19 +423,9 @@ bool gemm_plan_of(const GemmDesc& d, bool have_ws, int out[3]) {
   return true;
 }
 
-int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
-  if (!gemm_mfma_supported(d)) return OPTIMUS_EINVAL;
-  const bool vec_ok = epilogue_vec_ok(d);
-  // d.partials: the workspace that the planned split asked for.  A hook that another thread has set since may ask for more: then
-  // as without a workspace.
-  Plan plan = make_plan(d, vec_ok, d.partials != nullptr);
-  if (!plan.seq && gemm_partials_bytes(d, plan.splits) > d.partials_bytes) plan = make_plan(d, vec_ok, false);
-  const int vi = plan.variant;
-  if (vi == kAnyVariant) {
-    g_last_plan = kAnyVariant | (1 << 8);
-    return launch_gemm_generic(d, stream);
-  }
-  const Variant& v = kVariants[vi];
+// The kernel's view of a product under a plan (not the library's hooks).
+static KArgs kernel_args(const GemmDesc& d, const Plan& plan, bool vec_ok) {
+  const Variant& v = kVariants[plan.variant];
   KArgs ka;
   ka.A = (const bf16_t*)d.A;
   ka.B = (const bf16_t*)d.B;
@@ -447,8 +460,32 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   e.alpha = d.alpha; e.bias = d.bias; e.C = d.C; e.pre_act = d.pre_act; e.gelu_grad_of = d.gelu_grad_of;
   e.residual = d.residual; e.ldc = d.ldc; e.act = d.act; e.out_fp32 = d.out_fp32; e.in_bf16 = 1;
   e.vec_ok = vec_ok ? 1 : 0;
+  return ka;
+}
+static bool plain_store(const KArgs& ka) {
+  const EpiArgs& e = ka.epi;
+  return ka.splits == 1 && e.alpha == 1.0f && !e.bias && !e.pre_act && !e.act && !e.gelu_grad_of && !e.residual;
+}
+static long long workgroups(const KArgs& ka) { return (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits; }
+static CombineJob combine_job(const GemmDesc& d, const KArgs& ka) {
+  return CombineJob{d.partials, ka.splits, ka.nz, d.Mb, d.Nb, d.nz0, d.sC0, d.sC1, d.sBias0, ka.epi};
+}
+
+int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
+  if (!gemm_mfma_supported(d)) return OPTIMUS_EINVAL;
+  const bool vec_ok = epilogue_vec_ok(d);
+  // d.partials: the workspace that the planned split asked for.  A hook that another thread has set since may ask for more: then
+  // as without a workspace.
+  Plan plan = make_plan(d, vec_ok, d.partials != nullptr);
+  if (!plan.seq && gemm_partials_bytes(d, plan.splits) > d.partials_bytes) plan = make_plan(d, vec_ok, false);
+  const int vi = plan.variant;
+  if (vi == kAnyVariant) {
+    g_last_plan = kAnyVariant | (1 << 8);
+    return launch_gemm_generic(d, stream);
+  }
+  const KArgs ka = kernel_args(d, plan, vec_ok);
   if (ka.splits > 1 && gemm_partials_bytes(d, ka.splits) > d.partials_bytes) return OPTIMUS_EWORKSPACE;
-  long long nwg = (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits;
+  const long long nwg = workgroups(ka);
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
   int rc;
   // 64x64 tiles, at most two workgroups per CU (all that the LDS of the four stages admits): twice the loads in flight (figures:
@@ -456,8 +493,7 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   const bool deep = vi == 7 && !plan.ragged && !plan.seq && g_loop == 2 && nwg <= 2LL * num_cus();
   g_last_plan = plan.variant | (plan.splits << 8) | (plan.seq << 16) | (deep ? 1 << 17 : 0);
   if (deep) {
-    const bool plain = ka.splits == 1 && e.alpha == 1.0f && !e.bias && !e.pre_act && !e.act && !e.gelu_grad_of && !e.residual;
-    rc = launch_gemm_mfma_deep(plain, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
+    rc = launch_gemm_mfma_deep(plain_store(ka), d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   } else if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, plan.ragged == 2, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   else switch (vi) {
     case 0: rc = launch_layout<256, 256, 2, 4>(d, ka, nwg, stream); break;
@@ -471,15 +507,66 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
     case 9: rc = launch_layout<128, 256, 2, 2>(d, ka, nwg, stream); break;
     default: rc = OPTIMUS_EINVAL; break;
   }
-  if (rc != OPTIMUS_OK) return rc;
-  if (ka.splits > 1) {
-    long long total = ka.nz * d.Mb * ((d.Nb + 3) / 4);
-    long long blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(gemm_combine_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const float*)d.partials,
-                       ka.splits, ka.nz, d.Mb, d.Nb, d.nz0, d.sC0, d.sC1, d.sBias0, e);
-    rc = hip_launch_status();
+  if (rc != OPTIMUS_OK || ka.splits == 1) return rc;
+  CombineJobs jobs = {};
+  jobs.n = 1;
+  jobs.j[0] = combine_job(d, ka);
+  return launch_gemm_combines(jobs, stream);
+}
+
+// ---- two products in one launch (gemm_mfma_pair.hpp) ----
+// Not for a split that is walked inside the workgroups (whole grids, callers without workspace), panels beyond a buffer resource and
+// what the any-shape kernel takes, nor while a hook forces tile or loop.  The splits are those of the single launches: same bits.
+bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combines, hipStream_t stream, int* rc) {
+  if (!gemm_mfma_supported(x) || !gemm_mfma_supported(y) || g_loop != 2 || g_variant >= 0) return false;
+  if (!x.a_kcontig || !x.b_kcontig || y.a_kcontig || y.b_kcontig) return false;
+  const bool vec_x = epilogue_vec_ok(x), vec_y = epilogue_vec_ok(y);
+  Plan px = make_plan(x, vec_x, x.partials != nullptr), py = make_plan(y, vec_y, y.partials != nullptr);
+  if (px.variant == kAnyVariant || py.variant == kAnyVariant || px.seq || py.seq || px.ragged == 2 || py.ragged == 2) return false;
+  if (gemm_partials_bytes(x, px.splits) > x.partials_bytes || gemm_partials_bytes(y, py.splits) > y.partials_bytes) return false;
+  const bool ragged = px.ragged || py.ragged;
+  const long long ncu = num_cus();
+  const auto slabs_of = [](const GemmDesc& d, int sp) {
+    const long long slabs = (long long)d.nl * ((d.Kp + 2 * BK - 1) / (2 * BK)) * 2;
+    return (((slabs + sp - 1) / sp) + 1) & ~1LL;
+  };
+  const long long sx = slabs_of(x, px.splits), sy = slabs_of(y, py.splits);
+  const auto wgs_of = [](const GemmDesc& d, int v, int sp) {
+    return (long long)((d.Mb + kVariants[v].BM - 1) / kVariants[v].BM) * ((d.Nb + kVariants[v].BN - 1) / kVariants[v].BN) *
+           (d.nz0 * (long long)d.nz1) * sp;
+  };
+  // One tile for both, by the time of the longest workgroup on a CU of its own or of all of them over the CUs, whichever is more; time
+  // per slab of one workgroup by how many share its CU as make_plan has it, with the factors of the two forms.
+  const auto slab_us = [&](int v, long long res, bool is_y) {
+    if (v == 3) return (0.25f + 0.21f * (float)(res - 1)) * (is_y ? 1.04f : 1.14f);
+    const float t = ragged || res > 2 ? 0.155f + 0.045f * (float)(res - 1) : res == 1 ? 0.11f : 0.18f;
+    return is_y ? 1.25f * t : t;
+  };
+  int best = -1;
+  float best_cost = 0.f;
+  for (const int v : {7, 3}) {
+    if (!ragged && !(variant_fits(kVariants[v], x) && variant_fits(kVariants[v], y))) continue;
+    const long long wx = wgs_of(x, v, px.splits), wy = wgs_of(y, v, py.splits), per_cu = v == 3 ? 2 : 5;
+    const long long each = (wx + wy + ncu - 1) / ncu, res = each < per_cu ? each : per_cu;
+    const float ux = (float)sx * slab_us(v, res, false), uy = (float)sy * slab_us(v, res, true);
+    const float all = ((float)wx * ux + (float)wy * uy) / (float)(ncu * res);
+    const float lx = (float)sx * slab_us(v, 1, false), ly = (float)sy * slab_us(v, 1, true), one = lx > ly ? lx : ly;
+    const float cost = (v == 3 ? 5.5f : 4.0f) + (all > one ? all : one);
+    if (best < 0 || cost < best_cost) { best = v; best_cost = cost; }
   }
-  return rc;
+  if (best < 0) return false;
+  px.variant = py.variant = best;
+  px.ragged = py.ragged = ragged ? 1 : 0;
+  const KArgs kx = kernel_args(x, px, vec_x), ky = kernel_args(y, py, vec_y);
+  const long long nx = workgroups(kx), ny = workgroups(ky);
+  if (nx <= 0 || ny <= 0 || nx + ny > 0x7fffffffLL) return false;
+  PairLaunch p = {&kx, &ky, (unsigned)nx, (unsigned)ny, sy > sx ? 1 : 0, plain_store(kx), plain_store(ky), stream};
+  const bool deep = best == 7 && !ragged && nx + ny <= 2LL * ncu;
+  g_last_plan = best | (py.splits << 8) | (deep ? 1 << 17 : 0) | (1 << 18);
+  *rc = best == 7 ? launch_gemm_pair_64(deep, ragged, p) : launch_gemm_pair_128(ragged, p);
+  if (*rc == OPTIMUS_OK && kx.splits > 1) combines->j[combines->n++] = combine_job(x, kx);
+  if (*rc == OPTIMUS_OK && ky.splits > 1) combines->j[combines->n++] = combine_job(y, ky);
+  return true;
 }
 
 }  // namespace optimus

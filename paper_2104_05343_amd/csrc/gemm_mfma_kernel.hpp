@@ -402,8 +402,13 @@ struct Loop2 {
   static constexpr int RING32 = 2 * NST;                                        // the same space in 32-wide slabs
 };
 
+// elements of LDS that a workgroup of this tile and loop needs
+template <int BM, int BN, int LOOP>
+constexpr int lds_elems() { return (LOOP >= 2 ? Loop2<BM, BN, LOOP>::RING32 : NSTAGE) * (BM + BN) * BK; }
+
+// One tile of a product: workgroup wg of the nwg that the product has.
 template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool PLAIN, bool SEQ = false, int LOOP = 1, int FORM = 0>
-__global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gemm_mfma_kernel(const KArgs a) {
+__device__ __forceinline__ void gemm_mfma_tile(const KArgs& a, unsigned wg, const unsigned nwg, bf16_t* const lds_all) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr bool RAG = FORM >= 1, LONG = FORM == 2;
   static_assert(!SEQ || !PLAIN, "the range-wise accumulation exists with the full epilogue");
@@ -413,7 +418,6 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
   constexpr int TM = T::TM, TN = T::TN, MI = T::MI, NI = T::NI;
   constexpr int RING = LOOP >= 2 ? Loop2<BM, BN, LOOP>::RING32 : NSTAGE;   // slabs per operand (see read_frag_ring)
   constexpr int LDS_BYTES = RING * (T::A_ELEMS + T::B_ELEMS) * 2;
-  __shared__ __attribute__((aligned(1024))) bf16_t lds_all[RING * (T::A_ELEMS + T::B_ELEMS)];
   bf16_t* const ldsA = lds_all;
   bf16_t* const ldsB = lds_all + RING * T::A_ELEMS;
 
@@ -428,9 +432,8 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
   // neighbours sharing A rows / B columns also share an L2.
   // 32 bits: a launch has fewer than 2^31 workgroups, and short ones feel 64-bit divisions (the products of an attention backward, 16
   // matrices, s = 1000, d = 80: 70.2 us with them, 66.0 without).
-  unsigned wg = blockIdx.x;
   {
-    const unsigned nwg = gridDim.x, per = nwg >> 3, rem = nwg & 7, xcd = wg & 7, slot = wg >> 3;
+    const unsigned per = nwg >> 3, rem = nwg & 7, xcd = wg & 7, slot = wg >> 3;
     const unsigned start = xcd * per + (xcd < rem ? xcd : rem);  // XCDs 0..rem-1 own per+1 workgroups
     wg = start + slot;
   }
@@ -1208,6 +1211,12 @@ __global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gem
   }
   OPTIMUS_LAB_STAMP(3);
 #endif  // __HIP_DEVICE_COMPILE__
+}
+
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool PLAIN, bool SEQ = false, int LOOP = 1, int FORM = 0>
+__global__ __launch_bounds__(WM* WN * 64, (Occ<BM, BN, WM, WN>::value)) void gemm_mfma_kernel(const KArgs a) {
+  __shared__ __attribute__((aligned(1024))) bf16_t lds_all[lds_elems<BM, BN, LOOP>()];
+  gemm_mfma_tile<BM, BN, WM, WN, AKC, BKC, PLAIN, SEQ, LOOP, FORM>(a, blockIdx.x, gridDim.x, lds_all);
 }
 
 }  // namespace optimus
