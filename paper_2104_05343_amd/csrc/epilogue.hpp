@@ -27,6 +27,7 @@ struct CombineJob {
   int Mb, Nb, nz0;
   long long sC0, sC1, sBias0;
   EpiArgs epi;
+  int vec;   // whole quads in 16-byte partials, at most 8 splits: the short path
 };
 constexpr int kCombineJobs = 5;
 struct CombineJobs {

@@ -25,59 +25,98 @@ static std::atomic<int> g_last_plan{-1};
 int gemm_last_plan() { return g_last_plan; }
 
 // ---- fixed-order combine of panel-split partials + epilogue ----
-// The partial tiles of one product; a launch combines those of up to kCombineJobs products.
-__device__ __forceinline__ void combine_quad(const CombineJob& j, long long idx) {
-  const float* const partials = j.partials;
-  const int splits = j.splits, Mb = j.Mb, Nb = j.Nb;
-  EpiArgs e = j.epi;
-  long long quads_per_row = (Nb + 3) / 4;
-  long long total = j.nz * Mb * quads_per_row;
-  if (idx >= total) return;
-  int nq = (int)(idx % quads_per_row);
-  long long r = idx / quads_per_row;
-  int m = (int)(r % Mb);
-  long long z = r / Mb;
-  int n = nq * 4;
-  int nvalid = min(4, Nb - n);
-  float v[4] = {0.f, 0.f, 0.f, 0.f};
-  if ((Nb & 3) == 0 && ((size_t)partials & 15) == 0) {  // rows of the partial tiles are 16-byte aligned: one load per split, all in flight together
-    const float* p = partials + z * (long long)Mb * Nb + (long long)m * Nb + n;
-    const long long sstride = j.nz * (long long)Mb * Nb;
-#pragma unroll 8
-    for (int s = 0; s < splits; ++s) {
-      const float4 w = *(const float4*)(p + s * sstride);
-      v[0] += w.x; v[1] += w.y; v[2] += w.z; v[3] += w.w;
-    }
-  } else {
-    for (int s = 0; s < splits; ++s) {
-      const float* p = partials + ((long long)s * j.nz + z) * (long long)Mb * Nb + (long long)m * Nb + n;
-      for (int c = 0; c < nvalid; ++c) v[c] += p[c];
-    }
+// Four columns of a row a thread.  What bounds it is the launch and one round trip to memory: all partial tiles' loads and what the
+// epilogue reads are on their way before the first is waited for.  (In a loop over the splits the compiler waited for each load in turn.)
+template <int S>   // splits <= S: the loads past the last one repeat it
+__device__ __forceinline__ void combine_vec(const CombineJob& j, unsigned z, unsigned m, unsigned n) {
+  const long long block = (long long)j.Mb * j.Nb, stride = j.nz * block;
+  const float* p = j.partials + z * block + (long long)m * j.Nb + n;
+  const EpiArgs& e = j.epi;
+  const unsigned z1 = z / (unsigned)j.nz0, z0 = z - z1 * (unsigned)j.nz0;
+  const long long off = z1 * j.sC1 + z0 * j.sC0 + (long long)m * e.ldc + n;
+  float4 w[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) w[s] = *(const float4*)(p + (s < j.splits ? s : j.splits - 1) * stride);
+  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint2 zz = make_uint2(0, 0), rr = zz;
+  if (e.bias) bias = *(const float4*)(e.bias + z0 * j.sBias0 + n);
+  if (e.gelu_grad_of) zz = *(const uint2*)((const bf16_t*)e.gelu_grad_of + off);
+  if (e.residual) rr = *(const uint2*)((const bf16_t*)e.residual + off);
+  float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (s < j.splits) { t[0] += w[s].x; t[1] += w[s].y; t[2] += w[s].z; t[3] += w[s].w; }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) t[c] *= e.alpha;
+  if (e.bias) { t[0] += bias.x; t[1] += bias.y; t[2] += bias.z; t[3] += bias.w; }
+  if (e.pre_act) *(uint2*)((bf16_t*)e.pre_act + off) = make_uint2(pack2_bf16(t[0], t[1]), pack2_bf16(t[2], t[3]));
+  if (e.act == 1) gelu4<false>(t);
+  if (e.gelu_grad_of) {
+    const float g[4] = {__uint_as_float(zz.x << 16), __uint_as_float(zz.x & 0xffff0000u), __uint_as_float(zz.y << 16),
+                        __uint_as_float(zz.y & 0xffff0000u)};
+    gelu_grad_mul4<false>(t, g);
   }
-  int z1 = (int)(z / j.nz0), z0 = (int)(z % j.nz0);
-  if (e.bias) e.bias += z0 * j.sBias0;
-  epilogue_store4<false>(e, z1 * j.sC1 + z0 * j.sC0, m, n, v, nvalid);
+  if (e.residual) {
+    t[0] += __uint_as_float(rr.x << 16); t[1] += __uint_as_float(rr.x & 0xffff0000u);
+    t[2] += __uint_as_float(rr.y << 16); t[3] += __uint_as_float(rr.y & 0xffff0000u);
+  }
+  if (e.out_fp32) *(float4*)((float*)e.C + off) = make_float4(t[0], t[1], t[2], t[3]);
+  else *(uint2*)((bf16_t*)e.C + off) = make_uint2(pack2_bf16(t[0], t[1]), pack2_bf16(t[2], t[3]));
 }
-__global__ __launch_bounds__(256) void gemm_combine_kernel(const CombineJob j) {
-  combine_quad(j, (long long)blockIdx.x * blockDim.x + threadIdx.x);
+// quad idx of a job that takes combine_vec (CombineJob::vec).  The first workgroups wait for every line of code they run: the short path
+// is a kernel of its own, without 64-bit divisions, and divides by the block's rows only where there are several blocks.
+__device__ __forceinline__ void combine_quad_vec(const CombineJob& j, unsigned idx) {
+  const unsigned quads_per_row = (unsigned)j.Nb >> 2, r = idx / quads_per_row, n = (idx - r * quads_per_row) * 4;
+  unsigned z = 0, m = r;
+  if (j.nz > 1) { z = r / (unsigned)j.Mb; m = r - z * (unsigned)j.Mb; }
+  if (r >= (unsigned)j.nz * (unsigned)j.Mb) return;
+  if (j.splits <= 4) combine_vec<4>(j, z, m, n);
+  else combine_vec<8>(j, z, m, n);
+}
+__global__ __launch_bounds__(256) void gemm_combine_vec_kernel(const CombineJob j) {
+  combine_quad_vec(j, blockIdx.x * 256u + threadIdx.x);
 }
 __global__ __launch_bounds__(256) void gemm_combine_jobs_kernel(const CombineJobs jobs) {
   unsigned wg = blockIdx.x;
   int k = 0;
   while (k + 1 < jobs.n && wg >= jobs.blocks[k]) wg -= jobs.blocks[k++];
-  combine_quad(jobs.j[k], (long long)wg * blockDim.x + threadIdx.x);
+  combine_quad_vec(jobs.j[k], wg * 256u + threadIdx.x);
 }
-static long long combine_blocks(const CombineJob& j) { return (j.nz * j.Mb * ((j.Nb + 3) / 4) + 255) / 256; }
-int launch_gemm_combines(const CombineJobs& in, hipStream_t stream) {
-  if (in.n == 0) return OPTIMUS_OK;
-  if (in.n == 1) {
-    hipLaunchKernelGGL(gemm_combine_kernel, dim3((unsigned)combine_blocks(in.j[0])), dim3(256), 0, stream, in.j[0]);
-    return hip_launch_status();
+// any width, alignment and number of quads
+__global__ __launch_bounds__(256) void gemm_combine_kernel(const CombineJob j) {
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x, quads_per_row = (j.Nb + 3) / 4;
+  const int n = (int)(idx % quads_per_row) * 4, nvalid = min(4, j.Nb - n);
+  const long long r = idx / quads_per_row, z = r / j.Mb;
+  const int m = (int)(r % j.Mb);
+  if (z >= j.nz) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < j.splits; ++s) {
+    const float* p = j.partials + (s * j.nz + z) * (long long)j.Mb * j.Nb + (long long)m * j.Nb + n;
+    for (int c = 0; c < nvalid; ++c) v[c] += p[c];
   }
-  CombineJobs jobs = in;
+  const int z1 = (int)(z / j.nz0), z0 = (int)(z % j.nz0);
+  EpiArgs e = j.epi;
+  if (e.bias) e.bias += z0 * j.sBias0;
+  epilogue_store4<false>(e, z1 * j.sC1 + z0 * j.sC0, m, n, v, nvalid);
+}
+int launch_gemm_combines(const CombineJobs& in, hipStream_t stream) {
+  CombineJobs jobs = {};   // those of the short path
   long long blocks = 0;
-  for (int k = 0; k < jobs.n; ++k) blocks += jobs.blocks[k] = (unsigned)combine_blocks(jobs.j[k]);
-  hipLaunchKernelGGL(gemm_combine_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jobs);
+  for (int k = 0; k < in.n; ++k) {
+    const CombineJob& j = in.j[k];
+    const long long b = (j.nz * j.Mb * ((j.Nb + 3) / 4) + 255) / 256;
+    if (j.vec) {
+      blocks += jobs.blocks[jobs.n] = (unsigned)b;
+      jobs.j[jobs.n++] = j;
+    } else {
+      hipLaunchKernelGGL(gemm_combine_kernel, dim3((unsigned)b), dim3(256), 0, stream, j);
+      const int rc = hip_launch_status();
+      if (rc) return rc;
+    }
+  }
+  if (jobs.n == 0) return OPTIMUS_OK;
+  if (jobs.n == 1) hipLaunchKernelGGL(gemm_combine_vec_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jobs.j[0]);
+  else hipLaunchKernelGGL(gemm_combine_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jobs);
   return hip_launch_status();
 }
 
@@ -468,7 +507,9 @@ static bool plain_store(const KArgs& ka) {
 }
 static long long workgroups(const KArgs& ka) { return (long long)ka.tiles_m * ka.tiles_n * ka.nz * ka.splits; }
 static CombineJob combine_job(const GemmDesc& d, const KArgs& ka) {
-  return CombineJob{d.partials, ka.splits, ka.nz, d.Mb, d.Nb, d.nz0, d.sC0, d.sC1, d.sBias0, ka.epi};
+  // rows of the partial tiles and of everything the epilogue touches in whole quads, counted in 32 bits
+  const int vec = ka.epi.vec_ok && d.Nb % 4 == 0 && aligned16(d.partials) && ka.splits <= 8 && ka.nz * d.Mb * (d.Nb / 4) < (1LL << 31);
+  return CombineJob{d.partials, ka.splits, ka.nz, d.Mb, d.Nb, d.nz0, d.sC0, d.sC1, d.sBias0, ka.epi, vec};
 }
 
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
