@@ -111,20 +111,30 @@ struct LinearGrads {
   int64_t M, K, N;              // d_in is [M x K], d_out [M x N], W [K x N]
   const void* gelu_grad_of;     // or nullptr
 };
-int run_linear_grads(const LinearGrads& g, int q, int i, int j, void* ws_x, void* ws_y, size_t ws_bytes, hipStream_t st) {
+// ws_y: the weight gradient's partial tiles, ws_y_bytes of them.  What is left to be combined is handed out in *in_job (d_in; its C is null
+// if there is nothing) and added to *w_jobs.
+int run_linear_grads(const LinearGrads& g, int q, int i, int j, void* ws_x, size_t ws_x_bytes, void* ws_y, size_t ws_y_bytes, CombineJob* in_job,
+                     CombineJobs* w_jobs, hipStream_t st) {
   optimus_epilogue ex = {}, ey = {};
   ex.gelu_grad_of = g.gelu_grad_of;
   ey.out_fp32 = 1;
   GemmDesc x = summa_desc(OPTIMUS_FORM_ABT, g.d_out, g.w, g.d_in, g.M, g.N, g.K, q, i, j, OPTIMUS_BF16, &ex);
   GemmDesc y = summa_desc(OPTIMUS_FORM_ATB, g.in, g.d_out, g.d_w, g.K, g.M, g.N, q, i, j, OPTIMUS_BF16, &ey);
   const size_t nx = gemm_plan_bytes(x), ny = gemm_plan_bytes(y);
-  if (nx > 0 && nx <= ws_bytes) { x.partials = (float*)ws_x; x.partials_bytes = ws_bytes; }
-  if (ny > 0 && ny <= ws_bytes) { y.partials = (float*)ws_y; y.partials_bytes = ws_bytes; }
-  CombineJobs combines = {};
+  if (nx > 0 && nx <= ws_x_bytes) { x.partials = (float*)ws_x; x.partials_bytes = ws_x_bytes; }
+  if (ny > 0 && ny <= ws_y_bytes) { y.partials = (float*)ws_y; y.partials_bytes = ws_y_bytes; }
+  *in_job = CombineJob{};
+  CombineJobs jobs = {};
   int rc;
-  if (launch_gemm_pair(x, y, &combines, st, &rc)) return rc ? rc : launch_gemm_combines(combines, st);
-  if ((rc = launch_gemm(x, st))) return rc;
-  return launch_gemm(y, st);
+  if (!launch_gemm_pair(x, y, &jobs, st, &rc)) {
+    if ((rc = launch_gemm(x, st))) return rc;
+    return launch_gemm(y, st);
+  }
+  for (int k = 0; k < jobs.n; ++k) {
+    if (jobs.j[k].epi.C == x.C) *in_job = jobs.j[k];
+    else w_jobs->j[w_jobs->n++] = jobs.j[k];
+  }
+  return rc;
 }
 
 struct AttnDims {
@@ -524,6 +534,29 @@ size_t layer_gemm_ws(const optimus_layer_cfg* c) {
   return align256(mx);
 }
 
+// Partial tiles of a layer's four weight gradients on one stream, which stay until the end of the pass: each its place behind the last.
+// Nothing where two streams run.
+bool two_streams_pay(const optimus_layer_cfg* c, bool grid);
+void layer_weight_ws(const optimus_layer_cfg* c, int i, int j, size_t at[4], size_t* total) {
+  LayerGemm g[12];
+  layer_gemms(c, g);
+  *total = 0;
+  for (int k = 0; k < 4; ++k) {
+    at[k] = *total;
+    const LayerGemm& w = g[5 + 2 * k];
+    *total += align256(summa_ws_bytes(w.form, w.M, w.K, w.N, c->q, i, j, c->dtype, 0));
+  }
+}
+size_t layer_branch_ws(const optimus_layer_cfg* c, size_t gemm_bytes) {
+  size_t mx = gemm_bytes, at[4], total;
+  for (int grid = 0; grid < 2; ++grid) {
+    if (two_streams_pay(c, grid)) continue;
+    layer_weight_ws(c, grid ? -1 : 0, grid ? -1 : 0, at, &total);
+    if (total > mx) mx = total;
+  }
+  return mx;
+}
+
 }  // namespace
 
 extern "C" {
@@ -792,7 +825,8 @@ size_t optimus_layer_workspace_bytes(const optimus_layer_cfg* cfg) {
   AttnDims a;
   if (layer_check(cfg, 0, 0, &a)) return 0;
   // scores scratch of attention + split partials of the activation chain + split partials of the gradient branch
-  return layer_attn_ws(cfg, a) + 2 * layer_gemm_ws(cfg);
+  const size_t gemm_bytes = layer_gemm_ws(cfg);
+  return layer_attn_ws(cfg, a) + gemm_bytes + layer_branch_ws(cfg, gemm_bytes);
 }
 
 size_t optimus_layer_workspace_bytes_grid(const optimus_layer_cfg* cfg) {
@@ -890,7 +924,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   // workspace: [products, chain][products, branch][attention: everything that is left]
   void* gemm_ws = ws;
   void* attn_ws = (char*)ws + 2 * gemm_bytes;
-  const size_t attn_bytes = ws_bytes - 2 * gemm_bytes;
+  size_t attn_bytes = ws_bytes - 2 * gemm_bytes;
   LnDesc ln;
   if ((rc = ln_desc(M, h, q, i, j, dt, c->eps, &ln))) return rc;
   // gradient branch: its own stream and its own split workspace (see SideStream)
@@ -917,35 +951,93 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
 #define BRANCH_AFTER_MAIN(EV) do { if (ss && rc == OPTIMUS_OK) { rc = stream_after(gst, st, EV); forked = forked || rc == OPTIMUS_OK; } } while (0)
   BRANCH_AFTER_MAIN(ss->fork);
   // ---- out = h_mid + gelu W2 + b2 ----
-  // One stream: both products of a linear layer in one launch.  Two: the gradient of the weight on the branch.
-  const auto linear = [&](const void* d_y, const void* w, const void* in, void* d_in, float* d_w, int64_t k, int64_t n, const void* gelu_grad_of) {
+  // One stream: both products of a linear layer in one launch, the partial tiles of a panel split combined where they are needed: those
+  // of d_ln1_out and d_ln2_out by the LayerNorm, the weight gradients' at the end of the pass (if the workspace holds them that long;
+  // otherwise at once).  Two: the gradient of the weight on the branch.
+  CombineJob in_job = {};
+  CombineJobs w_jobs = {};
+  size_t w_at[4], w_total = 0;
+  if (!ss) layer_weight_ws(c, i, j, w_at, &w_total);
+  const size_t branch_bytes = w_total > gemm_bytes ? w_total : gemm_bytes;
+  const bool keep = w_total > 0 && ws_bytes >= layer_attn_ws(c, a) + gemm_bytes + branch_bytes;
+  if (keep) {
+    attn_ws = (char*)ws + gemm_bytes + branch_bytes;
+    attn_bytes = ws_bytes - gemm_bytes - branch_bytes;
+  }
+  const auto linear = [&](int nth, const void* d_y, const void* w, const void* in, void* d_in, float* d_w, int64_t k, int64_t n,
+                          const void* gelu_grad_of) {
     const LinearGrads g = {d_y, w, in, d_in, d_w, M, k * h, n * h, gelu_grad_of};
-    if (!ss) return run_linear_grads(g, q, i, j, gemm_ws, (char*)gemm_ws + gemm_bytes, gemm_bytes, st);
+    if (!ss) {
+      char* const branch = (char*)gemm_ws + gemm_bytes;
+      const size_t bytes = !keep ? gemm_bytes : nth < 3 ? w_at[nth + 1] - w_at[nth] : w_total - w_at[nth];
+      int r = run_linear_grads(g, q, i, j, gemm_ws, gemm_bytes, branch + (keep ? w_at[nth] : 0), bytes, &in_job, &w_jobs, st);
+      if (r) return r;
+      CombineJobs now = {};
+      if (in_job.partials && nth % 2 == 0) { now.j[now.n++] = in_job; in_job = CombineJob{}; }   // no LayerNorm follows
+      if (!keep) {
+        for (int m = 0; m < w_jobs.n; ++m) now.j[now.n++] = w_jobs.j[m];
+        w_jobs.n = 0;
+      }
+      return launch_gemm_combines(now, st);
+    }
     e = {}; e.gelu_grad_of = gelu_grad_of;
     const int r = run_summa(OPTIMUS_FORM_ABT, d_y, w, d_in, M, n * h, k * h, q, i, j, dt, &e, gemm_ws, gemm_bytes, stream, co_chain);
     if (r) return r;
     return run_summa(OPTIMUS_FORM_ATB, in, d_y, d_w, k * h, M, n * h, q, i, j, dt, &e32, grad_ws, gemm_bytes, gstream, co_branch);
   };
-  RUN(linear(t->d_out, t->w2, t->gelu, t->d_pre_gelu, t->d_w2, 4, 1, t->pre_gelu));   // d_pre = (d_out W2^T) * GeLU'(pre)
+  // LayerNorm backward behind linear(): its input, d_y, is complete or the partial tiles of in_job
+  const auto norm_bwd = [&](const void* d_y, const void* xhat, const float* rstd, const float* gamma, const void* d_res, void* d_in, float* d_g,
+                            float* d_b, float* stats) {
+    if (in_job.partials) {
+      if (!d_g && ln_bwd_partials_ok(in_job, d_y, xhat, gamma, d_res, d_in, ln))
+        return launch_ln_bwd_partials(in_job, xhat, rstd, gamma, d_res, d_in, stats, ln, st);
+      CombineJobs now = {};
+      now.j[now.n++] = in_job;
+      const int r = launch_gemm_combines(now, st);
+      if (r) return r;
+    }
+    return ln_backward(d_y, xhat, rstd, gamma, d_res, d_in, d_g, d_b, stats, ln, grid, st);
+  };
+  RUN(linear(0, t->d_out, t->w2, t->gelu, t->d_pre_gelu, t->d_w2, 4, 1, t->pre_gelu));   // d_pre = (d_out W2^T) * GeLU'(pre)
   if (ss) RUN(optimus_bias_grad(t->d_out, t->d_b2, M, h, q, i, j, dt, gstream));
   // ---- pre = ln2_out W1 + b1 ----
   BRANCH_AFTER_MAIN(ss->ready[0]);  // d_pre_gelu is complete
-  RUN(linear(t->d_pre_gelu, t->w1, t->ln2_out, t->d_ln2_out, t->d_w1, 1, 4, nullptr));
+  RUN(linear(1, t->d_pre_gelu, t->w1, t->ln2_out, t->d_ln2_out, t->d_w1, 1, 4, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_pre_gelu, t->d_b1, M, 4 * h, q, i, j, dt, gstream));
   // ---- LN2 backward, plus the residual branch: d_h_mid = d_out + LN2'(d_ln2_out) ----
-  RUN(ln_backward(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_g,
-                  ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_b, t->bstats2, ln, grid, st));
+  RUN(norm_bwd(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_g,
+               ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_b, t->bstats2));
   // ---- h_mid = x + attn Wo + bo ----
   BRANCH_AFTER_MAIN(ss->ready[1]);  // d_h_mid is complete
-  RUN(linear(t->d_h_mid, t->w_o, t->attn, t->d_attn, t->d_w_o, 1, 1, nullptr));
+  RUN(linear(2, t->d_h_mid, t->w_o, t->attn, t->d_attn, t->d_w_o, 1, 1, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_h_mid, t->d_b_o, M, h, q, i, j, dt, gstream));
   // ---- local attention backward ----
   RUN(layer_attention(true, c, t, i, j, attn_ws, attn_bytes, stream));
   // ---- qkv = ln1_out Wqkv + b ----
   BRANCH_AFTER_MAIN(ss->ready[2]);  // d_qkv is complete
-  RUN(linear(t->d_qkv, t->w_qkv, t->ln1_out, t->d_ln1_out, t->d_w_qkv, 1, 3, nullptr));
+  RUN(linear(3, t->d_qkv, t->w_qkv, t->ln1_out, t->d_ln1_out, t->d_w_qkv, 1, 3, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_qkv, t->d_b_qkv, M, 3 * h, q, i, j, dt, gstream));
-  if (sums_at_end) {   // column sums in one launch, their sources are still there; on a branch without the two that would wait
+  // ---- LN1 backward, plus the residual branch: d_x = d_h_mid + LN1'(d_ln1_out) ----
+  // On one stream ahead of the sums, which then find d_ln1_out complete; behind them if d_x takes the place of what they read.
+  const auto takes = [&](const void* p, int64_t k) {
+    const char *x0 = (const char*)t->d_x, *p0 = (const char*)p;
+    return x0 < p0 + M * k * h * 2 && p0 < x0 + M * h * 2;
+  };
+  const bool norm_last = ss || takes(t->d_pre_gelu, 4) || takes(t->d_qkv, 3) || takes(t->d_ln2_out, 1) || takes(t->xhat2, 1) ||
+                         takes(t->d_h_mid, 1) || takes(t->d_ln1_out, 1) || takes(t->xhat1, 1) || takes(t->d_out, 1);
+  if (norm_last && in_job.partials) {
+    CombineJobs now = {};
+    now.j[now.n++] = in_job;
+    in_job = CombineJob{};
+    RUN(launch_gemm_combines(now, st));
+  }
+  const auto norm1 = [&]() {
+    return norm_bwd(t->d_ln1_out, t->xhat1, t->rstd1, t->ln1_g, t->d_h_mid, t->d_x, ss ? t->d_ln1_g : nullptr, ss ? t->d_ln1_b : nullptr,
+                    t->bstats1);
+  };
+  if (!norm_last) RUN(norm1());
+  if (sums_at_end) {   // column sums, and the combines kept so far, in one launch; the sources are still there; on a branch without the two that
+                       // would wait
     const int rows = (int)(M / q), hb = (int)(h / q);
     const long long dev = grid ? 0 : (long long)i * q + j;
     const auto job = [&](const void* X, const void* W, float* sum, float* sum_w, int k) {
@@ -955,11 +1047,9 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
     const ColsumJobs jobs = {{job(t->d_pre_gelu, nullptr, t->d_b1, nullptr, 4), job(t->d_qkv, nullptr, t->d_b_qkv, nullptr, 3),
                               job(t->d_ln2_out, t->xhat2, t->d_ln2_b, t->d_ln2_g, 1), job(t->d_h_mid, nullptr, t->d_b_o, nullptr, 1),
                               job(t->d_ln1_out, t->xhat1, t->d_ln1_b, t->d_ln1_g, 1), job(t->d_out, nullptr, t->d_b2, nullptr, 1)}, ss ? 4 : 6};
-    RUN(launch_colsum_jobs(jobs, rows, grid ? q * q : 1, gst));
+    RUN(launch_colsum_jobs(jobs, rows, grid ? q * q : 1, &w_jobs, gst));
   }
-  // ---- LN1 backward, plus the residual branch: d_x = d_h_mid + LN1'(d_ln1_out) ----
-  RUN(ln_backward(t->d_ln1_out, t->xhat1, t->rstd1, t->ln1_g, t->d_h_mid, t->d_x, ss ? t->d_ln1_g : nullptr, ss ? t->d_ln1_b : nullptr,
-                  t->bstats1, ln, grid, st));
+  if (norm_last) RUN(norm1());
   // the caller's stream owns every result again
   if (ss && forked) {
     const int jr = stream_after(st, gst, ss->join);

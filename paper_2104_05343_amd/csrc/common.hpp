@@ -93,12 +93,13 @@ struct GemmDesc {
   int plan_for_batch;
 };
 
+struct CombineJob;    // epilogue.hpp
+struct CombineJobs;
 int launch_gemm(const GemmDesc& d, hipStream_t stream);           // picks one of the two below
 int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);    // fp32, or any bf16 shape, stride and alignment
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);       // bf16 rows on the 16-byte grid: direct-to-LDS tiles
 // A B^T (x) and A^T B (y) in one launch, y not reading what x writes; the combines that their panel splits want are added to
 // *combines.  False if the two do not go together: nothing is launched then.  *rc: status of the launch.
-struct CombineJobs;
 bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combines, hipStream_t stream, int* rc);
 int launch_gemm_combines(const CombineJobs& jobs, hipStream_t stream);
 bool gemm_mfma_supported(const GemmDesc& d);
@@ -133,7 +134,8 @@ struct ColsumJobs {
   ColsumJob j[6];
   int n;
 };
-int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, hipStream_t stream);
+// combines (or nullptr): panel splits to be combined beside the sums
+int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, const CombineJobs* combines, hipStream_t stream);
 
 struct LnDesc {
   int rows, cols;  // block dims M/q, H/q
@@ -154,6 +156,12 @@ int launch_ln_bwd_stats(const void* dY, const void* xhat, const float* gamma, fl
                         hipStream_t stream);
 int launch_ln_bwd_apply(const void* dY, const void* xhat, const float* rstd, const float* gamma, const void* dres,
                         void* dX, float* stats, const LnDesc& d, bool own_stats_ready, hipStream_t stream);
+// The same where dY is still the partial tiles of job j (which has its address): dY is summed, stored and used.  _ok: whether that job and
+// these blocks allow it (one device's block, or the whole grid's with a grid row in one workgroup).
+bool ln_bwd_partials_ok(const CombineJob& j, const void* dY, const void* xhat, const float* gamma, const void* dres, const void* dX,
+                        const LnDesc& d);
+int launch_ln_bwd_partials(const CombineJob& j, const void* xhat, const float* rstd, const float* gamma, const void* dres, void* dX, float* stats,
+                           const LnDesc& d, hipStream_t stream);
 // small blocks (narrow column strips; the kernel is latency-bound there)
 bool colsum_narrow(int rows, int cols);
 int launch_ln_param_grads(const void* dY, const void* xhat, float* dgamma_part, float* dbeta_part, const LnDesc& d,

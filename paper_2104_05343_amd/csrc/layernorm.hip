@@ -6,7 +6,7 @@
 // 16-byte loads, kept in registers, reduced with DPP-free shuffles, and written once.  Wider or unaligned
 // rows take a scalar path that re-reads the row.  Statistics are fp32; partials are always added in the
 // order l = 0..q-1 so that every device of a row, and grid and device mode, get identical bits.
-#include "common.hpp"
+#include "combine.hpp"
 
 namespace optimus {
 
@@ -41,12 +41,43 @@ template <> struct Vec<float> {
   __device__ static void st1(float* p, float v) { *p = v; }
 };
 
+// The partial tiles of the product that makes X (MODE 3): [splits][blocks of the launch][rows][cols], stride elements from one split to
+// the next; the sum, rounded, is X, and is stored there.
+struct LnPartials {
+  const float* p;
+  int splits;
+  long long stride;
+};
+
 struct LnArgs {
   int rows, cols, H, q;
   int i0, ni, j0, nj;
   float eps;
   int vec;  // fast path allowed
 };
+
+// eight columns of X: the splits' sum in their order (as combine_vec adds them), rounded; four splits' loads in flight
+__device__ __forceinline__ void ln_sum_partials(const float* p, const LnPartials& part, bf16_t* x, float* v) {
+  float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < part.splits; s0 += 4) {
+    float4 w[4][2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const float* ps = p + (s0 + s < part.splits ? s0 + s : part.splits - 1) * part.stride;
+      w[s][0] = *(const float4*)ps; w[s][1] = *(const float4*)(ps + 4);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (s0 + s < part.splits)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) { t[4 * h] += w[s][h].x; t[4 * h + 1] += w[s][h].y; t[4 * h + 2] += w[s][h].z; t[4 * h + 3] += w[s][h].w; }
+  }
+  const uint4 u = make_uint4(pack2_bf16(t[0], t[1]), pack2_bf16(t[2], t[3]), pack2_bf16(t[4], t[5]), pack2_bf16(t[6], t[7]));
+  *(uint4*)x = u;
+  const unsigned k[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { v[2 * i] = __uint_as_float(k[i] << 16); v[2 * i + 1] = __uint_as_float(k[i] & 0xffff0000u); }
+}
 
 // MODE 0: forward stats only.  MODE 1: forward apply (own partial computed here unless own_ready).
 // MODE 2: backward stats only. MODE 3: backward apply.
@@ -55,11 +86,14 @@ struct LnArgs {
 // wavefront adds them in the order l = 0..q-1: the same numbers in the same order as the two-kernel form
 // (statistics kernel, then apply with own_ready), in one pass over the input.  The partials are still written
 // to `stats`, which device-mode calls of the peers read.
-template <typename T, int MODE, bool RG = false>
+// PART (MODE 3, bf16, vector path): X does not exist yet, its product's partial tiles do (LnPartials).  A launch less, and X is read from
+// registers instead of memory: blocks of [1024 x 256], four ranges, 3.7 (combine) and 4.6 us before, now 5.4.
+template <typename T, int MODE, bool RG = false, bool PART = false>
 __global__ __launch_bounds__(RG ? 1024 : 256) void ln_kernel(const T* __restrict__ X, const T* __restrict__ X2, const float* __restrict__ gamma,
                                                  const float* __restrict__ beta, const float* __restrict__ rstd_in,
                                                  const T* __restrict__ dres, T* __restrict__ Y, T* __restrict__ xhat_out,
-                                                 float* __restrict__ rstd_out, float* __restrict__ stats, LnArgs a, int own_ready) {
+                                                 float* __restrict__ rstd_out, float* __restrict__ stats, LnArgs a, int own_ready, LnPartials part) {
+  static_assert(!PART || (MODE == 3 && sizeof(T) == 2), "partial tiles: the backward pass, bf16");
   constexpr int VN = Vec<T>::N;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -87,7 +121,8 @@ __global__ __launch_bounds__(RG ? 1024 : 256) void ln_kernel(const T* __restrict
     for (int c = 0; c < LN_MAXCH; ++c) {
       int col = (c * 64 + lane) * VN;
       if (col < a.cols) {
-        Vec<T>::load(x + col, v + c * VN);
+        if constexpr (PART) ln_sum_partials(part.p + (RG ? base : (long long)row * a.cols) + col, part, const_cast<T*>(x) + col, v + c * VN);
+        else Vec<T>::load(x + col, v + c * VN);
         if (MODE >= 2) {
           Vec<T>::load(x2 + col, w + c * VN);
 #pragma unroll
@@ -210,6 +245,7 @@ bool ln_rowgroup_ok(const LnDesc& d) { return d.j0 == 0 && d.nj == d.q && d.q >=
 template <typename T, int MODE>
 static int run(const void* X, const void* X2, const float* gamma, const float* beta, const float* rstd_in, const void* dres,
                void* Y, void* xhat, float* rstd_out, float* stats, const LnDesc& d, bool own_ready, hipStream_t stream) {
+  const LnPartials none = {};
   bool ok = al16(X) && (!X2 || al16(X2)) && (!dres || al16(dres)) && (!Y || al16(Y)) && (!xhat || al16(xhat)) &&
             (!gamma || al16(gamma)) && (!beta || al16(beta));
   LnArgs a = make_args(d, ok, (int)sizeof(T));
@@ -218,13 +254,13 @@ static int run(const void* X, const void* X2, const float* gamma, const float* b
       const int rpw = ln_rowgroup_rows(d);
       dim3 grid((unsigned)(d.rows / rpw), (unsigned)d.ni);
       hipLaunchKernelGGL((ln_kernel<T, MODE, true>), grid, dim3(64 * d.q * rpw), 0, stream, (const T*)X, (const T*)X2, gamma, beta,
-                         rstd_in, (const T*)dres, (T*)Y, (T*)xhat, rstd_out, stats, a, 0);
+                         rstd_in, (const T*)dres, (T*)Y, (T*)xhat, rstd_out, stats, a, 0, none);
       return hip_launch_status();
     }
   }
   dim3 grid((unsigned)((d.rows + 3) / 4), (unsigned)(d.ni * d.nj));
   hipLaunchKernelGGL((ln_kernel<T, MODE>), grid, dim3(256), 0, stream, (const T*)X, (const T*)X2, gamma, beta, rstd_in,
-                     (const T*)dres, (T*)Y, (T*)xhat, rstd_out, stats, a, own_ready ? 1 : 0);
+                     (const T*)dres, (T*)Y, (T*)xhat, rstd_out, stats, a, own_ready ? 1 : 0, none);
   return hip_launch_status();
 }
 
@@ -244,6 +280,36 @@ int launch_ln_bwd_stats(const void* dY, const void* xhat, const float* gamma, fl
 int launch_ln_bwd_apply(const void* dY, const void* xhat, const float* rstd, const float* gamma, const void* dres, void* dX,
                         float* stats, const LnDesc& d, bool own_ready, hipStream_t stream) {
   return LN_DISPATCH(3, dY, xhat, gamma, nullptr, rstd, dres, dX, nullptr, nullptr, stats, d, own_ready, stream);
+}
+
+bool ln_bwd_partials_ok(const CombineJob& j, const void* dY, const void* xhat, const float* gamma, const void* dres, const void* dX,
+                        const LnDesc& d) {
+  const EpiArgs& e = j.epi;
+  const long long first = ((long long)d.i0 * d.q + d.j0) * d.rows * d.cols;
+  if (!j.vec || d.dtype != OPTIMUS_BF16 || e.C != (const bf16_t*)dY + first || e.alpha != 1.0f || e.bias || e.pre_act || e.act || e.gelu_grad_of || e.residual || e.out_fp32)
+    return false;
+  const bool grid = ln_rowgroup_ok(d);
+  if (j.Mb != d.rows || j.Nb != d.cols || e.ldc != d.cols || j.nz != (grid ? (long long)d.ni * d.nj : 1) || (!grid && d.ni * d.nj != 1)) return false;
+  if (grid && (d.i0 != 0 || d.ni != d.q)) return false;
+  if (grid && j.nz > 1 && (j.sC0 != (long long)d.rows * d.cols || j.sC1 != j.sC0 * d.q || j.nz0 != d.q)) return false;
+  return make_args(d, al16(e.C) && al16(xhat) && al16(gamma) && (!dres || al16(dres)) && al16(dX), 2).vec;
+}
+int launch_ln_bwd_partials(const CombineJob& j, const void* xhat, const float* rstd, const float* gamma, const void* dres, void* dX, float* stats,
+                           const LnDesc& d, hipStream_t stream) {
+  const LnArgs a = make_args(d, true, 2);
+  const LnPartials part = {j.partials, j.splits, j.nz * j.Mb * (long long)j.Nb};
+  // the epilogue's C is the first block of the launch, the kernel's X the grid's first
+  const long long first = ((long long)d.i0 * d.q + d.j0) * d.rows * d.cols;
+  const bf16_t* X = (const bf16_t*)j.epi.C - first;
+  if (ln_rowgroup_ok(d)) {
+    const int rpw = ln_rowgroup_rows(d);
+    hipLaunchKernelGGL((ln_kernel<bf16_t, 3, true, true>), dim3((unsigned)(d.rows / rpw), (unsigned)d.ni), dim3(64 * d.q * rpw), 0, stream, X,
+                       (const bf16_t*)xhat, gamma, (const float*)nullptr, rstd, (const bf16_t*)dres, (bf16_t*)dX, (bf16_t*)nullptr, (float*)nullptr, stats, a, 0, part);
+  } else {
+    hipLaunchKernelGGL((ln_kernel<bf16_t, 3, false, true>), dim3((unsigned)((d.rows + 3) / 4)), dim3(256), 0, stream, X, (const bf16_t*)xhat, gamma,
+                       (const float*)nullptr, rstd, (const bf16_t*)dres, (bf16_t*)dX, (bf16_t*)nullptr, (float*)nullptr, stats, a, 0, part);
+  }
+  return hip_launch_status();
 }
 
 // ---- column sums over the rows of a block: dgamma/dbeta partials, bias gradients ----
@@ -359,9 +425,9 @@ __device__ __forceinline__ void colsum_strip(const T* __restrict__ X, const T* _
 // workgroups are dealt round-robin to the 8 XCDs: a contiguous range of strips each (whatever XCD the entry starts on), unless
 // a strip is whole lines, which no other shares
 template <int CL>
-__device__ __forceinline__ int cs_place() {
-  if (CL == 8) return blockIdx.x;
-  const int nwg = gridDim.x, slot = blockIdx.x >> 3, xcd = blockIdx.x & 7, rem = nwg & 7;
+__device__ __forceinline__ int cs_place(int wg, int nwg) {
+  if (CL == 8) return wg;
+  const int slot = wg >> 3, xcd = wg & 7, rem = nwg & 7;
   return xcd * (nwg >> 3) + (xcd < rem ? xcd : rem) + slot;
 }
 template <typename T, bool PROD, int ROWS, int CL, int PER>
@@ -372,19 +438,30 @@ __global__ __launch_bounds__(ROWS / PER * CL) void colsum_kernel(const T* __rest
   __shared__ float red2[ROWS / 8][8 * CL];
   const bool vec_rows = (ld % 8 == 0) && (sX % 8 == 0) && (((uintptr_t)X & 15) == 0) && (!PROD || ((uintptr_t)W & 15) == 0);
   const long long zx = (long long)blockIdx.y * sX, zo = (long long)blockIdx.y * sOut;
-  colsum_strip<T, PROD, ROWS, CL, PER>(X + zx, PROD ? W + zx : nullptr, out + zo, PROD ? out2 + zo : nullptr, rows, cols, ld, cs_place<CL>(), vec_rows, red, red2);
+  colsum_strip<T, PROD, ROWS, CL, PER>(X + zx, PROD ? W + zx : nullptr, out + zo, PROD ? out2 + zo : nullptr, rows, cols, ld, cs_place<CL>(blockIdx.x, gridDim.x), vec_rows, red, red2);
 }
 // Several sums in one launch: a layer's vector gradients, whose sources all live until the end of the backward pass.  As six
 // launches of 4 to 7 us each, the step of a 1024-wide layer (one device of 4 x 4) takes 250 us, as one 219; of two small
 // checkpointed layers on a 2 x 2 grid 362 and 328; of a 1280-wide layer with cut tiles 328 and 292 (four sums, on the branch).
+// The combines of panel splits that nothing of the pass waits for (a layer's weight gradients) ride behind them in the same grid:
+// 7.9 us for the sums and 15 for four combines of a 1024-wide layer (one device of 4 x 4) before, now 9.6 together.
 template <int ROWS, int CL, int PER>
-__global__ __launch_bounds__(ROWS / PER * CL) void colsum_jobs_kernel(const ColsumJobs jobs, int rows) {
+__global__ __launch_bounds__(ROWS / PER * CL) void colsum_jobs_kernel(const ColsumJobs jobs, int rows, unsigned strips, unsigned sums,
+                                                                      const CombineJobs combines) {
   __shared__ float red[ROWS / 8][8 * CL];
   __shared__ float red2[ROWS / 8][8 * CL];
-  int strip = cs_place<CL>(), k = 0;
+  if (blockIdx.x >= sums) {
+    unsigned wg = blockIdx.x - sums;
+    int k = 0;
+    while (k + 1 < combines.n && wg >= combines.blocks[k]) wg -= combines.blocks[k++];
+    combine_quad_vec(combines.j[k], wg * (ROWS / PER * CL) + threadIdx.x);
+    return;
+  }
+  const unsigned z = blockIdx.x / strips;
+  int strip = cs_place<CL>(blockIdx.x - z * strips, strips), k = 0;
   while (k + 1 < jobs.n && strip >= (jobs.j[k].cols + 8 * CL - 1) / (8 * CL)) strip -= (jobs.j[k++].cols + 8 * CL - 1) / (8 * CL);
   const ColsumJob& j = jobs.j[k];
-  const long long zx = (long long)blockIdx.y * rows * j.cols, zo = (long long)blockIdx.y * j.cols;
+  const long long zx = (long long)z * rows * j.cols, zo = (long long)z * j.cols;
   const bf16_t* X = (const bf16_t*)j.X + zx;
   const bf16_t* W = j.W ? (const bf16_t*)j.W + zx : nullptr;
   const bool vec_rows = j.cols % 8 == 0 && (((uintptr_t)j.X | (uintptr_t)j.W) & 15) == 0;
@@ -435,7 +512,7 @@ static void colsum_launch(dim3 batch, const T* X, const T* W, float* out, float*
 #undef OPTIMUS_COLSUM
 }
 
-int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, hipStream_t stream) {
+int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, const CombineJobs* combines, hipStream_t stream) {
   long long width = 0;
   int least = jobs.j[0].cols;
   for (int k = 0; k < jobs.n; ++k) { width += jobs.j[k].cols; least = jobs.j[k].cols < least ? jobs.j[k].cols : least; }
@@ -443,9 +520,21 @@ int launch_colsum_jobs(const ColsumJobs& jobs, int rows, int nz, hipStream_t str
   const int cl = cs_lanes<bf16_t>(width * nz, least, (unsigned)nz);
   unsigned strips = 0;
   for (int k = 0; k < jobs.n; ++k) strips += (unsigned)((jobs.j[k].cols + 8 * cl - 1) / (8 * cl));
-  const dim3 grid(strips, (unsigned)nz);
+  const int threads = (tall ? (cl == 8 ? 128 : 256) : 128) * cl;
+  CombineJobs with = {}, alone = {};
+  long long blocks = 0;
+  for (int k = 0; combines && k < combines->n; ++k) {
+    const CombineJob& j = combines->j[k];
+    if (!j.vec) { alone.j[alone.n++] = j; continue; }
+    blocks += with.blocks[with.n] = (unsigned)((j.nz * j.Mb * (j.Nb / 4) + threads - 1) / threads);
+    with.j[with.n++] = j;
+  }
+  const int rc = launch_gemm_combines(alone, stream);
+  if (rc) return rc;
+  const unsigned sums = strips * (unsigned)nz;
+  const dim3 grid((unsigned)(sums + blocks));
 #define OPTIMUS_COLSUM_JOBS(ROWS, CL, PER) \
-  hipLaunchKernelGGL((colsum_jobs_kernel<ROWS, CL, PER>), grid, dim3(ROWS / PER * CL), 0, stream, jobs, rows)
+  hipLaunchKernelGGL((colsum_jobs_kernel<ROWS, CL, PER>), grid, dim3(ROWS / PER * CL), 0, stream, jobs, rows, strips, sums, with)
   if (tall && cl == 8) OPTIMUS_COLSUM_JOBS(256, 8, 2);
   else if (tall && cl == 4) OPTIMUS_COLSUM_JOBS(256, 4, 1);
   else if (tall && cl == 2) OPTIMUS_COLSUM_JOBS(256, 2, 1);

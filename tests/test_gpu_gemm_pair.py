@@ -48,3 +48,40 @@ def test_pairs_equal_separate_launches(shape, device, deep, tile):
     for n in names:
         assert not torch.isnan(out[1][n]).any(), n
         assert torch.equal(out[0][n], out[1][n]), n
+
+
+@pytest.mark.parametrize("shape", [LayerShape(b=8, s=256, h=768, n=12, q=4), LayerShape(b=4, s=104, h=320, n=4, q=2)], ids=str)
+@pytest.mark.parametrize("d_x", ["d_x", "d_out", "d_ln1_out"])
+def test_workspace_without_room_and_gradient_in_place(shape, d_x):
+    """The weight gradients' partial tiles do not fit: combined at once.  d_x in the place of a tensor that the column sums read."""
+    inp = layer_inputs(3, shape, "bf16", perturb_affine=True)
+    cfg, T, lt, ws = alloc_layer(inp, shape, True)
+    opt.layer_fwd(cfg, lt, -1, -1, ws)
+    opt.layer_bwd(cfg, lt, -1, -1, ws)
+    i, j, q = 0, 1, shape.q
+
+    def block(t):
+        return t.view(q * q, -1)[i * q + j]
+    names = [n for n in BWD_OUT + FP32_MATS + list(VEC_PART) if n not in (d_x, "d_x")]
+    before = {n: T[n].clone() for n in ("d_out", "d_ln1_out")}
+    opt.layer_bwd(cfg, lt, i, j, ws)
+    torch.cuda.synchronize()
+    want = {n: T[n].clone() for n in names}
+    want_x = T["d_x"].clone()
+    M, h = shape.M, shape.h
+    products = [("abt", M, h, 4 * h), ("atb", 4 * h, M, h), ("abt", M, 4 * h, h), ("atb", h, M, 4 * h), ("abt", M, h, h), ("atb", h, M, h),
+                ("abt", M, 3 * h, h), ("atb", h, M, 3 * h), ("ab", M, h, 3 * h), ("ab", M, h, h), ("ab", M, h, 4 * h), ("ab", M, 4 * h, h)]
+    one = max(opt.summa_workspace_bytes(*p, q, c, c, opt.BF16) for p in products for c in (0, -1))
+    least = opt.attention_workspace_bytes(shape.b, shape.s, h, shape.n, q) + 2 * ((one + 255) // 256 * 256)
+    assert least < ws.numel() or shape.h != 768
+    for n, t in before.items():
+        T[n].copy_(t)
+    for n in names:
+        if n not in before:
+            block(T[n]).fill_(float("nan"))
+    lt2 = opt.make_layer_tensors({**T, "d_x": T[d_x]})
+    opt.layer_bwd(cfg, lt2, i, j, ws[:least])
+    torch.cuda.synchronize()
+    assert torch.equal(block(T[d_x]), block(want_x))
+    for n in names:
+        assert torch.equal(block(T[n]), block(want[n])), n
