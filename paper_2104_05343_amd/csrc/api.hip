@@ -465,23 +465,26 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
 }
 
 // Whether the second stream pays in a pass that is not captured.  On one stream both products of a linear layer go in one launch
-// (launch_gemm_pair); on two, a fork or the join costs the host 25 us (the wait on another stream's event, for the most part), five of
-// them in a backward pass: the host needs about 200 us for such a pass (165 with q = 1, where no product is split).  Two streams win
-// where the kernels on one take longer than that and the products run beside a long chain: the attention of a device with few
-// matrices is one along the sequence (30 us per 1024 rows fused, 36 with the scores in memory); and from 35 GF of products, where
-// tiles of 256x128 on both are the better use of the chip.  With q = 1 the weight gradients are few long workgroups that the pair's other
-// product fills up: from 200 GF there, below 24 as the kernels' time has it.
+// (launch_gemm_pair) and the combines ride in other launches; on two, a fork or the join costs the host 25 us (the wait on another
+// stream's event, for the most part), five of them in a backward pass: the host needs about 200 us for such a pass (165 with q = 1, where
+// no product is split).  Two streams win where the kernels on one take longer than that and the products run beside a long chain: the
+// attention of a device with few matrices is one along the sequence (30 us per 1024 rows fused, 36 with the scores in memory); and from 80
+// GF of products, where tiles of 256x128 on both are the better use of the chip: not in blocks that the tiles cut, which have no such.
+// With q = 1 the weight gradients are few long workgroups that the pair's other product fills up: from 200 GF there, below 24 as the
+// kernels' time has it.
 // Measured, step of one layer, two streams / one (us): 3 GF, s = 4096 262 / 278; 13 GF, s = 4096 284 / 300, s = 16384 769 / 876; 26 GF, s = 1024
-// 216 / 209, s = 1856 301 / 276, P 237 / 229; 29 GF, s = 512 229 / 216, P 235 / 220; 39 GF, s = 1000 267 / 276; 50 GF, s = 777 284 / 289; 52 GF,
-// s = 512 256 / 250, s = 2048 323 / 352; 75 GF, s = 333 369 / 356, P, s = 1504 439 / 450; 90 GF 406 / 427; 103 GF, s = 512 389 / 461, s = 4096
-// 764 / 781; 226 GF, s = 1000 782 / 728; 412 GF 952 / 973; 824 GF 862 / 902; q = 1, 52 GF, s = 1024 273 / 258, s = 4096 435 / 414, 79 GF 471 / 447,
-// 103 GF 377 / 343, 170 GF 730 / 692, 232 GF 604 / 632.
+// 216 / 193, s = 1856 301 / 262, P 237 / 214; 29 GF, s = 512 229 / 204, P 235 / 208; 50 GF, s = 777 283 / 280; 52 GF, s = 512 256 / 243, s = 2048
+// 325 / 336; 75 GF, s = 333 369 / 347, P, s = 1504 440 / 432; 90 GF 412 / 416; 103 GF, s = 512 390 / 446, s = 4096 761 / 763; 412 GF 950 / 961;
+// 824 GF 824 / 875.  Cut blocks: 39 GF 278 / 272, 86 GF 405 / 374, 75 GF, s = 1500 380 / 384, 157 GF 600 / 598, 226 GF 772 / 702, 302 GF 763 / 719,
+// 403 GF 971 / 878, 929 / 918.  q = 1: 52 GF, s = 1024 262 / 258, s = 4096 414 / 416, 79 GF 450 / 446, 103 GF 378 / 343, 232 GF 616 / 627.
 bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
   const double devices = grid ? (double)c->q * c->q : 1.0;
   const double gf = 48e-9 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
   const double one_us = 120.0 + 0.6 * gf + (c->fused_attention ? 0.030 : 0.036) * c->s;
+  const bool cut = (long long)c->b * c->s / c->q % 64 != 0 || c->h / c->q % 64 != 0;
+  if (cut && !grid) return c->s >= 4096;
   if (c->q == 1) return gf >= 200.0 || c->s > 8192 || (gf < 24.0 && one_us >= 165.0);
-  return gf >= 35.0 || one_us >= 200.0;
+  return gf >= (grid ? 35.0 : 80.0) || one_us >= 200.0;
 }
 // A captured pass pays the host once and keeps both streams (which an earlier pass, short or not, has created).  Replayed,
 // one stream / two: 1024-wide layer, one device of 4 x 4, step 219 / 196 us, fused 200 / 173, 3 GF 155 / 138, 4096-wide
