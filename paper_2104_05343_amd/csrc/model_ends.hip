@@ -90,47 +90,65 @@ __global__ __launch_bounds__(256) void embedding_fwd_kernel(const int* __restric
   }
 }
 
-// ---- embedding backward (owner view): workgroup = EB_ROWS table rows x EB_COLS columns of block (l, j) ----
+// inclusive prefix sums over the lanes, in the vector unit: within rows of 16 lanes, then a row's last lane to the rows behind it
+__device__ __forceinline__ unsigned wave_scan(unsigned v) {
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 to rows 1 and 3
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 to rows 2 and 3
+  return v;
+}
+
+// ---- embedding backward (owner view): workgroup = EB_ROWS table rows x 26OLS columns of block (l, j) ----
 // Token indices are scanned in chunks of 4096; the positions of a chunk that fall into the workgroup's rows are sorted by
 // row, in token order within a row (counting sort: ranks from ballots, prefix sums over wavefronts and rounds).  The
-// sorted list is cut into 16 consecutive parts, one per wavefront; a wavefront adds up a row's run in registers, a batch
-// of rows of dX in flight at a time (a lane covers four adjacent columns), and touches the accumulators in LDS only
+// sorted list is cut into 64 consecutive parts of at least four entries, one for each group of 16 lanes; a group adds up a row's run in
+// registers, a batch of rows of dX in flight at a time (a lane covers four adjacent columns), and touches the accumulators in LDS only
 // where the row changes.  Runs that lie inside one part have the row to themselves in this chunk; a part's first and last
-// run may continue in the neighbours' and are added in wavefront order afterwards.  The order of all additions is a
+// run may continue in the neighbours' and are added in part order afterwards.  The order of all additions is a
 // function of the token order alone, so the result is reproducible bit for bit.
-// Bound: the workgroup that owns the most frequent rows (text: a third of all tokens fall into 32 rows), one CU fetching
-// them.  Unsorted, with a read-modify-write in LDS and the address arithmetic of every lane per token, four wavefronts:
-// 187 us for 4096 tokens, 256 columns, v = 32768 over 4 blocks; now 37 us.
-constexpr int EB_ROWS = 32, EB_COLS = 256, EB_WAVES = 16, EB_CHUNK = 4096, EB_BATCH = 16;
+// Bound: the workgroup that owns the most frequent rows (text: half of all tokens fall into 128 rows), one CU fetching their columns, a
+// 128-byte line of bf16 each; in large tables the fixed chain of a workgroup (scan, sort, one gather), several rounds of them.
+// 128 rows x 64 columns against 32 x 256 in as many workgroups: a third of the bytes and of the list on the busiest CU, four parts a
+// wavefront.  Zipf tokens, bf16, us, before / now: 4096 tokens, 256 columns, v = 32768 over 4 blocks 37.1 / 18.0 (fp32 36.3 / 17.0), all tokens one
+// row 81 / 26, its 16 blocks in one launch 127 / 100; 131072 tokens 1105 / 459; 1024 tokens, 16384 rows of 1024 58 / 45; 64 tokens 11.3 / 6.5.
+constexpr int EB_ROWS = 128, 26OLS = 64, EB_WAVES = 16, 26HUNK = 4096;
+constexpr int EB_LANES = 26OLS / 4, EB_PARTS = EB_WAVES * 64 / EB_LANES;   // lanes that add up one part of the list, and parts
 template <typename T>
 __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int* __restrict__ tokens, const T* __restrict__ dX,
                                                                       float* __restrict__ d_table, EndArgs a) {
-  constexpr int ROUNDS = EB_CHUNK / (64 * EB_WAVES), SLOTS = EB_WAVES * ROUNDS;   // slot = 64 consecutive tokens
-  static_assert(SLOTS == 64 && EB_ROWS == 2 * EB_WAVES, "the prefix sums below: a lane per slot, two rows per wavefront");
-  __shared__ float acc[EB_ROWS * EB_COLS];
-  __shared__ int2 list[EB_CHUNK];                       // (token position, row inside the workgroup's range | grid row << 5)
-  __shared__ int hist[SLOTS][EB_ROWS + 1];              // entries of a slot in a row; then how many lie ahead of them in the row
-  __shared__ int row_total[EB_ROWS];
-  __shared__ float4 edge[EB_WAVES][2][64];              // sums of a part's first and last run
-  __shared__ int edge_row[EB_WAVES][2];
+  constexpr int ROUNDS = 26HUNK / (64 * EB_WAVES), SLOTS = EB_WAVES * ROUNDS;   // slot = 64 consecutive tokens
+  constexpr int RPW = EB_ROWS / EB_WAVES;
+  static_assert(SLOTS == 64 && EB_ROWS == 128 && EB_PARTS == 64, "the prefix sums, the row's bits and the edges below");
+  typedef unsigned long long u64;
+  __shared__ __attribute__((aligned(16))) float acc[EB_ROWS * 26OLS];
+  __shared__ u64 list[26HUNK];                        // row of dX (in the whole tensor) << 7 | row inside the workgroup's range
+  __shared__ unsigned short hist[SLOTS][EB_ROWS + 2];   // entries of a slot in a row; then how many lie ahead of them in the row
+  __shared__ int row_first[EB_ROWS + 1];                // entries of a row; then where it starts in the list
+  __shared__ float4 edge[2 * EB_PARTS][EB_LANES];       // sums of a part's first and last run
+  __shared__ int edge_row[2 * EB_PARTS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = tid / EB_LANES, pl = tid % EB_LANES;
   const int dev = blockIdx.z;
   const int l = a.i0 + dev / a.nj, j = a.j0 + dev % a.nj;
   const int r0 = blockIdx.y * EB_ROWS;                  // first table row (inside block l) of this workgroup
   const int nr = min(EB_ROWS, a.vb - r0);
   typedef T T4 __attribute__((ext_vector_type(4)));
-  const int c0 = blockIdx.x * EB_COLS + 4 * lane;       // first of this lane's four columns inside the block
+  const int c0 = blockIdx.x * 26OLS + 4 * pl;         // first of this lane's four columns inside the block
   const bool vec4 = a.hb % 4 == 0;                      // four columns exist or none does, and they are 8/16-byte aligned
   int col[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) col[k] = c0 + k < a.hb ? c0 + k : (vec4 ? k : 0);
-  for (int k = tid; k < EB_ROWS * EB_COLS; k += 64 * EB_WAVES) acc[k] = 0.f;
+  bool used = false;                                    // some token falls into these rows: acc is in use
   const int lo = l * a.vb + r0, hi = lo + nr;           // token indices that land in this workgroup's rows
   const long long total = (long long)a.q * a.rows;      // all tokens, grid row after grid row (below 2^31: host check)
-  for (long long base = 0; base < total; base += EB_CHUNK) {
+  for (long long base = 0; base < total; base += 26HUNK) {
     int row[ROUNDS], rank[ROUNDS];
-    for (int k = tid; k < SLOTS * (EB_ROWS + 1); k += 64 * EB_WAVES) (&hist[0][0])[k] = 0;
+    int any = 0;
+    for (int k = tid; k < SLOTS * (EB_ROWS + 2) / 2; k += 64 * EB_WAVES) ((unsigned*)&hist[0][0])[k] = 0;
     __syncthreads();                                    // (also: the previous chunk's list has been consumed)
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
@@ -138,84 +156,84 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
       const int tok = t < total ? clamp_token(tokens[t], a.v) : -1;
       const bool hit = tok >= lo && tok < hi;
       row[r] = hit ? tok - lo : -1;
-      unsigned long long same = __builtin_amdgcn_ballot_w64(hit);   // lanes with this lane's row
+      u64 same = __builtin_amdgcn_ballot_w64(hit);      // lanes with this lane's row
       if (same) {
+        any = 1;
 #pragma unroll
-        for (int b = 0; b < 5; ++b) {
-          const unsigned long long one = __builtin_amdgcn_ballot_w64(hit && ((row[r] >> b) & 1));
+        for (int b = 0; b < 7; ++b) {
+          const u64 one = __builtin_amdgcn_ballot_w64(hit && ((row[r] >> b) & 1));
           same &= ((row[r] >> b) & 1) ? one : ~one;
         }
         rank[r] = __builtin_popcountll(same & ((1ull << lane) - 1ull));
-        if (hit && rank[r] == 0) hist[wave * ROUNDS + r][row[r]] = __builtin_popcountll(same);
+        if (hit && rank[r] == 0) hist[wave * ROUNDS + r][row[r]] = (unsigned short)__builtin_popcountll(same);
       }
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int rw = 2 * wave + k, mine = hist[lane][rw];
-      int incl = mine;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-      }
-      hist[lane][rw] = incl - mine;
-      if (lane == 63) row_total[rw] = incl;
+    if (!__syncthreads_or(any)) continue;               // most workgroups of a large table
+    if (!used) {
+      for (int k = tid; k < EB_ROWS * 26OLS / 4; k += 64 * EB_WAVES) ((float4*)acc)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      used = true;
     }
-    __syncthreads();
-    int first = 0, n = 0;                               // lane r < 32: where row r starts in the list
     {
-      const int mine = lane < EB_ROWS ? row_total[lane] : 0;
-      int incl = mine;
+      // two rows to a word: a chunk's entries fit 16 bits
+      unsigned mine[RPW / 2];
+      unsigned* const h = (unsigned*)&hist[lane][RPW * wave];
 #pragma unroll
-      for (int d = 1; d < EB_ROWS; d <<= 1) {
-        const int up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-      }
-      first = incl - mine;
-      n = __builtin_amdgcn_readfirstlane(__shfl(incl, EB_ROWS - 1, 64));
-    }
-    if (n == 0) continue;
+      for (int k = 0; k < RPW / 2; ++k) mine[k] = h[k];
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-      const int start = __shfl(first, row[r] < 0 ? 0 : row[r], 64);
-      if (row[r] >= 0) {
-        const unsigned t = (unsigned)base + (wave * ROUNDS + r) * 64 + lane;
-        list[start + hist[wave * ROUNDS + r][row[r]] + rank[r]] = make_int2((int)t, row[r] | (int)(t / (unsigned)a.rows) << 5);
+      for (int k = 0; k < RPW / 2; ++k) {
+        const unsigned incl = wave_scan(mine[k]);
+        h[k] = incl - mine[k];
+        if (lane == 63) { row_first[RPW * wave + 2 * k] = (int)(incl & 0xffffu); row_first[RPW * wave + 2 * k + 1] = (int)(incl >> 16); }
       }
     }
-    if (tid < 2 * EB_WAVES) (&edge_row[0][0])[tid] = -1;
     __syncthreads();
-    const int q0 = (int)((long long)n * wave / EB_WAVES), q1 = (int)((long long)n * (wave + 1) / EB_WAVES);
+    int n;
+    {                                                   // every wavefront: lane k has rows 2k and 2k + 1
+      const int even = row_first[2 * lane], odd = row_first[2 * lane + 1];
+      const int incl = (int)wave_scan((unsigned)(even + odd));
+      n = __builtin_amdgcn_readlane(incl, 63);
+      __syncthreads();
+      if (wave == 0) { row_first[2 * lane] = incl - odd - even; row_first[2 * lane + 1] = incl - odd; }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+      if (row[r] >= 0) {
+        const unsigned t = (unsigned)base + (wave * ROUNDS + r) * 64 + lane, i = t / (unsigned)a.rows;
+        const u64 src = ((u64)i * a.q + j) * a.rows + (t - i * (unsigned)a.rows);
+        list[row_first[row[r]] + hist[wave * ROUNDS + r][row[r]] + rank[r]] = src << 7 | (unsigned)row[r];
+      }
+    if (tid < 2 * EB_PARTS) edge_row[tid] = -1;
+    __syncthreads();
+    const int len = max(4, (n + EB_PARTS - 1) / EB_PARTS), q0 = min(n, part * len), q1 = min(n, q0 + len);
     // No branch between the loads of a batch, and no arithmetic on them before all are requested: columns past the block
     // are read from its first ones and never stored.
-    auto add_runs = [&](auto vec_) {
+    auto add_runs = [&](auto vec_, auto batch_) {
+      constexpr int BATCH = decltype(batch_)::value;
       float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-      int cur = __builtin_amdgcn_readfirstlane(list[q0].y) & 31;
+      int cur = (int)list[q0] & (EB_ROWS - 1);
       bool head = true;                                 // still in the part's first run
-      for (int m0 = q0; m0 < q1; m0 += EB_BATCH) {
-        T4 x[EB_BATCH];
-        int rw[EB_BATCH];
+      for (int m0 = q0; m0 < q1; m0 += BATCH) {
+        T4 x[BATCH];
+        int rw[BATCH];
 #pragma unroll
-        for (int u = 0; u < EB_BATCH; ++u) {            // past the end: the last entry again, not added
-          const int2 e = list[min(m0 + u, q1 - 1)];
-          const int t = __builtin_amdgcn_readfirstlane(e.x), y = __builtin_amdgcn_readfirstlane(e.y);
-          const int i = y >> 5;
-          rw[u] = y & 31;
-          const T* src = dX + (((long long)i * a.q + j) * a.rows + (t - i * a.rows)) * a.hb;
+        for (int u = 0; u < BATCH; ++u) {               // past the end: the last entry again, not added
+          const u64 e = list[min(m0 + u, q1 - 1)];
+          rw[u] = (int)e & (EB_ROWS - 1);
+          const T* src = dX + (e >> 7) * a.hb;
           if constexpr (decltype(vec_)::value) x[u] = *(const T4*)(src + col[0]);
           else x[u] = T4{src[col[0]], src[col[1]], src[col[2]], src[col[3]]};
         }
 #pragma unroll
-        for (int u = 0; u < EB_BATCH; ++u) {
+        for (int u = 0; u < BATCH; ++u) {
           const bool there = m0 + u < q1;
           if (there && rw[u] != cur) {
             if (head) {
-              edge[wave][0][lane] = sum;
-              if (lane == 0) edge_row[wave][0] = cur;
+              edge[2 * part][pl] = sum;
+              if (pl == 0) edge_row[2 * part] = cur;
               head = false;
             } else {
-              float4* p = (float4*)(acc + cur * EB_COLS) + lane;
+              float4* p = (float4*)(acc + cur * 26OLS) + pl;
               const float4 w = *p;
               *p = make_float4(w.x + sum.x, w.y + sum.y, w.z + sum.z, w.w + sum.w);
             }
@@ -225,29 +243,45 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
           if (there) { sum.x += to_f32(x[u][0]); sum.y += to_f32(x[u][1]); sum.z += to_f32(x[u][2]); sum.w += to_f32(x[u][3]); }
         }
       }
-      edge[wave][1][lane] = sum;
-      if (lane == 0) edge_row[wave][1] = cur;
+      edge[2 * part + 1][pl] = sum;
+      if (pl == 0) edge_row[2 * part + 1] = cur;
     };
+    constexpr std::integral_constant<int, sizeof(T) == 2 ? 16 : 8> long_parts{};   // (fp32: 16 spill)
+    constexpr std::integral_constant<int, 4> short_parts{};
     if (q0 < q1) {
-      if (vec4) add_runs(std::true_type{});
-      else add_runs(std::false_type{});
+      if (!vec4) add_runs(std::false_type{}, short_parts);
+      else if (n <= 4 * EB_PARTS) add_runs(std::true_type{}, short_parts);
+      else add_runs(std::true_type{}, long_parts);
     }
     __syncthreads();
-    for (int w = 0; w < EB_WAVES; ++w) {                // wavefront k takes the rows r with r % 16 == k
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int r = __builtin_amdgcn_readfirstlane(edge_row[w][k]);
-        if (r < 0 || (r & (EB_WAVES - 1)) != wave) continue;
-        float4* p = (float4*)(acc + r * EB_COLS) + lane;
-        const float4 x = *p, y = edge[w][k][lane];
-        *p = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+    for (int h = 0; h < 2; ++h) {                       // in part order; wavefront k takes the rows r with r % 16 == k
+      const int er = edge_row[h * 64 + lane];
+      u64 todo = __builtin_amdgcn_ballot_w64(er >= 0 && (er & (EB_WAVES - 1)) == wave);
+      while (todo) {
+        const int at = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int r = __builtin_amdgcn_readlane(er, at);
+        if (lane < EB_LANES) {
+          float4* p = (float4*)(acc + r * 26OLS) + lane;
+          const float4 x = *p, y = edge[h * 64 + at][lane];
+          *p = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+        }
       }
     }
   }
   __syncthreads();
-  for (int k = tid; k < nr * EB_COLS; k += 64 * EB_WAVES) {
-    const int r = k / EB_COLS, c = blockIdx.x * EB_COLS + k % EB_COLS;
-    if (c < a.hb) d_table[(((long long)l * a.q + j) * a.vb + r0 + r) * a.hb + c] = acc[k];
+  float* const out = d_table + (((long long)l * a.q + j) * a.vb + r0) * a.hb;
+  if (vec4 && ((uintptr_t)out & 15) == 0) {
+    for (int k = tid; k < nr * EB_LANES; k += 64 * EB_WAVES) {
+      const int r = k / EB_LANES, c = blockIdx.x * 26OLS + 4 * (k % EB_LANES);
+      if (c < a.hb) *(float4*)(out + (long long)r * a.hb + c) = used ? ((const float4*)acc)[k] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    return;
+  }
+  for (int k = tid; k < nr * 26OLS; k += 64 * EB_WAVES) {
+    const int r = k / 26OLS, c = blockIdx.x * 26OLS + k % 26OLS;
+    if (c < a.hb) out[(long long)r * a.hb + c] = used ? acc[k] : 0.f;
   }
 }
 
@@ -401,8 +435,8 @@ int launch_embedding_fwd(const int* tokens, const void* table, void* out, const 
 }
 int launch_embedding_bwd(const int* tokens, const void* dX, float* d_table, const EndDesc& d, hipStream_t st) {
   EndArgs a = {d.rows, d.vb, d.hb, d.q, d.v, d.i0, d.ni, d.j0, d.nj};
-  const dim3 grid((d.hb + EB_COLS - 1) / EB_COLS, (d.vb + EB_ROWS - 1) / EB_ROWS, d.ni * d.nj);
-  if (grid.y > 65535 || grid.z > 65535) return OPTIMUS_ESHAPE;
+  const dim3 grid((d.hb + 26OLS - 1) / 26OLS, (d.vb + EB_ROWS - 1) / EB_ROWS, d.ni * d.nj);
+  if ((d.vb + 31) / 32 > 65535 || grid.z > 65535) return OPTIMUS_ESHAPE;   // blocks of at most 2 Mi rows
   if (d.dtype == OPTIMUS_BF16) embedding_bwd_kernel<bf16_t><<<grid, 64 * EB_WAVES, 0, st>>>(tokens, (const bf16_t*)dX, d_table, a);
   else embedding_bwd_kernel<float><<<grid, 64 * EB_WAVES, 0, st>>>(tokens, (const float*)dX, d_table, a);
   return hip_launch_status();

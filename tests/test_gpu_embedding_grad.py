@@ -44,3 +44,26 @@ def test_against_64_bit_sums(q, rows, vb, hb, kind, dtype):
     got = to_host(grid).reshape(q, q, vb, hb).transpose(0, 2, 1, 3).reshape(v, h)
     # at most one fp32 addition per token and three per wavefront and chunk that meet in a row
     assert np.all(np.abs(got - want) <= (M + 96) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("vb,hb", [(128, 64), (129, 65), (127, 132), (300, 4)])
+@pytest.mark.parametrize("M", [63, 256, 257, 2 * 4096 + 3])
+def test_edges_of_a_workgroups_rows_columns_and_parts(vb, hb, M):
+    """128 rows, 64 columns; parts of exactly four entries and of more; a third chunk of three tokens; rows nobody names are zeros."""
+    rng = np.random.default_rng(vb + M)
+    tok = rng.integers(0, vb, M).astype(np.int32)
+    tok[tok == 5] = 6
+    tok[rng.random(M) < 0.3] = vb - 1
+    dX = round_to_bf16(rng.standard_normal((M, hb)).astype(np.float32))
+    out = torch.full((vb * hb + 1,), float("nan"), device="cuda:0")
+    for shift in (0, 1):   # 16-byte aligned rows, and not
+        o = out[shift:shift + vb * hb]
+        opt.embedding_bwd(torch.from_numpy(tok).to("cuda:0"), mat_to_dev(dX, 1, "bf16"), o, M, vb, hb, 1, 0, 0, opt.BF16)
+        torch.cuda.synchronize()
+        want, mag = np.zeros((vb, hb)), np.zeros((vb, hb))
+        np.add.at(want, tok, dX.astype(np.float64))
+        np.add.at(mag, tok, np.abs(dX).astype(np.float64))
+        got = to_host(o).reshape(vb, hb)
+        # at most one fp32 addition per token and two per part and chunk that meet in a row
+        assert np.all(np.abs(got - want) <= (M + 3 * 128) * 2.0 ** -24 * mag)
+        assert not got[5].any()
