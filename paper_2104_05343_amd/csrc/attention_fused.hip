@@ -9,7 +9,7 @@ namespace {
 // K/V bytes per flop and two wavefronts per SIMD, for launches with more workgroups than compute units).
 // TILES_FIRST: a matrix's tiles first instead of all matrices' tiles of a rank first (see fwd_launch).
 template <int D, bool CAUSAL, int NRG, bool TILES_FIRST = false>
-__global__ __launch_bounds__(NRG * 128) void attn_fused_fwd_kernel(FusedArgs a) {
+__global__ __launch_bounds__(NRG * 128, D == 64 ? NRG : NRG / 2) void attn_fused_fwd_kernel(FusedArgs a) {   // two workgroups a CU of width 64
   constexpr int KS = D / 16, DT = D / 32, BQ = NRG * 32;
   __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][PAIR * D];  // [stage][K, V][pair tile]
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
@@ -56,13 +56,12 @@ __global__ __launch_bounds__(NRG * 128) void attn_fused_fwd_kernel(FusedArgs a) 
       const bf16_t* tV = lds[st][1] + par * BLK * D;
       const int kbase = kb * BLK;
       f32x16 sacc[2];
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2) {
-        sacc[t2] = zero16();
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          sacc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tK, t2 * 32, ks, lane), qf[ks], sacc[t2], 0, 0, 0);
-      }
+      sacc[0] = zero16();
+      sacc[1] = zero16();
+      pipelined<2 * KS, D == 64 ? 1 : 2>([&](int n) { return frag_rows<D>(tK, n / KS * 32, n % KS, lane); },
+                          [&](int n, const bf16x8& f) {
+                            sacc[n / KS] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n % KS], sacc[n / KS], 0, 0, 0);
+                          });
       // keys of this block past the row's limit exist only in the last blocks of the loop (wave-uniform test)
       const bool need_mask = CAUSAL ? (kbase + BLK - 1 > q0) : (kbase + BLK > s);
       if (need_mask) {
@@ -114,14 +113,10 @@ __global__ __launch_bounds__(NRG * 128) void attn_fused_fwd_kernel(FusedArgs a) 
         pf[t2][0] = pack_acc<0>(sacc[t2]);
         pf[t2][1] = pack_acc<1>(sacc[t2]);
       }
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tV, t2 * 32 + u * 16, dt * 32, lane),
-                                                               pf[t2][u], oacc[dt], 0, 0, 0);
+      pipelined<4 * DT, D == 64 ? 1 : 2>([&](int n) { return frag_cols_acc_order<D>(tV, n / DT * 16, n % DT * 32, lane); },
+                          [&](int n, const bf16x8& f) {
+                            oacc[n % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pf[n / (2 * DT)][n / DT & 1], oacc[n % DT], 0, 0, 0);
+                          });
     }
     wait_loads_and_barrier();
   }
@@ -196,7 +191,7 @@ __global__ __launch_bounds__(NRG * 128) void attn_fused_bwd_dkv_kernel(FusedArgs
 // of either kind.  rowsum(dO * O) comes from attn_fused_delta_kernel (launched before), so no workgroup waits for
 // another.  Same arithmetic per workgroup as the two separate kernels: same bits.
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void attn_fused_bwd_kernel(FusedArgs a, int ntiles, int nmat) {
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_fused_bwd_kernel(FusedArgs a, int ntiles, int nmat) {
   __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][PAIR * D];
   __shared__ __attribute__((aligned(16))) float ldsL[2][PAIR];
   __shared__ __attribute__((aligned(16))) float ldsD[2][PAIR];

@@ -185,9 +185,31 @@ struct TileLoader {
 };
 
 // all direct loads of this wavefront have landed, then the workgroup meets
+// The builtin: behind a wait in assembly the compiler waited again, inside the loop, for the fragments loaded ahead of it, and with
+// them for the tiles just requested.
 __device__ __forceinline__ void wait_loads_and_barrier() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
+  asm volatile("" ::: "memory");
   __syncthreads();
+}
+
+// N steps of matrix instructions on fragments from LDS, each step's read AHEAD steps before: left to itself the compiler reads a
+// fragment, waits for it and uses it, 64 clk of latency a matrix instruction of 32.  Two ahead (one in the forward of width 64, whose two
+// workgroups a CU allow 128 registers a lane); three and four measured the same, or spilled.  With the wait above, 16 matrices, causal,
+// forward and backward, us, before / now: s = 4096, d = 128 86 / 84 and 312 / 282, d = 64 57 / 52 and 188 / 178; eight of s = 512, d = 64 8.0 / 6.8
+// and 17.7 / 14.6; one of 2048, d = 64 20.9 / 17.0 and 48 / 37; no mask, 16 of 2048, d = 64 27 / 26 and 100 / 88.
+template <int N, int AHEAD, typename READ, typename USE>
+__device__ __forceinline__ void pipelined(READ read, USE use) {
+  decltype(read(0)) f[AHEAD + 1];
+#pragma unroll
+  for (int n = 0; n < AHEAD; ++n) f[n] = read(n);
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    if (n + AHEAD < N) f[(n + AHEAD) % (AHEAD + 1)] = read(n + AHEAD);
+    __builtin_amdgcn_sched_barrier(0);
+    use(n, f[n % (AHEAD + 1)]);
+  }
 }
 
 // ---------------------------------------------------------------- backward, dQ (and rowsum(dO * O))
@@ -262,41 +284,32 @@ __device__ __forceinline__ void bwd_dq_body(const FusedArgs& a, bf16_t (*lds)[2]
       const bf16_t* tK = lds[st][0] + par * BLK * D;
       const bf16_t* tV = lds[st][1] + par * BLK * D;
       const int kbase = kb * BLK;
-      f32x16 sacc[2], pacc[2];
+      const bool need_mask = CAUSAL ? (kbase + BLK - 1 > q0) : (kbase + BLK > s);
+      bf16x8 dsf[2][2];
+      // 32 keys at a time: with the scores of all 64 live, fragments on their way have no registers
 #pragma unroll
       for (int t2 = 0; t2 < 2; ++t2) {
-        sacc[t2] = zero16();
-        pacc[t2] = zero16();
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          sacc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tK, t2 * 32, ks, lane), qf[ks], sacc[t2], 0, 0, 0);
-          pacc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tV, t2 * 32, ks, lane), dof[ks], pacc[t2], 0, 0, 0);
-        }
-      }
-      const bool need_mask = CAUSAL ? (kbase + BLK - 1 > q0) : (kbase + BLK > s);
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
+        f32x16 sacc = zero16(), pacc = zero16();
+        pipelined<2 * KS, 2>([&](int n) { return frag_rows<D>(n & 1 ? tV : tK, t2 * 32, n / 2, lane); },
+                            [&](int n, const bf16x8& f) {
+                              f32x16& acc = n & 1 ? pacc : sacc;
+                              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, n & 1 ? dof[n / 2] : qf[n / 2], acc, 0, 0, 0);
+                            });
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = kbase + t2 * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-          float p = __builtin_amdgcn_exp2f(fmaf(sacc[t2][r], a.scale_log2, -lse2));
+          float p = __builtin_amdgcn_exp2f(fmaf(sacc[r], a.scale_log2, -lse2));
           if (need_mask && key > limit) p = 0.f;
-          sacc[t2][r] = p * (pacc[t2][r] - delta);  // dS^T
+          sacc[r] = p * (pacc[r] - delta);  // dS^T
         }
-      bf16x8 dsf[2][2];
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2) {
-        dsf[t2][0] = pack_acc<0>(sacc[t2]);
-        dsf[t2][1] = pack_acc<1>(sacc[t2]);
+        dsf[t2][0] = pack_acc<0>(sacc);
+        dsf[t2][1] = pack_acc<1>(sacc);
       }
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-            dqacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tK, t2 * 32 + u * 16, dt * 32, lane),
-                                                                dsf[t2][u], dqacc[dt], 0, 0, 0);
+      pipelined<4 * DT, 2>([&](int n) { return frag_cols_acc_order<D>(tK, n / DT * 16, n % DT * 32, lane); },
+                          [&](int n, const bf16x8& f) {
+                            const int dt = n % DT;
+                            dqacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dsf[n / (2 * DT)][n / DT & 1], dqacc[dt], 0, 0, 0);
+                          });
     }
     wait_loads_and_barrier();
   }
@@ -391,12 +404,13 @@ __device__ __forceinline__ void bwd_dkv_body(const FusedArgs& a, bf16_t (*lds)[2
       for (int t2 = 0; t2 < 2; ++t2) {
         sacc[t2] = zero16();
         pacc[t2] = zero16();
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          sacc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tQ, t2 * 32, ks, lane), kf[ks], sacc[t2], 0, 0, 0);
-          pacc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tG, t2 * 32, ks, lane), vf[ks], pacc[t2], 0, 0, 0);
-        }
       }
+      pipelined<4 * KS, 2>([&](int n) { return frag_rows<D>(n & 1 ? tG : tQ, n / (2 * KS) * 32, n / 2 % KS, lane); },
+                          [&](int n, const bf16x8& f) {
+                            const int t2 = n / (2 * KS), ks = n / 2 % KS;
+                            f32x16& acc = n & 1 ? pacc[t2] : sacc[t2];
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, n & 1 ? vf[ks] : kf[ks], acc, 0, 0, 0);
+                          });
       // masked: queries before the key (causal, only in the block on the diagonal) and padding queries
       const bool need_mask = (CAUSAL && qbase < k0 + 31) || (qbase + BLK > s);
       bf16x8 pf[2][2], dsf[2][2];
@@ -423,17 +437,12 @@ __device__ __forceinline__ void bwd_dkv_body(const FusedArgs& a, bf16_t (*lds)[2
         dsf[t2][0] = pack_acc<0>(pacc[t2]);
         dsf[t2][1] = pack_acc<1>(pacc[t2]);
       }
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            dvacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tG, t2 * 32 + u * 16, dt * 32, lane),
-                                                                pf[t2][u], dvacc[dt], 0, 0, 0);
-            dkacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tQ, t2 * 32 + u * 16, dt * 32, lane),
-                                                                dsf[t2][u], dkacc[dt], 0, 0, 0);
-          }
+      pipelined<8 * DT, 2>([&](int n) { return frag_cols_acc_order<D>(n & 1 ? tQ : tG, n / (2 * DT) * 16, n / 2 % DT * 32, lane); },
+                          [&](int n, const bf16x8& f) {
+                            const int dt = n / 2 % DT, t2 = n / (4 * DT), u = n / (2 * DT) & 1;
+                            f32x16& acc = n & 1 ? dkacc[dt] : dvacc[dt];
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, n & 1 ? dsf[t2][u] : pf[t2][u], acc, 0, 0, 0);
+                          });
     }
     wait_loads_and_barrier();
   }

@@ -14,7 +14,7 @@ namespace {
 // The queries' lse and rowsum(dO * O) go through a register and reach LDS at the end of an iteration: stored at its top,
 // the store would wait for its load and for all the tile loads issued before it.
 // Bound: LDS reads (44 KiB per wavefront and 32 x 32 scores, beside 1024 clk of matrix instructions).  Measured, 16
-// matrices, s = 4096, causal: four wavefronts with every fragment in registers, 64 keys per workgroup, 456 us; now 313 us.
+// matrices, s = 4096, causal: four wavefronts with every fragment in registers, 64 keys per workgroup, 456 us; with that 313, and with fragments read ahead of their use 282 for the whole backward.
 template <int D>
 struct WideLds {
   bf16_t block[2][2][BLK * D];   // [stage][Q, dO]
@@ -109,22 +109,28 @@ __device__ __forceinline__ void bwd_dkv_wide_body(const FusedArgs& a, WideLds<D>
       const bf16_t* tQ = lds.block[st][0];
       const bf16_t* tG = lds.block[st][1];
       f32x16 sacc = zero16(), pacc = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tQ, par * 32, ks, lane),
-                                                       ks < KREG ? kf[ks < KREG ? ks : 0] : frag_rows<D>(lds.k, rg * 32, ks, lane), sacc, 0, 0, 0);
-        pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<D>(tG, par * 32, ks, lane), frag_rows<D>(lds.v, rg * 32, ks, lane), pacc, 0, 0, 0);
-      }
+      struct Two { bf16x8 q, own; };
+      pipelined<2 * KS, 2>([&](int n) {
+                            const int ks = n / 2;
+                            Two f;
+                            f.q = frag_rows<D>(n & 1 ? tG : tQ, par * 32, ks, lane);
+                            if (n & 1) f.own = frag_rows<D>(lds.v, rg * 32, ks, lane);
+                            else f.own = ks < KREG ? kf[ks < KREG ? ks : 0] : frag_rows<D>(lds.k, rg * 32, ks, lane);
+                            return f;
+                          },
+                          [&](int n, const Two& f) {
+                            f32x16& acc = n & 1 ? pacc : sacc;
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.q, f.own, acc, 0, 0, 0);
+                          });
       const bool need_mask = (CAUSAL && q0 < k0 + 31) || (q0 + 32 > s);
       dkv_scores<CAUSAL>(sacc, pacc, lds.l[st] + par * 32, lds.d[st] + par * 32, q0, key, s, need_mask, a.scale_log2, g);
       const bf16x8 pf[2] = {pack_acc<0>(sacc), pack_acc<1>(sacc)}, dsf[2] = {pack_acc<0>(pacc), pack_acc<1>(pacc)};
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          dvacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tG, par * 32 + u * 16, dt * 32, lane), pf[u], dvacc[dt], 0, 0, 0);
-          dkacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_acc_order<D>(tQ, par * 32 + u * 16, dt * 32, lane), dsf[u], dkacc[dt], 0, 0, 0);
-        }
+      pipelined<4 * DT, 2>([&](int n) { return frag_cols_acc_order<D>(n & 1 ? tQ : tG, par * 32 + n / (2 * DT) * 16, n / 2 % DT * 32, lane); },
+                          [&](int n, const bf16x8& f) {
+                            const int dt = n / 2 % DT, u = n / (2 * DT);
+                            f32x16& acc = n & 1 ? dkacc[dt] : dvacc[dt];
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, n & 1 ? dsf[u] : pf[u], acc, 0, 0, 0);
+                          });
     }
     if (it + 1 < n_it) store_rows(st ^ 1);
     wait_loads_and_barrier();
