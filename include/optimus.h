@@ -428,7 +428,7 @@ void optimus_debug_set_corun_variants(int chain_v, int branch_v);
 int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, int i, int j, int corun, int have_ws, int* out3);
 /* The plan of the most recent matrix-core product launched by this process: variant | (panel splits << 8) |
  * (1 << 16 if the split is emulated inside each workgroup) | (1 << 17 if 64x64 tiles ran with four stages in LDS) |
- * (1 << 18 if it was the weight gradient of a pair in one launch);
+ * (1 << 18 if it was the weight gradient of a pair in one launch) | (1 << 19 if 128x64 or 128x128 tiles ran with four stages);
  * -1 before the first one.  Host state only, not synchronised between threads. */
 int optimus_debug_last_gemm_plan(void);
 /* The streams an optimus_layer_bwd of this size runs on when it is not captured (a captured one: two, once the library

@@ -447,6 +447,12 @@ def debug_last_gemm_deep() -> bool:
     return p >= 0 and bool(p >> 17 & 1)
 
 
+def debug_last_gemm_deep_wide() -> bool:
+    """Whether that product ran 128x64 or 128x128 tiles with four stages in LDS."""
+    p = lib().optimus_debug_last_gemm_plan()
+    return p >= 0 and bool(p >> 19 & 1)
+
+
 def debug_last_gemm_pair() -> bool:
     """Whether that product shared its launch with another one."""
     p = lib().optimus_debug_last_gemm_plan()

@@ -284,9 +284,14 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
       const int resident = (int)((in_round + ncu - 1) / ncu);             // workgroups on the fullest CU
       const float busy = in_round >= ncu ? 1.0f : (float)in_round / (float)ncu;  // share of the CUs in use
       float t_slab = c.t_lone + (c.t_full - c.t_lone) * busy * busy + c.t_more * (float)(resident - 1);
+      // One workgroup of 128x64 or 128x128 per CU has four stages (launch_gemm_mfma): [2048 x 4096 x 1024] in 128x64 tiles, ring / four stages, A B 33.3 /
+      // 25.1 us, A B^T 36.7 / 25.3; A B^T [2048 x 3072 x 1536] in 128x128 tiles 25 us, in 64x64 28.5.  (Not counted is the gain of 128x128 tiles in the other
+      // forms and of 128x64 in splits: that moves the splits of layers, of the 4096-wide one 836 -> 856 us, of a 1024-wide one 150 -> 158.)
+      const bool deep = !ragged && wgs <= ncu && (pass == 0 || d.corun == 0);
       // the 128x128 tile depends on the operand layouts: both k-contiguous (A B^T) is its slowest form, one of each its fastest
-      if (v == 3) t_slab *= d.a_kcontig && d.b_kcontig ? 1.14f : (d.a_kcontig ? 0.92f : 1.04f);
-      if (v == 6 && d.a_kcontig && d.b_kcontig) t_slab *= 1.18f;
+      if (v == 3) t_slab *= d.a_kcontig && d.b_kcontig ? (deep ? 1.0f : 1.14f) : (d.a_kcontig ? 0.92f : 1.04f);
+      if (v == 6 && deep && sp == 1) t_slab *= 0.7f;
+      else if (v == 6 && d.a_kcontig && d.b_kcontig) t_slab *= 1.18f;
       if (v == 7 && !d.a_kcontig) t_slab *= 1.25f;   // both operands through the transposing LDS reads
       // The form with four stages (at most two workgroups per CU), for long contractions and all layouts alike (by itself, one workgroup
       // per CU: A B 0.74 of the ring's time, A B^T 0.66, A^T B 0.86, nothing at 256 k).  [1024 x 4096 x 256] in four ranges of it against
@@ -482,12 +487,13 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
   const long long nwg = workgroups(ka);
   if (nwg <= 0 || nwg > 0x7fffffffLL) return OPTIMUS_ESHAPE;
   int rc;
-  // 64x64 tiles, at most two workgroups per CU (all that the LDS of the four stages admits): twice the loads in flight (figures:
-  // gemm_mfma_deep.hip).
-  const bool deep = vi == 7 && !plan.ragged && !plan.seq && g_loop == 2 && nwg <= 2LL * num_cus();
-  g_last_plan = plan.variant | (plan.splits << 8) | (plan.seq << 16) | (deep ? 1 << 17 : 0);
+  // 64x64 tiles, at most two workgroups per CU, 128x64 and 128x128 tiles, one (all that the LDS of the four stages admits): twice the
+  // loads in flight (figures: gemm_mfma_deep.hip).  Beside another product the wider tiles keep the ring, which can share a CU.
+  const bool deep = !plan.ragged && !plan.seq && g_loop == 2 &&
+                    (vi == 7 ? nwg <= 2LL * num_cus() : (vi == 6 || vi == 3) && nwg <= num_cus() && d.corun == 0);
+  g_last_plan = plan.variant | (plan.splits << 8) | (plan.seq << 16) | (deep ? 1 << (vi == 7 ? 17 : 19) : 0);
   if (deep) {
-    rc = launch_gemm_mfma_deep(plain_store(ka), d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
+    rc = launch_gemm_mfma_deep(vi, plain_store(ka), d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   } else if (plan.ragged) rc = launch_gemm_mfma_ragged(vi, plan.ragged == 2, d.a_kcontig, d.b_kcontig, ka, (unsigned)nwg, stream);
   else switch (vi) {
     case 0: rc = launch_layout<256, 256, 2, 4>(d, ka, nwg, stream); break;

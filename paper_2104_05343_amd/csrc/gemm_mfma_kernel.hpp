@@ -98,8 +98,8 @@ struct KArgs {
   EpiArgs epi;
 };
 
-// tile variant 7 with four stages of 64 k in LDS (gemm_mfma_deep.hip)
-int launch_gemm_mfma_deep(bool plain, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
+// tile variants 3, 6, 7 with four stages of 64 k in LDS (gemm_mfma_deep.hip)
+int launch_gemm_mfma_deep(int variant, bool plain, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
 // tile variants 3, 6, 7 in their ragged form, 3 also for long panels (gemm_mfma_ragged.hip)
 int launch_gemm_mfma_ragged(int variant, bool long_panels, int a_kcontig, int b_kcontig, const KArgs& ka, unsigned nwg, hipStream_t stream);
 
@@ -393,7 +393,7 @@ struct Occ {
 // LOOP selects the k-loop: 1 = ring of four 32-wide slabs, fragments read one sub-step ahead
 // (the loop described above); 2 = stages of 64 k, the fragments of a whole stage read into registers while the
 // matrix cores work on the registers of the stage before it (see the loop).
-// 3 = the loop of 2 with four stages, for 64x64 tiles in launches of few workgroups (gemm_mfma_deep.hip).
+// 3 = the loop of 2 with four stages, for the smaller tiles in launches of few workgroups (gemm_mfma_deep.hip).
 template <int BM, int BN, int LOOP = 2>
 struct Loop2 {
   // three stages where one workgroup owns the CU anyway (the 384-row tiles: 144 KiB); two stages otherwise, which is the

@@ -105,3 +105,30 @@ def test_partial_tiles_of_a_split(form, variant, Mb, Kp, Nb, q, deep):
     b = dB.view(q, q, Nb, Kp)[j].permute(1, 0, 2).reshape(Nb, K).t() if form == "abt" else dB.view(q, q, Kp, Nb)[:, j].reshape(K, Nb)
     want = a.float().cpu().double() @ b.float().cpu().double()
     assert rel_frobenius(got[i, j].float().cpu().numpy(), want.numpy()) <= TOL
+
+
+@pytest.mark.parametrize("tile,rows,cols", [(6, 128, 64), (3, 128, 128)])
+@pytest.mark.parametrize("form", ["ab", "abt", "atb"])
+@pytest.mark.parametrize("q,K", [(1, 64), (1, 192), (1, 256), (1, 320), (2, 640)])
+def test_wider_tiles(tile, rows, cols, form, q, K):
+    """One workgroup of 128x64 or 128x128 per CU: stages filled partly, exactly and several times over; one tile too many takes the ring."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for n, deep in ((3, True), (cus // (q * q), True), (cus + 1, False)):
+        M, N = rows * q, cols * n * q
+        A, B = gemm_inputs(K + n, form, M, K, N, "bf16", "n1", "n1")
+        dA, dB = mat_to_dev(A, q, "bf16"), mat_to_dev(B, q, "bf16")
+        out = []
+        try:
+            for variant in (tile, RING + tile):
+                opt.binding.debug_set_gemm_variant(variant)
+                c = empty(M * N, "bf16")
+                opt.summa(form, dA, dB, c, M, K, N, q, -1, -1, opt.BF16)
+                got, splits, walked = opt.binding.debug_last_gemm_plan()
+                assert got == tile
+                assert opt.binding.debug_last_gemm_deep_wide() == (deep and variant == tile and not walked)
+                torch.cuda.synchronize()
+                out.append(c)
+        finally:
+            opt.binding.debug_set_gemm_variant(-1)
+        assert _same_bits(*out)
+        assert rel_frobenius(mat_to_host(out[0], M, N, q), summa.product(form, A, B)) <= TOL
