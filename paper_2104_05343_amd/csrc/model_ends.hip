@@ -101,7 +101,7 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
   return v;
 }
 
-// ---- embedding backward (owner view): workgroup = EB_ROWS table rows x 26OLS columns of block (l, j) ----
+// ---- embedding backward (owner view): workgroup = EB_ROWS table rows x EB_COLS columns of block (l, j) ----
 // Token indices are scanned in chunks of 4096; the positions of a chunk that fall into the workgroup's rows are sorted by
 // row, in token order within a row (counting sort: ranks from ballots, prefix sums over wavefronts and rounds).  The
 // sorted list is cut into 64 consecutive parts of at least four entries, one for each group of 16 lanes; a group adds up a row's run in
@@ -114,17 +114,17 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
 // 128 rows x 64 columns against 32 x 256 in as many workgroups: a third of the bytes and of the list on the busiest CU, four parts a
 // wavefront.  Zipf tokens, bf16, us, before / now: 4096 tokens, 256 columns, v = 32768 over 4 blocks 37.1 / 18.0 (fp32 36.3 / 17.0), all tokens one
 // row 81 / 26, its 16 blocks in one launch 127 / 100; 131072 tokens 1105 / 459; 1024 tokens, 16384 rows of 1024 58 / 45; 64 tokens 11.3 / 6.5.
-constexpr int EB_ROWS = 128, 26OLS = 64, EB_WAVES = 16, 26HUNK = 4096;
-constexpr int EB_LANES = 26OLS / 4, EB_PARTS = EB_WAVES * 64 / EB_LANES;   // lanes that add up one part of the list, and parts
+constexpr int EB_ROWS = 128, EB_COLS = 64, EB_WAVES = 16, EB_CHUNK = 4096;
+constexpr int EB_LANES = EB_COLS / 4, EB_PARTS = EB_WAVES * 64 / EB_LANES;   // lanes that add up one part of the list, and parts
 template <typename T>
 __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int* __restrict__ tokens, const T* __restrict__ dX,
                                                                       float* __restrict__ d_table, EndArgs a) {
-  constexpr int ROUNDS = 26HUNK / (64 * EB_WAVES), SLOTS = EB_WAVES * ROUNDS;   // slot = 64 consecutive tokens
+  constexpr int ROUNDS = EB_CHUNK / (64 * EB_WAVES), SLOTS = EB_WAVES * ROUNDS;   // slot = 64 consecutive tokens
   constexpr int RPW = EB_ROWS / EB_WAVES;
   static_assert(SLOTS == 64 && EB_ROWS == 128 && EB_PARTS == 64, "the prefix sums, the row's bits and the edges below");
   typedef unsigned long long u64;
-  __shared__ __attribute__((aligned(16))) float acc[EB_ROWS * 26OLS];
-  __shared__ u64 list[26HUNK];                        // row of dX (in the whole tensor) << 7 | row inside the workgroup's range
+  __shared__ __attribute__((aligned(16))) float acc[EB_ROWS * EB_COLS];
+  __shared__ u64 list[EB_CHUNK];                        // row of dX (in the whole tensor) << 7 | row inside the workgroup's range
   __shared__ unsigned short hist[SLOTS][EB_ROWS + 2];   // entries of a slot in a row; then how many lie ahead of them in the row
   __shared__ int row_first[EB_ROWS + 1];                // entries of a row; then where it starts in the list
   __shared__ float4 edge[2 * EB_PARTS][EB_LANES];       // sums of a part's first and last run
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
   const int r0 = blockIdx.y * EB_ROWS;                  // first table row (inside block l) of this workgroup
   const int nr = min(EB_ROWS, a.vb - r0);
   typedef T T4 __attribute__((ext_vector_type(4)));
-  const int c0 = blockIdx.x * 26OLS + 4 * pl;         // first of this lane's four columns inside the block
+  const int c0 = blockIdx.x * EB_COLS + 4 * pl;         // first of this lane's four columns inside the block
   const bool vec4 = a.hb % 4 == 0;                      // four columns exist or none does, and they are 8/16-byte aligned
   int col[4];
 #pragma unroll
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
   bool used = false;                                    // some token falls into these rows: acc is in use
   const int lo = l * a.vb + r0, hi = lo + nr;           // token indices that land in this workgroup's rows
   const long long total = (long long)a.q * a.rows;      // all tokens, grid row after grid row (below 2^31: host check)
-  for (long long base = 0; base < total; base += 26HUNK) {
+  for (long long base = 0; base < total; base += EB_CHUNK) {
     int row[ROUNDS], rank[ROUNDS];
     int any = 0;
     for (int k = tid; k < SLOTS * (EB_ROWS + 2) / 2; k += 64 * EB_WAVES) ((unsigned*)&hist[0][0])[k] = 0;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
     }
     if (!__syncthreads_or(any)) continue;               // most workgroups of a large table
     if (!used) {
-      for (int k = tid; k < EB_ROWS * 26OLS / 4; k += 64 * EB_WAVES) ((float4*)acc)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int k = tid; k < EB_ROWS * EB_COLS / 4; k += 64 * EB_WAVES) ((float4*)acc)[k] = make_float4(0.f, 0.f, 0.f, 0.f);
       used = true;
     }
     {
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
               if (pl == 0) edge_row[2 * part] = cur;
               head = false;
             } else {
-              float4* p = (float4*)(acc + cur * 26OLS) + pl;
+              float4* p = (float4*)(acc + cur * EB_COLS) + pl;
               const float4 w = *p;
               *p = make_float4(w.x + sum.x, w.y + sum.y, w.z + sum.z, w.w + sum.w);
             }
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
         todo &= todo - 1;
         const int r = __builtin_amdgcn_readlane(er, at);
         if (lane < EB_LANES) {
-          float4* p = (float4*)(acc + r * 26OLS) + lane;
+          float4* p = (float4*)(acc + r * EB_COLS) + lane;
           const float4 x = *p, y = edge[h * 64 + at][lane];
           *p = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
         }
@@ -274,13 +274,13 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
   float* const out = d_table + (((long long)l * a.q + j) * a.vb + r0) * a.hb;
   if (vec4 && ((uintptr_t)out & 15) == 0) {
     for (int k = tid; k < nr * EB_LANES; k += 64 * EB_WAVES) {
-      const int r = k / EB_LANES, c = blockIdx.x * 26OLS + 4 * (k % EB_LANES);
+      const int r = k / EB_LANES, c = blockIdx.x * EB_COLS + 4 * (k % EB_LANES);
       if (c < a.hb) *(float4*)(out + (long long)r * a.hb + c) = used ? ((const float4*)acc)[k] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     return;
   }
-  for (int k = tid; k < nr * 26OLS; k += 64 * EB_WAVES) {
-    const int r = k / 26OLS, c = blockIdx.x * 26OLS + k % 26OLS;
+  for (int k = tid; k < nr * EB_COLS; k += 64 * EB_WAVES) {
+    const int r = k / EB_COLS, c = blockIdx.x * EB_COLS + k % EB_COLS;
     if (c < a.hb) out[(long long)r * a.hb + c] = used ? acc[k] : 0.f;
   }
 }
@@ -435,7 +435,7 @@ int launch_embedding_fwd(const int* tokens, const void* table, void* out, const 
 }
 int launch_embedding_bwd(const int* tokens, const void* dX, float* d_table, const EndDesc& d, hipStream_t st) {
   EndArgs a = {d.rows, d.vb, d.hb, d.q, d.v, d.i0, d.ni, d.j0, d.nj};
-  const dim3 grid((d.hb + 26OLS - 1) / 26OLS, (d.vb + EB_ROWS - 1) / EB_ROWS, d.ni * d.nj);
+  const dim3 grid((d.hb + EB_COLS - 1) / EB_COLS, (d.vb + EB_ROWS - 1) / EB_ROWS, d.ni * d.nj);
   if ((d.vb + 31) / 32 > 65535 || grid.z > 65535) return OPTIMUS_ESHAPE;   // blocks of at most 2 Mi rows
   if (d.dtype == OPTIMUS_BF16) embedding_bwd_kernel<bf16_t><<<grid, 64 * EB_WAVES, 0, st>>>(tokens, (const bf16_t*)dX, d_table, a);
   else embedding_bwd_kernel<float><<<grid, 64 * EB_WAVES, 0, st>>>(tokens, (const float*)dX, d_table, a);
