@@ -252,7 +252,13 @@ int optimus_attention_fused_bwd_static(const void* qkv, const void* attn, const 
  * In grid mode (i = j = -1) each stage runs for all q*q devices before the
  * next starts, filling every block of every tensor.  With explicit (i, j) only
  * that device's blocks are recomputed; peers' blocks of the previous stage must
- * be resident (left by a grid-mode call on the same tensors). */
+ * be resident (left by a grid-mode call on the same tensors).
+ * Shared memory in the backward pass.  A matrix that it writes may lie where another one lies that is not needed
+ * any more, in this order: d_pre_gelu; d_w2, d_b2; d_ln2_out; d_w1, d_b1; d_ln2_g, d_ln2_b, d_h_mid (from d_ln2_out, xhat2, d_out); d_attn;
+ * d_w_o, d_b_o; d_qkv; d_ln1_out; d_w_qkv, d_b_qkv; d_ln1_g, d_ln1_b, d_x (from d_ln1_out, xhat1, d_h_mid).  In place, element for
+ * element: d_pre_gelu of pre_gelu, d_h_mid of d_out or d_ln2_out, d_x of d_h_mid or d_ln1_out.  Where the faster schedules would
+ * still read what is overwritten, the pass keeps to that order on `stream`, with the same bits.  Statistics and vector gradients share
+ * memory with nothing.  (What has been overwritten is of course no peer's block for a later call on one device.) */
 typedef struct {
   int b, s, h, n, q;
   float eps;

@@ -495,6 +495,34 @@ bool captured(hipStream_t caller) {
   return cs != hipStreamCaptureStatusNone;
 }
 
+// Whether two matrices of a backward pass share memory in a way that its schedule does not bear.  Steps of the pass, as both schedules keep
+// them: 0 d_pre_gelu, d_w2; 1 d_ln2_out, d_w1; 2 LayerNorm 2; 3 d_attn, d_w_o; 4 attention; 5 d_ln1_out, d_w_qkv; 6 LayerNorm 1.  A matrix
+// is written in step `first` (-1: before the pass) and read for the last time in `one` (one stream: products in pairs, column sums at the end)
+// or in `two` (what the branch reads, it may read until the join, 7).  One stream bears d_x anywhere: optimus_layer_bwd looks for that itself.
+bool sharing_breaks(const optimus_layer_cfg* c, const optimus_layer_tensors* t, bool two, bool ln2_sums_on_branch) {
+  struct Use { const void* p; int64_t bytes; int first, one, two; };
+  const int64_t act = (int64_t)c->b * c->s * c->h * 2, w = (int64_t)c->h * c->h * 2;
+  const int64_t heads = (int64_t)c->b * c->n;
+  const int ln2 = ln2_sums_on_branch ? 7 : 2;
+  const int pre = t->pre_gelu == t->d_pre_gelu ? -1 : 0;   // in place: each element is read by the thread that overwrites it
+  const Use use[] = {
+      {t->d_out, act, -1, 6, 7}, {t->w2, 4 * w, -1, 0, 0}, {t->pre_gelu, 4 * act, -1, pre, pre}, {t->gelu, 4 * act, -1, 0, 7},
+      {t->w1, 4 * w, -1, 1, 1}, {t->ln2_out, act, -1, 1, 7}, {t->xhat2, act, -1, 6, ln2}, {t->w_o, w, -1, 3, 3}, {t->attn, act, -1, 4, 7},
+      {t->qkv, 3 * act, -1, 4, 4}, {t->w_qkv, 3 * w, -1, 5, 5}, {t->ln1_out, act, -1, 5, 7}, {t->xhat1, act, -1, 6, 6},
+      c->fused_attention ? Use{t->lse, heads * c->s * 4, -1, 4, 4} : Use{t->probs, heads * c->s * c->s * 2, -1, 4, 4},
+      {t->d_pre_gelu, 4 * act, 0, 6, 7}, {t->d_w2, 8 * w, 0, 0, 0}, {t->d_ln2_out, act, 1, 6, ln2}, {t->d_w1, 8 * w, 1, 1, 1},
+      {t->d_h_mid, act, 2, 6, 7}, {t->d_attn, act, 3, 4, 4}, {t->d_w_o, 2 * w, 3, 3, 3}, {t->d_qkv, 3 * act, 4, 6, 7},
+      {t->d_ln1_out, act, 5, 6, 6}, {t->d_w_qkv, 6 * w, 5, 5, 5}, {t->d_x, act, 6, 6, 6}};
+  for (const Use& a : use) {
+    if (a.first < 0 || (a.first == 6 && !two)) continue;
+    for (const Use& b : use)
+      if (b.first < a.first && (two ? b.two : b.one) >= a.first && (const char*)a.p < (const char*)b.p + b.bytes &&
+          (const char*)b.p < (const char*)a.p + a.bytes)
+        return true;
+  }
+  return false;
+}
+
 // Device address of `scratch` on the current device (each GPU holds its own copy at its own address): looked up on
 // the first call made with that device current, kept afterwards.
 std::mutex g_scratch_mutex;
@@ -933,15 +961,20 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   // gradient branch: its own stream and its own split workspace (see SideStream)
   SideStream* ss = side_stream(st);   // asked for in any case: a later call may be captured, and then it has to be there
   if (ss && !two_streams_pay(c, grid) && !captured(st)) ss = nullptr;
+  // LayerNorm 2's parameter gradients need d_ln2_out only.  Small blocks: the chain is a string of short kernels and
+  // the column sums are one more serial step of it, so they go to the branch (measured: the step 5 % shorter at
+  // [1024 x 256] blocks).  Large blocks: the branch, with its transposing products, is the longer stream already.
+  const bool narrow = colsum_narrow((int)(M / q), (int)(h / q));
+  // Matrices that share memory: one stream where the branch could still read what the chain overwrites; and step after step in the order
+  // of the header where a pair of products or a column sum at the end could.
+  if (ss && sharing_breaks(c, t, true, narrow)) ss = nullptr;
+  const bool in_order = !ss && sharing_breaks(c, t, false, false);
   const int co_chain = ss ? 1 : 0, co_branch = ss ? 2 : 0;   // products planned for company only where they have it
   hipStream_t gst = ss ? ss->s : st;
   void* gstream = (void*)gst;
   void* grad_ws = ss ? (char*)gemm_ws + gemm_bytes : gemm_ws;
-  // LayerNorm 2's parameter gradients need d_ln2_out only.  Small blocks: the chain is a string of short kernels and
-  // the column sums are one more serial step of it, so they go to the branch (measured: the step 5 % shorter at
-  // [1024 x 256] blocks).  Large blocks: the branch, with its transposing products, is the longer stream already.
-  const bool ln2_grads_on_branch = ss && colsum_narrow((int)(M / q), (int)(h / q));
-  const bool sums_at_end = !ss || ln2_grads_on_branch;   // small blocks: the column sums are launches, not bytes
+  const bool ln2_grads_on_branch = ss && narrow;
+  const bool sums_at_end = ss ? narrow : !in_order;   // small blocks: the column sums are launches, not bytes
   optimus_epilogue e = {};
   optimus_epilogue e32 = {};
   e32.out_fp32 = 1;
@@ -960,7 +993,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   CombineJob in_job = {};
   CombineJobs w_jobs = {};
   size_t w_at[4], w_total = 0;
-  if (!ss) layer_weight_ws(c, i, j, w_at, &w_total);
+  if (!ss && !in_order) layer_weight_ws(c, i, j, w_at, &w_total);
   const size_t branch_bytes = w_total > gemm_bytes ? w_total : gemm_bytes;
   const bool keep = w_total > 0 && ws_bytes >= layer_attn_ws(c, a) + gemm_bytes + branch_bytes;
   if (keep) {
@@ -970,7 +1003,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
   const auto linear = [&](int nth, const void* d_y, const void* w, const void* in, void* d_in, float* d_w, int64_t k, int64_t n,
                           const void* gelu_grad_of) {
     const LinearGrads g = {d_y, w, in, d_in, d_w, M, k * h, n * h, gelu_grad_of};
-    if (!ss) {
+    if (!ss && !in_order) {
       char* const branch = (char*)gemm_ws + gemm_bytes;
       const size_t bytes = !keep ? gemm_bytes : nth < 3 ? w_at[nth + 1] - w_at[nth] : w_total - w_at[nth];
       int r = run_linear_grads(g, q, i, j, gemm_ws, gemm_bytes, branch + (keep ? w_at[nth] : 0), bytes, &in_job, &w_jobs, st);
@@ -999,17 +1032,21 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
       const int r = launch_gemm_combines(now, st);
       if (r) return r;
     }
+    if (in_order) {   // the sums first: d_in may take d_y's place
+      const int r = launch_ln_param_grads(d_y, xhat, d_g, d_b, ln, st);
+      return r ? r : ln_backward(d_y, xhat, rstd, gamma, d_res, d_in, nullptr, nullptr, stats, ln, grid, st);
+    }
     return ln_backward(d_y, xhat, rstd, gamma, d_res, d_in, d_g, d_b, stats, ln, grid, st);
   };
   RUN(linear(0, t->d_out, t->w2, t->gelu, t->d_pre_gelu, t->d_w2, 4, 1, t->pre_gelu));   // d_pre = (d_out W2^T) * GeLU'(pre)
-  if (ss) RUN(optimus_bias_grad(t->d_out, t->d_b2, M, h, q, i, j, dt, gstream));
+  if (ss || in_order) RUN(optimus_bias_grad(t->d_out, t->d_b2, M, h, q, i, j, dt, gstream));
   // ---- pre = ln2_out W1 + b1 ----
   BRANCH_AFTER_MAIN(ss->ready[0]);  // d_pre_gelu is complete
   RUN(linear(1, t->d_pre_gelu, t->w1, t->ln2_out, t->d_ln2_out, t->d_w1, 1, 4, nullptr));
   if (!sums_at_end) RUN(optimus_bias_grad(t->d_pre_gelu, t->d_b1, M, 4 * h, q, i, j, dt, gstream));
   // ---- LN2 backward, plus the residual branch: d_h_mid = d_out + LN2'(d_ln2_out) ----
-  RUN(norm_bwd(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_g,
-               ln2_grads_on_branch || !ss ? nullptr : t->d_ln2_b, t->bstats2));
+  RUN(norm_bwd(t->d_ln2_out, t->xhat2, t->rstd2, t->ln2_g, t->d_out, t->d_h_mid, sums_at_end ? nullptr : t->d_ln2_g,
+               sums_at_end ? nullptr : t->d_ln2_b, t->bstats2));
   // ---- h_mid = x + attn Wo + bo ----
   BRANCH_AFTER_MAIN(ss->ready[1]);  // d_h_mid is complete
   RUN(linear(2, t->d_h_mid, t->w_o, t->attn, t->d_attn, t->d_w_o, 1, 1, nullptr));
@@ -1026,7 +1063,7 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
     const char *x0 = (const char*)t->d_x, *p0 = (const char*)p;
     return x0 < p0 + M * k * h * 2 && p0 < x0 + M * h * 2;
   };
-  const bool norm_last = ss || takes(t->d_pre_gelu, 4) || takes(t->d_qkv, 3) || takes(t->d_ln2_out, 1) || takes(t->xhat2, 1) ||
+  const bool norm_last = ss || in_order || takes(t->d_pre_gelu, 4) || takes(t->d_qkv, 3) || takes(t->d_ln2_out, 1) || takes(t->xhat2, 1) ||
                          takes(t->d_h_mid, 1) || takes(t->d_ln1_out, 1) || takes(t->xhat1, 1) || takes(t->d_out, 1);
   if (norm_last && in_job.partials) {
     CombineJobs now = {};
@@ -1035,8 +1072,8 @@ int optimus_layer_bwd(const optimus_layer_cfg* c, const optimus_layer_tensors* t
     RUN(launch_gemm_combines(now, st));
   }
   const auto norm1 = [&]() {
-    return norm_bwd(t->d_ln1_out, t->xhat1, t->rstd1, t->ln1_g, t->d_h_mid, t->d_x, ss ? t->d_ln1_g : nullptr, ss ? t->d_ln1_b : nullptr,
-                    t->bstats1);
+    return norm_bwd(t->d_ln1_out, t->xhat1, t->rstd1, t->ln1_g, t->d_h_mid, t->d_x, ss || in_order ? t->d_ln1_g : nullptr,
+                    ss || in_order ? t->d_ln1_b : nullptr, t->bstats1);
   };
   if (!norm_last) RUN(norm1());
   if (sums_at_end) {   // column sums, and the combines kept so far, in one launch; the sources are still there; on a branch without the two that
