@@ -284,13 +284,15 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
       const int resident = (int)((in_round + ncu - 1) / ncu);             // workgroups on the fullest CU
       const float busy = in_round >= ncu ? 1.0f : (float)in_round / (float)ncu;  // share of the CUs in use
       float t_slab = c.t_lone + (c.t_full - c.t_lone) * busy * busy + c.t_more * (float)(resident - 1);
-      // One workgroup of 128x64 or 128x128 per CU has four stages (launch_gemm_mfma): [2048 x 4096 x 1024] in 128x64 tiles, ring / four stages, A B 33.3 /
-      // 25.1 us, A B^T 36.7 / 25.3; A B^T [2048 x 3072 x 1536] in 128x128 tiles 25 us, in 64x64 28.5.  (Not counted is the gain of 128x128 tiles in the other
-      // forms and of 128x64 in splits: that moves the splits of layers, of the 4096-wide one 836 -> 856 us, of a 1024-wide one 150 -> 158.)
+      // One workgroup of 128x64 or 128x128 per CU has four stages (launch_gemm_mfma).  128x64 tiles, ring / four stages, us: [2048 x 4096 x 1024] A B 33.6 /
+      // 25.5, A B^T 37.4 / 25.8, A^T B 28.2 / 26.3, [768 x 8192 x 2304] 60 / 44, 68 / 45, 50 / 46; 128x128: 42.4 / 40.3, 49.9 / 41.4, 43.5 / 40.9.  Contractions of more
+      // than 6144 that can be split are better off so: operands from memory, split / one range of 128x64, A B^T [3072 x 8192 x 512] 43 / 54, A^T B [384 x
+      // 8192 x 4096] 43 / 65, A B^T [2048 x 6144 x 1024] 41 / 34.  Not counted: 128x128 tiles' gain where it is under 10 % (A B, A^T B), and 128x64 in splits, which
+      // hardly occur in one workgroup per CU.  The split is the one of the product by itself; in company the launch has the ring.
       const bool deep = !ragged && wgs <= ncu && (pass == 0 || d.corun == 0);
       // the 128x128 tile depends on the operand layouts: both k-contiguous (A B^T) is its slowest form, one of each its fastest
       if (v == 3) t_slab *= d.a_kcontig && d.b_kcontig ? (deep ? 1.0f : 1.14f) : (d.a_kcontig ? 0.92f : 1.04f);
-      if (v == 6 && deep && sp == 1) t_slab *= 0.7f;
+      if (v == 6 && deep && sp == 1 && (!d.a_kcontig || !splittable || slabs <= 192)) t_slab *= d.a_kcontig ? 0.7f : 0.9f;
       else if (v == 6 && d.a_kcontig && d.b_kcontig) t_slab *= 1.18f;
       if (v == 7 && !d.a_kcontig) t_slab *= 1.25f;   // both operands through the transposing LDS reads
       // The form with four stages (at most two workgroups per CU), for long contractions and all layouts alike (by itself, one workgroup

@@ -68,6 +68,16 @@ def test_few_tiles_of_panels_over_a_gib(form, M, K, N):
     assert plan(form, M, K, N, 1, 0, 0)[0] == 5
 
 
+# Long contractions in several panels, outputs of about one 128x64 tile per CU: split, where one workgroup would walk 256 slabs; up to 6144 not.
+@pytest.mark.parametrize("split,form,Mb,K,Nb,q", [(True, "atb", 384, 8192, 4096, 2), (True, "atb", 768, 8192, 2048, 4), (True, "atb", 512, 8192, 4096, 8),
+                                                  (True, "abt", 3072, 8192, 512, 4), (True, "abt", 384, 8192, 4096, 2), (True, "ab", 512, 8192, 4096, 8),
+                                                  (False, "abt", 2048, 6144, 1024, 4), (False, "ab", 768, 4096, 2048, 8), (False, "atb", 512, 4096, 3072, 2)])
+def test_split_of_long_contractions(split, form, Mb, K, Nb, q):
+    variant, splits, _ = plan(form, Mb * q, K, Nb * q, q, 0, 0)
+    assert (splits > 1) == split
+    assert split or variant == 6
+
+
 def test_no_split_without_panels_and_errors():
     # q = 1: one panel, nothing to split
     assert plan("ab", 2048, 4096, 1024, 1, 0, 0)[1] == 1
