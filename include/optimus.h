@@ -432,6 +432,9 @@ void optimus_debug_set_corun_variants(int chain_v, int branch_v);
  * grid mode, not on corun.  OPTIMUS_EDTYPE when the matrix-core tiles do not take the shape (rows of A or B not
  * multiples of 8 elements, panels beyond the 2 GiB a buffer load reaches, shapes the any-shape kernel runs faster). */
 int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, int i, int j, int corun, int have_ws, int* out3);
+/* Whether the input's and the weight's gradient of a linear layer y = x W, x [M x K], W [K x N], would share a launch in an
+ * optimus_layer_bwd on one stream (host arithmetic only; -1 for invalid arguments). */
+int optimus_debug_plan_pair(int64_t M, int64_t K, int64_t N, int q, int i, int j);
 /* The plan of the most recent matrix-core product launched by this process: variant | (panel splits << 8) |
  * (1 << 16 if the split is emulated inside each workgroup) | (1 << 17 if 64x64 tiles ran with four stages in LDS) |
  * (1 << 18 if it was the weight gradient of a pair in one launch) | (1 << 19 if 128x64 or 128x128 tiles ran with four stages);

@@ -127,6 +127,7 @@ SIGNATURES = {
     "optimus_debug_last_gemm_plan": (_INT, []),
     "optimus_debug_layer_bwd_streams": (_INT, [C.POINTER(LayerCfg), _INT, _INT]),
     "optimus_debug_plan_summa": (_INT, [_INT, _I64, _I64, _I64, _INT, _INT, _INT, _INT, _INT, C.POINTER(C.c_int)]),
+    "optimus_debug_plan_pair": (_INT, [_I64, _I64, _I64, _INT, _INT, _INT]),
     "optimus_debug_mfma_rate": (_INT, [_P, _INT, _INT, _INT, _P]),
 }
 
@@ -433,6 +434,14 @@ def debug_plan_summa(form, M, K, N, q, i, j, corun=0, have_ws=True):
     f = FORMS[form] if isinstance(form, str) else form
     _check(lib().optimus_debug_plan_summa(f, M, K, N, q, i, j, corun, 1 if have_ws else 0, out), "optimus_debug_plan_summa")
     return out[0], out[1], out[2]
+
+
+def debug_plan_pair(M, K, N, q, i, j) -> bool:
+    """Whether a layer's backward pass on one stream would launch both gradients of y = x W, x [M x K], W [K x N], together."""
+    r = lib().optimus_debug_plan_pair(M, K, N, q, i, j)
+    if r < 0:
+        raise OptimusError(ESHAPE, "optimus_debug_plan_pair")
+    return bool(r)
 
 
 def debug_last_gemm_plan():

@@ -1134,6 +1134,17 @@ int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, i
   d.corun = corun;
   return gemm_plan_of(d, have_ws != 0, out3) ? OPTIMUS_OK : OPTIMUS_EDTYPE;
 }
+int optimus_debug_plan_pair(int64_t M, int64_t K, int64_t N, int q, int i, int j) {
+  if (check_mkn(M, K, N, q) || check_coords(q, i, j)) return -1;
+  void* const fake = (void*)(uintptr_t)4096;
+  optimus_epilogue ey = {};
+  ey.out_fp32 = 1;
+  GemmDesc x = summa_desc(OPTIMUS_FORM_ABT, fake, fake, fake, M, N, K, q, i, j, OPTIMUS_BF16, nullptr);
+  GemmDesc y = summa_desc(OPTIMUS_FORM_ATB, fake, fake, fake, K, M, N, q, i, j, OPTIMUS_BF16, &ey);
+  x.partials = y.partials = (float*)fake;
+  x.partials_bytes = y.partials_bytes = SIZE_MAX;
+  return gemm_pair_planned(x, y) ? 1 : 0;
+}
 int optimus_debug_last_gemm_plan(void) { return gemm_last_plan(); }
 int optimus_debug_layer_bwd_streams(const optimus_layer_cfg* c, int i, int j) {
   AttnDims a;

@@ -99,8 +99,9 @@ int launch_gemm(const GemmDesc& d, hipStream_t stream);           // picks one o
 int launch_gemm_generic(const GemmDesc& d, hipStream_t stream);    // fp32, or any bf16 shape, stride and alignment
 int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream);       // bf16 rows on the 16-byte grid: direct-to-LDS tiles
 // A B^T (x) and A^T B (y) in one launch, y not reading what x writes; the combines that their panel splits want are added to
-// *combines.  False if the two do not go together: nothing is launched then.  *rc: status of the launch.
+// *combines.  False if the two do not go together, or are faster one by one: nothing is launched then.  *rc: status of the launch.
 bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combines, hipStream_t stream, int* rc);
+bool gemm_pair_planned(const GemmDesc& x, const GemmDesc& y);       // whether it would launch them
 int launch_gemm_combines(const CombineJobs& jobs, hipStream_t stream);
 bool gemm_mfma_supported(const GemmDesc& d);
 int launch_mfma_rate(float* out, int workgroups, int iters, int random_data, hipStream_t stream);   // probe.hip

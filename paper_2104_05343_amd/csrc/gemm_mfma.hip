@@ -202,6 +202,7 @@ struct Plan {
   int splits;
   int ragged;  // 1: the tile's ragged form; 2: the same for long panels
   int seq;  // 1: the split is emulated inside each workgroup (KArgs::seq_splits): same bits, no partial tiles, no combine
+  float us;  // the estimate it was chosen by
 };
 
 // have_ws: the caller's workspace holds the partial tiles of the planned split.  Without it the same split is
@@ -221,7 +222,7 @@ int num_cus() {
 
 // forced, forced_corun: the hooks as make_plan read them
 static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int forced, int forced_corun) {
-  Plan best = {kAnyVariant, 1, 0, 0};
+  Plan best = {kAnyVariant, 1, 0, 0, 0.f};
   if (forced == kAnyVariant) return best;
   const bool long_panels = !panels_in_window(d);
   if (long_panels && !long_panels_ok(d)) return best;
@@ -315,7 +316,7 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
       if (!found || cost < best_cost) {
         found = true;
         best_cost = cost;
-        best = {v, sp, best.ragged, 0};
+        best = {v, sp, best.ragged, 0, cost};
       }
       // A launch with many blocks has workgroups enough without the split: one workgroup then walks all the slabs of
       // its tile and adds them up range by range as the split workgroups and their combine would (identical bits).
@@ -328,7 +329,7 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
         const float cost1 = c.fixed_us + c.out_us_per_mib * out_mib * (float)batch + (float)rounds1 * (float)slabs * t1;
         if (cost1 < best_cost) {
           best_cost = cost1;
-          best = {v, sp, best.ragged, 1};
+          best = {v, sp, best.ragged, 1, cost1};
         }
       }
     }
@@ -518,11 +519,15 @@ int launch_gemm_mfma(const GemmDesc& d, hipStream_t stream) {
 
 // ---- two products in one launch (gemm_mfma_pair.hpp) ----
 // Not for a split that is walked inside the workgroups (whole grids, callers without workspace), panels beyond a buffer resource and
-// what the any-shape kernel takes, nor while a hook forces tile or loop.  The splits are those of the single launches: same bits.
-bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combines, hipStream_t stream, int* rc) {
+// what the any-shape kernel takes, nor while a hook forces tile or loop, nor where the two single launches are the faster ones.  The splits
+// are those of the single launches: same bits.
+struct PairPlan {
+  Plan x, y;
+  long long sx, sy;   // slabs that a workgroup walks
+};
+static bool plan_pair(const GemmDesc& x, const GemmDesc& y, bool vec_x, bool vec_y, PairPlan* out) {
   if (!gemm_mfma_supported(x) || !gemm_mfma_supported(y) || g_loop != 2 || g_variant >= 0) return false;
   if (!x.a_kcontig || !x.b_kcontig || y.a_kcontig || y.b_kcontig) return false;
-  const bool vec_x = epilogue_vec_ok(x), vec_y = epilogue_vec_ok(y);
   Plan px = make_plan(x, vec_x, x.partials != nullptr), py = make_plan(y, vec_y, y.partials != nullptr);
   if (px.variant == kAnyVariant || py.variant == kAnyVariant || px.seq || py.seq || px.ragged == 2 || py.ragged == 2) return false;
   if (gemm_partials_bytes(x, px.splits) > x.partials_bytes || gemm_partials_bytes(y, py.splits) > y.partials_bytes) return false;
@@ -557,13 +562,38 @@ bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combine
     if (best < 0 || cost < best_cost) { best = v; best_cost = cost; }
   }
   if (best < 0) return false;
+  // The single launches, tiles of their own choice, where their estimates are less in sum.  A pair of 64x64 tiles, many to a CU, takes up to
+  // 1.6 times its estimate, both products' panels being in the L2s at once: in large blocks that 128 does not divide.  Measured, us, pair / single
+  // launches, rows x contraction x columns of the input's gradient, 64x64 tiles: [2048 x 3840 x 3840] 218 / 132, [4096 x 2688 x 5376] 383 / 271,
+  // [8000 x 2048 x 2048] 233 / 165, but [8192 x 6912 x 576] 230 / 263; 128x128 tiles: [4096 x 2048 x 8192] 251 / 218, [4096 x 8192 x 2048] 240 /
+  // 221, [4096 x 2048 x 2048] 65 / 70; cut: [2000 x 5120 x 5120] 225 / 272, [8008 x 8192 x 2048] 517 / 505.
+  // And where the input's gradient is one long workgroup per CU at most, with four stages by itself and a slot of the ring among y's many short
+  // ones: [2048 x 6144 x 384] 72 / 56, [2048 x 6144 x 512] 77 / 59, [1024 x 6144 x 1024] 66 / 50, but [2048 x 3072 x 384] 29 / 37.
+  if (px.variant == 7 && px.splits == 1 && !px.ragged && wgs_of(x, 7, 1) <= ncu && sx >= 144 && sx >= 3 * sy) return false;
+  if (best_cost * (best == 7 && !ragged && wgs_of(x, 7, px.splits) + wgs_of(y, 7, py.splits) >= 5 * ncu ? 1.25f : 1.0f) > px.us + py.us) return false;
   px.variant = py.variant = best;
   px.ragged = py.ragged = ragged ? 1 : 0;
+  *out = {px, py, sx, sy};
+  return true;
+}
+
+bool gemm_pair_planned(const GemmDesc& x, const GemmDesc& y) {
+  PairPlan p;
+  return plan_pair(x, y, epilogue_vec_ok(x), epilogue_vec_ok(y), &p);
+}
+
+bool launch_gemm_pair(const GemmDesc& x, const GemmDesc& y, CombineJobs* combines, hipStream_t stream, int* rc) {
+  const bool vec_x = epilogue_vec_ok(x), vec_y = epilogue_vec_ok(y);
+  PairPlan plan;
+  if (!plan_pair(x, y, vec_x, vec_y, &plan)) return false;
+  const Plan &px = plan.x, &py = plan.y;
+  const int best = px.variant;
+  const bool ragged = px.ragged != 0;
   const KArgs kx = kernel_args(x, px, vec_x), ky = kernel_args(y, py, vec_y);
   const long long nx = workgroups(kx), ny = workgroups(ky);
   if (nx <= 0 || ny <= 0 || nx + ny > 0x7fffffffLL) return false;
-  PairLaunch p = {&kx, &ky, (unsigned)nx, (unsigned)ny, sy > sx ? 1 : 0, plain_store(kx), plain_store(ky), stream};
-  const bool deep = best == 7 && !ragged && nx + ny <= 2LL * ncu;
+  PairLaunch p = {&kx, &ky, (unsigned)nx, (unsigned)ny, plan.sy > plan.sx ? 1 : 0, plain_store(kx), plain_store(ky), stream};
+  const bool deep = best == 7 && !ragged && nx + ny <= 2LL * num_cus();
   g_last_plan = best | (py.splits << 8) | (deep ? 1 << 17 : 0) | (1 << 18);
   *rc = best == 7 ? launch_gemm_pair_64(deep, ragged, p) : launch_gemm_pair_128(ragged, p);
   if (*rc == OPTIMUS_OK && kx.splits > 1) combines->j[combines->n++] = combine_job(x, kx);

@@ -184,3 +184,16 @@ def test_partial_tiles_fit_the_workspace_under_changing_hooks(switched_hook):
     assert len(seen) >= 2
     for _, splits, walked in seen:
         assert walked or splits == 1 or 4 * splits * (M // q) * (N // q) <= small, seen
+
+
+# M, K, N, q of y = x W: small blocks, one of which may be cut, and blocks with tiles of 128x128 share a launch; large ones whose 64x64 tiles
+# would, or whose own tiles are twice as wide, and one long workgroup per CU beside many short ones do not
+@pytest.mark.parametrize("pair,shape", [(True, (4096, 4096, 1024, 4)), (True, (1024, 512, 2048, 2)), (True, (8000, 1280, 5120, 4)), (True, (8008, 2048, 8192, 2)),
+                                        (True, (8192, 16384, 4096, 4)), (False, (8192, 15360, 3840, 4)), (False, (32000, 8192, 2048, 4)),
+                                        (False, (8192, 5376, 1344, 1)), (False, (4096, 8192, 2048, 1)), (False, (8192, 1536, 6144, 4)),
+                                        (False, (2048, 2048, 6144, 2)), (True, (4096, 768, 3072, 2)), (False, (4096, 2048, 8192, 1))])
+def test_pairs_of_a_layer_backward(pair, shape):
+    M, K, N, q = shape
+    assert opt.binding.debug_plan_pair(M, K, N, q, q - 1, 0) == pair
+    with pytest.raises(opt.OptimusError):
+        opt.binding.debug_plan_pair(0, K, N, q, 0, 0)
