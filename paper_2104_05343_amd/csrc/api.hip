@@ -464,27 +464,47 @@ int stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
   return OPTIMUS_OK;
 }
 
+// Whether both gradients of y = x W, x [M x K], W [K x N], on tensors as they are allocated go in one launch
+bool pair_planned(int64_t M, int64_t K, int64_t N, int q, int i, int j) {
+  void* const fake = (void*)(uintptr_t)4096;   // a plan depends on shapes, strides and 16-byte alignment only
+  optimus_epilogue ey = {};
+  ey.out_fp32 = 1;
+  GemmDesc x = summa_desc(OPTIMUS_FORM_ABT, fake, fake, fake, M, N, K, q, i, j, OPTIMUS_BF16, nullptr);
+  GemmDesc y = summa_desc(OPTIMUS_FORM_ATB, fake, fake, fake, K, M, N, q, i, j, OPTIMUS_BF16, &ey);
+  x.partials = y.partials = (float*)fake;
+  x.partials_bytes = y.partials_bytes = SIZE_MAX;
+  return gemm_pair_planned(x, y);
+}
+
 // Whether the second stream pays in a pass that is not captured.  On one stream both products of a linear layer go in one launch
 // (launch_gemm_pair) and the combines ride in other launches; on two, a fork or the join costs the host 25 us (the wait on another
-// stream's event, for the most part), five of them in a backward pass: the host needs about 200 us for such a pass (165 with q = 1, where
-// no product is split).  Two streams win where the kernels on one take longer than that and the products run beside a long chain: the
+// stream's event, for the most part), five of them in a backward pass: the host needs about 200 us for such a pass (a little less with
+// q = 1, where no product is split).  Two streams win where the kernels on one take longer than that and the products run beside a long chain: the
 // attention of a device with few matrices is one along the sequence (30 us per 1024 rows fused, 36 with the scores in memory); and from 80
-// GF of products, where tiles of 256x128 on both are the better use of the chip: not in blocks that the tiles cut, which have no such.
-// With q = 1 the weight gradients are few long workgroups that the pair's other product fills up: from 200 GF there, below 24 as the
-// kernels' time has it.
-// Measured, step of one layer, two streams / one (us): 3 GF, s = 4096 262 / 278; 13 GF, s = 4096 284 / 300, s = 16384 769 / 876; 26 GF, s = 1024
-// 216 / 193, s = 1856 301 / 262, P 237 / 214; 29 GF, s = 512 229 / 204, P 235 / 208; 50 GF, s = 777 283 / 280; 52 GF, s = 512 256 / 243, s = 2048
-// 325 / 336; 75 GF, s = 333 369 / 347, P, s = 1504 440 / 432; 90 GF 412 / 416; 103 GF, s = 512 390 / 446, s = 4096 761 / 763; 412 GF 950 / 961;
-// 824 GF 824 / 875.  Cut blocks: 39 GF 278 / 272, 86 GF 405 / 374, 75 GF, s = 1500 380 / 384, 157 GF 600 / 598, 226 GF 772 / 702, 302 GF 763 / 719,
-// 403 GF 971 / 878, 929 / 918.  q = 1: 52 GF, s = 1024 262 / 258, s = 4096 414 / 416, 79 GF 450 / 446, 103 GF 378 / 343, 232 GF 616 / 627.
+// GF of products, where tiles of 256x128 on both are the better use of the chip: not in blocks that the tiles of 64x64 cut, which have no
+// such, and from 600 GF not where 128 does not divide the width (64x64 tiles on both streams crowd the L2s); and from 35 GF where the
+// products of h -> 4h do not go together.  With q = 1 the weight gradients are few long workgroups that the pair's other product fills up:
+// from 200 GF there, below 24 as the kernels' time has it; the grid of one device is that device.
+// Measured, step of one layer, two streams / one (us): 3 GF, s = 4096 225 / 209; 6 GF, s = 8200 365 / 390; 13 GF, s = 4096 256 / 230, s = 16384 650 / 730;
+// 26 GF, s = 512 217 / 194, 210 / 185; 52 GF, s = 512 256 / 238, 298 / 273, s = 4096 352 / 365; 79 GF 366 / 357; 103 GF, s = 512 384 / 365, 392 / 389, 484 / 436;
+// 116 GF 414 / 425, 494 / 447, 430 / 416; 161 GF 542 / 529, 558 / 634; 412 GF 814 / 868, 838 / 895; 825 GF 1369 / 1421; 1649 GF 2269 / 2286.  h -> 4h apart: 40 GF
+// 252 / 264, 58 GF 294 / 313, 79 GF 355 / 385.  Widths that 128 does not divide: 130 GF 526 / 554, 322 GF 1292 / 1264, 522 GF 1665 / 1755, 644 GF 2582 / 2367, 710 GF
+// 1927 / 1840, 2447 / 2131, 1450 GF 4631 / 4011, 2013 GF 7732 / 6258.  Cut blocks: 38 GF 282 / 255, 101 GF 379 / 368, 157 GF 602 / 599, 403 GF 1151 / 1082, 806 GF
+// 1738 / 1695, 1612 GF 3605 / 3334, 6449 GF 13981 / 11900; s = 4100: 6 GF 284 / 303, 13 GF 277 / 255, 52 GF 412 / 398, 206 GF 815 / 791, 825 GF 2097 / 1906; s = 16400:
+// 13 GF 722 / 804, 52 GF 1319 / 1404, 206 GF 1663 / 1614.  q = 1: 1 GF, s = 1536 184 / 133, 6 GF, s = 2048 179 / 165, 13 GF, s = 4096 269 / 277; 52 GF, s = 1024 281 / 271, 103 GF 412 / 399, 155 GF 525 / 521, 412 GF 1010 / 1036, 825 GF 1416 / 1443.
+// Whole grids: 26 GF 213 / 221, 334 / 326, 52 GF 330 / 333, 273 / 254, 103 GF 374 / 401; cut 34 GF 255 / 280, 259 / 286, 13 GF 205 / 177, 134 GF 457 / 532.
 bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
+  if (c->q == 1) grid = false;
   const double devices = grid ? (double)c->q * c->q : 1.0;
   const double gf = 48e-9 * (double)c->b * c->s * (double)c->h * c->h / ((double)c->q * c->q) * devices;
   const double one_us = 120.0 + 0.6 * gf + (c->fused_attention ? 0.030 : 0.036) * c->s;
-  const bool cut = (long long)c->b * c->s / c->q % 64 != 0 || c->h / c->q % 64 != 0;
-  if (cut && !grid) return c->s >= 4096;
-  if (c->q == 1) return gf >= 200.0 || c->s > 8192 || (gf < 24.0 && one_us >= 165.0);
-  return gf >= (grid ? 35.0 : 80.0) || one_us >= 200.0;
+  const int64_t M = (int64_t)c->b * c->s, h = c->h;
+  const bool cut = M / c->q % 64 != 0 || h / c->q % 64 != 0;
+  if (grid) return gf >= (cut ? 24.0 : 35.0) || one_us >= 200.0;
+  if (cut) return c->s >= 4096 && c->s >= 200.0 * gf;
+  if (gf >= 600.0 && h / c->q % 128 != 0) return false;
+  if (c->q == 1) return gf >= 200.0 || c->s > 8192 || (gf < 24.0 && one_us >= 185.0);
+  return gf >= 80.0 || one_us >= 200.0 || (gf >= 35.0 && !pair_planned(M, h, 4 * h, c->q, 0, 0));
 }
 // A captured pass pays the host once and keeps both streams (which an earlier pass, short or not, has created).  Replayed,
 // one stream / two: 1024-wide layer, one device of 4 x 4, step 219 / 196 us, fused 200 / 173, 3 GF 155 / 138, 4096-wide
@@ -1136,14 +1156,7 @@ int optimus_debug_plan_summa(int form, int64_t M, int64_t K, int64_t N, int q, i
 }
 int optimus_debug_plan_pair(int64_t M, int64_t K, int64_t N, int q, int i, int j) {
   if (check_mkn(M, K, N, q) || check_coords(q, i, j)) return -1;
-  void* const fake = (void*)(uintptr_t)4096;
-  optimus_epilogue ey = {};
-  ey.out_fp32 = 1;
-  GemmDesc x = summa_desc(OPTIMUS_FORM_ABT, fake, fake, fake, M, N, K, q, i, j, OPTIMUS_BF16, nullptr);
-  GemmDesc y = summa_desc(OPTIMUS_FORM_ATB, fake, fake, fake, K, M, N, q, i, j, OPTIMUS_BF16, &ey);
-  x.partials = y.partials = (float*)fake;
-  x.partials_bytes = y.partials_bytes = SIZE_MAX;
-  return gemm_pair_planned(x, y) ? 1 : 0;
+  return pair_planned(M, K, N, q, i, j) ? 1 : 0;
 }
 int optimus_debug_last_gemm_plan(void) { return gemm_last_plan(); }
 int optimus_debug_layer_bwd_streams(const optimus_layer_cfg* c, int i, int j) {

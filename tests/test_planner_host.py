@@ -113,6 +113,20 @@ def test_streams_of_the_whole_grid_and_refused_arguments():
     assert opt.binding.debug_layer_bwd_streams(opt.LayerCfg(8, 512, 1024, 15, 4, 1e-5, 1, opt.BF16, 0), 0, 0) == -1
 
 
+# Lines of the stream rule: cut blocks at any size, one device as a grid, wide blocks that 128 does not divide, linear layers whose products do not go
+# together.  Last column: the whole grid.
+@pytest.mark.parametrize("streams,shape,grid", [
+    (1, (1, 8, 1001, 4096, 32, 1), False), (1, (4, 4, 4100, 4096, 32, 1), False), (2, (4, 4, 16400, 256, 4, 1), False), (1, (4, 4, 16400, 1024, 16, 1), False),
+    (1, (1, 1, 1536, 128, 2, 1), False), (1, (1, 8, 1001, 1024, 16, 1), False), (1, (1, 8, 1001, 1024, 16, 1), True), (1, (1, 1, 4100, 512, 8, 1), False), (1, (1, 1, 4100, 512, 8, 1), True),
+    (1, (1, 16, 1024, 1600, 25, 1), False), (1, (4, 32, 1024, 3840, 60, 1), False), (2, (4, 32, 1024, 2304, 36, 1), False), (2, (4, 16, 1024, 4096, 32, 1), False),
+    (2, (4, 16, 512, 1536, 24, 1), False), (2, (4, 16, 512, 1792, 28, 1), False), (1, (4, 8, 512, 1536, 24, 1), False), (1, (4, 32, 512, 1024, 16, 1), False),
+    (2, (4, 8, 333, 512, 8, 1), True), (1, (4, 4, 512, 512, 8, 1), True), (2, (4, 8, 512, 512, 8, 1), True)])
+def test_lines_of_the_stream_rule(streams, shape, grid):
+    q, b, s, h, n, fused = shape
+    cfg = opt.LayerCfg(b, s, h, n, q, 1e-5, 1, opt.BF16, fused)
+    assert opt.binding.debug_layer_bwd_streams(cfg, *((-1, -1) if grid else (0, 0))) == streams
+
+
 SWITCH_HOOK = """
 extern void optimus_debug_set_gemm_variant(int);
 void switch_hook(volatile int* stop) { while (!*stop) { optimus_debug_set_gemm_variant(3); optimus_debug_set_gemm_variant(-1); } }
