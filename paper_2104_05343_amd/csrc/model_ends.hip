@@ -125,7 +125,8 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
   typedef unsigned long long u64;
   __shared__ __attribute__((aligned(16))) float acc[EB_ROWS * EB_COLS];
   __shared__ u64 list[EB_CHUNK];                        // row of dX (in the whole tensor) << 7 | row inside the workgroup's range
-  __shared__ unsigned short hist[SLOTS][EB_ROWS + 2];   // entries of a slot in a row; then how many lie ahead of them in the row
+  __shared__ __attribute__((aligned(4))) unsigned short hist[SLOTS][EB_ROWS + 2];   // entries of a slot in a row; then how many lie ahead of
+                                                        // them in the row; read two rows to a word
   __shared__ int row_first[EB_ROWS + 1];                // entries of a row; then where it starts in the list
   __shared__ float4 edge[2 * EB_PARTS][EB_LANES];       // sums of a part's first and last run
   __shared__ int edge_row[2 * EB_PARTS];
