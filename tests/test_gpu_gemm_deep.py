@@ -132,3 +132,78 @@ def test_wider_tiles(tile, rows, cols, form, q, K):
             opt.binding.debug_set_gemm_variant(-1)
         assert _same_bits(*out)
         assert rel_frobenius(mat_to_host(out[0], M, N, q), summa.product(form, A, B)) <= TOL
+
+
+# one device's block: the wider tiles in every range of a split, up to one workgroup on each of 256 CUs
+@pytest.mark.parametrize("form", ["ab", "abt", "atb"])
+@pytest.mark.parametrize("variant,Mb,Kp,Nb,q", [(6, 256, 1024, 256, 4), (6, 1024, 1024, 512, 4), (3, 256, 1024, 256, 4), (3, 512, 2048, 768, 4)])
+def test_wider_tiles_in_a_split(form, variant, Mb, Kp, Nb, q):
+    M, K, N, i, j = q * Mb, q * Kp, q * Nb, 2, 1
+    gen = torch.Generator(device="cuda:0").manual_seed(Mb + Nb)
+    dA, dB = (torch.randn(n, device="cuda:0", generator=gen).to(torch.bfloat16) for n in (M * K, K * N))
+    bias = torch.randn(N, device="cuda:0", generator=gen)
+    out = []
+    try:
+        for loop in (0, RING):
+            opt.binding.debug_set_gemm_variant(loop + variant)
+            ws = torch.full((opt.summa_workspace_bytes(form, M, K, N, q, i, j, opt.BF16),), 0xFF, dtype=torch.uint8, device="cuda:0")
+            C = empty(M * N, "bf16")
+            opt.summa_ex(form, dA, dB, C, M, K, N, q, i, j, opt.BF16, bias=bias, act=1, ws=ws)
+            tile, splits, walked = opt.binding.debug_last_gemm_plan()
+            assert tile == variant and splits > 1 and not walked
+            assert opt.binding.debug_last_gemm_deep_wide() == (not loop)
+            torch.cuda.synchronize()
+            out.append(C.view(q, q, Mb, Nb)[i, j])
+    finally:
+        opt.binding.debug_set_gemm_variant(-1)
+    assert _same_bits(out[0].contiguous(), out[1].contiguous()) and not torch.isnan(out[0]).any()
+
+
+@pytest.mark.parametrize("form", ["ab", "abt", "atb"])
+@pytest.mark.parametrize("variant", [3, 6])
+def test_wider_tiles_with_every_epilogue(form, variant):
+    M, K, N = 256, 320, 384
+    gen = torch.Generator(device="cuda:0").manual_seed(variant)
+    dA, dB, pre_in, res = (torch.randn(n, device="cuda:0", generator=gen).to(torch.bfloat16) for n in (M * K, K * N, M * N, M * N))
+    bias = torch.randn(N, device="cuda:0", generator=gen)
+    out = []
+    try:
+        for loop in (0, RING):
+            opt.binding.debug_set_gemm_variant(loop + variant)
+            pre, act, back, wide = empty(M * N, "bf16"), empty(M * N, "bf16"), empty(M * N, "bf16"), empty(M * N, "fp32")
+            for C, epi in ((act, dict(bias=bias, pre_act=pre, act=1)), (back, dict(gelu_grad_of=pre_in, residual=res)), (wide, dict(out_fp32=True))):
+                opt.summa_ex(form, dA, dB, C, M, K, N, 1, 0, 0, opt.BF16, **epi)
+                assert opt.binding.debug_last_gemm_deep_wide() == (not loop)
+            torch.cuda.synchronize()
+            out.append((pre, act, back, wide))
+    finally:
+        opt.binding.debug_set_gemm_variant(-1)
+    for x, y in zip(*out):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)) and not torch.isnan(x.float()).any()
+
+
+@pytest.mark.parametrize("variant,d", [(3, 128), (6, 128), (6, 64)])
+def test_wider_tiles_along_the_diagonal(variant, d):
+    """The causal products of the attention: tiles above the diagonal skipped, contractions that end or begin at it."""
+    b, s, n = 1, 768 if d == 64 else 512, 2
+    h = n * d
+    gen = torch.Generator(device="cuda:0").manual_seed(d)
+    qkv, d_attn = (torch.randn(m, device="cuda:0", generator=gen).to(torch.bfloat16) for m in (b * s * 3 * h, b * s * h))
+    ws = torch.empty(opt.attention_workspace_bytes(b, s, h, n, 1), dtype=torch.uint8, device="cuda:0")
+    out = []
+    try:
+        for loop in (0, RING):
+            opt.binding.debug_set_gemm_variant(loop + variant)
+            P, O, g = empty(b * n * s * s, "bf16"), empty(b * s * h, "bf16"), empty(b * s * 3 * h, "bf16")
+            ws.fill_(0xFF)
+            opt.attention_fwd(qkv, P, O, b, s, h, n, 1, 0, 0, True, opt.BF16, ws)
+            assert opt.binding.debug_last_gemm_plan()[0] == variant and opt.binding.debug_last_gemm_deep_wide() == (not loop)
+            ws.fill_(0xFF)
+            opt.attention_bwd(qkv, P, d_attn, g, b, s, h, n, 1, 0, 0, True, opt.BF16, ws)
+            assert opt.binding.debug_last_gemm_plan()[0] == variant and opt.binding.debug_last_gemm_deep_wide() == (not loop)
+            torch.cuda.synchronize()
+            out.append((P, O, g))
+    finally:
+        opt.binding.debug_set_gemm_variant(-1)
+    for x, y in zip(*out):
+        assert _same_bits(x, y) and not torch.isnan(x.float()).any()

@@ -85,3 +85,46 @@ def test_workspace_without_room_and_gradient_in_place(shape, d_x):
     assert torch.equal(block(T[d_x]), block(want_x))
     for n in names:
         assert torch.equal(block(T[n]), block(want[n])), n
+
+
+# Products of y = x W in the order of the backward pass, [columns of x, columns of y] in units of h
+LINEAR = [(4, 1), (1, 4), (1, 1), (1, 3)]
+
+
+@pytest.mark.parametrize("shape,in_splits,w_splits", [
+    (LayerShape(b=2, s=64, h=320, n=4, q=2), (1, 5, 1, 1), (1, 1, 1, 1)),      # a row's two wavefronts add five ranges each: a second trip
+    (LayerShape(b=4, s=64, h=640, n=4, q=4), (1, 8, 1, 8), (1, 1, 1, 1)),      # four wavefronts, eight ranges, both LayerNorms
+    (LayerShape(b=4, s=384, h=128, n=4, q=2), (1, 1, 1, 1), (6, 6, 6, 6)),     # four blocks of every weight gradient behind the column sums
+    (LayerShape(b=4, s=384, h=144, n=6, q=2), (1, 1, 1, 1), (6, 6, 6, 6)),     # rows of 72 columns
+], ids=str)
+def test_partial_tiles_of_the_whole_grid(shape, in_splits, w_splits):
+    """Splits that are not walked in a whole-grid pass: the LayerNorm that adds them for whole rows, their combines in the grid of the sums."""
+    M, h, q = shape.M, shape.h, shape.q
+    plan = opt.binding.debug_plan_summa
+    for (k, n), x, w in zip(LINEAR, in_splits, w_splits):
+        assert plan("abt", M, n * h, k * h, q, -1, -1)[1:] == (x, 0) and plan("atb", k * h, M, n * h, q, -1, -1)[1:] == (w, 0)
+        assert opt.binding.debug_plan_pair(M, k * h, n * h, q, -1, -1)
+    inp = layer_inputs(shape.s, shape, "bf16", perturb_affine=True)
+    cfg, T, lt, ws = alloc_layer(inp, shape, True)
+    assert opt.binding.debug_layer_bwd_streams(cfg, -1, -1) == 1
+    opt.layer_fwd(cfg, lt, -1, -1, ws)
+    names = BWD_OUT + FP32_MATS + list(VEC_PART) + ["bstats1", "bstats2"]
+    out = []
+    try:
+        for hook in (SEPARATE, -1):
+            opt.binding.debug_set_gemm_variant(hook)
+            ws.fill_(0xFF)
+            for n in names:
+                T[n].fill_(float("nan"))
+            opt.layer_bwd(cfg, lt, -1, -1, ws)
+            assert opt.binding.debug_last_gemm_pair() == (hook == -1)
+            torch.cuda.synchronize()
+            out.append({n: T[n].clone() for n in names})
+    finally:
+        opt.binding.debug_set_gemm_variant(-1)
+    ws.fill_(0xFF)
+    opt.layer_bwd(cfg, lt, q - 1, 0, ws)     # one device's blocks again, the peers' as they are
+    torch.cuda.synchronize()
+    for n in names:
+        assert not torch.isnan(out[1][n]).any(), n
+        assert torch.equal(out[0][n], out[1][n]) and torch.equal(T[n], out[1][n]), n
