@@ -658,6 +658,10 @@ def main():
         out["cpu_baseline"] = {"value": round(cpu_flops / (c1 - c0) / 1e12, 4), "unit": "TFLOP/s", "cores": threads,
                                "kind": "oracle", "sample": sample, "seconds": round(c1 - c0, 2),
                                "os_cpu_count": os.cpu_count()}
+    # the result is one line that a reader of the last few kilobytes of stdout finds whole; the tables go to stderr
+    tables = {k: out.pop(k) for k in ("per_config", "gemms", "bandwidth_kernels", "model_ends", "grid_launch", "stack", "stack_fused_attention",
+                                      "other_workload_steps", "mfma_ceiling", "step_fused_attention") if k in out}
+    print(json.dumps(tables, ensure_ascii=False), file=sys.stderr)
     print(json.dumps(out, ensure_ascii=False))
 
 
