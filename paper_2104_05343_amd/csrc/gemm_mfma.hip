@@ -288,12 +288,15 @@ static Plan compute_plan(const GemmDesc& d, bool vec_ok, bool have_ws, int force
       // One workgroup of 128x64 or 128x128 per CU has four stages (launch_gemm_mfma).  128x64 tiles, ring / four stages, us: [2048 x 4096 x 1024] A B 33.6 /
       // 25.5, A B^T 37.4 / 25.8, A^T B 28.2 / 26.3, [768 x 8192 x 2304] 60 / 44, 68 / 45, 50 / 46; 128x128: 42.4 / 40.3, 49.9 / 41.4, 43.5 / 40.9.  Contractions of more
       // than 6144 that can be split are better off so: operands from memory, split / one range of 128x64, A B^T [3072 x 8192 x 512] 43 / 54, A^T B [384 x
-      // 8192 x 4096] 43 / 65, A B^T [2048 x 6144 x 1024] 41 / 34.  Not counted: 128x128 tiles' gain where it is under 10 % (A B, A^T B), and 128x64 in splits, which
-      // hardly occur in one workgroup per CU.  The split is the one of the product by itself; in company the launch has the ring.
+      // 8192 x 4096] 43 / 65, A B^T [2048 x 6144 x 1024] 41 / 34.  In one panel of 8192 and more the loads want 160 workgroups: A B [768 x 12288 x 1536],
+      // 144 of them or 288 of 64x64, 90 / 70, [640 x 8192 x 2048], 160 or 320, 50 / 53.  Not counted: 128x128 tiles' gain where it is under 10 % (A B,
+      // A^T B), and 128x64 in splits, which hardly occur in one workgroup per CU.  The split is the one of the product by itself; in company the
+      // launch has the ring.
       const bool deep = !ragged && wgs <= ncu && (pass == 0 || d.corun == 0);
       // the 128x128 tile depends on the operand layouts: both k-contiguous (A B^T) is its slowest form, one of each its fastest
       if (v == 3) t_slab *= d.a_kcontig && d.b_kcontig ? (deep ? 1.0f : 1.14f) : (d.a_kcontig ? 0.92f : 1.04f);
-      if (v == 6 && deep && sp == 1 && (!d.a_kcontig || !splittable || slabs <= 192)) t_slab *= d.a_kcontig ? 0.7f : 0.9f;
+      const bool few = d.a_kcontig && !splittable && slabs >= 256 && 8 * wgs < 5 * ncu;
+      if (v == 6 && deep && sp == 1 && (!d.a_kcontig || !splittable || slabs <= 192) && !few) t_slab *= d.a_kcontig ? 0.7f : 0.9f;
       else if (v == 6 && d.a_kcontig && d.b_kcontig) t_slab *= 1.18f;
       if (v == 7 && !d.a_kcontig) t_slab *= 1.25f;   // both operands through the transposing LDS reads
       // The form with four stages (at most two workgroups per CU), for long contractions and all layouts alike (by itself, one workgroup

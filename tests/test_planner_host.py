@@ -78,6 +78,12 @@ def test_split_of_long_contractions(split, form, Mb, K, Nb, q):
     assert split or variant == 6
 
 
+# one panel: 144 workgroups of 128x64 with a long contraction give way to 288 of 64x64, 160 and shorter ones do not
+@pytest.mark.parametrize("variant,form,M,K,N", [(7, "ab", 768, 12288, 1536), (7, "abt", 3072, 16384, 384), (6, "ab", 768, 6144, 1536), (6, "ab", 640, 8192, 2048)])
+def test_tile_of_long_contractions_in_one_panel(variant, form, M, K, N):
+    assert plan(form, M, K, N, 1, 0, 0) == (variant, 1, 0)
+
+
 def test_no_split_without_panels_and_errors():
     # q = 1: one panel, nothing to split
     assert plan("ab", 2048, 4096, 1024, 1, 0, 0)[1] == 1
