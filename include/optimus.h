@@ -307,20 +307,25 @@ typedef struct {
   float* lse;     /* [q][q][(b/q)(n/q)][s] fp32, forward tensor; only with fused_attention (else may be NULL) */
 } optimus_layer_tensors;
 
-/* Scratch bytes optimus_layer_fwd / _bwd need in `ws` (attention scores and
+/* Scratch bytes optimus_layer_fwd / _bwd want in `ws`: attention scores and
  * their gradients for one device -- with fused_attention only one fp32 per
  * query row --, plus split-k partial tiles: one region for
- * the activation chain and one for the parameter-gradient branch, which
- * optimus_layer_bwd runs concurrently on a stream of the library's own that
+ * the activation chain and one for the parameter gradients, with room for all
+ * four weight gradients' tiles where a pass runs on `stream` alone and combines
+ * them at its end.  Less is accepted down to regions of the largest product's
+ * tiles: each weight gradient is then combined at once, with the same bits.
+ * In longer passes optimus_layer_bwd runs the parameter gradients concurrently
+ * on a stream of the library's own that
  * it forks from and joins back into `stream` with events; when the call
  * returns, every kernel of both is ordered before later work on `stream`.
  * The library creates that stream (default priority) and its events on the
  * first call per device that is not made under stream capture; until then the
  * branch runs on `stream` itself, as it does in every call too short for a
- * second stream to pay unless that call is captured.  They are shared by all
+ * second stream to pay unless that call is captured, and where matrices share
+ * memory that both streams would use.  They are shared by all
  * calls on a device:
  * optimus_layer_bwd must not be called from several host threads at once
- * for the same device.) */
+ * for the same device. */
 size_t optimus_layer_workspace_bytes(const optimus_layer_cfg* cfg);
 /* The size to give whole-grid calls (i = j = -1) that should run fast: the minimum above plus attention scratch
  * for more devices, so that the unfused attention of several devices is one batch per launch instead of one device

@@ -488,10 +488,11 @@ bool pair_planned(int64_t M, int64_t K, int64_t N, int q, int i, int j) {
 // Measured, step of one layer, two streams / one (us): 3 GF, s = 4096 225 / 209; 6 GF, s = 8200 365 / 390; 13 GF, s = 4096 256 / 230, s = 16384 650 / 730;
 // 26 GF, s = 512 217 / 194, 210 / 185; 52 GF, s = 512 256 / 238, 298 / 273, s = 4096 352 / 365; 79 GF 366 / 357; 103 GF, s = 512 384 / 365, 392 / 389, 484 / 436;
 // 116 GF 414 / 425, 494 / 447, 430 / 416; 161 GF 542 / 529, 558 / 634; 412 GF 814 / 868, 838 / 895; 825 GF 1369 / 1421; 1649 GF 2269 / 2286.  h -> 4h apart: 40 GF
-// 252 / 264, 58 GF 294 / 313, 79 GF 355 / 385.  Widths that 128 does not divide: 130 GF 526 / 554, 322 GF 1292 / 1264, 522 GF 1665 / 1755, 644 GF 2582 / 2367, 710 GF
+// 250 / 250, 58 GF 283 / 297, 250 / 261, 79 GF 349 / 371.  Widths that 128 does not divide: 130 GF 526 / 554, 322 GF 1292 / 1264, 522 GF 1665 / 1755, 644 GF 2582 / 2367, 710 GF
 // 1927 / 1840, 2447 / 2131, 1450 GF 4631 / 4011, 2013 GF 7732 / 6258.  Cut blocks: 38 GF 282 / 255, 101 GF 379 / 368, 157 GF 602 / 599, 403 GF 1151 / 1082, 806 GF
 // 1738 / 1695, 1612 GF 3605 / 3334, 6449 GF 13981 / 11900; s = 4100: 6 GF 284 / 303, 13 GF 277 / 255, 52 GF 412 / 398, 206 GF 815 / 791, 825 GF 2097 / 1906; s = 16400:
-// 13 GF 722 / 804, 52 GF 1319 / 1404, 206 GF 1663 / 1614.  q = 1: 1 GF, s = 1536 184 / 133, 6 GF, s = 2048 179 / 165, 13 GF, s = 4096 269 / 277; 52 GF, s = 1024 281 / 271, 103 GF 412 / 399, 155 GF 525 / 521, 412 GF 1010 / 1036, 825 GF 1416 / 1443.
+// 13 GF 722 / 804, 52 GF 1319 / 1404, 206 GF 1663 / 1614.  q = 1: 1 GF, s = 1536 184 / 133, 6 GF, s = 2048 179 / 165, 13 GF, s = 4096 269 / 277; 52 GF, s = 1024
+// 281 / 271, 103 GF 412 / 399, 155 GF 525 / 521, 412 GF 1010 / 1036, 825 GF 1416 / 1443.
 // Whole grids: 26 GF 213 / 221, 334 / 326, 52 GF 330 / 333, 273 / 254, 103 GF 374 / 401; cut 34 GF 255 / 280, 259 / 286, 13 GF 205 / 177, 134 GF 457 / 532.
 bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
   if (c->q == 1) grid = false;
@@ -506,9 +507,10 @@ bool two_streams_pay(const optimus_layer_cfg* c, bool grid) {
   if (c->q == 1) return gf >= 200.0 || c->s > 8192 || (gf < 24.0 && one_us >= 185.0);
   return gf >= 80.0 || one_us >= 200.0 || (gf >= 35.0 && !pair_planned(M, h, 4 * h, c->q, 0, 0));
 }
-// A captured pass pays the host once and keeps both streams (which an earlier pass, short or not, has created).  Replayed,
-// one stream / two: 1024-wide layer, one device of 4 x 4, step 219 / 196 us, fused 200 / 173, 3 GF 155 / 138, 4096-wide
-// 968 / 873; layers of less than 1 GF are shorter on one (110 / 123, 99 / 106; whole grids of small blocks 193 / 240).
+// A captured pass pays the host once and keeps both streams (which an earlier pass, short or not, has created): from before the joint launches,
+// when two were the shorter ones replayed from 1 GF on.  They are so for the wide layers only by now.  Replayed, one stream / two, us: 4096-wide
+// layer, one device of 4 x 4, 914 / 837, fused 893 / 829, of 8 x 8 917 / 855; 39 GF, cut, 273 / 263; 52 GF 236 / 244, 248 / 256; 103 GF 392 / 400; 26 GF 183 / 199;
+// 1024-wide layer, one device of 4 x 4, 156 / 173, fused 139 / 154; 3 GF 116 / 132; 0.4 GF 95 / 122; whole grids of small blocks 149 / 192, 165 / 237.
 bool captured(hipStream_t caller) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(caller, &cs) != hipSuccess) { (void)hipGetLastError(); return false; }

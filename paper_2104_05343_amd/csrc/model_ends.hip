@@ -3,7 +3,7 @@
 //     token indices of grid row i (every device of a row has them) and the table block (l, j) of every l is resident:
 //     out_ij[t] = table block (tok / (v/q), j), row tok % (v/q).  Pure copy: bit exact, HBM bound.
 //   * embedding gradient: d_table_lj = sum_i one_hot_il^T dX_ij, the A^T B form reduced within column j onto its owner
-//     (l, j).  Computed as the owner sees it: a workgroup owns 32 table rows x 256 columns of the block as fp32
+//     (l, j).  Computed as the owner sees it: a workgroup owns 128 table rows x 64 columns of the block as fp32
 //     accumulators in LDS, scans ALL token indices, adds the rows of dX whose token falls into its rows and writes
 //     its piece once.  No atomics, an order of additions fixed by the token order: deterministic, and rows that no
 //     token refers to are written as zeros.

@@ -42,7 +42,8 @@ def test_against_64_bit_sums(q, rows, vb, hb, kind, dtype):
     np.add.at(want, np.clip(tok, 0, v - 1), dX.astype(np.float64))
     np.add.at(mag, np.clip(tok, 0, v - 1), np.abs(dX).astype(np.float64))
     got = to_host(grid).reshape(q, q, vb, hb).transpose(0, 2, 1, 3).reshape(v, h)
-    # at most one fp32 addition per token and three per wavefront and chunk that meet in a row
+    # longest chain of fp32 additions to an element: a part's tokens (a 64th of a chunk's, at least four), then two for each part that meets in
+    # the row, chunk after chunk: below M + 96 at these sizes
     assert np.all(np.abs(got - want) <= (M + 96) * 2.0 ** -24 * mag)
 
 
