@@ -105,7 +105,7 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
 // Token indices are scanned in chunks of 4096; the positions of a chunk that fall into the workgroup's rows are sorted by
 // row, in token order within a row (counting sort: ranks from ballots, prefix sums over wavefronts and rounds).  The
 // sorted list is cut into 64 consecutive parts of at least four entries, one for each group of 16 lanes; a group adds up a row's run in
-// registers, a batch of rows of dX in flight at a time (a lane covers four adjacent columns), and touches the accumulators in LDS only
+// registers, a batch of rows of dX in flight at a time (a lane covers four columns), and touches the accumulators in LDS only
 // where the row changes.  Runs that lie inside one part have the row to themselves in this chunk; a part's first and last
 // run may continue in the neighbours' and are added in part order afterwards.  The order of all additions is a
 // function of the token order alone, so the result is reproducible bit for bit.
@@ -113,7 +113,8 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
 // 128-byte line of bf16 each; in large tables the fixed chain of a workgroup (scan, sort, one gather), several rounds of them.
 // 128 rows x 64 columns against 32 x 256 in as many workgroups: a third of the bytes and of the list on the busiest CU, four parts a
 // wavefront.  Zipf tokens, bf16, us, before / now: 4096 tokens, 256 columns, v = 32768 over 4 blocks 37.1 / 18.0 (fp32 36.3 / 17.0), all tokens one
-// row 81 / 26, its 16 blocks in one launch 127 / 100; 131072 tokens 1105 / 459; 1024 tokens, 16384 rows of 1024 58 / 45; 64 tokens 11.3 / 6.5.
+// row 81 / 26, its 16 blocks in one launch 127 / 100; 131072 tokens 1105 / 459; 1024 tokens, 16384 rows of 1024 58 / 45; 64 tokens 11.3 / 6.5.  Widths that are no multiple of four, uniform tokens over
+// 500 rows, 16384 of them, fp32, 32 x 256 / 128 x 64 with adjacent columns / with every 16th: width 63 67 / 96 / 49, 127 88 / 97 / 50.
 constexpr int EB_ROWS = 128, EB_COLS = 64, EB_WAVES = 16, EB_CHUNK = 4096;
 constexpr int EB_LANES = EB_COLS / 4, EB_PARTS = EB_WAVES * 64 / EB_LANES;   // lanes that add up one part of the list, and parts
 template <typename T>
@@ -138,11 +139,13 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
   const int r0 = blockIdx.y * EB_ROWS;                  // first table row (inside block l) of this workgroup
   const int nr = min(EB_ROWS, a.vb - r0);
   typedef T T4 __attribute__((ext_vector_type(4)));
-  const int c0 = blockIdx.x * EB_COLS + 4 * pl;         // first of this lane's four columns inside the block
   const bool vec4 = a.hb % 4 == 0;                      // four columns exist or none does, and they are 8/16-byte aligned
+  // a lane's four columns inside the block: adjacent ones; or, where they are loaded one by one, every 16th, so that a load of 16 lanes is one
+  // piece of memory
+  const int c0 = blockIdx.x * EB_COLS + (vec4 ? 4 * pl : pl), dc = vec4 ? 1 : EB_LANES;
   int col[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) col[k] = c0 + k < a.hb ? c0 + k : (vec4 ? k : 0);
+  for (int k = 0; k < 4; ++k) col[k] = c0 + k * dc < a.hb ? c0 + k * dc : (vec4 ? k : 0);
   bool used = false;                                    // some token falls into these rows: acc is in use
   const int lo = l * a.vb + r0, hi = lo + nr;           // token indices that land in this workgroup's rows
   const long long total = (long long)a.q * a.rows;      // all tokens, grid row after grid row (below 2^31: host check)
@@ -281,8 +284,9 @@ __global__ __launch_bounds__(64 * EB_WAVES) void embedding_bwd_kernel(const int*
     return;
   }
   for (int k = tid; k < nr * EB_COLS; k += 64 * EB_WAVES) {
-    const int r = k / EB_COLS, c = blockIdx.x * EB_COLS + k % EB_COLS;
-    if (c < a.hb) out[(long long)r * a.hb + c] = used ? acc[k] : 0.f;
+    const int r = k / EB_COLS, cc = k % EB_COLS, c = blockIdx.x * EB_COLS + cc;
+    const int at = r * EB_COLS + (vec4 ? cc : cc % EB_LANES * 4 + cc / EB_LANES);
+    if (c < a.hb) out[(long long)r * a.hb + c] = used ? acc[at] : 0.f;
   }
 }
 
